@@ -38,15 +38,15 @@ def _workload():
 def _kernel_name(W: int, tuning, g) -> str:
     """Name of the extension-kernel instantiation the library runs for
     visited sets of W words under this tuning on graph g (mirrors the
-    dispatch: the thread-per-parent kernel stages the CSR in LDS when its
-    3n + 2m + 4 words fit in 16 KiB)."""
+    dispatch on the graph of chains: the thread-per-parent kernel stages its
+    CSR in LDS when its 4n + 2m + 4 words fit in 16 KiB)."""
     i = W.bit_length() - 1
     items, var = tuning["items"][i], tuning["variant"][i]
     if var != 0:
         while items > 1 and items * W > 32:
             items //= 2
     if var != 0 and items * W <= 32:
-        staged = "true" if 4 * (3 * g.n + 2 * g.n_edges + 4) <= 16384 else "false"
+        staged = "true" if 4 * (4 * g.n + 2 * g.n_edges + 4) <= 16384 else "false"
         return f"k_extend_tp<{W}, {items}, {256 if var == 1 else 1024}, {staged}>"
     return f"k_extend_lb<{W}, {items}>"
 
@@ -109,10 +109,34 @@ def _measured_traffic(kernel: str, summary: str = "k_extend_cfg209_hbm_traffic.m
 
 
 def _bytes_per_extension(n: int) -> int:
-    """Algorithmic HBM bytes per path extension: the child's 8-byte record is
-    written once and read once as a parent (16 B), and its visited set of
-    ceil(n / 64) words is written once and read once."""
-    return 16 + 2 * 8 * ((n + 63) // 64)
+    """Algorithmic HBM bytes per path extension in a graph of n chains: the
+    child's 10-byte record is written once and read once as a parent (20 B),
+    and its visited set of ceil(n / 64) words is written once and read once."""
+    return 20 + 2 * 8 * ((n + 63) // 64)
+
+
+def _chains(g):
+    """g with every straight line (each vertex the only predecessor of its
+    only successor) taken as one vertex: the graph that the extension runs
+    on.  For graphs with an entry and an exit."""
+    from paper_2210_16998_amd import cfggen
+    succ = [[int(w) for w in g.succ(v)] for v in range(g.n)]
+    indeg = [0] * g.n
+    for r in succ:
+        for w in r:
+            indeg[w] += 1
+    nxt = [r[0] if len(r) == 1 and indeg[r[0]] == 1 and r[0] != v else -1
+           for v, r in enumerate(succ)]
+    heads = sorted(set(range(g.n)) - set(nxt))
+    last, chain = {}, {}
+    for k, h in enumerate(heads):
+        v = h
+        chain[v] = k
+        while nxt[v] >= 0:
+            v = nxt[v]
+            chain[v] = k
+        last[k] = v
+    return cfggen.from_edges(len(heads), [(k, chain[w]) for k in last for w in succ[last[k]]])
 
 
 def _paper_form(args):
@@ -382,9 +406,14 @@ def _whole_path(g, args, stream, copy_gbs: float, traffic_summary: str, pool_cap
     torch.cuda.synchronize()
     ms_timed = 1000.0 * (time.perf_counter() - t2) / args.steps
     n_pp, n_ext = st["n_pp"], st["n_extensions"]
-    bpe = _bytes_per_extension(g.n)
+    # the kernel extends paths of chains: their number is that of the simple
+    # paths of the graph of chains
+    x = _chains(g)
+    _, st_x = tpg.prime_paths(tpg.load_cfg(x, tpg.TPG_LOAD_ANY_DIGRAPH), ws=ws,
+                              flags=flags | tpg.TPG_DIGEST_ONLY, stream=stream)
+    bpe = _bytes_per_extension(x.n)
     avg = k_ms / max(1, k_launches)
-    per_launch = n_ext * bpe / max(1, st["n_extend_launches"])
+    per_launch = st_x["n_extensions"] * bpe / max(1, st["n_extend_launches"])
     achieved = per_launch / (avg * 1e-3) / 1e9 if avg > 0 else 0.0
 
     # plain per-CFG two-pass form of the same graph, for context
@@ -402,9 +431,9 @@ def _whole_path(g, args, stream, copy_gbs: float, traffic_summary: str, pool_cap
         return statistics.median(p[key] for p in phases)
 
     W = 1
-    while W * 64 < g.n:
+    while W * 64 < x.n:
         W *= 2
-    kname = _kernel_name(W, tpg.get_tuning(ws), g)
+    kname = _kernel_name(W, tpg.get_tuning(ws), x)
     traffic = _measured_traffic(kname, traffic_summary)
     dev_bytes = st["device_bytes"]
     ws.close()
@@ -428,6 +457,7 @@ def _whole_path(g, args, stream, copy_gbs: float, traffic_summary: str, pool_cap
                      "measured_frac": measured / HBM_PEAK_GBS if measured else None,
                      "copy_GBps": copy_gbs, "frac_of_copy": achieved / copy_gbs,
                      "algorithmic_bytes_per_launch": per_launch, "bytes_per_extension": bpe,
+                     "chains": x.n, "chain_extensions": st_x["n_extensions"],
                      "launches_per_step": st["n_extend_launches"], "avg_launch_ms": avg},
     }
 

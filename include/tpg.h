@@ -458,7 +458,8 @@ void tpg_batch_result_free(tpg_batch_result* r);
  * Launch-shape tuning of the frontier-extension kernel.
  *
  * Per visited-set width W = 2^i words (index i = 0..6; W is the register
- * width, ceil(V / 64) rounded up to a power of two): the most parents per
+ * width, ceil(V / 64) rounded up to a power of two, where V counts each
+ * straight line of the graph as one vertex): the most parents per
  * thread (1, 2, 4 or 8; a tile is threads * items parents and claims its
  * slice of the next level with one device-scope atomic), persistent
  * workgroups per compute unit (1..32) and the kernel variant (0: load-

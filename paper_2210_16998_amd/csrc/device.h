@@ -10,10 +10,12 @@ namespace tpg {
 
 constexpr int kBlock = 256;  // threads per workgroup for path kernels (4 waves)
 
-// A path-tree node is stored as two 32-bit words:
-//   par  : global index of the parent node (-1 for a single-vertex path)
-//   info : last vertex, graph-wide id (bits 0-16) | first vertex, id local to
+// The path tree is built over chains (straight lines of the graph, each
+// taken as one vertex; see Chains).  A node is one path of chains, stored as
+//   par  : global index of the parent node (-1 for a single chain)
+//   info : last chain, graph-wide id (bits 0-16) | first chain, id local to
 //          its component (bits 17-28) | flags (bits 29-31)
+//   tl   : vertices of its chains, each chain once
 // Several CFGs can be processed as one disjoint union ("components"); a
 // visited set indexes the local ids of the path's own component.
 constexpr uint32_t kVMask = 0x1FFFFu;
@@ -54,12 +56,23 @@ struct DGraph {
   const int32_t* centry;// [n_comp] entry (graph-wide id)
   const int32_t* cexit; // [n_comp] exit (graph-wide id)
   int32_t n, n_comp;
-  // sp, s, pp, p and loc lie back to back in one buffer starting at sp:
-  // int32 words from sp through the end of loc (what a kernel stages in LDS)
+  // The graph of chains only: vertices per chain; sp, s, pp, p, loc and len
+  // lie back to back in one buffer starting at sp, n_stage int32 words in
+  // all (what a kernel stages in LDS).
+  const int32_t* len;   // [n]
   int32_t n_stage;
+  int32_t max_comp;     // vertices of the largest component, every chain's counted
 };
 
-// Largest CSR (sp .. loc, bytes) that the extension kernel stages in LDS.
+// The vertices behind a graph of chains (graph-wide ids).
+struct DChains {
+  const int32_t* off;  // [n + 1] rows of v
+  const int32_t* v;    // vertices of every chain, in order
+  const int32_t* of;   // per vertex: its chain
+  const int32_t* pos;  // per vertex: its place there
+};
+
+// Largest CSR (sp .. len, bytes) that the extension kernel stages in LDS.
 constexpr int kGraphLdsBytes = 16384;
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }

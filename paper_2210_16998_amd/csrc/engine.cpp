@@ -26,11 +26,18 @@ struct OutSet {
   int64_t n_pp = 0, n_ppv = 0, n_tp = 0, n_tpv = 0;
 };
 
-// A disjoint union of CFGs laid out as one graph (host side).
+// A disjoint union of CFGs laid out as one graph (host side), and the same
+// union with its chains contracted, which the path tree is built over.
 struct HostUnion {
   int32_t n = 0, n_comp = 0, W = 1;  // W: visited-set words in registers (power of two)
-  int32_t Wu = 1;                     // words stored per visited set: ceil(largest component / 64)
+  int32_t Wu = 1;                     // words stored per visited set: ceil(most chains of a component / 64)
+  int32_t max_comp = 1;               // vertices of the largest component
   std::vector<int32_t> sp{0}, s, pp{0}, p, loc, comp, cbase{0}, centry, cexit;
+  int32_t xn = 0;  // chains
+  std::vector<int32_t> xsp{0}, xs, xpp{0}, xp, xloc, xlen, xcomp, xcbase{0};
+  std::vector<int32_t> choff{0}, chv, chof, chpos;  // see DChains
+  std::vector<int32_t> xhead;                       // first vertex of every chain
+  std::vector<int32_t> rot;  // chains of two or more vertices, ascending
   std::vector<uint64_t> uids;
 };
 
@@ -99,14 +106,16 @@ struct tpg_workspace {
   // unions (by graph uids) whose predicted capacities could not be allocated
   std::vector<std::vector<uint64_t>> pred_failed;
   DevBuf g_csr;
-  DGraph dg{};
+  DGraph dg{}, xg{};   // the union, and the union of its chains
+  DChains ch{};
+  const int32_t* d_rot = nullptr;  // HostUnion::rot
 
   // path tree
-  DevBuf par, info, cstart, nch, mask0, mask1, ls;
+  DevBuf par, info, cstart, nch, tl, mask0, mask1, ls;
   int64_t rec_cap = 0, mask_cap = 0;
   int mask_words = 0;
   // ranking
-  DevBuf sub_cnt, pp_len, leaf_by_rank, totals, cycles;
+  DevBuf sub_cnt, pp_len, leaf_by_rank, totals;  // totals: see PathTotals
   // scans
   DevBuf scan_status, scan_ctr, scalars;
   DevBuf scan2_status, scalars2;  // the side stream's own scan scratch
@@ -125,6 +134,7 @@ struct tpg_workspace {
   // pinned host mirrors
   LevelState* h_ls = nullptr;
   int64_t* h_scalars = nullptr;
+  int64_t* h_totals = nullptr;  // PathTotals::host_words of the largest graph
 
   std::vector<hipEvent_t> ev_pool;
 
@@ -142,9 +152,11 @@ struct tpg_workspace {
     hipGraphExec_t exec = nullptr;
   };
   SeqGraph rank_up, rank_down;
-  // level-1 seeds of the next build: first vertices seed_lo .. seed_lo + seed_n - 1
-  // (seed_n < 0: every vertex of the union)
+  // level-1 seeds of the next build: chains seed_lo .. seed_lo + seed_n - 1
+  // (seed_n < 0: every chain of the union), which hold the first vertices
+  // range_lo .. range_lo + range_n - 1
   int32_t seed_lo = 0, seed_n = -1;
+  int32_t range_lo = 0, range_n = 0;
   DevBuf digest;  // [2] set digest of the last digest_set call
   DevBuf grp_key, grp_hist;  // last-vertex grouping: keys, per-tile histograms
   // longest-first covering: prime-path hash table, covering pairs, order,
@@ -307,58 +319,103 @@ double predicted_paths(const float* predicted, int32_t i, int L) {
   return std::expm1(std::min(x, 40.0));
 }
 
-void add_component(HostUnion& U, const tpg_graph* g) {
-  const int32_t base = U.n;
+// Appends g to the union.  block: 0 the chains of the graph handle, else
+// chains cut at multiples of `block` vertices (1: no contraction).
+void add_component(HostUnion& U, const tpg_graph* g, int32_t block = 0) {
+  Chains cut;
+  if (block > 0) cut = contract_chains(*g, block);
+  const Chains& c = block > 0 ? cut : g->chains;
+  const int32_t base = U.n, xbase = U.xn;
+  auto rows = [](std::vector<int32_t>& ptr, std::vector<int32_t>& col, int32_t at,
+                 const std::vector<int32_t>& gptr, const std::vector<int32_t>& gcol) {
+    const int32_t k0 = (int32_t)col.size();
+    for (size_t v = 1; v < gptr.size(); ++v) ptr.push_back(k0 + gptr[v]);
+    for (int32_t w : gcol) col.push_back(at + w);
+  };
+  rows(U.sp, U.s, base, g->succ_ptr, g->succ);
+  rows(U.pp, U.p, base, g->pred_ptr, g->pred);
+  rows(U.xsp, U.xs, xbase, c.sp, c.s);
+  rows(U.xpp, U.xp, xbase, c.pp, c.p);
+  rows(U.choff, U.chv, base, c.off, c.v);
   for (int32_t v = 0; v < g->n; ++v) {
-    for (int32_t k = g->succ_ptr[v]; k < g->succ_ptr[v + 1]; ++k) U.s.push_back(base + g->succ[k]);
-    U.sp.push_back((int32_t)U.s.size());
-    for (int32_t k = g->pred_ptr[v]; k < g->pred_ptr[v + 1]; ++k) U.p.push_back(base + g->pred[k]);
-    U.pp.push_back((int32_t)U.p.size());
     U.loc.push_back(v);
     U.comp.push_back(U.n_comp);
+    U.chof.push_back(xbase + c.of[v]);
+    U.chpos.push_back(c.pos[v]);
+  }
+  for (int32_t x = 0; x < c.n; ++x) {
+    const int32_t len = c.off[x + 1] - c.off[x];
+    U.xloc.push_back(x);
+    U.xlen.push_back(len);
+    U.xhead.push_back(base + c.v[c.off[x]]);
+    U.xcomp.push_back(U.n_comp);
+    if (len > 1) U.rot.push_back(xbase + x);
   }
   U.centry.push_back(base + g->entry);
   U.cexit.push_back(base + g->exit);
   U.n += g->n;
+  U.xn += c.n;
   U.cbase.push_back(U.n);
+  U.xcbase.push_back(U.xn);
   U.n_comp += 1;
-  U.W = std::max(U.W, pow2_words(g->n));
-  U.Wu = std::max(U.Wu, (g->n + 63) / 64);
-  U.uids.push_back(g->uid);
+  U.W = std::max(U.W, pow2_words(c.n));
+  U.Wu = std::max(U.Wu, (c.n + 63) / 64);
+  U.max_comp = std::max(U.max_comp, g->n);
+  U.uids.push_back(g->uid | (uint64_t)block << 48);  // block <= TPG_MAX_VERTICES
 }
 
 tpg_status upload_union(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   // a recorded or captured call always uploads, so that every replay does
   if (ws->io_mode == 0 && ws->union_uids == U.uids) return TPG_OK;
-  const size_t n1 = (size_t)U.n + 1, m = U.s.size(), nc = (size_t)U.n_comp;
-  const size_t words = 2 * n1 + 2 * (m + 1) + 2 * (size_t)U.n + (nc + 1) + 2 * nc + 8;
-  TPG_TRY(ws_reserve(ws, ws->g_csr, sizeof(int32_t) * words));
+  // everything goes up in one copy; a pad word follows arrays that may be empty
+  std::vector<int32_t> blob;
+  const std::vector<int32_t>* parts[] = {
+      &U.sp, &U.s, &U.pp, &U.p, &U.loc, &U.comp, &U.cbase, &U.centry, &U.cexit,
+      &U.xsp, &U.xs, &U.xpp, &U.xp, &U.xloc, &U.xlen, &U.xcomp, &U.xcbase,
+      &U.choff, &U.chv, &U.chof, &U.chpos, &U.rot};
+  constexpr int kParts = sizeof(parts) / sizeof(parts[0]);
+  size_t words = 0, at[kParts];
+  for (int i = 0; i < kParts; ++i) {
+    at[i] = words;
+    words += parts[i]->size() + (parts[i] == &U.s || parts[i] == &U.p || parts[i] == &U.xs ||
+                                 parts[i] == &U.xp);
+  }
+  blob.assign(words + 1, 0);
+  for (int i = 0; i < kParts; ++i)
+    std::copy(parts[i]->begin(), parts[i]->end(), blob.begin() + at[i]);
+  TPG_TRY(ws_reserve(ws, ws->g_csr, sizeof(int32_t) * blob.size()));
   int32_t* q = ws->g_csr.as<int32_t>();
-  hipError_t err = hipSuccess;
-  auto put = [&](const std::vector<int32_t>& v, size_t pad) -> int32_t* {
-    int32_t* at = q;
-    if (!v.empty() && err == hipSuccess)
-      err = hipMemcpyAsync(at, io_src(ws, v.data(), sizeof(int32_t) * v.size()),
-                           sizeof(int32_t) * v.size(), hipMemcpyHostToDevice, st);
-    q += v.size() + pad;
-    return at;
-  };
-  DGraph d{};
-  d.sp = put(U.sp, 0);
-  d.s = put(U.s, 1);
-  d.pp = put(U.pp, 0);
-  d.p = put(U.p, 1);
-  d.loc = put(U.loc, 0);
-  d.comp = put(U.comp, 0);
-  d.cbase = put(U.cbase, 0);
-  d.centry = put(U.centry, 0);
-  d.cexit = put(U.cexit, 0);
+  TPG_HIP(hipMemcpyAsync(q, io_src(ws, blob.data(), sizeof(int32_t) * blob.size()),
+                         sizeof(int32_t) * blob.size(), hipMemcpyHostToDevice, st));
+  DGraph d{}, x{};
+  d.sp = q + at[0];
+  d.s = q + at[1];
+  d.pp = q + at[2];
+  d.p = q + at[3];
+  d.loc = q + at[4];
+  d.comp = q + at[5];
+  d.cbase = q + at[6];
+  d.centry = q + at[7];
+  d.cexit = q + at[8];
   d.n = U.n;
   d.n_comp = U.n_comp;
-  d.n_stage = (int32_t)(d.comp - d.sp);
-  TPG_HIP(err);
-  if (ws->io_mode != 2) TPG_HIP(hipStreamSynchronize(st));  // the host vectors are freed after
+  x.sp = q + at[9];
+  x.s = q + at[10];
+  x.pp = q + at[11];
+  x.p = q + at[12];
+  x.loc = q + at[13];
+  x.len = q + at[14];
+  x.comp = q + at[15];
+  x.cbase = q + at[16];
+  x.n = U.xn;
+  x.n_comp = U.n_comp;
+  x.n_stage = (int32_t)(at[15] - at[9]);
+  x.max_comp = U.max_comp;
+  if (ws->io_mode != 2) TPG_HIP(hipStreamSynchronize(st));  // the host copy goes
   ws->dg = d;
+  ws->xg = x;
+  ws->ch = DChains{q + at[17], q + at[18], q + at[19], q + at[20]};
+  ws->d_rot = q + at[21];
   ws->union_uids = U.uids;
   return TPG_OK;
 }
@@ -376,9 +433,11 @@ tpg_status reserve_tree(tpg_workspace* ws, int64_t rec, int64_t msk, int W, hipS
   TPG_TRY(ws_reserve(ws, ws->cstart, sizeof(int32_t) * (rec + 1), keep_rec > 0, st,
                      sizeof(int32_t) * (keep_rec + 1)));
   TPG_TRY(ws_reserve(ws, ws->nch, (size_t)rec, keep_rec > 0, st, (size_t)keep_rec));
+  TPG_TRY(ws_reserve(ws, ws->tl, sizeof(uint16_t) * rec, keep_rec > 0, st, sizeof(uint16_t) * keep_rec));
   ws->rec_cap = std::min<int64_t>(ws->par.cap / sizeof(int32_t), ws->cstart.cap / sizeof(int32_t) - 1);
   ws->rec_cap = std::min<int64_t>(ws->rec_cap, ws->info.cap / sizeof(uint32_t));
   ws->rec_cap = std::min<int64_t>(ws->rec_cap, (int64_t)ws->nch.cap);
+  ws->rec_cap = std::min<int64_t>(ws->rec_cap, (int64_t)(ws->tl.cap / sizeof(uint16_t)));
   ws->rec_cap = std::min<int64_t>(ws->rec_cap, kMaxTreeNodes);  // buffers may hold more
   // Visited sets are word-major (word q of slot j at q * mask_cap + j), so the
   // stride is the capacity: both buffers always have the same size, and the
@@ -414,6 +473,7 @@ tpg_status reserve_tree(tpg_workspace* ws, int64_t rec, int64_t msk, int W, hipS
   }
   ws->mask_cap = (int64_t)(std::min(ws->mask0.cap, ws->mask1.cap) / (sizeof(uint64_t) * W));
   TPG_TRY(ws_reserve(ws, ws->ls, sizeof(LevelState)));
+  TPG_TRY(ws_reserve(ws, ws->totals, sizeof(uint64_t) * PathTotals::words(ws->xg)));
   ws->mask_words = W;
   return TPG_OK;
 }
@@ -421,19 +481,21 @@ tpg_status reserve_tree(tpg_workspace* ws, int64_t rec, int64_t msk, int W, hipS
 ExtArgs make_args(tpg_workspace* ws, int grid = 0) {
   ExtArgs a{};
   a.tiles_target = std::max(64, grid / 2);
-  a.g = ws->dg;
+  a.g = ws->xg;
   a.t.par = ws->par.as<int32_t>();
   a.t.info = ws->info.as<uint32_t>();
   a.t.cstart = ws->cstart.as<int32_t>();
   a.t.nch = ws->nch.as<uint8_t>();
+  a.t.tl = ws->tl.as<uint16_t>();
   a.t.mask[0] = ws->mask0.as<uint64_t>();
   a.t.mask[1] = ws->mask1.as<uint64_t>();
   a.t.rec_cap = ws->rec_cap;
   a.t.mask_cap = ws->mask_cap;
   a.t.mask_words = ws->mask_words;
   a.ls = ws->ls.as<LevelState>();
+  a.tot = ws->totals.as<uint64_t>();
   a.seed_lo = ws->seed_n >= 0 ? ws->seed_lo : 0;
-  a.seed_n = ws->seed_n >= 0 ? ws->seed_n : ws->dg.n;
+  a.seed_n = ws->seed_n >= 0 ? ws->seed_n : ws->xg.n;
   return a;
 }
 
@@ -477,7 +539,10 @@ struct TreeResult {
   std::vector<int64_t> count, off;
   int64_t n_nodes = 0;
   int64_t n_overflows = 0;
-  int64_t peak = 0;
+  // simple paths by number of entries (index), and their total, from the
+  // nodes' length histogram
+  std::vector<int64_t> paths;
+  int64_t n_paths = 0;
   double ms_kernel = 0.0;
   int64_t launches = 0;
 };
@@ -588,7 +653,7 @@ tpg_status launch_levels_graph(tpg_workspace* ws, const ExtArgs& a, int W, int i
 
 // Frees the path tree and the visited-set buffers (capacities back to zero).
 void release_tree(tpg_workspace* ws) {
-  for (DevBuf* b : {&ws->par, &ws->info, &ws->cstart, &ws->nch, &ws->mask0, &ws->mask1})
+  for (DevBuf* b : {&ws->par, &ws->info, &ws->cstart, &ws->nch, &ws->tl, &ws->mask0, &ws->mask1})
     ws_release(ws, *b);
   ws->rec_cap = 0;
   ws->mask_cap = 0;
@@ -678,7 +743,7 @@ tpg_status build_tree_onepass(tpg_workspace* ws, const HostUnion& U, hipStream_t
   const int W = U.W;
   const int64_t held_msk =
       (ws->mask_words && ws->mask_cap) ? ws->mask_cap * ws->mask_words / U.Wu : 0;
-  const TreeCaps first = onepass_first_caps(ws->rec_cap, held_msk, U.n, rec0, msk0);
+  const TreeCaps first = onepass_first_caps(ws->rec_cap, held_msk, U.xn, rec0, msk0);
   TPG_TRY(reserve_tree(ws, first.rec, first.msk, U.Wu, st, 0, -1, 0));
   int wi = 0;
   while ((1 << wi) < W) ++wi;
@@ -720,7 +785,6 @@ tpg_status build_tree_onepass(tpg_workspace* ws, const HostUnion& U, hipStream_t
     R.count[L] = L <= Lmax ? cnt[L] : 0;
     R.off[L] = off;
     off += R.count[L];
-    R.peak = std::max(R.peak, R.count[L]);
   }
   R.n_nodes = off;
   return TPG_OK;
@@ -730,8 +794,8 @@ tpg_status build_tree_onepass(tpg_workspace* ws, const HostUnion& U, hipStream_t
 tpg_status build_tree_twopass(tpg_workspace* ws, const HostUnion& U, hipStream_t st, Timer& tm,
                               TreeResult& R) {
   const int W = U.W;
-  int64_t rec = std::max<int64_t>(ws->rec_cap, (int64_t)U.n + 4096);
-  int64_t msk = (int64_t)U.n + 1024;
+  int64_t rec = std::max<int64_t>(ws->rec_cap, (int64_t)U.xn + 4096);
+  int64_t msk = (int64_t)U.xn + 1024;
   if (ws->mask_words && ws->mask_cap)
     msk = std::max<int64_t>(msk, ws->mask_cap * ws->mask_words / U.Wu);
   TPG_TRY(reserve_tree(ws, rec, msk, U.Wu, st, 0, -1, 0));
@@ -742,7 +806,6 @@ tpg_status build_tree_twopass(tpg_workspace* ws, const HostUnion& U, hipStream_t
   int L = 1;
   int64_t base = 0, F = a.seed_n, prev = 0;
   R.count[1] = F;
-  R.peak = F;
   for (;;) {
     TPG_TRY(reserve_scan(ws, F));
     hipEvent_t e0 = tm.mark();
@@ -778,7 +841,6 @@ tpg_status build_tree_twopass(tpg_workspace* ws, const HostUnion& U, hipStream_t
     R.launches += 1;
     R.off[L + 1] = base + F;
     R.count[L + 1] = total;
-    R.peak = std::max(R.peak, total);
     prev = base;
     base += F;
     F = total;
@@ -796,21 +858,50 @@ struct PPResult {
 
 BfsOut bfs_views(tpg_workspace* ws, int n);
 
+// Simple paths by length (index: entries) from the histograms that the device
+// counted over the nodes below level 1 (see k_path_lengths) and the seeded
+// chains' own paths; everything the seeds stand for.
+void path_counts(const tpg_workspace* ws, const HostUnion& U, const int64_t* hist, int64_t bins,
+                 TreeResult& R) {
+  R.paths.assign(bins + 1, 0);
+  const int64_t* h1 = hist;
+  const int64_t* h2 = hist + bins;
+  int64_t s1 = 0, s2 = 0, c2 = 0;
+  for (int64_t e = bins - 1; e >= 1; --e) {
+    s1 += h1[e];
+    s2 += h2[e];
+    c2 += s2;
+    R.paths[e] = s1 + c2;
+  }
+  const int32_t lo = ws->seed_n >= 0 ? ws->seed_lo : 0;
+  const int32_t n = ws->seed_n >= 0 ? ws->seed_n : U.xn;
+  for (int32_t x = lo; x < lo + n; ++x)
+    for (int32_t l = 1; l <= U.xlen[x]; ++l) R.paths[l] += U.xlen[x] - l + 1;
+  while (R.paths.size() > 2 && R.paths.back() == 0) R.paths.pop_back();
+  R.n_paths = 0;
+  for (int64_t c : R.paths) R.n_paths += c;
+}
+
 tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream_t st,
-                                const TreeResult& R, PPResult& P, OutSet& o) {
+                                TreeResult& R, PPResult& P, OutSet& o) {
   ExtArgs a = make_args(ws);
   const int64_t N = R.n_nodes;
   TPG_TRY(ws_reserve(ws, ws->sub_cnt, sizeof(uint32_t) * N));
-  TPG_TRY(ws_reserve(ws, ws->totals, sizeof(int64_t) * 4));
-  TPG_TRY(ws_reserve(ws, ws->cycles, sizeof(uint64_t) * (kCycleSlots + 1)));
+  TPG_TRY(ws_reserve(ws, ws->rb0, sizeof(int64_t) * (U.n + 2)));
   uint32_t* sc = ws->sub_cnt.as<uint32_t>();
+  // output positions by first vertex; with every vertex in range they are also
+  // the test paths' runs by first vertex
+  int64_t* rb = ws->rb0.as<int64_t>();
+  const bool all = ws->seed_n < 0;
+  const int32_t range_lo = all ? 0 : ws->range_lo, range_n = all ? U.n : ws->range_n;
   // the levels' ranges and every buffer the sweeps touch key their graphs
   std::vector<uint8_t> key;
   key_add(key, a);
+  key_add(key, ws->ch);
   key_add(key, sc);
-  key_add(key, ws->cycles.p);
-  key_add(key, ws->totals.p);
-  key_add(key, U.n);
+  key_add(key, rb);
+  key_add(key, range_lo);
+  key_add(key, range_n);
   key_add(key, R.Lmax);
   for (int L = 1; L <= R.Lmax; ++L) {
     key_add(key, R.off[L]);
@@ -821,61 +912,62 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
   // however little it does)
   constexpr int kRun = 2;  // 3 measured slower: deeper per-thread chains
   TPG_TRY(run_seq(ws, ws->rank_up, std::move(key), st, [&]() -> hipError_t {
-    hipError_t e = launch_zero_u64(ws->cycles.as<uint64_t>(), kCycleSlots, st);
-    unsigned long long* ncyc = ws->cycles.as<unsigned long long>();
+    hipError_t e = launch_path_lengths(a, R.count[1], N, st);
     for (int L = R.Lmax; L >= 1 && e == hipSuccess;) {
       const int n = std::min(kRun, L);  // levels L - n + 1 .. L
       const int top = L - n + 1;
-      e = n > 1 ? launch_up_run(a, n - 1, R.off[top], R.count[top], sc, ncyc, st)
-                : launch_up(a, top, R.off[top], R.count[top], sc, ncyc, st);
+      e = n > 1 ? launch_up_run(a, n - 1, R.off[top], R.count[top], sc, st)
+                : launch_up(a, R.off[top], R.count[top], sc, st);
       L -= n;
     }
-    if (e == hipSuccess)
-      e = launch_roots(a, R.count[1], sc, nullptr, nullptr, ws->totals.as<int64_t>(), 0, nullptr, ncyc,
-                       st);
+    if (e == hipSuccess) e = launch_roots(a, ws->ch, range_lo, range_n, sc, rb, st);
     return e;
   }));
-  TPG_TRY(io_read(ws, st, ws->h_scalars, ws->totals.p, sizeof(int64_t)));
-  TPG_TRY(io_read(ws, st, ws->h_scalars + 2, ws->cycles.as<uint64_t>() + kCycleSlots,
-                  sizeof(int64_t)));
-  P.n_pp = ws->h_scalars[0];
-  P.n_cycles = ws->h_scalars[2];
-  TPG_TRY(ws_reserve(ws, ws->leaf_by_rank, sizeof(int64_t) * (P.n_pp + 1)));
+  TPG_TRY(io_read(ws, st, ws->h_totals, ws->totals.p,
+                  sizeof(int64_t) * PathTotals::host_words(ws->xg)));
+  P.n_pp = ws->h_totals[PathTotals::kPP];
+  P.n_cycles = ws->h_totals[PathTotals::kCycles];
+  path_counts(ws, U, ws->h_totals + PathTotals::kHist, PathTotals::bins(ws->xg), R);
+  if (P.n_pp > kMaxTreeNodes || R.n_paths > kMaxTreeNodes)
+    return fail(TPG_ERR_UNSUPPORTED, "more than 2^31 simple paths in one run");
+  TPG_TRY(ws_reserve(ws, ws->leaf_by_rank, sizeof(uint64_t) * (P.n_pp + 1)));
   TPG_TRY(ws_reserve(ws, ws->pp_len, sizeof(int32_t) * (P.n_pp + 1)));
   TPG_TRY(ws_reserve(ws, o.pp_off, sizeof(int64_t) * (P.n_pp + 1)));
   TPG_TRY(ws_reserve(ws, o.comp_starts, sizeof(int64_t) * 4 * (U.n_comp + 1)));
   TPG_TRY(reserve_scan(ws, P.n_pp));
-  int64_t* lbr = ws->leaf_by_rank.as<int64_t>();
+  uint64_t* leaf = ws->leaf_by_rank.as<uint64_t>();
   int32_t* len = ws->pp_len.as<int32_t>();
-  // with every vertex a root (in id order) the root ranks are also the test
-  // paths' runs by first vertex
-  int64_t* rbw = nullptr;
-  if (ws->seed_lo == 0 && R.count[1] == U.n) {
-    TPG_TRY(ws_reserve(ws, ws->rb0, sizeof(int64_t) * (U.n + 2)));
-    rbw = ws->rb0.as<int64_t>();
-  }
-  ws->rb_ready = rbw != nullptr;
-  key_add(key_down, lbr);
+  ws->rb_ready = all;
+  // the seeded chains of two or more vertices
+  const auto r0 = std::lower_bound(U.rot.begin(), U.rot.end(), a.seed_lo);
+  const auto r1 = std::lower_bound(U.rot.begin(), U.rot.end(), a.seed_lo + a.seed_n);
+  const int32_t* rot = ws->d_rot + (r0 - U.rot.begin());
+  const int32_t n_rot = P.n_cycles > 0 ? (int32_t)(r1 - r0) : 0;
+  key_add(key_down, leaf);
   key_add(key_down, len);
-  key_add(key_down, rbw);
+  key_add(key_down, rot);
+  key_add(key_down, n_rot);
   TPG_TRY(run_seq(ws, ws->rank_down, std::move(key_down), st, [&]() -> hipError_t {
-    hipError_t e =
-        launch_roots(a, R.count[1], sc, lbr, len, ws->totals.as<int64_t>(), 1, rbw, nullptr, st);
-    for (int L = 1; L < R.Lmax && e == hipSuccess;) {
-      const int n = std::min(kRun, R.Lmax - L);  // parents of levels L .. L + n - 1
-      e = n > 1 ? launch_down_run(a, n - 1, L, R.off[L], R.count[L], sc, lbr, len, st)
-                : launch_down(a, L, R.off[L], R.count[L], sc, lbr, len, st);
+    hipError_t e = hipSuccess;
+    // level 1 always (a tree of one level has leaves there), then the parents
+    // of the levels below
+    for (int L = 1; (L == 1 || L < R.Lmax) && e == hipSuccess;) {
+      const int n = std::max(1, std::min(kRun, R.Lmax - L));  // parents of levels L .. L + n - 1
+      e = n > 1 ? launch_down_run(a, n - 1, L, R.off[L], R.count[L], sc, leaf, len, st)
+                : launch_down(a, L, R.off[L], R.count[L], sc, leaf, len, st);
       L += n;
     }
+    if (e == hipSuccess) e = launch_rotations(a, ws->ch, rot, n_rot, range_lo, rb, leaf, len, st);
     return e;
   }));
   // offsets of the prime paths: a scan of their lengths
   int64_t* scal = ws->scalars.as<int64_t>();
   TPG_HIP(scan_i32_to_i64(len, o.pp_off.as<int64_t>(), P.n_pp, 0, scal + 6,
                           ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  int64_t* cs = o.comp_starts.as<int64_t>();
-  TPG_HIP(launch_comp_pp_starts(ws->dg, sc, o.pp_off.as<int64_t>(), ws->totals.as<int64_t>(), cs,
-                                cs + (U.n_comp + 1), st));
+  if (U.n_comp > 1) {
+    int64_t* cs = o.comp_starts.as<int64_t>();
+    TPG_HIP(launch_comp_pp_starts(ws->dg, rb, o.pp_off.as<int64_t>(), cs, cs + (U.n_comp + 1), st));
+  }
   TPG_TRY(io_read(ws, st, ws->h_scalars + 6, scal + 6, sizeof(int64_t)));
   P.n_vtx = ws->h_scalars[6];
   TPG_TRY(ws_reserve(ws, o.pp_vtx, sizeof(int32_t) * (P.n_vtx + 1)));
@@ -894,8 +986,8 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
                     ws->tp_lead.as<int4>()};
     ws->tp_len_ready = true;
   }
-  TPG_HIP(launch_pp_write(a, lbr, o.pp_off.as<int64_t>(), P.n_pp, o.pp_vtx.as<int32_t>(), tpx,
-                          st));
+  TPG_HIP(launch_pp_write(a, ws->ch, U.n, leaf, o.pp_off.as<int64_t>(), P.n_pp,
+                          o.pp_vtx.as<int32_t>(), tpx, st));
   o.n_pp = P.n_pp;
   o.n_ppv = P.n_vtx;
   return TPG_OK;
@@ -981,7 +1073,7 @@ tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, 
   TPG_TRY(ws_reserve(ws, ws->keep_pos, sizeof(int64_t) * (np + 1)));
   int64_t* cnt = ws->keep_cnt.as<int64_t>();
   int64_t* at = ws->keep_pos.as<int64_t>();
-  TPG_HIP(launch_cover(U.W, ws->dg, tp_off, tp_vtx, np, mul, ws->cov_keys.as<uint64_t>(),
+  TPG_HIP(launch_cover(pow2_words(U.max_comp), ws->dg, tp_off, tp_vtx, np, mul, ws->cov_keys.as<uint64_t>(),
                        ws->cov_vals.as<int32_t>(), slots - 1, cnt, at, nullptr, nullptr, 0, misc + 1,
                        st));
   TPG_HIP(scan_i64(cnt, at, np, 0, sc + 12, ws->scan_status.as<uint64_t>(),
@@ -991,7 +1083,7 @@ tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, 
   const int64_t npairs = hs[10];
   TPG_TRY(ws_reserve(ws, ws->pair_p, sizeof(int32_t) * (npairs + 1)));
   TPG_TRY(ws_reserve(ws, ws->pair_q, sizeof(int32_t) * (npairs + 1)));
-  TPG_HIP(launch_cover(U.W, ws->dg, tp_off, tp_vtx, np, mul, ws->cov_keys.as<uint64_t>(),
+  TPG_HIP(launch_cover(pow2_words(U.max_comp), ws->dg, tp_off, tp_vtx, np, mul, ws->cov_keys.as<uint64_t>(),
                        ws->cov_vals.as<int32_t>(), slots - 1, cnt, at, ws->pair_p.as<int32_t>(),
                        ws->pair_q.as<int32_t>(), 1, misc + 1, st));
   TPG_HIP(hipMemcpyAsync(hs + 11, misc + 1, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
@@ -1322,9 +1414,9 @@ tpg_status run_pp(const HostUnion& U, CallCtx& c, Timer& tm, TreeResult& R, PPRe
 
 void add_stats(tpg_stats* s, const HostUnion& U, const TreeResult& R, const PPResult& P,
                const TPResult* T) {
-  s->n_levels = std::max<int64_t>(s->n_levels, R.Lmax);
-  s->n_nodes += R.n_nodes;
-  s->n_extensions += R.n_nodes - R.count[1];
+  s->n_levels = std::max<int64_t>(s->n_levels, (int64_t)R.paths.size() - 1);
+  s->n_nodes += R.n_paths;
+  s->n_extensions += R.n_paths - R.paths[1];
   s->n_cycles += P.n_cycles;
   s->n_pp += P.n_pp;
   s->n_pp_vertices += P.n_vtx;
@@ -1336,7 +1428,7 @@ void add_stats(tpg_stats* s, const HostUnion& U, const TreeResult& R, const PPRe
   s->n_overflows += R.n_overflows;
   s->ms_extend_kernel += R.ms_kernel;
   s->n_extend_launches += R.launches;
-  s->peak_level_nodes = std::max<int64_t>(s->peak_level_nodes, R.peak);
+  for (int64_t c : R.paths) s->peak_level_nodes = std::max(s->peak_level_nodes, c);
   s->n_unions += 1;
 }
 
@@ -1362,17 +1454,23 @@ tpg_status call_chunk(CallCtx& c, const tpg_paths& chunk, int64_t first, int64_t
 tpg_status prime_paths_stream(const tpg_graph* g, CallCtx& c, tpg_paths* out) {
   if (!c.opts || !c.opts->on_chunk) return fail(TPG_ERR_INVALID_ARG, "TPG_STREAM needs opts.on_chunk");
   if (c.opts->chunk_vertices < 0) return fail(TPG_ERR_INVALID_ARG, "chunk_vertices < 0");
+  const int32_t cv = std::min(c.opts->chunk_vertices > 0 ? c.opts->chunk_vertices : 32, g->n);
+  // chains cut at the ranges' bounds: each belongs to one range, and a range's
+  // chains are neighbours in id (they are numbered by their heads)
   HostUnion U;
-  add_component(U, g);
-  const int32_t cv = c.opts->chunk_vertices > 0 ? c.opts->chunk_vertices : 32;
+  add_component(U, g, cv);
   Timer tm{c.ws, c.st, false};
   tpg_stats acc{};
   std::vector<int64_t> levels;
   uint64_t dg[2] = {0, 0};
   OutSet& o = c.ws->out[0];
   for (int32_t lo = 0; lo < U.n; lo += cv) {
-    c.ws->seed_lo = lo;
-    c.ws->seed_n = std::min(cv, U.n - lo);
+    const int32_t hi = std::min(lo + cv, U.n);
+    const int32_t* xl = U.xhead.data();
+    c.ws->seed_lo = (int32_t)(std::lower_bound(xl, xl + U.xn, lo) - xl);
+    c.ws->seed_n = (int32_t)(std::lower_bound(xl, xl + U.xn, hi) - xl) - c.ws->seed_lo;
+    c.ws->range_lo = lo;
+    c.ws->range_n = hi - lo;
     TreeResult R;
     PPResult P;
     TPG_TRY(run_pp(U, c, tm, R, P, o, nullptr));
@@ -1384,14 +1482,14 @@ tpg_status prime_paths_stream(const tpg_graph* g, CallCtx& c, tpg_paths* out) {
     TPG_TRY(export_paths(o.pp_off, o.pp_vtx, P.n_pp, P.n_vtx, c.flags & TPG_OUT_DEVICE, c.st, &chunk));
     chunk.digest[0] = cd[0];
     chunk.digest[1] = cd[1];
-    const tpg_status rc = call_chunk(c, chunk, lo, lo + c.ws->seed_n);
+    const tpg_status rc = call_chunk(c, chunk, lo, hi);
     tpg_paths_free(&chunk);
     TPG_TRY(rc);
     out->n_paths += P.n_pp;
     out->n_vertices += P.n_vtx;
     add_stats(&acc, U, R, P, nullptr);
-    if ((int)levels.size() <= R.Lmax) levels.resize(R.Lmax + 1, 0);
-    for (int L = 1; L <= R.Lmax; ++L) levels[L] += R.count[L];
+    if (levels.size() < R.paths.size()) levels.resize(R.paths.size(), 0);
+    for (size_t L = 1; L < R.paths.size(); ++L) levels[L] += R.paths[L];
   }
   c.ws->seed_n = -1;
   out->digest[0] = dg[0];
@@ -1491,7 +1589,10 @@ tpg_status tpg_workspace_create(int32_t device, tpg_workspace** out) {
     return fail(TPG_ERR_DEVICE, "side stream / events");
   }
   if (hipHostMalloc((void**)&ws->h_ls, sizeof(LevelState), hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc((void**)&ws->h_scalars, sizeof(int64_t) * 16, hipHostMallocDefault) != hipSuccess) {
+      hipHostMalloc((void**)&ws->h_scalars, sizeof(int64_t) * 16, hipHostMallocDefault) != hipSuccess ||
+      hipHostMalloc((void**)&ws->h_totals,
+                    sizeof(int64_t) * (PathTotals::kHist + 2 * (PathTotals::kLenPad + TPG_MAX_VERTICES)),
+                    hipHostMallocDefault) != hipSuccess) {
     tpg_workspace_free(ws);
     return fail(TPG_ERR_OOM_HOST, "pinned host buffers");
   }
@@ -1508,9 +1609,9 @@ void tpg_workspace_free(tpg_workspace* ws) {
   if (ws->cg.exec) (void)hipGraphExecDestroy(ws->cg.exec);
   if (ws->io_check) (void)hipHostFree(ws->io_check);
   if (ws->io_stage) (void)hipHostFree(ws->io_stage);
-  DevBuf* bufs[] = {&ws->g_csr, &ws->par, &ws->info, &ws->cstart, &ws->nch, &ws->mask0,
+  DevBuf* bufs[] = {&ws->g_csr, &ws->par, &ws->info, &ws->cstart, &ws->nch, &ws->tl, &ws->mask0,
                     &ws->mask1, &ws->ls, &ws->sub_cnt, &ws->pp_len,
-                    &ws->leaf_by_rank, &ws->totals, &ws->cycles, &ws->scan_status,
+                    &ws->leaf_by_rank, &ws->totals, &ws->scan_status,
                     &ws->scan_ctr, &ws->scalars, &ws->bfs_i32, &ws->pfx_off, &ws->sfx_off,
                     &ws->pfx, &ws->sfx, &ws->pfx_pk, &ws->sfx_pk, &ws->tp_len, &ws->tp_off, &ws->tp_vtx, &ws->tp_key, &ws->tp_pk, &ws->idx0,
                     &ws->idx1, &ws->grp_cnt, &ws->rb0, &ws->rb1, &ws->merge_split, &ws->tp_lead, &ws->keep_cnt, &ws->keep_len,
@@ -1545,6 +1646,7 @@ void tpg_workspace_free(tpg_workspace* ws) {
   drop_seq_graph(ws->rank_down);
   if (ws->h_ls) (void)hipHostFree(ws->h_ls);
   if (ws->h_scalars) (void)hipHostFree(ws->h_scalars);
+  if (ws->h_totals) (void)hipHostFree(ws->h_totals);
   if (ws->own_stream) (void)hipStreamDestroy(ws->own_stream);
   if (ws->side_stream) (void)hipStreamDestroy(ws->side_stream);
   if (ws->ev_fork) (void)hipEventDestroy(ws->ev_fork);
@@ -1597,7 +1699,7 @@ tpg_status tpg_prime_paths(const tpg_graph* g, const tpg_opts* opts, tpg_paths* 
     }
     if (c.opts && c.opts->level_counts)
       for (int L = 0; L < c.opts->level_counts_len; ++L)
-        c.opts->level_counts[L] = (L <= R.Lmax && L < (int)R.count.size()) ? R.count[L] : 0;
+        c.opts->level_counts[L] = L < (int)R.paths.size() ? R.paths[L] : 0;
   }
   for (auto& e : phase)
     if (e) (void)hipEventDestroy(e);
@@ -1723,9 +1825,10 @@ struct ComponentUnion {
   }
 };
 
+// block: see add_component.
 tpg_status component_union(const tpg_graph* g, const std::vector<int32_t>& comp,
-                           const std::vector<uint8_t>& fl, bool rev, ComponentUnion& S,
-                           HostUnion& U) {
+                           const std::vector<uint8_t>& fl, bool rev, int32_t block,
+                           ComponentUnion& S, HostUnion& U) {
   std::map<int32_t, std::vector<int32_t>> members;
   for (int32_t v = 0; v < g->n; ++v)
     if (fl[v] & kSccCyclic) members[comp[v]].push_back(v);
@@ -1753,7 +1856,7 @@ tpg_status component_union(const tpg_graph* g, const std::vector<int32_t>& comp,
     tpg_graph* h = nullptr;
     TPG_TRY(tpg_load_cfg_csr(k, rp.data(), ci.data(), 0, k - 1, TPG_LOAD_ANY_DIGRAPH, &h));
     S.gs.push_back(h);
-    add_component(U, h);
+    add_component(U, h, block);
     for (int32_t v : vs) {
       S.orig.push_back(v);
       S.vfl.push_back((uint8_t)(((fl[v] & kSccEntryVertex) ? 1 : 0) |
@@ -1770,9 +1873,10 @@ tpg_status extract_device(CallCtx& c, const tpg_graph* g, const std::vector<int3
   tpg_workspace* ws = c.ws;
   hipStream_t st = c.st;
   for (int rev = 0; rev < 2; ++rev) {
+    // the marks are per vertex: the tree is built without contraction
     ComponentUnion S;
     HostUnion U;
-    TPG_TRY(component_union(g, comp, fl, rev != 0, S, U));
+    TPG_TRY(component_union(g, comp, fl, rev != 0, 1, S, U));
     const int nsets = rev ? 1 : 2;
     const int slot[2] = {rev ? 1 : 0, 2};
     TPG_TRY(reserve_scan(ws, 16));
@@ -1975,7 +2079,7 @@ tpg_status tpg_scc_internal_pps(const tpg_graph* g, const tpg_opts* opts, tpg_pa
   TPG_TRY(components_host(c, g, comp, fl));
   ComponentUnion S;
   HostUnion U;
-  TPG_TRY(component_union(g, comp, fl, false, S, U));
+  TPG_TRY(component_union(g, comp, fl, false, 0, S, U));
   DevBuf& ooff = ws->cm_off[0];
   DevBuf& ovtx = ws->cm_vtx[0];
   if (U.n == 0) {
@@ -2396,16 +2500,18 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
                       std::vector<int64_t>& pp_first, std::vector<int64_t>& tp_first,
                       int64_t& ppv, int64_t& tpv) {
   tpg_workspace* ws = c.ws;
-  // unions: one per visited-set width class, split at 2^17 vertices and, with
-  // predictions and a pool cap, at half the cap of predicted footprint
+  // unions: one per visited-set width class, with the graphs of at most 64
+  // vertices apart (a graph's test-path runs are padded to those of the
+  // union's largest); split at 2^17 vertices and, with predictions and a pool
+  // cap, at half the cap of predicted footprint
   std::vector<std::vector<int32_t>> unions;
   {
-    std::vector<std::vector<int32_t>> cls(8);
+    std::vector<std::vector<int32_t>> cls(8);  // 0: at most 64 vertices; 1 + log2(words)
     for (int32_t i = 0; i < n_graphs; ++i) {
-      const int w = pow2_words(graphs[i]->n);
+      const int w = pow2_words(graphs[i]->chains.n);
       int k = 0;
       while ((1 << k) < w) ++k;
-      cls[k].push_back(i);
+      cls[graphs[i]->n <= 64 ? 0 : 1 + k].push_back(i);
     }
     for (int k = 0; k < 8; ++k) {
       std::vector<int32_t> cur;
@@ -2415,7 +2521,7 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
         double gm = 0;
         if (predicted && ws->cap) {
           for (int L = 0; L < 64; ++L) gm += predicted_paths(predicted, i, L);
-          gm *= 24.0 + 2.0 * 8.0 * (1 << k);
+          gm *= 24.0 + 2.0 * 8.0 * (k ? 1 << (k - 1) : 1);
         }
         if (!cur.empty() && (nv + graphs[i]->n > kMaxUnionVertices ||
                              (ws->cap && mem + gm > 0.5 * (double)ws->cap))) {
@@ -2462,7 +2568,11 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
       // never more than the record limit, the pool cap or half the free
       // device memory: an over-prediction costs capacity, not the call
       double rec_lim = (double)INT32_MAX - 2, msk_lim = (double)INT32_MAX - 2;
-      const double node_b = 13.0, set_b = 2.0 * 8.0 * U.Wu;
+      const double node_b = 15.0, set_b = 2.0 * 8.0 * U.Wu;
+      // The predictions count simple paths; nodes are paths of chains, of which
+      // both ends' choices shrink with the share of chains among the vertices
+      // (levels are fewer too, so a single one shrinks with one end's only).
+      const double share = (double)U.xn / (double)U.n;
       size_t free_b = 0, total_b = 0;
       if (ws->io_mode != 2 && hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b > 0) {
         rec_lim = std::min(rec_lim, 0.5 * (double)free_b / node_b);
@@ -2474,8 +2584,8 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
         rec_lim = std::min(rec_lim, 0.5 * (double)ws->cap / node_b);
         msk_lim = std::min(msk_lim, 0.25 * (double)ws->cap / set_b);
       }
-      rec0 = (int64_t)std::min(1.25 * tot + U.n + 1024, rec_lim);
-      msk0 = (int64_t)std::min(1.25 * peak + 1024, msk_lim);
+      rec0 = (int64_t)std::min(1.25 * share * share * tot + U.n + 1024, rec_lim);
+      msk0 = (int64_t)std::min(1.25 * share * peak + 1024, msk_lim);
       io_value(ws, rec0);  // free device memory may differ between calls
       io_value(ws, msk0);
       if (c.stats) {
@@ -2509,9 +2619,7 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
       TPG_TRY(ws_reserve(ws, ws->lvl_comp, sizeof(int64_t) * 64 * (size_t)nc));
       TPG_HIP(launch_zero_u64(ws->lvl_comp.as<uint64_t>(), 64 * (int64_t)nc, c.st));
       ExtArgs a = make_args(ws);
-      for (int L = 1; L <= R.Lmax; ++L)
-        TPG_HIP(launch_level_comp_counts(a, L, R.off[L], R.count[L], ws->lvl_comp.as<int64_t>(),
-                                         c.st));
+      TPG_HIP(launch_level_comp_counts(a, R.n_nodes, ws->lvl_comp.as<int64_t>(), c.st));
       std::vector<int64_t> h((size_t)64 * nc);
       TPG_HIP(hipMemcpyAsync(h.data(), ws->lvl_comp.p, sizeof(int64_t) * h.size(),
                              hipMemcpyDeviceToHost, c.st));
@@ -2844,7 +2952,7 @@ tpg_status tpg_autotune(const tpg_graph* const* graphs, int32_t n_graphs, const 
   // one union per visited-set width (first 2^17 vertices of each width)
   std::vector<HostUnion> unions(7);
   for (int32_t i = 0; i < n_graphs; ++i) {
-    const int w = pow2_words(graphs[i]->n);
+    const int w = pow2_words(graphs[i]->chains.n);
     int k = 0;
     while ((1 << k) < w) ++k;
     if (unions[k].n + graphs[i]->n <= kMaxUnionVertices) add_component(unions[k], graphs[i]);

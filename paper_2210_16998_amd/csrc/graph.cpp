@@ -36,6 +36,68 @@ tpg_status fail(tpg_status s, const char* fmt, ...) {
 
 static std::atomic<uint64_t> g_uid{1};
 
+Chains contract_chains(const tpg_graph& g, int32_t block) {
+  const int32_t n = g.n;
+  Chains c;
+  // next[v]: the vertex after v on its chain (-1: v ends it)
+  std::vector<int32_t> next(n, -1);
+  std::vector<uint8_t> head(n, 1);
+  if (block != 1)
+    for (int32_t v = 0; v < n; ++v) {
+      if (g.succ_ptr[v + 1] - g.succ_ptr[v] != 1) continue;
+      const int32_t w = g.succ[g.succ_ptr[v]];
+      if (w == v || g.pred_ptr[w + 1] - g.pred_ptr[w] != 1) continue;
+      if (block > 0 && v / block != w / block) continue;
+      next[v] = w;
+      head[w] = 0;
+    }
+  // a ring (every vertex of a component on one chain that closes) has no
+  // head yet: it starts at its smallest vertex
+  std::vector<uint8_t> on(n, 0);
+  for (int32_t v = 0; v < n; ++v)
+    if (head[v])
+      for (int32_t x = v; x >= 0; x = next[x]) on[x] = 1;
+  for (int32_t v = 0; v < n; ++v) {
+    if (on[v]) continue;
+    head[v] = 1;
+    for (int32_t x = v;; x = next[x]) {
+      on[x] = 1;
+      if (next[x] == v) {
+        next[x] = -1;
+        break;
+      }
+    }
+  }
+  c.of.assign(n, 0);
+  c.pos.assign(n, 0);
+  c.off.assign(1, 0);
+  c.v.reserve(n);
+  for (int32_t v = 0; v < n; ++v) {
+    if (!head[v]) continue;
+    int32_t k = 0;
+    for (int32_t x = v; x >= 0; x = next[x]) {
+      c.of[x] = c.n;
+      c.pos[x] = k++;
+      c.v.push_back(x);
+    }
+    c.n += 1;
+    c.off.push_back((int32_t)c.v.size());
+  }
+  c.sp.assign(c.n + 1, 0);
+  c.pp.assign(c.n + 1, 0);
+  for (int32_t x = 0; x < c.n; ++x) {
+    const int32_t h = c.v[c.off[x]], t = c.v[c.off[x + 1] - 1];
+    // a last vertex's successors are heads, ascending; a head's predecessors
+    // are last vertices, whose chains are put in order
+    for (int32_t k = g.succ_ptr[t]; k < g.succ_ptr[t + 1]; ++k) c.s.push_back(c.of[g.succ[k]]);
+    for (int32_t k = g.pred_ptr[h]; k < g.pred_ptr[h + 1]; ++k) c.p.push_back(c.of[g.pred[k]]);
+    std::sort(c.p.begin() + c.pp[x], c.p.end());
+    c.sp[x + 1] = (int32_t)c.s.size();
+    c.pp[x + 1] = (int32_t)c.p.size();
+  }
+  return c;
+}
+
 }  // namespace tpg
 
 using namespace tpg;
@@ -194,6 +256,12 @@ tpg_status tpg_load_cfg_csr(int32_t n, const int64_t* row_ptr, const int32_t* co
         return fail(TPG_ERR_UNREACHABLE, "vertex %d is %s", v,
                     !seen[v] ? "unreachable from entry" : "unable to reach exit");
       }
+  }
+  try {
+    g->chains = contract_chains(*g, 0);
+  } catch (const std::bad_alloc&) {
+    delete g;
+    return fail(TPG_ERR_OOM_HOST, "graph handle");
   }
   *out = g;
   return TPG_OK;

@@ -11,6 +11,26 @@
 
 #include "../../include/tpg.h"
 
+namespace tpg {
+
+// A graph with its straight lines contracted: a chain v_1 -> .. -> v_m, where
+// each v_i (i < m) has v_(i+1) as its only successor and is its only
+// predecessor, becomes one vertex.  Chains are numbered by their first vertex
+// (the head), ascending; a chain's successors are its last vertex's, its
+// predecessors its head's.  What the path kernels make of it:
+//  * a simple path that enters a chain goes through it to its end or stops
+//    inside it, so every acyclic prime path is made of whole chains;
+//  * a closed cycle through a chain of m vertices is one cycle of chains and
+//    gives m prime paths, one from each of the chain's vertices.
+struct Chains {
+  int32_t n = 0;                 // chains
+  std::vector<int32_t> off, v;   // vertices of chain x, in order: v[off[x] .. off[x + 1])
+  std::vector<int32_t> of, pos;  // per vertex: its chain and its place there
+  std::vector<int32_t> sp, s, pp, p;  // contracted CSR and its reverse (rows ascending)
+};
+
+}  // namespace tpg
+
 struct tpg_graph {
   int32_t n = 0;
   int32_t entry = 0, exit = 0;
@@ -19,6 +39,7 @@ struct tpg_graph {
   // canonical forward CSR (rows ascending, unique) and reverse CSR
   std::vector<int32_t> succ_ptr, succ;
   std::vector<int32_t> pred_ptr, pred;
+  tpg::Chains chains;  // the graph with its straight lines contracted
   uint64_t uid = 0;  // identifies the graph in device caches
   // structural features, computed once on first use
   mutable std::once_flag feat_once;
@@ -26,6 +47,10 @@ struct tpg_graph {
 };
 
 namespace tpg {
+
+// Chains of g.  block > 0: a chain holds vertices of one block of `block`
+// consecutive ids only (block 1: every vertex is a chain of its own).
+Chains contract_chains(const tpg_graph& g, int32_t block);
 
 void set_error(const char* fmt, ...);
 tpg_status fail(tpg_status s, const char* fmt, ...);

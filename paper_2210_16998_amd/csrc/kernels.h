@@ -32,6 +32,7 @@ struct TreeBufs {
   uint32_t* info;     // [rec_cap]
   int32_t* cstart;    // [rec_cap + 1] global index of the first child
   uint8_t* nch;       // [rec_cap] number of children (<= 64) or leaf kind (nch_code)
+  uint16_t* tl;       // [rec_cap] vertices of the node's chains, each chain once
   uint64_t* mask[2];  // visited sets of the odd levels, alternating [mask_cap * mask_words]
   int64_t rec_cap;
   int64_t mask_cap;
@@ -44,10 +45,25 @@ struct ExtArgs {
   TreeBufs t;
   LevelState* ls;
   int64_t tiles_target;  // one-pass tiles per level aimed at (tile size grows above it)
-  // level 1: paths <v> for the first vertices v = seed_lo .. seed_lo + seed_n - 1
-  // (node k holds vertex seed_lo + k; all vertices unless a call streams by
+  // level 1: paths <x> for the chains x = seed_lo .. seed_lo + seed_n - 1
+  // (node k holds chain seed_lo + k; all chains unless a call streams by
   // first-vertex range)
   int32_t seed_lo, seed_n;
+  uint64_t* tot;  // PathTotals of this tree, cleared by the seeding
+};
+
+// What the ranking reports of a tree, int64 words: the prime paths, the
+// closed cycles, then two histograms of kLenPad + max_comp bins by path
+// length (see k_path_lengths), then one uint32 per chain: the cycles closed
+// in its tree.
+struct PathTotals {
+  static constexpr int kPP = 0, kCycles = 1, kHist = 2, kLenPad = 2;
+  __host__ __device__ static int64_t bins(const DGraph& g) { return kLenPad + (int64_t)g.max_comp; }
+  __host__ __device__ static int64_t host_words(const DGraph& g) { return kHist + 2 * bins(g); }
+  __host__ __device__ static int64_t words(const DGraph& g) { return host_words(g) + ((int64_t)g.n + 1) / 2; }
+  __host__ __device__ static uint32_t* root_cycles(const DGraph& g, uint64_t* tot) {
+    return reinterpret_cast<uint32_t*>(tot + host_words(g));
+  }
 };
 
 // --- path tree -------------------------------------------------------------
@@ -69,33 +85,37 @@ hipError_t launch_fill(int W, const ExtArgs& a, int L, int64_t prev, int64_t bas
                        hipStream_t st);
 
 // --- ranking / materialization ---------------------------------------------
+// Lengths of all simple paths behind the nodes [first, n_nodes) (first: the
+// level-1 nodes are left to the host) into a.tot's histograms, and the cycles
+// closed in every root's tree.
+hipError_t launch_path_lengths(const ExtArgs& a, int64_t first, int64_t n_nodes, hipStream_t st);
 // sub_cnt: PP leaves per subtree (k_up), then rewritten top-down into the
-// rank of the subtree's first PP (or 0xFFFFFFFF when it has none).
-// n_cycles: kCycleSlots counters, zeroed before the sweep; a workgroup adds
-// its closed cycles to slot blockIdx.x % kCycleSlots (one address for all
-// would serialize the adds of a large level)
-constexpr int kCycleSlots = 64;
-hipError_t launch_up(const ExtArgs& a, int L, int64_t base, int64_t F, uint32_t* sub_cnt,
-                     unsigned long long* n_cycles, hipStream_t st);
-// mode 0: totals[0] = #PP (no change to the arrays) and, with n_cycles given,
-// n_cycles[kCycleSlots] = the sum of its slots; mode 1: level-1 ranks, root
-// leaves recorded (leaf_by_rank, pp_len = 1), and with rb given (roots =
-// every vertex, in id order) rb[v] = rank of the first prime path whose
-// first vertex is >= v (v = 0 .. n_roots).
-hipError_t launch_roots(const ExtArgs& a, int64_t n_roots, uint32_t* sub_cnt, int64_t* leaf_by_rank,
-                        int32_t* pp_len, int64_t* totals, int mode, int64_t* rb,
-                        unsigned long long* n_cycles, hipStream_t st);
-// parents of level L: ranks to the children; PP leaves record node and length
+// output position of the subtree's first PP (0xFFFFFFFF when it has none).
+hipError_t launch_up(const ExtArgs& a, int64_t base, int64_t F, uint32_t* sub_cnt, hipStream_t st);
+// rb[v - range_lo] = output position of the first prime path whose first
+// vertex is >= v, for the range_n vertices from range_lo (those of the seeded
+// chains) and one past them; the roots' positions into sub_cnt; the prime
+// paths and the closed cycles into a.tot.
+hipError_t launch_roots(const ExtArgs& a, const DChains& ch, int32_t range_lo, int32_t range_n,
+                        uint32_t* sub_cnt, int64_t* rb, hipStream_t st);
+// A prime path's leaf: its node (bits 0-31), the place in its first chain
+// where it starts (bits 32-44), and bit 63 when it is a cycle.
+constexpr int kLeafStartShift = 32;
+constexpr uint64_t kLeafCycle = 1ull << 63;
+// parents of level L: positions to the children; PP leaves record node and length
 hipError_t launch_down(const ExtArgs& a, int L, int64_t base, int64_t F, uint32_t* sub_cnt,
-                       int64_t* leaf_by_rank, int32_t* pp_len, hipStream_t st);
+                       uint64_t* leaf, int32_t* pp_len, hipStream_t st);
 // the same for depth + 1 levels in one launch (depth 1 or 2; base, F: the
-// run's top level L): counts of levels L .. L + depth, and ranks handed down
-// by the parents of levels L .. L + depth
+// run's top level L): counts of levels L .. L + depth, and positions handed
+// down by the parents of levels L .. L + depth
 hipError_t launch_up_run(const ExtArgs& a, int depth, int64_t base, int64_t F, uint32_t* sub_cnt,
-                         unsigned long long* n_cycles, hipStream_t st);
+                         hipStream_t st);
 hipError_t launch_down_run(const ExtArgs& a, int depth, int L, int64_t base, int64_t F,
-                           uint32_t* sub_cnt, int64_t* leaf_by_rank, int32_t* pp_len,
-                           hipStream_t st);
+                           uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len, hipStream_t st);
+// the prime paths that start inside the n_rot chains rot[] (see k_rotations)
+hipError_t launch_rotations(const ExtArgs& a, const DChains& ch, const int32_t* rot, int32_t n_rot,
+                            int32_t range_lo, const int64_t* rb, uint64_t* leaf, int32_t* pp_len,
+                            hipStream_t st);
 // What the prime-path writer also records for the test paths when the BFS
 // tables are ready (tp_len null: nothing): per prime path i, the length of
 // its test path, and lead[i] = the first index t >= 1 whose entry's BFS
@@ -110,8 +130,10 @@ struct PPWriteTp {
   // and e at lead (-1 if none), and the first vertex
   int4* lead;
 };
-hipError_t launch_pp_write(const ExtArgs& a, const int64_t* leaf_by_rank, const int64_t* pp_off,
-                           int64_t n_pp, int32_t* pp_vtx, const PPWriteTp& tp, hipStream_t st);
+// n: vertices of the union
+hipError_t launch_pp_write(const ExtArgs& a, const DChains& ch, int32_t n, const uint64_t* leaf,
+                           const int64_t* pp_off, int64_t n_pp, int32_t* pp_vtx,
+                           const PPWriteTp& tp, hipStream_t st);
 
 // --- scans -------------------------------------------------------------------
 // out[i] = add + sum(in[0..i)), *total = add + sum(in); n may be 0.
@@ -273,10 +295,10 @@ hipError_t launch_bfs_dist(const DGraph& g, const BfsOut& b, hipStream_t st);
 hipError_t launch_bfs_tables(const DGraph& g, const BfsOut& b, hipStream_t st);
 hipError_t launch_localize(const int32_t* loc, int32_t* v, int64_t n, hipStream_t st);
 // per-component output starts: pp_start[c] = rank of the first PP of c and
-// ppv_start[c] = offset of its first entry (after the PP offsets exist)
-hipError_t launch_comp_pp_starts(const DGraph& g, const uint32_t* sub_cnt, const int64_t* pp_off,
-                                 const int64_t* totals, int64_t* pp_start, int64_t* ppv_start,
-                                 hipStream_t st);
+// ppv_start[c] = offset of its first entry (after the PP offsets exist; rb:
+// see launch_roots, over all vertices; c = n_comp: the totals)
+hipError_t launch_comp_pp_starts(const DGraph& g, const int64_t* rb, const int64_t* pp_off,
+                                 int64_t* pp_start, int64_t* ppv_start, hipStream_t st);
 
 // test-path lengths, and rb[v] = first prime path with first vertex >= v
 // (v = 0..n); either output may be null (not computed)
@@ -347,8 +369,9 @@ inline int64_t pack_chunks(const PackDesc& e) {
 hipError_t launch_pack(const int64_t* src_off, const int32_t* src_vtx, const PackDesc* d,
                        int32_t n_desc, int64_t n_chunks, int64_t* dst_off, int32_t* dst_vtx,
                        hipStream_t st);
-// lvl_comp[c * 64 + min(L, 64) - 1] += paths of level L in component c
-hipError_t launch_level_comp_counts(const ExtArgs& a, int L, int64_t base, int64_t F,
-                                    int64_t* lvl_comp, hipStream_t st);
+// lvl_comp[c * 64 + min(L, 64) - 1] += simple paths of L entries in component
+// c, over the tree's n_nodes nodes
+hipError_t launch_level_comp_counts(const ExtArgs& a, int64_t n_nodes, int64_t* lvl_comp,
+                                    hipStream_t st);
 
 }  // namespace tpg

@@ -14,6 +14,19 @@
 //
 // How (the paper's asynchronous thread-per-vertex schedule and its per-vertex
 // path tables are not used):
+//  * The graph's straight lines (chains) are taken as single vertices, so a
+//    node of the tree is a path of chains, and level L holds the paths of L
+//    chains.  That is exact: an acyclic prime path is made of whole chains, a
+//    cycle through a chain starts at each of its vertices once (k_rotations),
+//    and the simple paths that begin or end inside a chain follow from the
+//    chains' lengths (k_path_lengths).  A CFG's statements sit mostly on such
+//    lines: the 400-vertex stress CFG has 189 chains, and its tree 1.85e8
+//    nodes on 36 levels instead of 4.66e8 on 213; a ~200-vertex CFG about a
+//    quarter of the nodes and half the levels.  Whole calls on it went from
+//    41.0 to 30.8 ms, on a 212-vertex CFG from 3.27 to 1.88 ms, on a
+//    1000-vertex one (174 chains) from 24.9 to 6.7 ms, and a batch of 4096
+//    from 24.1 to 11.1 ms.  "Vertex" below means a vertex of the graph of
+//    chains.
 //  * All paths of one level form a frontier of (parent index, vertex) nodes;
 //    the children of one parent are contiguous and in ascending successor
 //    order, and each node records where its children start and how many
@@ -50,7 +63,7 @@ namespace tpg {
 // ---------------------------------------------------------------------------
 // level 1
 // ---------------------------------------------------------------------------
-__global__ void k_seed(ExtArgs a) {
+__global__ void k_seed(ExtArgs a, int64_t tot_words) {
   const int n = a.seed_n;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   LevelState* ls = a.ls;
@@ -68,9 +81,11 @@ __global__ void k_seed(ExtArgs a) {
     const int v = a.seed_lo + (int)i;
     a.t.par[i] = -1;
     a.t.info[i] = make_info(v, a.g.loc[v], 0);
+    a.t.tl[i] = (uint16_t)a.g.len[v];
   }
+  for (int64_t k = i; k < tot_words; k += (int64_t)gridDim.x * blockDim.x) a.tot[k] = 0;
   // visited sets of level 1 (stored, buffer 0): one bit each, at the
-  // vertex's local id
+  // chain's local id
   const int W = a.t.mask_words;
   for (int64_t k = i; k < (int64_t)n * W; k += (int64_t)gridDim.x * blockDim.x) {
     const int q = (int)(k / n), j = (int)(k % n);
@@ -82,8 +97,10 @@ __global__ void k_seed(ExtArgs a) {
 hipError_t launch_seed(const ExtArgs& a, hipStream_t st) {
   if (a.seed_lo < 0 || a.seed_n < 1 || a.seed_lo + a.seed_n > a.g.n) return hipErrorInvalidValue;
   const int64_t work = std::max<int64_t>(kMaxLevels, (int64_t)a.seed_n * a.t.mask_words);
-  const int grid = (int)std::min<int64_t>(1024, (work + kBlock - 1) / kBlock + 1);
-  k_seed<<<grid, kBlock, 0, st>>>(a);
+  // one thread at least per seed
+  const int64_t grid = std::max<int64_t>((a.seed_n + kBlock - 1) / kBlock,
+                                         std::min<int64_t>(1024, (work + kBlock - 1) / kBlock + 1));
+  k_seed<<<(unsigned)grid, kBlock, 0, st>>>(a, PathTotals::words(a.g));
   return hipGetLastError();
 }
 
@@ -245,18 +262,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 &
     g.pp = s_graph + (a.g.pp - a.g.sp);
     g.p = s_graph + (a.g.p - a.g.sp);
     g.loc = s_graph + (a.g.loc - a.g.sp);
+    g.len = s_graph + (a.g.len - a.g.sp);
   }
   for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
     const int64_t tb = t * TR;
     // records and visited sets of the thread's parents (independent loads;
     // rows outside the level read parent 0's set and are ignored)
     uint32_t inf[ITEMS];
+    int tl[ITEMS];
     uint64_t m[ITEMS][W];
 #pragma unroll
     for (int i = 0; i < ITEMS; ++i) {
       const int64_t j = tb + i * NT + tid;
       const bool ok = i < ir && j < F;
       inf[i] = ok ? a.t.info[base + j] : F_CYC;
+      tl[i] = ok ? a.t.tl[base + j] : 0;
       path_mask_load<W>(a, L, prev, base + (ok ? j : 0), ok ? j : 0, m[i]);
     }
     // choice masks and the terminal filter
@@ -331,6 +351,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 &
           if (cg < a.t.rec_cap) {
             a.t.par[cg] = (int32_t)(base + j);
             a.t.info[cg] = make_info(w, v1l, wl == v1l ? F_CYC : 0u);
+            a.t.tl[cg] = (uint16_t)(tl[i] + (wl == v1l ? 0 : g.len[w]));
           }
           if (mnxt && wl != v1l && cl < a.t.mask_cap)
             store_child_mask<W>(mnxt, a.t.mask_cap, a.t.mask_words, cl, m[i], wl);
@@ -473,6 +494,7 @@ __global__ __launch_bounds__(kBlock) void k_extend_lb(ExtArgs a, int li) {
       if (cg < a.t.rec_cap) {
         a.t.par[cg] = (int32_t)(base + tb + o);
         a.t.info[cg] = make_info(w, v1l, wl == v1l ? F_CYC : 0u);
+        a.t.tl[cg] = (uint16_t)(a.t.tl[base + tb + o] + (wl == v1l ? 0 : a.g.len[w]));
       }
       if (mnxt && wl != v1l && cl < a.t.mask_cap) {
         uint64_t pm[W];
@@ -604,6 +626,7 @@ __global__ __launch_bounds__(kBlock) void k_fill(ExtArgs a, int L, int64_t prev,
     const int wl = w - cb;
     a.t.par[c] = (int32_t)(base + j);
     a.t.info[c] = make_info(w, v1l, wl == v1l ? F_CYC : 0u);
+    a.t.tl[c] = (uint16_t)(a.t.tl[base + j] + (wl == v1l ? 0 : a.g.len[w]));
     if (mnxt && wl != v1l) store_child_mask<W>(mnxt, a.t.mask_cap, a.t.mask_words, c - nbase, m, wl);
     ++c;
   }
@@ -641,158 +664,266 @@ hipError_t launch_fill(int W, const ExtArgs& a, int L, int64_t prev, int64_t bas
 // canonical order: subtree counts bottom-up, ranks top-down
 // ---------------------------------------------------------------------------
 // sub_cnt[g] = prime-path leaves in g's subtree (k_up), then rewritten top-down
-// into the rank of the subtree's first prime path, or kNoRank when the
-// subtree holds none (k_down then skips it after one 4-byte read).
+// into the output position of the subtree's first prime path, or kNoRank when
+// the subtree holds none (k_down then skips it after one 4-byte read).
 constexpr uint32_t kNoRank = 0xFFFFFFFFu;
 
-__global__ __launch_bounds__(kBlock) void k_up(ExtArgs a, int L, int64_t base, int64_t F,
-                                               uint32_t* sub_cnt, unsigned long long* n_cycles) {
-  __shared__ int32_t s_w[kBlock / 64];
-  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  int cyc = 0;
-  if (j < F) {
-    const int64_t g = base + j;
-    const uint8_t k = a.t.nch[g];
-    uint32_t c = 0;
-    if (k >= kNchPP) {
-      c = 1;
-      cyc = k == kNchCycle ? 1 : 0;
-    } else if (k) {
-      const int64_t c0 = a.t.cstart[g], c1 = c0 + k;
-      for (int64_t x = c0; x < c1; ++x) c += sub_cnt[x];
-    }
-    sub_cnt[g] = c;
+// Simple paths by length, from the nodes.  A node <x1 .. xk> of chains (k >=
+// 2, not a cycle) of T vertices stands for the paths that start at any of
+// x1's m1 vertices and end at any of xk's mk: lengths T - d, as many as there
+// are (a, b) with a < m1, b < mk, a + b = d.  A cycle of S vertices stands
+// for the paths that come back into x1, up to the vertex they started at:
+// m1 - d of length S + 1 - d for d < m1 (the m1 with d = 0 are the closed
+// cycles).  Both are sums over the bins from the top: with m1 = 1 two entries
+// of the first histogram, summed once, else three or four of the second,
+// summed twice.  Bins are counted in LDS (kept `copies` times, by lane, as a
+// wave's nodes share few lengths) and added to a.tot once per workgroup.
+// Reads 6 bytes a node.
+__global__ __launch_bounds__(kBlock) void k_path_lengths(ExtArgs a, int64_t first, int64_t n_nodes,
+                                                         int bins, int copies, int lds_roots) {
+  extern __shared__ unsigned long long s_hist[];
+  unsigned long long* h2 = s_hist;                                   // [bins * copies]
+  int32_t* h1 = reinterpret_cast<int32_t*>(h2 + bins * copies);      // [bins * copies]
+  uint32_t* s_cyc = reinterpret_cast<uint32_t*>(h1 + bins * copies); // [lds_roots]
+  uint32_t* g_cyc = PathTotals::root_cycles(a.g, a.tot);
+  const int tid = (int)threadIdx.x;
+  for (int i = tid; i < bins * copies; i += kBlock) {
+    h2[i] = 0;
+    h1[i] = 0;
   }
-  int32_t tot;
-  block_excl_scan<kBlock, int32_t>(cyc, tot, s_w);
-  if (threadIdx.x == 0 && tot) atomicAdd(n_cycles + blockIdx.x % kCycleSlots, (unsigned long long)tot);
-}
-
-hipError_t launch_up(const ExtArgs& a, int L, int64_t base, int64_t F, uint32_t* sub_cnt,
-                     unsigned long long* n_cycles, hipStream_t st) {
-  if (F == 0) return hipSuccess;
-  k_up<<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, L, base, F, sub_cnt, n_cycles);
-  return hipGetLastError();
-}
-
-// Level-1 nodes: an exclusive scan of their subtree counts gives the rank of
-// their first prime path.  totals[0] = #PP.  One workgroup of 1024 threads.
-__global__ __launch_bounds__(1024) void k_roots(ExtArgs a, int64_t n_roots, uint32_t* sub_cnt,
-                                                int64_t* leaf_by_rank, int32_t* pp_len,
-                                                int64_t* totals, int mode, int64_t* rb,
-                                                unsigned long long* n_cycles) {
-  __shared__ int64_t s_w[16];
-  int64_t carry = 0;
-  for (int64_t b = 0; b < n_roots; b += 1024) {
-    const int64_t i = b + threadIdx.x;
-    const int64_t c = i < n_roots ? (int64_t)sub_cnt[i] : 0;
-    int64_t tc;
-    const int64_t pc = block_excl_scan<1024, int64_t>(c, tc, s_w);
-    if (i < n_roots && mode == 1) {
-      const int64_t rank = carry + pc;
-      if (rb) rb[i] = rank;  // root i is vertex i: its first prime path's rank
-      sub_cnt[i] = (uint32_t)rank;
-      if (a.t.nch[i] >= kNchPP) {
-        leaf_by_rank[rank] = i;
-        pp_len[rank] = 1;
+  for (int i = tid; i < lds_roots; i += kBlock) s_cyc[i] = 0;
+  __syncthreads();
+  const int cp = tid & (copies - 1);
+  auto add1 = [&](int bin, int x) { atomicAdd(&h1[bin * copies + cp], x); };
+  auto add2 = [&](int bin, int x) {
+    atomicAdd(&h2[bin * copies + cp], (unsigned long long)(long long)x);
+  };
+  const int64_t step = (int64_t)gridDim.x * kBlock;
+  for (int64_t x = first + (int64_t)blockIdx.x * kBlock + tid; x < n_nodes; x += step) {
+    const uint32_t inf = a.t.info[x];
+    const int T = a.t.tl[x];
+    const int v = node_v(inf);
+    const int v1 = v - a.g.loc[v] + node_v1l(inf);
+    const int m1 = a.g.len[v1];
+    if (inf & F_CYC) {
+      atomicAdd(lds_roots ? &s_cyc[v1] : &g_cyc[v1], 1u);
+      if (m1 == 1) {
+        add1(T + 1, 1);
+        add1(T, -1);
+      } else {
+        add2(T + 1, m1);
+        add2(T, -(m1 + 1));
+        add2(T - m1, 1);
+      }
+    } else {
+      const int mk = a.g.len[v];
+      if (m1 == 1) {
+        add1(T, 1);
+        add1(T - mk, -1);
+      } else {
+        add2(T, 1);
+        add2(T - m1, -1);
+        add2(T - mk, -1);
+        add2(T - m1 - mk, 1);
       }
     }
-    carry += tc;
   }
-  if (threadIdx.x == 0 && mode == 0) totals[0] = carry;
-  if (mode == 0 && n_cycles && threadIdx.x < 64) {  // the first wave sums the cycle slots
-    unsigned long long c = 0;
-    for (int s = (int)threadIdx.x; s < kCycleSlots; s += 64) c += n_cycles[s];
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-      const unsigned lo = __shfl_xor((unsigned)c, d, 64), hi = __shfl_xor((unsigned)(c >> 32), d, 64);
-      c += ((unsigned long long)hi << 32) | lo;
+  __syncthreads();
+  unsigned long long* out = reinterpret_cast<unsigned long long*>(a.tot) + PathTotals::kHist;
+  for (int i = tid; i < bins; i += kBlock) {
+    long long c1 = 0;
+    unsigned long long c2 = 0;
+    for (int c = 0; c < copies; ++c) {
+      c1 += h1[i * copies + c];
+      c2 += h2[i * copies + c];
     }
-    if (threadIdx.x == 0) n_cycles[kCycleSlots] = c;
+    if (c1) atomicAdd(out + i, (unsigned long long)c1);
+    if (c2) atomicAdd(out + bins + i, c2);
   }
-  if (threadIdx.x == 0 && mode == 1 && rb) rb[n_roots] = carry;
+  for (int i = tid; i < lds_roots; i += kBlock)
+    if (s_cyc[i]) atomicAdd(&g_cyc[i], s_cyc[i]);
 }
 
-hipError_t launch_roots(const ExtArgs& a, int64_t n_roots, uint32_t* sub_cnt, int64_t* leaf_by_rank,
-                        int32_t* pp_len, int64_t* totals, int mode, int64_t* rb,
-                        unsigned long long* n_cycles, hipStream_t st) {
-  k_roots<<<1, 1024, 0, st>>>(a, n_roots, sub_cnt, leaf_by_rank, pp_len, totals, mode, rb,
-                              n_cycles);
+hipError_t launch_path_lengths(const ExtArgs& a, int64_t first, int64_t n_nodes, hipStream_t st) {
+  if (n_nodes <= first) return hipSuccess;
+  const int bins = (int)PathTotals::bins(a.g);
+  const int copies = bins <= 512 ? 4 : 1;
+  // every root's cycles counted in LDS when they fit 4 KiB (a large union's
+  // roots share few addresses anyway)
+  const int lds_roots = a.g.n <= 1024 ? a.g.n : 0;
+  const size_t lds = (size_t)bins * copies * 12 + sizeof(uint32_t) * (size_t)lds_roots;
+  if (lds > 65536) return hipErrorInvalidValue;
+  const int64_t grid = std::min<int64_t>(1024, (n_nodes - first + 8 * kBlock - 1) / (8 * kBlock));
+  k_path_lengths<<<(unsigned)grid, kBlock, lds, st>>>(a, first, n_nodes, bins, copies, lds_roots);
   return hipGetLastError();
 }
 
-// Parents of level L hand ranks to their children in slot order; a prime
-// path leaf records its node and length (L + 1 entries) under its rank.
-__global__ __launch_bounds__(kBlock) void k_down(ExtArgs a, int L, int64_t base, int64_t F,
-                                                 uint32_t* sub_cnt, int64_t* leaf_by_rank,
-                                                 int32_t* pp_len) {
+__global__ __launch_bounds__(kBlock) void k_up(ExtArgs a, int64_t base, int64_t F,
+                                               uint32_t* sub_cnt) {
   const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (j >= F) return;
   const int64_t g = base + j;
-  uint32_t r = sub_cnt[g];
   const uint8_t k = a.t.nch[g];
-  if (r == kNoRank || k == 0 || k >= kNchPP) return;
-  const int64_t c0 = a.t.cstart[g], c1 = c0 + k;
-  for (int64_t x = c0; x < c1; ++x) {
-    const uint32_t cc = sub_cnt[x];
-    sub_cnt[x] = cc ? r : kNoRank;
-    if (cc && a.t.nch[x] >= kNchPP) {
-      leaf_by_rank[r] = x;
-      pp_len[r] = L + 1;
+  uint32_t c = 0;
+  if (k >= kNchPP) {
+    c = 1;
+  } else if (k) {
+    const int64_t c0 = a.t.cstart[g], c1 = c0 + k;
+    for (int64_t x = c0; x < c1; ++x) c += sub_cnt[x];
+  }
+  sub_cnt[g] = c;
+}
+
+hipError_t launch_up(const ExtArgs& a, int64_t base, int64_t F, uint32_t* sub_cnt,
+                     hipStream_t st) {
+  if (F == 0) return hipSuccess;
+  k_up<<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, base, F, sub_cnt);
+  return hipGetLastError();
+}
+
+// Output positions by first vertex: a scan over the range's vertices in id
+// order of the prime paths that start there, which are all of its root's for
+// the head of a chain and its root's cycles for another vertex of one.  The
+// head's position is where its root's leaves go.  One workgroup, kRootItems
+// vertices per thread and step.
+constexpr int kRootItems = 8;
+__global__ __launch_bounds__(1024) void k_roots(ExtArgs a, DChains ch, int32_t range_lo,
+                                                int32_t range_n, uint32_t* sub_cnt, int64_t* rb) {
+  __shared__ int64_t s_w[16];
+  const uint32_t* cyc = PathTotals::root_cycles(a.g, a.tot);
+  int64_t carry = 0, cycles = 0;
+  for (int32_t b = 0; b < range_n; b += 1024 * kRootItems) {
+    const int32_t i0 = b + (int32_t)threadIdx.x * kRootItems;
+    int32_t root[kRootItems];  // the root whose head this vertex is (-1: not a head)
+    int64_t c[kRootItems];
+    int64_t sum = 0;
+#pragma unroll
+    for (int j = 0; j < kRootItems; ++j) {
+      root[j] = -1;
+      c[j] = 0;
+      if (i0 + j < range_n) {
+        const int v = range_lo + i0 + j;
+        const int x = ch.of[v];
+        const uint32_t cx = cyc[x];
+        cycles += cx;
+        c[j] = cx;
+        if (ch.pos[v] == 0) {
+          root[j] = x - a.seed_lo;
+          c[j] = sub_cnt[root[j]];
+        }
+        sum += c[j];
+      }
+    }
+    int64_t total;
+    int64_t at = carry + block_excl_scan<1024, int64_t>(sum, total, s_w);
+#pragma unroll
+    for (int j = 0; j < kRootItems; ++j) {
+      if (i0 + j < range_n) rb[i0 + j] = at;
+      if (root[j] >= 0) sub_cnt[root[j]] = c[j] ? (uint32_t)at : kNoRank;
+      at += c[j];
+    }
+    carry += total;
+  }
+  int64_t all;
+  (void)block_excl_scan<1024, int64_t>(cycles, all, s_w);
+  if (threadIdx.x == 0) {
+    rb[range_n] = carry;
+    a.tot[PathTotals::kPP] = (uint64_t)carry;
+    a.tot[PathTotals::kCycles] = (uint64_t)all;
+  }
+}
+
+hipError_t launch_roots(const ExtArgs& a, const DChains& ch, int32_t range_lo, int32_t range_n,
+                        uint32_t* sub_cnt, int64_t* rb, hipStream_t st) {
+  k_roots<<<1, 1024, 0, st>>>(a, ch, range_lo, range_n, sub_cnt, rb);
+  return hipGetLastError();
+}
+
+// A prime-path leaf's record under its output position: a cycle's path holds
+// its first vertex twice.
+__device__ __forceinline__ void put_leaf(const ExtArgs& a, int64_t x, uint8_t k, uint32_t r,
+                                         uint64_t* leaf, int32_t* pp_len) {
+  const bool cyc = k == kNchCycle;
+  leaf[r] = (uint64_t)x | (cyc ? kLeafCycle : 0ull);
+  pp_len[r] = (int32_t)a.t.tl[x] + (cyc ? 1 : 0);
+}
+
+// x (position r, nch code k) hands positions to its children in slot order;
+// with D > 0 each internal child with prime paths below then does the same
+// for its own children.
+template <int D>
+__device__ __forceinline__ void down_node(const ExtArgs& a, int64_t x, uint8_t k, uint32_t r,
+                                          uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len) {
+  if (k == 0 || k >= kNchPP) return;
+  const int64_t c0 = a.t.cstart[x], c1 = c0 + k;
+  for (int64_t y = c0; y < c1; ++y) {
+    const uint32_t cc = sub_cnt[y];
+    const uint8_t ky = a.t.nch[y];
+    sub_cnt[y] = cc ? r : kNoRank;
+    if (cc) {
+      if (ky >= kNchPP) {
+        put_leaf(a, y, ky, r, leaf, pp_len);
+      } else if constexpr (D > 0) {
+        down_node<D - 1>(a, y, ky, r, sub_cnt, leaf, pp_len);
+      }
     }
     r += cc;
   }
 }
 
+// Parents of levels L .. L + D in one launch (thread per node of L).  A
+// level-1 node can be a leaf itself.
+template <int D>
+__global__ __launch_bounds__(kBlock) void k_down_run(ExtArgs a, int L, int64_t base, int64_t F,
+                                                     uint32_t* sub_cnt, uint64_t* leaf,
+                                                     int32_t* pp_len) {
+  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (j >= F) return;
+  const uint32_t r = sub_cnt[base + j];
+  if (r == kNoRank) return;
+  const uint8_t k = a.t.nch[base + j];
+  if (L == 1 && k >= kNchPP) put_leaf(a, base + j, k, r, leaf, pp_len);
+  down_node<D>(a, base + j, k, r, sub_cnt, leaf, pp_len);
+}
+
 hipError_t launch_down(const ExtArgs& a, int L, int64_t base, int64_t F, uint32_t* sub_cnt,
-                       int64_t* leaf_by_rank, int32_t* pp_len, hipStream_t st) {
+                       uint64_t* leaf, int32_t* pp_len, hipStream_t st) {
   if (F == 0) return hipSuccess;
-  k_down<<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, L, base, F, sub_cnt,
-                                                                    leaf_by_rank, pp_len);
+  k_down_run<0><<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, L, base, F, sub_cnt,
+                                                                          leaf, pp_len);
   return hipGetLastError();
 }
 
-// D + 1 levels per launch (D = 1, 2): a launch costs ~7 us however little it
-// does, and a sweep has one per level.  One thread per node x of the run's
-// top level does the per-level work for x and for its descendants down to D
-// levels below (they are x's alone, and each count or rank is read right
-// after this thread wrote it); the recursion unrolls at compile time.
-template <int D>
-__device__ __forceinline__ uint32_t up_node(const ExtArgs& a, int64_t x, uint32_t* sub_cnt,
-                                            int& cyc) {
-  const uint8_t k = a.t.nch[x];
-  uint32_t c = 0;
-  if (k >= kNchPP) {
-    c = 1;
-    cyc += k == kNchCycle ? 1 : 0;
-  } else if (k) {
-    const int64_t c0 = a.t.cstart[x], c1 = c0 + k;
-    for (int64_t y = c0; y < c1; ++y) {
-      if constexpr (D > 0)
-        c += up_node<D - 1>(a, y, sub_cnt, cyc);
-      else
-        c += sub_cnt[y];
-    }
-  }
-  sub_cnt[x] = c;
-  return c;
+hipError_t launch_down_run(const ExtArgs& a, int depth, int L, int64_t base, int64_t F,
+                           uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len, hipStream_t st) {
+  if (F == 0) return hipSuccess;
+  if (depth != 1) return hipErrorInvalidValue;
+  k_down_run<1><<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, L, base, F, sub_cnt,
+                                                                          leaf, pp_len);
+  return hipGetLastError();
 }
 
-// The same for D = 1 with the loads batched: x's children's codes and child
-// ranges kSweepBatch at a time, then their own children's counts all
-// together, so that a thread waits for about three load latencies instead of
-// a few per child.  (The down sweep keeps its per-child loop: batched the
-// same way it measured slower, its stores and rank chain per child.)
+// Two levels per launch (depth 1): a launch costs ~7 us however little it
+// does, and a sweep has one per level.  One thread per node x of the run's
+// upper level does the work for x and for its children (they are x's alone,
+// and each count is read right after this thread wrote it).  The loads are
+// batched: x's children's codes and child ranges kSweepBatch at a time, then
+// their own children's counts all together, so that a thread waits for about
+// three load latencies instead of a few per child.  (The down sweep keeps its
+// per-child loop: batched the same way it measured slower, its stores and
+// position chain per child.)
 constexpr int kSweepBatch = 4;
 __device__ __forceinline__ bool nch_internal(uint8_t k) { return k >= 1 && k < kNchPP; }
 
-__device__ __forceinline__ void up_node_batched(const ExtArgs& a, int64_t x, uint32_t* sub_cnt,
-                                                int& cyc) {
+__global__ __launch_bounds__(kBlock) void k_up_run(ExtArgs a, int64_t base, int64_t F,
+                                                   uint32_t* sub_cnt) {
+  const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (t >= F) return;
+  const int64_t x = base + t;
   const uint8_t k = a.t.nch[x];
   uint32_t c = 0;
   if (k >= kNchPP) {
     c = 1;
-    cyc += k == kNchCycle ? 1 : 0;
   } else if (k) {
     const int64_t c0 = a.t.cstart[x];
     for (int j0 = 0; j0 < k; j0 += kSweepBatch) {
@@ -806,10 +937,7 @@ __device__ __forceinline__ void up_node_batched(const ExtArgs& a, int64_t x, uin
       }
       uint32_t cy[kSweepBatch];
 #pragma unroll
-      for (int j = 0; j < kSweepBatch; ++j) {
-        cy[j] = ky[j] >= kNchPP ? 1u : 0u;
-        cyc += ky[j] == kNchCycle ? 1 : 0;
-      }
+      for (int j = 0; j < kSweepBatch; ++j) cy[j] = ky[j] >= kNchPP ? 1u : 0u;
       for (int g0 = 0;; g0 += kSweepBatch) {
         uint32_t v[kSweepBatch][kSweepBatch];
 #pragma unroll
@@ -838,83 +966,74 @@ __device__ __forceinline__ void up_node_batched(const ExtArgs& a, int64_t x, uin
   sub_cnt[x] = c;
 }
 
-template <int D>
-__global__ __launch_bounds__(kBlock) void k_up_run(ExtArgs a, int64_t base, int64_t F,
-                                                   uint32_t* sub_cnt,
-                                                   unsigned long long* n_cycles) {
-  __shared__ int32_t s_w[kBlock / 64];
-  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  int cyc = 0;
-  if (j < F) {
-    if constexpr (D == 1)
-      up_node_batched(a, base + j, sub_cnt, cyc);
-    else
-      up_node<D>(a, base + j, sub_cnt, cyc);
-  }
-  int32_t tot;
-  block_excl_scan<kBlock, int32_t>(cyc, tot, s_w);
-  if (threadIdx.x == 0 && tot) atomicAdd(n_cycles + blockIdx.x % kCycleSlots, (unsigned long long)tot);
-}
-
 hipError_t launch_up_run(const ExtArgs& a, int depth, int64_t base, int64_t F, uint32_t* sub_cnt,
-                         unsigned long long* n_cycles, hipStream_t st) {
+                         hipStream_t st) {
   if (F == 0) return hipSuccess;
-  const unsigned grid = (unsigned)((F + kBlock - 1) / kBlock);
-  if (depth == 1)
-    k_up_run<1><<<grid, kBlock, 0, st>>>(a, base, F, sub_cnt, n_cycles);
-  else if (depth == 2)
-    k_up_run<2><<<grid, kBlock, 0, st>>>(a, base, F, sub_cnt, n_cycles);
-  else
-    return hipErrorInvalidValue;
+  if (depth != 1) return hipErrorInvalidValue;
+  k_up_run<<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, base, F, sub_cnt);
   return hipGetLastError();
 }
 
-// x (level L, rank r, nch code k) hands ranks to its children; with D > 0
-// each ranked internal child then does the same for its own children.
-template <int D>
-__device__ __forceinline__ void down_node(const ExtArgs& a, int L, int64_t x, uint8_t k,
-                                          uint32_t r, uint32_t* sub_cnt, int64_t* leaf_by_rank,
-                                          int32_t* pp_len) {
-  if (k == 0 || k >= kNchPP) return;
-  const int64_t c0 = a.t.cstart[x], c1 = c0 + k;
-  for (int64_t y = c0; y < c1; ++y) {
-    const uint32_t cc = sub_cnt[y];
-    const uint8_t ky = a.t.nch[y];
-    sub_cnt[y] = cc ? r : kNoRank;
-    if (cc) {
-      if (ky >= kNchPP) {
-        leaf_by_rank[r] = y;
-        pp_len[r] = L + 1;
-      } else if constexpr (D > 0) {
-        down_node<D - 1>(a, L + 1, y, ky, r, sub_cnt, leaf_by_rank, pp_len);
-      }
+// A cycle of chains found from the head of its first chain x is a prime path
+// from each of x's other vertices too: the j-th vertex's prime paths are the
+// root's cycles, in the same order (they pass the rest of x, then differ
+// where the root's do).  One workgroup per chain of two or more vertices
+// takes its root's leaves 16 Ki at a time and gives the cycles among them
+// their places after every other vertex's position.
+constexpr int kRotItems = 16;
+__global__ __launch_bounds__(1024) void k_rotations(ExtArgs a, DChains ch, const int32_t* rot,
+                                                    int32_t range_lo, const int64_t* rb,
+                                                    uint64_t* leaf, int32_t* pp_len) {
+  __shared__ int32_t s_w[16];
+  const int x = rot[blockIdx.x];
+  if (PathTotals::root_cycles(a.g, a.tot)[x] == 0) return;
+  const int o = ch.off[x], m = ch.off[x + 1] - o;
+  const int head = ch.v[o] - range_lo;
+  const int64_t p0 = rb[head], p1 = rb[head + 1];
+  const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
+  int64_t carry = 0;
+  for (int64_t b = p0; b < p1; b += 1024 * kRotItems) {
+    // a wave's leaves are consecutive: 64 at a time
+    const int64_t w0 = b + (int64_t)wave * 64 * kRotItems + lane;
+    uint64_t lf[kRotItems];
+#pragma unroll
+    for (int i = 0; i < kRotItems; ++i) lf[i] = w0 + 64 * i < p1 ? leaf[w0 + 64 * i] : 0ull;
+    int mine = 0;
+#pragma unroll
+    for (int i = 0; i < kRotItems; ++i) mine += __builtin_popcountll(__ballot(lf[i] >> 63));
+    if (lane == 0) s_w[wave] = mine;
+    __syncthreads();
+    int64_t at = carry;
+    int all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      at += w < wave ? s_w[w] : 0;
+      all += s_w[w];
     }
-    r += cc;
+    carry += all;
+#pragma unroll
+    for (int i = 0; i < kRotItems; ++i) {
+      const uint64_t cyc = __ballot(lf[i] >> 63);
+      if (lf[i] >> 63) {
+        const int64_t k = at + __builtin_popcountll(cyc & ((1ull << lane) - 1));
+        const int32_t len = pp_len[w0 + 64 * i];
+        for (int j = 1; j < m; ++j) {
+          const int64_t r = rb[ch.v[o + j] - range_lo] + k;
+          leaf[r] = lf[i] | (uint64_t)j << kLeafStartShift;
+          pp_len[r] = len;
+        }
+      }
+      at += __builtin_popcountll(cyc);
+    }
+    __syncthreads();  // s_w is read before the next step writes it
   }
 }
 
-// Parents of levels L .. L + D in one launch (thread per node of L).
-template <int D>
-__global__ __launch_bounds__(kBlock) void k_down_run(ExtArgs a, int L, int64_t base, int64_t F,
-                                                     uint32_t* sub_cnt, int64_t* leaf_by_rank,
-                                                     int32_t* pp_len) {
-  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (j >= F) return;
-  const uint32_t r = sub_cnt[base + j];
-  if (r != kNoRank) down_node<D>(a, L, base + j, a.t.nch[base + j], r, sub_cnt, leaf_by_rank, pp_len);
-}
-
-hipError_t launch_down_run(const ExtArgs& a, int depth, int L, int64_t base, int64_t F,
-                           uint32_t* sub_cnt, int64_t* leaf_by_rank, int32_t* pp_len,
-                           hipStream_t st) {
-  if (F == 0) return hipSuccess;
-  const unsigned grid = (unsigned)((F + kBlock - 1) / kBlock);
-  if (depth == 1)
-    k_down_run<1><<<grid, kBlock, 0, st>>>(a, L, base, F, sub_cnt, leaf_by_rank, pp_len);
-  else if (depth == 2)
-    k_down_run<2><<<grid, kBlock, 0, st>>>(a, L, base, F, sub_cnt, leaf_by_rank, pp_len);
-  else
-    return hipErrorInvalidValue;
+hipError_t launch_rotations(const ExtArgs& a, const DChains& ch, const int32_t* rot, int32_t n_rot,
+                            int32_t range_lo, const int64_t* rb, uint64_t* leaf, int32_t* pp_len,
+                            hipStream_t st) {
+  if (n_rot <= 0) return hipSuccess;
+  k_rotations<<<(unsigned)n_rot, 1024, 0, st>>>(a, ch, rot, range_lo, rb, leaf, pp_len);
   return hipGetLastError();
 }
 
@@ -935,22 +1054,43 @@ hipError_t launch_down_run(const ExtArgs& a, int depth, int L, int64_t base, int
 constexpr int kPPSeg = 16;
 constexpr int kPPRow = kPPSeg + 1;  // LDS row stride (odd: rows fall in different banks)
 
-__global__ __launch_bounds__(kBlock) void k_pp_write(ExtArgs a, const int64_t* leaf_by_rank,
-                                                     const int64_t* pp_off, int64_t n_pp,
-                                                     int32_t* pp_vtx, PPWriteTp tp) {
+// LDS: the chains' rows (off, v) are staged as 16-bit words (the union has at
+// most kStageVertices vertices), so that a step inside a chain costs an LDS
+// read; only a step to the parent's chain loads from the tree.
+constexpr int kStageVertices = 2048;
+
+template <bool LDS>
+__global__ __launch_bounds__(kBlock) void k_pp_write(ExtArgs a, DChains ch, int32_t n,
+                                                     const uint64_t* leaf, const int64_t* pp_off,
+                                                     int64_t n_pp, int32_t* pp_vtx, PPWriteTp tp) {
   __shared__ int32_t s_row[kBlock * kPPRow];
   __shared__ int64_t s_lo[kBlock];
   __shared__ int32_t s_len[kBlock];
   __shared__ int32_t s_done[kBlock];
+  extern __shared__ uint16_t s_ch[];  // v [n], then off [g.n + 1]
   const int tid = (int)threadIdx.x, lane = lane_id(), wb = tid - lane;
   const int64_t i = (int64_t)blockIdx.x * kBlock + tid;
+  if constexpr (LDS) {
+    for (int k = tid; k < n; k += kBlock) s_ch[k] = (uint16_t)ch.v[k];
+    for (int k = tid; k <= a.g.n; k += kBlock) s_ch[n + k] = (uint16_t)ch.off[k];
+    __syncthreads();
+  }
+  auto row_of = [&](int x) { return LDS ? (int)s_ch[n + x] : ch.off[x]; };
+  auto vertex = [&](int k) { return LDS ? (int)s_ch[k] : ch.v[k]; };
   int64_t lo = 0;
   int32_t len = 0;
-  int32_t x = -1;
+  int32_t up = -1;          // parent of the node whose chain is being walked
+  int32_t c0 = 0, at = -1;  // the chain's row begins at c0; the next vertex is v[at]
   if (i < n_pp) {
     lo = pp_off[i];
     len = (int32_t)(pp_off[i + 1] - lo);
-    x = (int32_t)leaf_by_rank[i];
+    const uint64_t lf = leaf[i];
+    const int32_t x = (int32_t)(lf & 0xFFFFFFFFu);
+    const int c = node_v(a.t.info[x]);
+    up = a.t.par[x];
+    c0 = row_of(c);
+    // a cycle ends at the vertex it starts at
+    at = (lf & kLeafCycle) ? c0 + (int)((lf >> kLeafStartShift) & 0x1FFF) : row_of(c + 1) - 1;
   }
   s_lo[tid] = lo;
   s_len[tid] = len;
@@ -974,10 +1114,15 @@ __global__ __launch_bounds__(kBlock) void k_pp_write(ExtArgs a, const int64_t* l
     for (int m = kPPSeg - 1; m >= 0; --m) {
       const int k = kb + m;
       v[m] = -1;
-      if (k < len && x >= 0) {
-        v[m] = node_v(a.t.info[x]);
-        x = a.t.par[x];
+      if (k < len) {
+        v[m] = vertex(at);
         done = k;
+        if (--at < c0 && up >= 0) {  // on to the parent's chain
+          const int c = node_v(a.t.info[up]);
+          up = a.t.par[up];
+          c0 = row_of(c);
+          at = row_of(c + 1) - 1;
+        }
       }
     }
 #pragma unroll
@@ -1025,11 +1170,17 @@ __global__ __launch_bounds__(kBlock) void k_pp_write(ExtArgs a, const int64_t* l
   }
 }
 
-hipError_t launch_pp_write(const ExtArgs& a, const int64_t* leaf_by_rank, const int64_t* pp_off,
-                           int64_t n_pp, int32_t* pp_vtx, const PPWriteTp& tp, hipStream_t st) {
+hipError_t launch_pp_write(const ExtArgs& a, const DChains& ch, int32_t n, const uint64_t* leaf,
+                           const int64_t* pp_off, int64_t n_pp, int32_t* pp_vtx,
+                           const PPWriteTp& tp, hipStream_t st) {
   if (n_pp == 0) return hipSuccess;
-  k_pp_write<<<(unsigned)((n_pp + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, leaf_by_rank, pp_off,
-                                                                          n_pp, pp_vtx, tp);
+  const unsigned grid = (unsigned)((n_pp + kBlock - 1) / kBlock);
+  if (n <= kStageVertices) {
+    const size_t lds = sizeof(uint16_t) * ((size_t)n + a.g.n + 1);
+    k_pp_write<true><<<grid, kBlock, lds, st>>>(a, ch, n, leaf, pp_off, n_pp, pp_vtx, tp);
+  } else {
+    k_pp_write<false><<<grid, kBlock, 0, st>>>(a, ch, n, leaf, pp_off, n_pp, pp_vtx, tp);
+  }
   return hipGetLastError();
 }
 
@@ -1037,43 +1188,49 @@ hipError_t launch_pp_write(const ExtArgs& a, const int64_t* leaf_by_rank, const 
 
 namespace tpg {
 
-// After the ranks and the offsets exist: first prime path of each component
-// (its first root's rank) and the offset of that path's first entry.
-__global__ void k_comp_pp_starts(DGraph g, const uint32_t* sub_cnt, const int64_t* pp_off,
-                                 const int64_t* totals, int64_t* pp_start, int64_t* ppv_start) {
+// After the positions and the offsets exist: first prime path of each
+// component and the offset of that path's first entry.
+__global__ void k_comp_pp_starts(DGraph g, const int64_t* rb, const int64_t* pp_off,
+                                 int64_t* pp_start, int64_t* ppv_start) {
   const int c = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (c < g.n_comp) {
-    const int64_t r = sub_cnt[g.cbase[c]];
-    pp_start[c] = r;
-    ppv_start[c] = pp_off[r];
-  }
-  if (c == g.n_comp) {
-    pp_start[c] = totals[0];
-    ppv_start[c] = pp_off[totals[0]];
-  }
+  if (c > g.n_comp) return;
+  const int64_t r = rb[g.cbase[c]];
+  pp_start[c] = r;
+  ppv_start[c] = pp_off[r];
 }
 
-hipError_t launch_comp_pp_starts(const DGraph& g, const uint32_t* sub_cnt, const int64_t* pp_off,
-                                 const int64_t* totals, int64_t* pp_start, int64_t* ppv_start,
-                                 hipStream_t st) {
+hipError_t launch_comp_pp_starts(const DGraph& g, const int64_t* rb, const int64_t* pp_off,
+                                 int64_t* pp_start, int64_t* ppv_start, hipStream_t st) {
   k_comp_pp_starts<<<(unsigned)((g.n_comp + 1 + kBlock - 1) / kBlock), kBlock, 0, st>>>(
-      g, sub_cnt, pp_off, totals, pp_start, ppv_start);
+      g, rb, pp_off, pp_start, ppv_start);
   return hipGetLastError();
 }
 
-__global__ void k_level_comp_counts(ExtArgs a, int L, int64_t base, int64_t F, int64_t* lvl) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= F) return;
-  const int c = a.g.comp[node_v(a.t.info[base + j])];
-  const int b = (L < 64 ? L : 64) - 1;
-  atomicAdd((unsigned long long*)&lvl[(int64_t)c * 64 + b], 1ull);
+// Every node's paths by length, one by one (see k_path_lengths; level 1: the
+// paths inside one chain).
+__global__ void k_level_comp_counts(ExtArgs a, int64_t n_nodes, int64_t* lvl) {
+  const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (x >= n_nodes) return;
+  const uint32_t inf = a.t.info[x];
+  const int T = a.t.tl[x], v = node_v(inf);
+  const int m1 = a.g.len[v - a.g.loc[v] + node_v1l(inf)], mk = a.g.len[v];
+  const bool cyc = inf & F_CYC, one = x < a.seed_n;
+  unsigned long long* row = reinterpret_cast<unsigned long long*>(lvl) + (int64_t)a.g.comp[v] * 64;
+  const int top = cyc ? T + 1 : T, nd = one || cyc ? m1 : m1 + mk - 1;
+  unsigned long long deep = 0;
+  for (int d = 0; d < nd; ++d) {
+    const int c = cyc ? m1 - d : one ? d + 1 : min(min(d + 1, nd - d), min(m1, mk));
+    if (top - d >= 64) deep += (unsigned long long)c;
+    else atomicAdd(row + (top - d) - 1, (unsigned long long)c);
+  }
+  if (deep) atomicAdd(row + 63, deep);
 }
 
-hipError_t launch_level_comp_counts(const ExtArgs& a, int L, int64_t base, int64_t F,
-                                    int64_t* lvl_comp, hipStream_t st) {
-  if (F == 0) return hipSuccess;
-  k_level_comp_counts<<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, L, base, F,
-                                                                                lvl_comp);
+hipError_t launch_level_comp_counts(const ExtArgs& a, int64_t n_nodes, int64_t* lvl_comp,
+                                    hipStream_t st) {
+  if (n_nodes == 0) return hipSuccess;
+  k_level_comp_counts<<<(unsigned)((n_nodes + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, n_nodes,
+                                                                                      lvl_comp);
   return hipGetLastError();
 }
 

@@ -126,7 +126,6 @@ extern "C" tpg_status tpg_prime_path_types_noalloc(const tpg_graph* g, const int
   d.cexit = tail + 3;
   d.n = n;
   d.n_comp = 1;
-  d.n_stage = (int32_t)(d.comp - d.sp);
   TPG_HIP(hipMemcpyAsync((void*)d.sp, g->succ_ptr.data(), 4 * g->succ_ptr.size(),
                          hipMemcpyHostToDevice, st));
   if (m)
