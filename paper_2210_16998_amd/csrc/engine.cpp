@@ -36,6 +36,7 @@ struct HostUnion {
   int32_t xn = 0;  // chains
   std::vector<int32_t> xsp{0}, xs, xpp{0}, xp, xloc, xlen, xcomp, xcbase{0};
   std::vector<int32_t> choff{0}, chv, chof, chpos;  // see DChains
+  std::vector<int32_t> gbase{0};  // arcs off the BFS tree and exit paths, by component
   std::vector<int32_t> xhead;                       // first vertex of every chain
   std::vector<int32_t> rot;  // chains of two or more vertices, ascending
   std::vector<uint64_t> uids;
@@ -108,7 +109,8 @@ struct tpg_workspace {
   DevBuf g_csr;
   DGraph dg{}, xg{};   // the union, and the union of its chains
   DChains ch{};
-  const int32_t* d_rot = nullptr;  // HostUnion::rot
+  const int32_t* d_gbase = nullptr;  // HostUnion::gbase
+  const int32_t* d_rot = nullptr;    // HostUnion::rot
 
   // path tree
   DevBuf par, info, cstart, nch, tl, mask0, mask1, ls;
@@ -118,13 +120,15 @@ struct tpg_workspace {
   DevBuf sub_cnt, pp_len, leaf_by_rank, totals;  // totals: see PathTotals
   // scans
   DevBuf scan_status, scan_ctr, scalars;
-  DevBuf scan2_status, scalars2;  // the side stream's own scan scratch
+  DevBuf scan2_status;  // the side stream's own scan scratch
   // test paths
-  DevBuf bfs_i32, pfx_off, sfx_off, pfx, sfx, pfx_pk, sfx_pk;
-  DevBuf tp_len, tp_off, tp_vtx, tp_key, tp_pk, idx0, idx1, grp_cnt, rb0, rb1, merge_split, tp_lead;
-  bool tp_len_ready = false;  // the prime-path writer filled tp_len and tp_lead for this union
-  bool rb_ready = false;      // the root ranking wrote the runs by first vertex into rb0
-  DevBuf keep_cnt, keep_len, keep_pos, keep_voff, comp_cnt;
+  DevBuf bfs_i32, pfx_off, sfx_off, pfx, sfx;
+  DevBuf rb0;                         // output positions by first vertex
+  DevBuf tp_links, tp_order, tp_first;  // TpTree's chain links, the arcs' order and places
+  DevBuf canon, leaf_canon;           // see TpTree
+  DevBuf row_src, row_len;            // rows of a reordered set: source path, length
+  DevBuf spl_off, spl_vtx;            // the covering's spliced test paths
+  DevBuf chunk_off;                   // rebased offsets of a streamed chunk
   // per-level, per-component counts (batched labels)
   DevBuf lvl_comp;
   // outputs: out[0] single-graph calls, out[k] the unions of a batch
@@ -151,17 +155,17 @@ struct tpg_workspace {
     std::vector<uint8_t> key;
     hipGraphExec_t exec = nullptr;
   };
-  SeqGraph rank_up, rank_down;
+  SeqGraph rank_up, rank_down, tp_sweeps;
   // level-1 seeds of the next build: chains seed_lo .. seed_lo + seed_n - 1
   // (seed_n < 0: every chain of the union), which hold the first vertices
   // range_lo .. range_lo + range_n - 1
   int32_t seed_lo = 0, seed_n = -1;
   int32_t range_lo = 0, range_n = 0;
   DevBuf digest;  // [2] set digest of the last digest_set call
-  DevBuf grp_key, grp_hist;  // last-vertex grouping: keys, per-tile histograms
+  DevBuf grp_key, grp_hist, grp_base;  // last-vertex grouping: keys, per-tile histograms, their scan
   // longest-first covering: prime-path hash table, covering pairs, order,
-  // coverers per path, round states, chosen list
-  DevBuf cov_keys, cov_vals, cov_misc, pair_p, pair_q, cov_pos, gstate0, gstate1, cov_flag;
+  // coverers per path, round states
+  DevBuf cov_keys, cov_vals, cov_misc, cov_cnt, cov_at, pair_p, pair_q, cov_pos, gstate0, gstate1;
   // components and prime-path types: Tarjan scratch, labels, flags, counters
   // (n_comp int32 at 0, type counts u64 at 64), a host path set's copy, types
   DevBuf scc_work, scc_comp, scc_flags, scc_misc, ty_off, ty_vtx, ty_types;
@@ -357,6 +361,8 @@ void add_component(HostUnion& U, const tpg_graph* g, int32_t block = 0) {
   U.xn += c.n;
   U.cbase.push_back(U.n);
   U.xcbase.push_back(U.xn);
+  // every chain but the entry's has one BFS-tree arc; the exit's path counts too
+  U.gbase.push_back(U.gbase.back() + (int32_t)c.s.size() - (c.n - 1) + 1);
   U.n_comp += 1;
   U.W = std::max(U.W, pow2_words(c.n));
   U.Wu = std::max(U.Wu, (c.n + 63) / 64);
@@ -372,7 +378,7 @@ tpg_status upload_union(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   const std::vector<int32_t>* parts[] = {
       &U.sp, &U.s, &U.pp, &U.p, &U.loc, &U.comp, &U.cbase, &U.centry, &U.cexit,
       &U.xsp, &U.xs, &U.xpp, &U.xp, &U.xloc, &U.xlen, &U.xcomp, &U.xcbase,
-      &U.choff, &U.chv, &U.chof, &U.chpos, &U.rot};
+      &U.choff, &U.chv, &U.chof, &U.chpos, &U.gbase, &U.rot};
   constexpr int kParts = sizeof(parts) / sizeof(parts[0]);
   size_t words = 0, at[kParts];
   for (int i = 0; i < kParts; ++i) {
@@ -415,7 +421,8 @@ tpg_status upload_union(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   ws->dg = d;
   ws->xg = x;
   ws->ch = DChains{q + at[17], q + at[18], q + at[19], q + at[20]};
-  ws->d_rot = q + at[21];
+  ws->d_gbase = q + at[21];
+  ws->d_rot = q + at[22];
   ws->union_uids = U.uids;
   return TPG_OK;
 }
@@ -857,6 +864,7 @@ struct PPResult {
 };
 
 BfsOut bfs_views(tpg_workspace* ws, int n);
+TpTree tp_tree(tpg_workspace* ws, int xn);
 
 // Simple paths by length (index: entries) from the histograms that the device
 // counted over the nodes below level 1 (see k_path_lengths) and the seeded
@@ -916,13 +924,16 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
     for (int L = R.Lmax; L >= 1 && e == hipSuccess;) {
       const int n = std::min(kRun, L);  // levels L - n + 1 .. L
       const int top = L - n + 1;
-      e = n > 1 ? launch_up_run(a, n - 1, R.off[top], R.count[top], sc, st)
+      e = n > 1 ? launch_up_run(a, R.off[top], R.count[top], sc, st)
                 : launch_up(a, R.off[top], R.count[top], sc, st);
       L -= n;
     }
     if (e == hipSuccess) e = launch_roots(a, ws->ch, range_lo, range_n, sc, rb, st);
     return e;
   }));
+  // the BFS ran beside the extension: its row totals come with the others
+  const bool with_tp = ws->bfs_pending;
+  if (with_tp) TPG_HIP(hipStreamWaitEvent(st, ws->ev_join, 0));
   TPG_TRY(io_read(ws, st, ws->h_totals, ws->totals.p,
                   sizeof(int64_t) * PathTotals::host_words(ws->xg)));
   P.n_pp = ws->h_totals[PathTotals::kPP];
@@ -937,7 +948,12 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
   TPG_TRY(reserve_scan(ws, P.n_pp));
   uint64_t* leaf = ws->leaf_by_rank.as<uint64_t>();
   int32_t* len = ws->pp_len.as<int32_t>();
-  ws->rb_ready = all;
+  TpTree tt{};
+  if (with_tp) {
+    TPG_TRY(ws_reserve(ws, ws->canon, sizeof(int32_t) * N));
+    TPG_TRY(ws_reserve(ws, ws->leaf_canon, sizeof(int32_t) * (P.n_pp + 1)));
+    tt = tp_tree(ws, U.xn);
+  }
   // the seeded chains of two or more vertices
   const auto r0 = std::lower_bound(U.rot.begin(), U.rot.end(), a.seed_lo);
   const auto r1 = std::lower_bound(U.rot.begin(), U.rot.end(), a.seed_lo + a.seed_n);
@@ -947,17 +963,18 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
   key_add(key_down, len);
   key_add(key_down, rot);
   key_add(key_down, n_rot);
+  key_add(key_down, tt);
   TPG_TRY(run_seq(ws, ws->rank_down, std::move(key_down), st, [&]() -> hipError_t {
     hipError_t e = hipSuccess;
     // level 1 always (a tree of one level has leaves there), then the parents
     // of the levels below
     for (int L = 1; (L == 1 || L < R.Lmax) && e == hipSuccess;) {
       const int n = std::max(1, std::min(kRun, R.Lmax - L));  // parents of levels L .. L + n - 1
-      e = n > 1 ? launch_down_run(a, n - 1, L, R.off[L], R.count[L], sc, leaf, len, st)
-                : launch_down(a, L, R.off[L], R.count[L], sc, leaf, len, st);
+      e = n > 1 ? launch_down_run(a, tt, L, R.off[L], R.count[L], sc, leaf, len, st)
+                : launch_down(a, tt, L, R.off[L], R.count[L], sc, leaf, len, st);
       L += n;
     }
-    if (e == hipSuccess) e = launch_rotations(a, ws->ch, rot, n_rot, range_lo, rb, leaf, len, st);
+    if (e == hipSuccess) e = launch_rotations(a, ws->ch, tt, rot, n_rot, range_lo, rb, leaf, len, st);
     return e;
   }));
   // offsets of the prime paths: a scan of their lengths
@@ -971,23 +988,8 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
   TPG_TRY(io_read(ws, st, ws->h_scalars + 6, scal + 6, sizeof(int64_t)));
   P.n_vtx = ws->h_scalars[6];
   TPG_TRY(ws_reserve(ws, o.pp_vtx, sizeof(int32_t) * (P.n_vtx + 1)));
-  // with the BFS under way (test paths follow), the writer also records each
-  // test path's length and where its prime path leaves the BFS tree, with
-  // the entries around that point; the BFS ran beside the extension and is
-  // long done
-  PPWriteTp tpx{};
-  ws->tp_len_ready = false;
-  if (ws->bfs_pending) {
-    TPG_TRY(ws_reserve(ws, ws->tp_len, sizeof(int64_t) * (P.n_pp + 1)));
-    TPG_TRY(ws_reserve(ws, ws->tp_lead, sizeof(int4) * (P.n_pp + 1)));
-    TPG_HIP(hipStreamWaitEvent(st, ws->ev_join, 0));
-    const BfsOut bv = bfs_views(ws, U.n);
-    tpx = PPWriteTp{bv.parent, bv.pfx_off, bv.sfx_off, ws->tp_len.as<int64_t>(),
-                    ws->tp_lead.as<int4>()};
-    ws->tp_len_ready = true;
-  }
   TPG_HIP(launch_pp_write(a, ws->ch, U.n, leaf, o.pp_off.as<int64_t>(), P.n_pp,
-                          o.pp_vtx.as<int32_t>(), tpx, st));
+                          o.pp_vtx.as<int32_t>(), st));
   o.n_pp = P.n_pp;
   o.n_ppv = P.n_vtx;
   return TPG_OK;
@@ -1006,48 +1008,72 @@ BfsOut bfs_views(tpg_workspace* ws, int n) {
   b.next = bi + 3 * n;
   b.pre = bi + 4 * n;
   b.pend = bi + 5 * n;
-  b.cfirst = bi + 6 * n;
-  b.ccnt = bi + 7 * n;
-  b.bq = bi + 8 * n;
   b.pfx_off = ws->pfx_off.as<int64_t>();
   b.sfx_off = ws->sfx_off.as<int64_t>();
+  b.pfx = ws->pfx.as<int32_t>();
+  b.sfx = ws->sfx.as<int32_t>();
   return b;
 }
 
-// BFS distances, tree ranks and prefix/suffix table offsets of the uploaded
-// union, on the side stream after everything already queued on `st`.
+TpTree tp_tree(tpg_workspace* ws, int xn) {
+  TpTree t{};
+  t.tpar = ws->tp_links.as<int32_t>();
+  t.nx = t.tpar + xn;
+  t.canon = ws->canon.as<int32_t>();
+  t.leaf_canon = ws->leaf_canon.as<int32_t>();
+  return t;
+}
+
+// BFS distances, tree ranks, prefix / suffix row offsets and the arcs'
+// test-path order of the uploaded union, on the side stream after everything
+// already queued on `st`.
 tpg_status bfs_start(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   const int n = U.n;
-  TPG_TRY(ws_reserve(ws, ws->bfs_i32, sizeof(int32_t) * 9 * (size_t)n));
+  TPG_TRY(ws_reserve(ws, ws->bfs_i32, sizeof(int32_t) * 6 * (size_t)n));
   TPG_TRY(ws_reserve(ws, ws->pfx_off, sizeof(int64_t) * (n + 1)));
   TPG_TRY(ws_reserve(ws, ws->sfx_off, sizeof(int64_t) * (n + 1)));
   TPG_TRY(ws_reserve(ws, ws->scan2_status, sizeof(uint64_t) * (scan_tiles(n) + 2)));
-  TPG_TRY(ws_reserve(ws, ws->scalars2, sizeof(int64_t) * 8));
+  TPG_TRY(ws_reserve(ws, ws->totals, sizeof(uint64_t) * PathTotals::words(ws->xg)));
+  TPG_TRY(ws_reserve(ws, ws->tp_links, sizeof(int32_t) * 2 * (size_t)U.xn));
+  TPG_TRY(ws_reserve(ws, ws->tp_order, sizeof(int32_t) * (size_t)(U.gbase.back() + 1)));
   const BfsOut b = bfs_views(ws, n);
   hipStream_t side = ws->side_stream;
-  int64_t* sc2 = ws->scalars2.as<int64_t>();
+  int64_t* tot = ws->totals.as<int64_t>();
   TPG_HIP(hipEventRecord(ws->ev_fork, st));
   TPG_HIP(hipStreamWaitEvent(side, ws->ev_fork, 0));
   TPG_HIP(launch_bfs_dist(ws->dg, b, side));
-  TPG_HIP(scan_i32_to_i64(b.dist_f, b.pfx_off, n, 0, sc2 + 0, ws->scan2_status.as<uint64_t>(),
+  TPG_HIP(scan_i32_to_i64(b.dist_f, b.pfx_off, n, 0, tot + PathTotals::kPfx, ws->scan2_status.as<uint64_t>(),
                           nullptr, side));
-  TPG_HIP(scan_i32_to_i64(b.dist_b, b.sfx_off, n, 0, sc2 + 1, ws->scan2_status.as<uint64_t>(),
+  TPG_HIP(scan_i32_to_i64(b.dist_b, b.sfx_off, n, 0, tot + PathTotals::kSfx, ws->scan2_status.as<uint64_t>(),
                           nullptr, side));
+  TPG_HIP(launch_tp_arcs(ws->dg, ws->xg, ws->ch, b, tp_tree(ws, U.xn), ws->d_gbase,
+                         ws->tp_order.as<int32_t>(), side));
   TPG_HIP(hipEventRecord(ws->ev_join, side));
   ws->bfs_pending = true;
   return TPG_OK;
 }
 
-// Longest-first covering (see kernels_cover.hip): from the spliced test
-// paths of all np prime paths, the chosen ones in prime-path order into idx0
-// and their per-first-vertex runs into rb0; *n_sel their number.
+// Longest-first covering (see kernels_cover.hip) over the spliced test paths
+// of all np prime paths: gstate0[i] = 1 for the chosen prime paths.
 tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, int64_t np,
-                         const OutSet& o, int64_t* n_sel) {
+                         const OutSet& o, const BfsOut& b) {
   const int n = U.n;
   int64_t* sc = ws->scalars.as<int64_t>();
   int64_t* hs = ws->h_scalars;
   TPG_TRY(ws_reserve(ws, ws->cov_misc, sizeof(uint64_t) * 4));
   uint64_t* misc = ws->cov_misc.as<uint64_t>();  // [0] shared hashes, [1] missing windows, [2] undecided
+  // the spliced test paths, in the prime paths' order
+  TPG_TRY(ws_reserve(ws, ws->row_len, sizeof(int32_t) * (np + 1)));
+  TPG_TRY(ws_reserve(ws, ws->spl_off, sizeof(int64_t) * (np + 1)));
+  TPG_HIP(launch_row_len(nullptr, np, o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), &b,
+                         ws->row_len.as<int32_t>(), st));
+  TPG_HIP(scan_i32_to_i64(ws->row_len.as<int32_t>(), ws->spl_off.as<int64_t>(), np, 0, sc + 12,
+                          ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
+  TPG_HIP(hipMemcpyAsync(hs + 10, sc + 12, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+  TPG_HIP(hipStreamSynchronize(st));
+  TPG_TRY(ws_reserve(ws, ws->spl_vtx, sizeof(int32_t) * (hs[10] + 1)));
+  TPG_HIP(launch_emit_rows(nullptr, np, hs[10], o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), &b,
+                           ws->spl_off.as<int64_t>(), ws->spl_vtx.as<int32_t>(), st));
   // hash table of the prime paths, load factor <= 1/2
   int64_t slots = 1024;
   while (slots < 2 * np) slots <<= 1;
@@ -1067,12 +1093,12 @@ tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, 
     if (hs[10] == 0) break;
   }
   // covering pairs: count, offsets, write
-  const int64_t* tp_off = ws->tp_off.as<int64_t>();
-  const int32_t* tp_vtx = ws->tp_vtx.as<int32_t>();
-  TPG_TRY(ws_reserve(ws, ws->keep_cnt, sizeof(int64_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->keep_pos, sizeof(int64_t) * (np + 1)));
-  int64_t* cnt = ws->keep_cnt.as<int64_t>();
-  int64_t* at = ws->keep_pos.as<int64_t>();
+  const int64_t* tp_off = ws->spl_off.as<int64_t>();
+  const int32_t* tp_vtx = ws->spl_vtx.as<int32_t>();
+  TPG_TRY(ws_reserve(ws, ws->cov_cnt, sizeof(int64_t) * (np + 1)));
+  TPG_TRY(ws_reserve(ws, ws->cov_at, sizeof(int64_t) * (np + 1)));
+  int64_t* cnt = ws->cov_cnt.as<int64_t>();
+  int64_t* at = ws->cov_at.as<int64_t>();
   TPG_HIP(launch_cover(pow2_words(U.max_comp), ws->dg, tp_off, tp_vtx, np, mul, ws->cov_keys.as<uint64_t>(),
                        ws->cov_vals.as<int32_t>(), slots - 1, cnt, at, nullptr, nullptr, 0, misc + 1,
                        st));
@@ -1096,18 +1122,18 @@ tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, 
   const int64_t nh = nkeys * std::max<int64_t>(nt, 1);
   TPG_TRY(ws_reserve(ws, ws->grp_key, sizeof(int32_t) * (np + 1)));
   TPG_TRY(ws_reserve(ws, ws->grp_hist, sizeof(int64_t) * (nh + 1)));
-  TPG_TRY(ws_reserve(ws, ws->keep_len, sizeof(int64_t) * (nh + 1)));
-  TPG_TRY(ws_reserve(ws, ws->idx1, sizeof(int32_t) * (np + 1)));
+  TPG_TRY(ws_reserve(ws, ws->grp_base, sizeof(int64_t) * (nh + 1)));
+  TPG_TRY(ws_reserve(ws, ws->row_src, sizeof(int32_t) * (np + 1)));
   TPG_TRY(ws_reserve(ws, ws->cov_pos, sizeof(int32_t) * (np + 1)));
   TPG_TRY(reserve_scan(ws, std::max(np, nh)));
   int32_t* key = ws->grp_key.as<int32_t>();
-  int32_t* perm = ws->idx1.as<int32_t>();
+  int32_t* perm = ws->row_src.as<int32_t>();
   TPG_HIP(launch_len_key(o.pp_off.as<int64_t>(), np, (int64_t)n + 1, key, st));
   TPG_HIP(launch_zero_u64(ws->grp_hist.as<uint64_t>(), nh, st));
   TPG_HIP(launch_key_hist(key, np, nt, ws->grp_hist.as<uint64_t>(), st));
-  TPG_HIP(scan_i64(ws->grp_hist.as<int64_t>(), ws->keep_len.as<int64_t>(), nh, 0, sc + 13,
+  TPG_HIP(scan_i64(ws->grp_hist.as<int64_t>(), ws->grp_base.as<int64_t>(), nh, 0, sc + 13,
                    ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  TPG_HIP(launch_last_place(key, np, nt, ws->keep_len.as<int64_t>(), perm, st));
+  TPG_HIP(launch_last_place(key, np, nt, ws->grp_base.as<int64_t>(), perm, st));
   TPG_HIP(launch_invert(perm, np, ws->cov_pos.as<int32_t>(), st));
   // rounds until every path is decided
   TPG_TRY(ws_reserve(ws, ws->gstate0, (size_t)np + 8));
@@ -1127,139 +1153,88 @@ tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, 
     TPG_HIP(hipStreamSynchronize(st));
     if (hs[10] == 0) break;
   }
-  // the chosen paths in prime-path order and their runs by first vertex
-  TPG_TRY(ws_reserve(ws, ws->cov_flag, sizeof(int32_t) * (np + 1)));
-  TPG_HIP(launch_chosen_flags(state, np, ws->cov_flag.as<int32_t>(), st));
-  TPG_HIP(scan_i32_to_i64(ws->cov_flag.as<int32_t>(), at, np, 0, sc + 15,
-                          ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  TPG_HIP(launch_chosen_list(state, at, np, ws->idx0.as<int32_t>(), st));
-  TPG_HIP(hipMemcpyAsync(hs + 10, sc + 15, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  TPG_HIP(hipStreamSynchronize(st));
-  TPG_HIP(launch_chosen_runs(ws->idx0.as<int32_t>(), hs[10], o.pp_off.as<int64_t>(),
-                             o.pp_vtx.as<int32_t>(), n, ws->rb0.as<int64_t>(), st));
-  *n_sel = hs[10];
   return TPG_OK;
 }
 
+// Test paths of the ranked union (rank_and_materialize has filled the canons):
+// marks, places by two sweeps, lengths, rows.
 tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t st,
-                             const PPResult& P, TPResult& T, OutSet& o, bool greedy = false) {
-  const int n = U.n;
+                             const TreeResult& R, const PPResult& P, TPResult& T, OutSet& o,
+                             bool greedy = false) {
   const int nc = U.n_comp;
-  if (!ws->bfs_pending) TPG_TRY(bfs_start(ws, U, st));
   ws->bfs_pending = false;
-  TPG_HIP(hipStreamWaitEvent(st, ws->ev_join, 0));
   const int64_t np = P.n_pp;
   T.n_spliced = np;
-  const int eb = n > 1 ? 32 - __builtin_clz((unsigned)n) : 1;  // bits of entry + 1 <= n
-  TPG_TRY(reserve_scan(ws, std::max<int64_t>(np, n)));
-  BfsOut b = bfs_views(ws, n);
-  int64_t* sc = ws->scalars.as<int64_t>();
-
-  TPG_TRY(ws_reserve(ws, ws->tp_len, sizeof(int64_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->tp_off, sizeof(int64_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->rb0, sizeof(int64_t) * (n + 2)));
-  TPG_TRY(ws_reserve(ws, ws->rb1, sizeof(int64_t) * (n + 2)));
-  TPG_TRY(ws_reserve(ws, ws->idx0, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->idx1, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->tp_key, sizeof(uint64_t) * kTpKeyWords * (np + 1)));
-  const bool from_writer = ws->tp_len_ready, rb_from_roots = ws->rb_ready;
-  ws->tp_len_ready = false;
-  ws->rb_ready = false;
-  TPG_HIP(launch_tp_len(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np, n, b,
-                        from_writer ? nullptr : ws->tp_len.as<int64_t>(),
-                        rb_from_roots ? nullptr : ws->rb0.as<int64_t>(), st));
-  TPG_HIP(scan_i64(ws->tp_len.as<int64_t>(), ws->tp_off.as<int64_t>(), np, 0, sc,
-                   ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  TPG_TRY(io_read(ws, st, ws->h_scalars, sc, sizeof(int64_t)));
-  TPG_TRY(io_read(ws, st, ws->h_scalars + 4, ws->scalars2.p, 2 * sizeof(int64_t)));
-  const int64_t tp_total = ws->h_scalars[0];
-  TPG_TRY(ws_reserve(ws, ws->pfx, sizeof(int32_t) * (ws->h_scalars[4] + 1)));
-  TPG_TRY(ws_reserve(ws, ws->sfx, sizeof(int32_t) * (ws->h_scalars[5] + 1)));
-  b.pfx = ws->pfx.as<int32_t>();
-  b.sfx = ws->sfx.as<int32_t>();
+  const int32_t ng = U.gbase.back();
+  TPG_TRY(reserve_scan(ws, np));
+  TPG_TRY(ws_reserve(ws, ws->row_src, sizeof(int32_t) * (np + 1)));
+  TPG_TRY(ws_reserve(ws, ws->row_len, sizeof(int32_t) * (np + 1)));
+  TPG_TRY(ws_reserve(ws, ws->tp_first, sizeof(int64_t) * (ng + 1)));
+  TPG_TRY(ws_reserve(ws, ws->pfx, sizeof(int32_t) * (ws->h_totals[PathTotals::kPfx] + 1)));
+  TPG_TRY(ws_reserve(ws, ws->sfx, sizeof(int32_t) * (ws->h_totals[PathTotals::kSfx] + 1)));
+  const BfsOut b = bfs_views(ws, U.n);
   TPG_HIP(launch_bfs_tables(ws->dg, b, st));
-  const int pe = 64 / eb;
-  // packed rows: row v at off[v] / pe + 2 v, ceil(len / pe) + 1 words each
-  TPG_TRY(ws_reserve(ws, ws->pfx_pk, sizeof(uint64_t) * (ws->h_scalars[4] / pe + 2 * (int64_t)n + 4)));
-  TPG_TRY(ws_reserve(ws, ws->sfx_pk, sizeof(uint64_t) * (ws->h_scalars[5] / pe + 2 * (int64_t)n + 4)));
-  b.pfx_pk = ws->pfx_pk.as<uint64_t>();
-  b.sfx_pk = ws->sfx_pk.as<uint64_t>();
-  TPG_HIP(launch_pack_tables(n, b, eb, st));
-  // the plain spliced entries only for the covering, which reads them
-  if (greedy) TPG_TRY(ws_reserve(ws, ws->tp_vtx, sizeof(int32_t) * (tp_total + 1)));
-  TPG_TRY(ws_reserve(ws, ws->tp_pk, sizeof(uint64_t) * ((tp_total + pe - 1) / pe + 2 * np + 4)));
-  TPG_HIP(launch_tp_write(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np, b,
-                          ws->tp_off.as<int64_t>(), greedy ? ws->tp_vtx.as<int32_t>() : nullptr,
-                          ws->tp_key.as<uint64_t>(), ws->tp_pk.as<uint64_t>(), eb,
-                          ws->idx0.as<int32_t>(), from_writer ? ws->tp_lead.as<int4>() : nullptr,
-                          st));
-  // with longest-first covering only the chosen test paths are sorted
-  int64_t nm = np;
-  if (greedy) TPG_TRY(greedy_select(ws, U, st, np, o, &nm));
-  // merge the per-first-vertex runs
-  TpOrder K{ws->tp_off.as<int64_t>(), ws->tp_key.as<uint64_t>(), ws->tp_pk.as<uint64_t>(), eb,
-            pe};
-  int64_t runs = n, final_runs = 1;
-  TPG_TRY(ws_reserve(ws, ws->merge_split, sizeof(int64_t) * merge_split_slots(nm)));
-  DevBuf* ri = &ws->rb0;
-  DevBuf* ro = &ws->rb1;
-  DevBuf* ii = &ws->idx0;
-  DevBuf* io = &ws->idx1;
-  if (nc > 1) {
-    // a union of graphs: merge within each graph only (its runs padded to a
-    // power of two), as the graphs' test paths already follow each other in
-    // order; worth it when that takes fewer rounds
-    int32_t largest = 1;
-    for (int c = 0; c < nc; ++c) largest = std::max(largest, U.cbase[c + 1] - U.cbase[c]);
-    int R = 0;
-    while ((1 << R) < largest) ++R;
-    int R_all = 0;
-    while ((int64_t)1 << R_all < n) ++R_all;
-    if (R < R_all) {
-      const int64_t P = (int64_t)nc << R;
-      TPG_TRY(ws_reserve(ws, ws->rb0, sizeof(int64_t) * (std::max<int64_t>(P, n) + 2), true, st,
-                         sizeof(int64_t) * (n + 1)));
-      TPG_TRY(ws_reserve(ws, ws->rb1, sizeof(int64_t) * (std::max<int64_t>(P, n) + 2)));
-      TPG_HIP(launch_pad_runs(ws->dg, ws->rb0.as<int64_t>(), R, P, ws->rb1.as<int64_t>(), st));
-      std::swap(ri, ro);
-      runs = P;
-      final_runs = nc;
+  if (greedy) TPG_TRY(greedy_select(ws, U, st, np, o, b));
+  // the prime paths' parents are not read any more: the marks take their place
+  const ExtArgs a = make_args(ws);
+  const TpTree tt = tp_tree(ws, U.xn);
+  int32_t* rep = ws->par.as<int32_t>();
+  uint32_t* cnt = ws->sub_cnt.as<uint32_t>();
+  int32_t* src = ws->row_src.as<int32_t>();
+  int64_t* first = ws->tp_first.as<int64_t>();
+  const int32_t* order = ws->tp_order.as<int32_t>();
+  const uint64_t* leaf = ws->leaf_by_rank.as<uint64_t>();
+  const uint8_t* state = greedy ? ws->gstate0.as<uint8_t>() : nullptr;
+  std::vector<uint8_t> key;
+  key_add(key, a);
+  key_add(key, tt);
+  key_add(key, cnt);
+  key_add(key, src);
+  key_add(key, first);
+  key_add(key, order);
+  key_add(key, ng);
+  key_add(key, leaf);
+  key_add(key, state);
+  key_add(key, np);
+  key_add(key, R.Lmax);
+  for (int L = 1; L <= R.Lmax; ++L) {
+    key_add(key, R.off[L]);
+    key_add(key, R.count[L]);
+  }
+  TPG_TRY(run_seq(ws, ws->tp_sweeps, std::move(key), st, [&]() -> hipError_t {
+    hipError_t e = launch_zero_u32(reinterpret_cast<uint32_t*>(rep), R.n_nodes, st);
+    if (e == hipSuccess) e = launch_tp_mark(a, tt, leaf, np, state, rep, st);
+    // levels 2 and below, two to a launch
+    for (int L = R.Lmax; L >= 2 && e == hipSuccess;) {
+      const int n = L >= 3 ? 2 : 1;
+      const int top = L - n + 1;
+      e = n > 1 ? launch_tp_up_run(a, R.off[top], R.count[top], rep, cnt, st)
+                : launch_tp_up(a, R.off[top], R.count[top], rep, cnt, st);
+      L -= n;
     }
-  }
-  while (runs > final_runs) {
-    TPG_HIP(launch_merge_round(K, ii->as<int32_t>(), io->as<int32_t>(), ri->as<int64_t>(), runs,
-                               nm, ws->merge_split.as<int64_t>(), st));
-    TPG_HIP(launch_next_runs(ri->as<int64_t>(), runs, ro->as<int64_t>(), st));
-    std::swap(ri, ro);
-    std::swap(ii, io);
-    runs = (runs + 1) / 2;
-  }
-  // dedup
-  TPG_TRY(ws_reserve(ws, ws->keep_cnt, sizeof(int64_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->keep_len, sizeof(int64_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->keep_pos, sizeof(int64_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->keep_voff, sizeof(int64_t) * (np + 1)));
-  TPG_HIP(launch_dedup_flags(K, ii->as<int32_t>(), nm, ws->keep_cnt.as<int64_t>(),
-                             ws->keep_len.as<int64_t>(), st));
-  TPG_HIP(scan_i64(ws->keep_cnt.as<int64_t>(), ws->keep_pos.as<int64_t>(), nm, 0, sc + 2,
-                   ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  TPG_HIP(scan_i64(ws->keep_len.as<int64_t>(), ws->keep_voff.as<int64_t>(), nm, 0, sc + 3,
-                   ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  TPG_TRY(io_read(ws, st, ws->h_scalars + 2, sc + 2, 2 * sizeof(int64_t)));
-  T.n_tp = ws->h_scalars[2];
-  T.n_vtx = ws->h_scalars[3];
+    if (e == hipSuccess) e = launch_tp_arc_starts(a, order, ng, rep, cnt, first, src, st);
+    for (int L = 2; L <= R.Lmax && e == hipSuccess; L += 2)
+      e = launch_tp_down_run(a, tt.nx, R.off[L], R.count[L], rep, cnt, src, st);
+    return e;
+  }));
+  int64_t* sc = ws->scalars.as<int64_t>();
+  TPG_TRY(io_read(ws, st, ws->h_scalars, first + ng, sizeof(int64_t)));
+  T.n_tp = ws->h_scalars[0];
   TPG_TRY(ws_reserve(ws, o.tp_off, sizeof(int64_t) * (T.n_tp + 1)));
+  TPG_HIP(launch_row_len(src, T.n_tp, o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), &b,
+                         ws->row_len.as<int32_t>(), st));
+  TPG_HIP(scan_i32_to_i64(ws->row_len.as<int32_t>(), o.tp_off.as<int64_t>(), T.n_tp, 0, sc,
+                          ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
+  TPG_TRY(io_read(ws, st, ws->h_scalars, sc, sizeof(int64_t)));
+  T.n_vtx = ws->h_scalars[0];
   TPG_TRY(ws_reserve(ws, o.tp_vtx, sizeof(int32_t) * (T.n_vtx + 1)));
-  TPG_HIP(launch_unpack_gather(ws->tp_off.as<int64_t>(), ws->tp_pk.as<uint64_t>(),
-                               o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), b, eb,
-                               ii->as<int32_t>(), nm, ws->keep_pos.as<int64_t>(),
-                               ws->keep_voff.as<int64_t>(), ws->keep_len.as<int64_t>(),
-                               o.tp_off.as<int64_t>(), o.tp_vtx.as<int32_t>(), st));
-  TPG_HIP(launch_set_i64(o.tp_off.as<int64_t>() + T.n_tp, sc + 3, st));
-  int64_t* cs = o.comp_starts.as<int64_t>();
-  if (nc > 1)
-    TPG_HIP(launch_comp_bounds(o.tp_off.as<int64_t>(), o.tp_vtx.as<int32_t>(), T.n_tp, ws->dg.comp,
-                               nc, cs + 2 * (nc + 1), cs + 3 * (nc + 1), st));
+  TPG_HIP(launch_emit_rows(src, T.n_tp, T.n_vtx, o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), &b,
+                           o.tp_off.as<int64_t>(), o.tp_vtx.as<int32_t>(), st));
+  if (nc > 1) {
+    int64_t* cs = o.comp_starts.as<int64_t>();
+    TPG_HIP(launch_comp_tp_starts(nc, ws->d_gbase, first, o.tp_off.as<int64_t>(),
+                                  cs + 2 * (nc + 1), cs + 3 * (nc + 1), st));
+  }
   o.n_tp = T.n_tp;
   o.n_tpv = T.n_vtx;
   return TPG_OK;
@@ -1300,33 +1275,28 @@ tpg_status group_by_last(tpg_workspace* ws, int32_t n_keys, hipStream_t st, OutS
   const int64_t nh = (int64_t)n_keys * std::max<int64_t>(nt, 1);
   TPG_TRY(ws_reserve(ws, ws->grp_key, sizeof(int32_t) * (np + 1)));
   TPG_TRY(ws_reserve(ws, ws->grp_hist, sizeof(int64_t) * (nh + 1)));
-  TPG_TRY(ws_reserve(ws, ws->keep_len, sizeof(int64_t) * (std::max(np, nh) + 1)));
-  TPG_TRY(ws_reserve(ws, ws->keep_pos, sizeof(int64_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->keep_voff, sizeof(int64_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->idx0, sizeof(int32_t) * (np + 1)));
+  TPG_TRY(ws_reserve(ws, ws->grp_base, sizeof(int64_t) * (nh + 1)));
+  TPG_TRY(ws_reserve(ws, ws->row_src, sizeof(int32_t) * (np + 1)));
+  TPG_TRY(ws_reserve(ws, ws->row_len, sizeof(int32_t) * (np + 1)));
   TPG_TRY(ws_reserve(ws, o.ppg_off, sizeof(int64_t) * (np + 1)));
   TPG_TRY(ws_reserve(ws, o.ppg_vtx, sizeof(int32_t) * (nv + 1)));
   TPG_TRY(reserve_scan(ws, std::max(np, nh)));
   int64_t* sc = ws->scalars.as<int64_t>();
   uint64_t* hist = ws->grp_hist.as<uint64_t>();
-  int64_t* base = ws->keep_len.as<int64_t>();  // the scanned histograms
-  int32_t* perm = ws->idx0.as<int32_t>();
+  int64_t* base = ws->grp_base.as<int64_t>();  // the scanned histograms
+  int32_t* perm = ws->row_src.as<int32_t>();
   TPG_HIP(launch_zero_u64(hist, nh, st));
   TPG_HIP(launch_last_hist(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np, nt,
                            ws->grp_key.as<int32_t>(), hist, st));
   TPG_HIP(scan_i64(reinterpret_cast<const int64_t*>(hist), base, nh, 0, sc + 10,
                    ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
   TPG_HIP(launch_last_place(ws->grp_key.as<int32_t>(), np, nt, base, perm, st));
-  // row lengths in the new order (reusing the histogram buffer is safe: the
-  // placement above has consumed it), their offsets, then the rows
-  int64_t* len = ws->keep_len.as<int64_t>();
-  TPG_HIP(launch_perm_lens(o.pp_off.as<int64_t>(), perm, np, len, ws->keep_pos.as<int64_t>(), st));
-  TPG_HIP(scan_i64(len, ws->keep_voff.as<int64_t>(), np, 0, sc + 11, ws->scan_status.as<uint64_t>(),
-                   ws->scan_ctr.as<uint32_t>(), st));
-  TPG_HIP(launch_gather(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), perm, np,
-                        ws->keep_pos.as<int64_t>(), ws->keep_voff.as<int64_t>(), len,
-                        o.ppg_off.as<int64_t>(), o.ppg_vtx.as<int32_t>(), st));
-  TPG_HIP(launch_set_i64(o.ppg_off.as<int64_t>() + np, sc + 11, st));
+  TPG_HIP(launch_row_len(perm, np, o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), nullptr,
+                         ws->row_len.as<int32_t>(), st));
+  TPG_HIP(scan_i32_to_i64(ws->row_len.as<int32_t>(), o.ppg_off.as<int64_t>(), np, 0, sc + 11,
+                          ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
+  TPG_HIP(launch_emit_rows(perm, np, nv, o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), nullptr,
+                           o.ppg_off.as<int64_t>(), o.ppg_vtx.as<int32_t>(), st));
   return TPG_OK;
 }
 
@@ -1513,7 +1483,7 @@ tpg_status test_paths_stream_out(CallCtx& c, const OutSet& o, int64_t n_tp) {
   const bool dev = c.flags & TPG_OUT_DEVICE;
   std::vector<int64_t> off;
   std::vector<int32_t> vtx;
-  DevBuf& doff = c.ws->tp_len;  // scratch for rebased device offsets (free after the sort)
+  DevBuf& doff = c.ws->chunk_off;
   if (dev) TPG_TRY(ws_reserve(c.ws, doff, sizeof(int64_t) * (std::min(cp, n_tp) + 1)));
   for (int64_t k = 0; k < n_tp; k += cp) {
     const int64_t cnt = std::min(cp, n_tp - k);
@@ -1613,12 +1583,12 @@ void tpg_workspace_free(tpg_workspace* ws) {
                     &ws->mask1, &ws->ls, &ws->sub_cnt, &ws->pp_len,
                     &ws->leaf_by_rank, &ws->totals, &ws->scan_status,
                     &ws->scan_ctr, &ws->scalars, &ws->bfs_i32, &ws->pfx_off, &ws->sfx_off,
-                    &ws->pfx, &ws->sfx, &ws->pfx_pk, &ws->sfx_pk, &ws->tp_len, &ws->tp_off, &ws->tp_vtx, &ws->tp_key, &ws->tp_pk, &ws->idx0,
-                    &ws->idx1, &ws->grp_cnt, &ws->rb0, &ws->rb1, &ws->merge_split, &ws->tp_lead, &ws->keep_cnt, &ws->keep_len,
-                    &ws->keep_pos, &ws->keep_voff, &ws->comp_cnt, &ws->lvl_comp, &ws->b_pp_off,
-                    &ws->scan2_status, &ws->scalars2, &ws->digest, &ws->grp_key, &ws->grp_hist,
-                    &ws->cov_keys, &ws->cov_vals, &ws->cov_misc, &ws->pair_p, &ws->pair_q,
-                    &ws->cov_pos, &ws->gstate0, &ws->gstate1, &ws->cov_flag,
+                    &ws->pfx, &ws->sfx, &ws->rb0, &ws->tp_links, &ws->tp_order, &ws->tp_first,
+                    &ws->canon, &ws->leaf_canon, &ws->row_src, &ws->row_len, &ws->spl_off,
+                    &ws->spl_vtx, &ws->chunk_off, &ws->lvl_comp, &ws->b_pp_off,
+                    &ws->scan2_status, &ws->digest, &ws->grp_key, &ws->grp_hist, &ws->grp_base,
+                    &ws->cov_keys, &ws->cov_vals, &ws->cov_misc, &ws->cov_cnt, &ws->cov_at,
+                    &ws->pair_p, &ws->pair_q, &ws->cov_pos, &ws->gstate0, &ws->gstate1,
                     &ws->scc_work, &ws->scc_comp, &ws->scc_flags, &ws->scc_misc, &ws->ty_off,
                     &ws->ty_vtx, &ws->ty_types, &ws->cg_cnt, &ws->cg_off, &ws->cg_src,
                     &ws->cg_dst, &ws->cx_qb, &ws->cx_cnt0, &ws->cx_cnt1, &ws->cx_node,
@@ -1644,6 +1614,7 @@ void tpg_workspace_free(tpg_workspace* ws) {
   drop_level_graphs(ws);
   drop_seq_graph(ws->rank_up);
   drop_seq_graph(ws->rank_down);
+  drop_seq_graph(ws->tp_sweeps);
   if (ws->h_ls) (void)hipHostFree(ws->h_ls);
   if (ws->h_scalars) (void)hipHostFree(ws->h_scalars);
   if (ws->h_totals) (void)hipHostFree(ws->h_totals);
@@ -2452,7 +2423,7 @@ tpg_status tpg_test_paths(const tpg_graph* g, const tpg_opts* opts, tpg_paths* p
   OutSet& o = c.ws->out[0];
   tpg_status s = run_pp(U, c, tm, R, P, o, &ext_done, 0, 0, true);
   if (s == TPG_OK && timing) TPG_HIP(hipEventRecord(phase[1], c.st));
-  if (s == TPG_OK) s = test_paths_device(c.ws, U, c.st, P, T, o, c.flags & TPG_TP_GREEDY);
+  if (s == TPG_OK) s = test_paths_device(c.ws, U, c.st, R, P, T, o, c.flags & TPG_TP_GREEDY);
   if (s == TPG_OK && timing) TPG_HIP(hipEventRecord(phase[2], c.st));
   // with TPG_STREAM the sets come back as counts and digests and the test
   // paths go through on_chunk
@@ -2612,7 +2583,7 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
       s_pp = run_pp(U, c, tm, R, P, o, nullptr, 0, 0, true);
     }
     TPG_TRY(s_pp);
-    TPG_TRY(test_paths_device(ws, U, c.st, P, T, o));
+    TPG_TRY(test_paths_device(ws, U, c.st, R, P, T, o));
     const int nc = U.n_comp;
     if (want_levels) {
       // per-graph path counts of levels 1..64 (deeper levels pooled into 64)

@@ -52,12 +52,13 @@ struct ExtArgs {
   uint64_t* tot;  // PathTotals of this tree, cleared by the seeding
 };
 
-// What the ranking reports of a tree, int64 words: the prime paths, the
+// What the ranking reports of a tree, int64 words: the totals of the prefix
+// and suffix rows (the BFS's, kept by the seeding), the prime paths, the
 // closed cycles, then two histograms of kLenPad + max_comp bins by path
 // length (see k_path_lengths), then one uint32 per chain: the cycles closed
 // in its tree.
 struct PathTotals {
-  static constexpr int kPP = 0, kCycles = 1, kHist = 2, kLenPad = 2;
+  static constexpr int kPfx = 0, kSfx = 1, kPP = 2, kCycles = 3, kHist = 4, kLenPad = 2;
   __host__ __device__ static int64_t bins(const DGraph& g) { return kLenPad + (int64_t)g.max_comp; }
   __host__ __device__ static int64_t host_words(const DGraph& g) { return kHist + 2 * bins(g); }
   __host__ __device__ static int64_t words(const DGraph& g) { return host_words(g) + ((int64_t)g.n + 1) / 2; }
@@ -102,38 +103,35 @@ hipError_t launch_roots(const ExtArgs& a, const DChains& ch, int32_t range_lo, i
 // where it starts (bits 32-44), and bit 63 when it is a cycle.
 constexpr int kLeafStartShift = 32;
 constexpr uint64_t kLeafCycle = 1ull << 63;
+// What the test paths' order needs of the tree (see k_tp_mark in
+// kernels_tp.hip); canon null: not wanted.
+struct TpTree {
+  int32_t* tpar;        // per chain: the chain before it in the BFS tree (-1: none)
+  int32_t* nx;          // per chain: the chain after it on the shortest way to the exit
+  int32_t* canon;       // per node: the node of its path without the chains before the
+                        // last one of its first BFS-tree part (-1: all of it is one)
+  int32_t* leaf_canon;  // the same per prime path
+};
 // parents of level L: positions to the children; PP leaves record node and length
-hipError_t launch_down(const ExtArgs& a, int L, int64_t base, int64_t F, uint32_t* sub_cnt,
-                       uint64_t* leaf, int32_t* pp_len, hipStream_t st);
-// the same for depth + 1 levels in one launch (depth 1 or 2; base, F: the
-// run's top level L): counts of levels L .. L + depth, and positions handed
-// down by the parents of levels L .. L + depth
-hipError_t launch_up_run(const ExtArgs& a, int depth, int64_t base, int64_t F, uint32_t* sub_cnt,
+hipError_t launch_down(const ExtArgs& a, const TpTree& t, int L, int64_t base, int64_t F,
+                       uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len, hipStream_t st);
+// the same for two levels in one launch (base, F: the upper one, level L)
+hipError_t launch_up_run(const ExtArgs& a, int64_t base, int64_t F, uint32_t* sub_cnt,
                          hipStream_t st);
-hipError_t launch_down_run(const ExtArgs& a, int depth, int L, int64_t base, int64_t F,
+// both for the test paths' marked nodes instead of the PP leaves
+hipError_t launch_tp_up(const ExtArgs& a, int64_t base, int64_t F, const int32_t* rep,
+                        uint32_t* cnt, hipStream_t st);
+hipError_t launch_tp_up_run(const ExtArgs& a, int64_t base, int64_t F, const int32_t* rep,
+                            uint32_t* cnt, hipStream_t st);
+hipError_t launch_down_run(const ExtArgs& a, const TpTree& t, int L, int64_t base, int64_t F,
                            uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len, hipStream_t st);
 // the prime paths that start inside the n_rot chains rot[] (see k_rotations)
-hipError_t launch_rotations(const ExtArgs& a, const DChains& ch, const int32_t* rot, int32_t n_rot,
-                            int32_t range_lo, const int64_t* rb, uint64_t* leaf, int32_t* pp_len,
-                            hipStream_t st);
-// What the prime-path writer also records for the test paths when the BFS
-// tables are ready (tp_len null: nothing): per prime path i, the length of
-// its test path, and lead[i] = the first index t >= 1 whose entry's BFS
-// parent is not entry t - 1 (the path's length when there is none).
-struct PPWriteTp {
-  const int32_t* parent;   // BFS parent of each vertex
-  const int64_t* pfx_off;  // prefix / suffix table offsets (their lengths)
-  const int64_t* sfx_off;
-  int64_t* tp_len;
-  // per prime path: (lead, w, e, v1): the first entry index t >= 1 whose BFS
-  // parent is not entry t - 1 (the length if none), the entries w at lead - 1
-  // and e at lead (-1 if none), and the first vertex
-  int4* lead;
-};
+hipError_t launch_rotations(const ExtArgs& a, const DChains& ch, const TpTree& t,
+                            const int32_t* rot, int32_t n_rot, int32_t range_lo, const int64_t* rb,
+                            uint64_t* leaf, int32_t* pp_len, hipStream_t st);
 // n: vertices of the union
 hipError_t launch_pp_write(const ExtArgs& a, const DChains& ch, int32_t n, const uint64_t* leaf,
-                           const int64_t* pp_off, int64_t n_pp, int32_t* pp_vtx,
-                           const PPWriteTp& tp, hipStream_t st);
+                           const int64_t* pp_off, int64_t n_pp, int32_t* pp_vtx, hipStream_t st);
 
 // --- scans -------------------------------------------------------------------
 // out[i] = add + sum(in[0..i)), *total = add + sum(in); n may be 0.
@@ -213,10 +211,6 @@ hipError_t launch_last_hist(const int64_t* off, const int32_t* vtx, int64_t n, i
 // tile's earlier paths with the same key (base: exclusive scan of hist)
 hipError_t launch_last_place(const int32_t* key, int64_t n, int64_t ntiles, const int64_t* base,
                              int32_t* perm, hipStream_t st);
-// len[k] = length of path perm[k], pos[k] = k (the gather's inputs)
-hipError_t launch_perm_lens(const int64_t* off, const int32_t* perm, int64_t n, int64_t* len,
-                            int64_t* pos, hipStream_t st);
-
 // --- test paths by longest-first covering (kernels_cover.hip) ----------------
 // Hash table of the prime paths (keys / vals of mask + 1 slots, keys zeroed);
 // dups counts hashes shared by two prime paths (then retry with another mul).
@@ -245,12 +239,6 @@ hipError_t launch_round_pairs(const int32_t* pair_p, const int32_t* pair_q, int6
                               uint8_t* block, hipStream_t st);
 hipError_t launch_round_decide(int64_t n, uint8_t* state, uint8_t* drop, uint8_t* block,
                                uint64_t* undecided, hipStream_t st);
-hipError_t launch_chosen_flags(const uint8_t* state, int64_t n, int32_t* flag, hipStream_t st);
-// list[at[q]] = q for the chosen paths; then their runs by first vertex
-hipError_t launch_chosen_list(const uint8_t* state, const int64_t* at, int64_t n, int32_t* list,
-                              hipStream_t st);
-hipError_t launch_chosen_runs(const int32_t* list, int64_t m, const int64_t* pp_off,
-                              const int32_t* pp_vtx, int nv, int64_t* rb, hipStream_t st);
 // Set digest of paths [0, n) (offsets off, entries vtx): out[0] = sum and
 // out[1] = xor of the per-path FNV-1a 64 hashes of (k, v_1 .. v_k) as int32
 // little-endian bytes; out is cleared first.
@@ -270,26 +258,8 @@ struct BfsOut {
   int32_t* sfx;      // [sfx_off[n]]
   int32_t* pre;      // [n] graph-wide preorder rank in the BFS tree (children ascending)
   int32_t* pend;     // [n] end of v's subtree rank range
-  int32_t* cfirst;   // [n] v's tree children: bq[cfirst[v] .. cfirst[v] + ccnt[v]), ascending
-  int32_t* ccnt;     // [n]
-  int32_t* bq;       // [n] the search queue (graph-wide ids)
-  uint64_t* pfx_pk;  // prefix rows packed like the test paths (see k_pack_tables)
-  uint64_t* sfx_pk;  // suffix rows packed likewise
 };
-// What the test-path comparison reads: per test path kTpKeyWords 64-bit keys
-// (see k_tp_keys: two words of tree position, then kTpKeyTail words of the
-// entries after the tree prefix) and, for the ties the keys leave, the
-// packed entries.
-constexpr int kTpKeyTail = 4;
-constexpr int kTpKeyWords = 2 + kTpKeyTail;
-struct TpOrder {
-  const int64_t* off;   // [n + 1] test-path offsets
-  const uint64_t* key;  // [kTpKeyWords n], 16-byte aligned
-  const uint64_t* pk;   // the entries packed (see k_tp_write)
-  int eb;               // bits per packed entry (entry + 1; 0 = past the end)
-  int pe;               // packed entries per 64-bit word, 64 / eb
-};
-// one workgroup per component: dist_f, parent, pre, pend, tree children, dist_b, next
+// one workgroup per component: dist_f, parent, pre, pend, dist_b, next
 hipError_t launch_bfs_dist(const DGraph& g, const BfsOut& b, hipStream_t st);
 // after pfx_off / sfx_off are scans of dist_f / dist_b: fill pfx / sfx
 hipError_t launch_bfs_tables(const DGraph& g, const BfsOut& b, hipStream_t st);
@@ -300,51 +270,35 @@ hipError_t launch_localize(const int32_t* loc, int32_t* v, int64_t n, hipStream_
 hipError_t launch_comp_pp_starts(const DGraph& g, const int64_t* rb, const int64_t* pp_off,
                                  int64_t* pp_start, int64_t* ppv_start, hipStream_t st);
 
-// test-path lengths, and rb[v] = first prime path with first vertex >= v
-// (v = 0..n); either output may be null (not computed)
-hipError_t launch_tp_len(const int64_t* pp_off, const int32_t* pp_vtx, int64_t n_pp, int n,
-                         const BfsOut& b, int64_t* tp_len, int64_t* rb, hipStream_t st);
-// writes the test paths packed (pk: (n_entries + pe - 1) / pe + 2 n_pp + 4
-// words, pe = 64 / eb), their comparison keys, idx[i] = i and, when tp_vtx
-// is not null, their plain entries
-// Packed prefix / suffix rows of every vertex (after the tables exist).
-hipError_t launch_pack_tables(int n, const BfsOut& b, int eb, hipStream_t st);
-// lead: what the prime-path writer recorded (null: found here by a scan)
-hipError_t launch_tp_write(const int64_t* pp_off, const int32_t* pp_vtx, int64_t n_pp,
-                           const BfsOut& b, const int64_t* tp_off, int32_t* tp_vtx,
-                           uint64_t* key, uint64_t* pk, int eb, int32_t* idx,
-                           const int4* lead, hipStream_t st);
-// one round of pairwise merging of sorted runs [rb[r], rb[r+1]) of idx;
-// split: device scratch of merge_split_slots(n) int64 (the tiles' splits and pairs)
-hipError_t launch_merge_round(const TpOrder& K, const int32_t* idx_in, int32_t* idx_out,
-                              const int64_t* rb, int64_t n_runs, int64_t n, int64_t* split,
-                              hipStream_t st);
-int64_t merge_split_slots(int64_t n);
-hipError_t launch_next_runs(const int64_t* rb, int64_t n_runs, int64_t* rb_out, hipStream_t st);
-// the per-vertex runs rb[0..n] of a union, each graph's padded to 2^R runs:
-// out[0..n_out], n_out = n_comp * 2^R
-hipError_t launch_pad_runs(const DGraph& g, const int64_t* rb, int R, int64_t n_out, int64_t* out,
-                           hipStream_t st);
-hipError_t launch_dedup_flags(const TpOrder& K, const int32_t* idx, int64_t n, int64_t* keep_cnt,
-                              int64_t* keep_len, hipStream_t st);
-// copies the kept paths (keep_len[k] > 0) of idx to out_off / out_vtx
-hipError_t launch_gather(const int64_t* tp_off, const int32_t* tp_vtx, const int32_t* idx,
-                         int64_t n, const int64_t* keep_pos, const int64_t* keep_voff,
-                         const int64_t* keep_len, int64_t* out_off, int32_t* out_vtx,
-                         hipStream_t st);
-// the same for test paths held packed (tp_off: their entry offsets, pk: the
-// words k_tp_write built with eb bits per entry; the words that hold only
-// prefix entries come from the packed prefix rows in b, test path a having
-// been spliced from prime path a of pp_off / pp_vtx)
-hipError_t launch_unpack_gather(const int64_t* tp_off, const uint64_t* pk, const int64_t* pp_off,
-                                const int32_t* pp_vtx, const BfsOut& b, int eb,
-                                const int32_t* idx, int64_t n, const int64_t* keep_pos,
-                                const int64_t* keep_voff, const int64_t* keep_len,
-                                int64_t* out_off, int32_t* out_vtx, hipStream_t st);
-// start[c] / vstart[c] (c = 0..n_comp) of a sorted path list; off[n] = total
-hipError_t launch_comp_bounds(const int64_t* off, const int32_t* vtx, int64_t n,
-                              const int32_t* comp, int n_comp, int64_t* start, int64_t* vstart,
-                              hipStream_t st);
+// The arcs off the BFS tree in test-path order (see k_tp_arc_order) and the
+// chains' links t.tpar, t.nx; gbase[c]: the components' first places there
+// (c = 0 .. n_comp).
+constexpr int kArcSlotBits = 6;  // a successor slot; chain ids take 17 bits
+hipError_t launch_tp_arcs(const DGraph& g, const DGraph& x, const DChains& ch, const BfsOut& b,
+                          const TpTree& t, const int32_t* gbase, int32_t* order, hipStream_t st);
+// rep[node] = prime path + 1 for the node of every test path (state: see
+// k_tp_mark); rep must be zero
+hipError_t launch_tp_mark(const ExtArgs& a, const TpTree& t, const uint64_t* leaf, int64_t n_pp,
+                          const uint8_t* state, int32_t* rep, hipStream_t st);
+// cnt: marked nodes per subtree (launch_tp_up*), rewritten into places (see
+// k_tp_arc_starts) for the n arcs of order; src[place] = prime path
+hipError_t launch_tp_arc_starts(const ExtArgs& a, const int32_t* order, int32_t n,
+                                const int32_t* rep, uint32_t* cnt, int64_t* first, int32_t* src,
+                                hipStream_t st);
+// places from the nodes of a level down through the next one
+hipError_t launch_tp_down_run(const ExtArgs& a, const int32_t* nx, int64_t base, int64_t F,
+                              const int32_t* rep, uint32_t* cnt, int32_t* src, hipStream_t st);
+// rows r < n, each prime path src[r] (null: r), with b between its prefix and
+// suffix rows: their lengths, and the rows at out_off (n_entries in all)
+hipError_t launch_row_len(const int32_t* src, int64_t n, const int64_t* pp_off,
+                          const int32_t* pp_vtx, const BfsOut* b, int32_t* len, hipStream_t st);
+hipError_t launch_emit_rows(const int32_t* src, int64_t n, int64_t n_entries, const int64_t* pp_off,
+                            const int32_t* pp_vtx, const BfsOut* b, const int64_t* out_off,
+                            int32_t* out_vtx, hipStream_t st);
+// start[c] / vstart[c] (c = 0 .. n_comp) of the test paths
+hipError_t launch_comp_tp_starts(int n_comp, const int32_t* gbase, const int64_t* first,
+                                 const int64_t* off, int64_t* start, int64_t* vstart,
+                                 hipStream_t st);
 hipError_t launch_set_i64(int64_t* p, const int64_t* src, hipStream_t st);
 hipError_t launch_set_value_i64(int64_t* p, int64_t value, hipStream_t st);
 

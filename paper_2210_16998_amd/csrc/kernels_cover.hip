@@ -216,35 +216,6 @@ __global__ __launch_bounds__(kBlock) void k_round_decide(int64_t n, uint8_t* sta
   if (lane_id() == 0 && b) atomicAdd(undecided, (unsigned long long)__builtin_popcountll(b));
 }
 
-// Chosen paths in prime-path order: flags for a scan, then the list and the
-// per-first-vertex run counts of the merge.
-__global__ __launch_bounds__(kBlock) void k_chosen_flags(const uint8_t* state, int64_t n,
-                                                         int32_t* flag) {
-  const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (q < n) flag[q] = state[q] == 1 ? 1 : 0;
-}
-
-__global__ __launch_bounds__(kBlock) void k_chosen_list(const uint8_t* state, const int64_t* at,
-                                                        int64_t n, int32_t* list) {
-  const int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (q < n && state[q] == 1) list[at[q]] = (int32_t)q;
-}
-
-// Runs of the chosen list by first vertex (the list is in prime-path order,
-// hence grouped by first vertex): rb[u] = first position whose first vertex
-// is >= u, rb[nv] = m.
-__global__ __launch_bounds__(kBlock) void k_chosen_runs(const int32_t* list, int64_t m,
-                                                        const int64_t* pp_off, const int32_t* pp_vtx,
-                                                        int nv, int64_t* rb) {
-  const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (k >= m) return;
-  const int cur = pp_vtx[pp_off[list[k]]];
-  const int prev = k == 0 ? -1 : pp_vtx[pp_off[list[k - 1]]];
-  for (int u = prev + 1; u <= cur; ++u) rb[u] = k;
-  if (k == m - 1)
-    for (int u = cur + 1; u <= nv; ++u) rb[u] = m;
-}
-
 template <int W>
 hipError_t launch_cover_w(const DGraph& g, const int64_t* tp_off, const int32_t* tp_vtx, int64_t n,
                           uint64_t mul, const uint64_t* keys, const int32_t* vals, int64_t mask,
@@ -324,27 +295,6 @@ hipError_t launch_round_decide(int64_t n, uint8_t* state, uint8_t* drop, uint8_t
   if (n == 0) return hipSuccess;
   k_round_decide<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(
       n, state, drop, block, reinterpret_cast<unsigned long long*>(undecided));
-  return hipGetLastError();
-}
-
-hipError_t launch_chosen_flags(const uint8_t* state, int64_t n, int32_t* flag, hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  k_chosen_flags<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(state, n, flag);
-  return hipGetLastError();
-}
-
-hipError_t launch_chosen_list(const uint8_t* state, const int64_t* at, int64_t n, int32_t* list,
-                              hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  k_chosen_list<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(state, at, n, list);
-  return hipGetLastError();
-}
-
-hipError_t launch_chosen_runs(const int32_t* list, int64_t m, const int64_t* pp_off,
-                              const int32_t* pp_vtx, int nv, int64_t* rb, hipStream_t st) {
-  if (m == 0) return hipSuccess;
-  k_chosen_runs<<<(unsigned)((m + kBlock - 1) / kBlock), kBlock, 0, st>>>(list, m, pp_off, pp_vtx,
-                                                                         nv, rb);
   return hipGetLastError();
 }
 

@@ -83,7 +83,7 @@ __global__ void k_seed(ExtArgs a, int64_t tot_words) {
     a.t.info[i] = make_info(v, a.g.loc[v], 0);
     a.t.tl[i] = (uint16_t)a.g.len[v];
   }
-  for (int64_t k = i; k < tot_words; k += (int64_t)gridDim.x * blockDim.x) a.tot[k] = 0;
+  for (int64_t k = PathTotals::kPP + i; k < tot_words; k += (int64_t)gridDim.x * blockDim.x) a.tot[k] = 0;
   // visited sets of level 1 (stored, buffer 0): one bit each, at the
   // chain's local id
   const int W = a.t.mask_words;
@@ -667,6 +667,7 @@ hipError_t launch_fill(int W, const ExtArgs& a, int L, int64_t prev, int64_t bas
 // into the output position of the subtree's first prime path, or kNoRank when
 // the subtree holds none (k_down then skips it after one 4-byte read).
 constexpr uint32_t kNoRank = 0xFFFFFFFFu;
+__device__ __forceinline__ bool nch_internal(uint8_t k) { return k >= 1 && k < kNchPP; }
 
 // Simple paths by length, from the nodes.  A node <x1 .. xk> of chains (k >=
 // 2, not a cycle) of T vertices stands for the paths that start at any of
@@ -758,16 +759,22 @@ hipError_t launch_path_lengths(const ExtArgs& a, int64_t first, int64_t n_nodes,
   return hipGetLastError();
 }
 
+// What a node counts for itself: TP the test-path marks, else the PP leaves.
+template <bool TP>
+__device__ __forceinline__ uint32_t own_count(uint8_t k, const int32_t* rep, int64_t x) {
+  if constexpr (TP) return rep[x] != 0 ? 1u : 0u;
+  return k >= kNchPP ? 1u : 0u;
+}
+
+template <bool TP>
 __global__ __launch_bounds__(kBlock) void k_up(ExtArgs a, int64_t base, int64_t F,
-                                               uint32_t* sub_cnt) {
+                                               const int32_t* rep, uint32_t* sub_cnt) {
   const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (j >= F) return;
   const int64_t g = base + j;
   const uint8_t k = a.t.nch[g];
-  uint32_t c = 0;
-  if (k >= kNchPP) {
-    c = 1;
-  } else if (k) {
+  uint32_t c = own_count<TP>(k, rep, g);
+  if (k > 0 && k < kNchPP) {
     const int64_t c0 = a.t.cstart[g], c1 = c0 + k;
     for (int64_t x = c0; x < c1; ++x) c += sub_cnt[x];
   }
@@ -777,7 +784,15 @@ __global__ __launch_bounds__(kBlock) void k_up(ExtArgs a, int64_t base, int64_t 
 hipError_t launch_up(const ExtArgs& a, int64_t base, int64_t F, uint32_t* sub_cnt,
                      hipStream_t st) {
   if (F == 0) return hipSuccess;
-  k_up<<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, base, F, sub_cnt);
+  k_up<false><<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, base, F, nullptr,
+                                                                        sub_cnt);
+  return hipGetLastError();
+}
+
+hipError_t launch_tp_up(const ExtArgs& a, int64_t base, int64_t F, const int32_t* rep,
+                        uint32_t* cnt, hipStream_t st) {
+  if (F == 0) return hipSuccess;
+  k_up<true><<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, base, F, rep, cnt);
   return hipGetLastError();
 }
 
@@ -848,23 +863,54 @@ __device__ __forceinline__ void put_leaf(const ExtArgs& a, int64_t x, uint8_t k,
   pp_len[r] = (int32_t)a.t.tl[x] + (cyc ? 1 : 0);
 }
 
-// x (position r, nch code k) hands positions to its children in slot order;
-// with D > 0 each internal child with prime paths below then does the same
-// for its own children.
-template <int D>
-__device__ __forceinline__ void down_node(const ExtArgs& a, int64_t x, uint8_t k, uint32_t r,
-                                          uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len) {
+// The node of the child's path without its BFS-tree part (see TpTree), from
+// that of its parent x (k children), cx, where child y is x's slot-th.  The
+// dropped chains only took choices away, so the parent's node has at least
+// x's children, in the same order.
+__device__ __forceinline__ int32_t canon_child(const ExtArgs& a, const TpTree& t, int64_t x,
+                                               uint8_t k, int32_t cx, int64_t y, int slot) {
+  if (cx == (int32_t)x) return (int32_t)y;
+  if (cx < 0) {
+    const int vx = node_v(a.t.info[x]), vy = node_v(a.t.info[y]);
+    if (t.tpar[vy] == vx) return -1;
+    // the first arc off the BFS tree: the child of vx's root (root k is chain k)
+    int s = 0;
+    const int s0 = a.g.sp[vx], s1 = a.g.sp[vx + 1];
+    while (s0 + s + 1 < s1 && a.g.s[s0 + s] != vy) ++s;
+    return a.t.cstart[vx] + s;
+  }
+  const int32_t c0 = a.t.cstart[cx];
+  const int kc = a.t.nch[cx];
+  if (kc == k) return c0 + slot;
+  const int vy = node_v(a.t.info[y]);
+  int s = slot;
+  while (s + 1 < kc && node_v(a.t.info[c0 + s]) != vy) ++s;
+  return c0 + s;
+}
+
+// x (position r, nch code k, canon cx) hands positions to its children in slot
+// order; with D > 0 each internal child with prime paths below then does the
+// same for its own children.
+template <int D, bool TP>
+__device__ __forceinline__ void down_node(const ExtArgs& a, const TpTree& t, int64_t x, uint8_t k,
+                                          int32_t cx, uint32_t r, uint32_t* sub_cnt,
+                                          uint64_t* leaf, int32_t* pp_len) {
   if (k == 0 || k >= kNchPP) return;
   const int64_t c0 = a.t.cstart[x], c1 = c0 + k;
   for (int64_t y = c0; y < c1; ++y) {
     const uint32_t cc = sub_cnt[y];
     const uint8_t ky = a.t.nch[y];
-    sub_cnt[y] = cc ? r : kNoRank;
+    if (D == 0) sub_cnt[y] = cc ? r : kNoRank;
     if (cc) {
+      int32_t cy = -1;
+      if constexpr (TP) cy = canon_child(a, t, x, k, cx, y, (int)(y - c0));
       if (ky >= kNchPP) {
         put_leaf(a, y, ky, r, leaf, pp_len);
+        if constexpr (TP) t.leaf_canon[r] = cy;
       } else if constexpr (D > 0) {
-        down_node<D - 1>(a, y, ky, r, sub_cnt, leaf, pp_len);
+        down_node<D - 1, TP>(a, t, y, ky, cy, r, sub_cnt, leaf, pp_len);
+      } else {
+        if constexpr (TP) t.canon[y] = cy;
       }
     }
     r += cc;
@@ -872,38 +918,49 @@ __device__ __forceinline__ void down_node(const ExtArgs& a, int64_t x, uint8_t k
 }
 
 // Parents of levels L .. L + D in one launch (thread per node of L).  A
-// level-1 node can be a leaf itself.
-template <int D>
-__global__ __launch_bounds__(kBlock) void k_down_run(ExtArgs a, int L, int64_t base, int64_t F,
-                                                     uint32_t* sub_cnt, uint64_t* leaf,
+// level-1 node can be a leaf itself.  The nodes' canons pass from launch to
+// launch in t.canon, one level in D + 1.
+template <int D, bool TP>
+__global__ __launch_bounds__(kBlock) void k_down_run(ExtArgs a, TpTree t, int L, int64_t base,
+                                                     int64_t F, uint32_t* sub_cnt, uint64_t* leaf,
                                                      int32_t* pp_len) {
   const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (j >= F) return;
   const uint32_t r = sub_cnt[base + j];
   if (r == kNoRank) return;
   const uint8_t k = a.t.nch[base + j];
-  if (L == 1 && k >= kNchPP) put_leaf(a, base + j, k, r, leaf, pp_len);
-  down_node<D>(a, base + j, k, r, sub_cnt, leaf, pp_len);
+  int32_t cx = -1;
+  if (TP && L > 1 && nch_internal(k)) cx = t.canon[base + j];
+  if (L == 1 && k >= kNchPP) {
+    put_leaf(a, base + j, k, r, leaf, pp_len);
+    if constexpr (TP) t.leaf_canon[r] = -1;
+  }
+  down_node<D, TP>(a, t, base + j, k, cx, r, sub_cnt, leaf, pp_len);
 }
 
-hipError_t launch_down(const ExtArgs& a, int L, int64_t base, int64_t F, uint32_t* sub_cnt,
-                       uint64_t* leaf, int32_t* pp_len, hipStream_t st) {
+hipError_t launch_down(const ExtArgs& a, const TpTree& t, int L, int64_t base, int64_t F,
+                       uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len, hipStream_t st) {
   if (F == 0) return hipSuccess;
-  k_down_run<0><<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, L, base, F, sub_cnt,
-                                                                          leaf, pp_len);
+  const unsigned grid = (unsigned)((F + kBlock - 1) / kBlock);
+  if (t.canon)
+    k_down_run<0, true><<<grid, kBlock, 0, st>>>(a, t, L, base, F, sub_cnt, leaf, pp_len);
+  else
+    k_down_run<0, false><<<grid, kBlock, 0, st>>>(a, t, L, base, F, sub_cnt, leaf, pp_len);
   return hipGetLastError();
 }
 
-hipError_t launch_down_run(const ExtArgs& a, int depth, int L, int64_t base, int64_t F,
+hipError_t launch_down_run(const ExtArgs& a, const TpTree& t, int L, int64_t base, int64_t F,
                            uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len, hipStream_t st) {
   if (F == 0) return hipSuccess;
-  if (depth != 1) return hipErrorInvalidValue;
-  k_down_run<1><<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, L, base, F, sub_cnt,
-                                                                          leaf, pp_len);
+  const unsigned grid = (unsigned)((F + kBlock - 1) / kBlock);
+  if (t.canon)
+    k_down_run<1, true><<<grid, kBlock, 0, st>>>(a, t, L, base, F, sub_cnt, leaf, pp_len);
+  else
+    k_down_run<1, false><<<grid, kBlock, 0, st>>>(a, t, L, base, F, sub_cnt, leaf, pp_len);
   return hipGetLastError();
 }
 
-// Two levels per launch (depth 1): a launch costs ~7 us however little it
+// Two levels per launch: a launch costs ~7 us however little it
 // does, and a sweep has one per level.  One thread per node x of the run's
 // upper level does the work for x and for its children (they are x's alone,
 // and each count is read right after this thread wrote it).  The loads are
@@ -913,18 +970,16 @@ hipError_t launch_down_run(const ExtArgs& a, int depth, int L, int64_t base, int
 // per-child loop: batched the same way it measured slower, its stores and
 // position chain per child.)
 constexpr int kSweepBatch = 4;
-__device__ __forceinline__ bool nch_internal(uint8_t k) { return k >= 1 && k < kNchPP; }
 
+template <bool TP>
 __global__ __launch_bounds__(kBlock) void k_up_run(ExtArgs a, int64_t base, int64_t F,
-                                                   uint32_t* sub_cnt) {
+                                                   const int32_t* rep, uint32_t* sub_cnt) {
   const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (t >= F) return;
   const int64_t x = base + t;
   const uint8_t k = a.t.nch[x];
-  uint32_t c = 0;
-  if (k >= kNchPP) {
-    c = 1;
-  } else if (k) {
+  uint32_t c = own_count<TP>(k, rep, x);
+  if (nch_internal(k)) {
     const int64_t c0 = a.t.cstart[x];
     for (int j0 = 0; j0 < k; j0 += kSweepBatch) {
       uint8_t ky[kSweepBatch];
@@ -937,7 +992,8 @@ __global__ __launch_bounds__(kBlock) void k_up_run(ExtArgs a, int64_t base, int6
       }
       uint32_t cy[kSweepBatch];
 #pragma unroll
-      for (int j = 0; j < kSweepBatch; ++j) cy[j] = ky[j] >= kNchPP ? 1u : 0u;
+      for (int j = 0; j < kSweepBatch; ++j)
+        cy[j] = j0 + j < k ? own_count<TP>(ky[j], rep, c0 + j0 + j) : 0u;
       for (int g0 = 0;; g0 += kSweepBatch) {
         uint32_t v[kSweepBatch][kSweepBatch];
 #pragma unroll
@@ -966,11 +1022,18 @@ __global__ __launch_bounds__(kBlock) void k_up_run(ExtArgs a, int64_t base, int6
   sub_cnt[x] = c;
 }
 
-hipError_t launch_up_run(const ExtArgs& a, int depth, int64_t base, int64_t F, uint32_t* sub_cnt,
+hipError_t launch_up_run(const ExtArgs& a, int64_t base, int64_t F, uint32_t* sub_cnt,
                          hipStream_t st) {
   if (F == 0) return hipSuccess;
-  if (depth != 1) return hipErrorInvalidValue;
-  k_up_run<<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, base, F, sub_cnt);
+  k_up_run<false><<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, base, F, nullptr,
+                                                                            sub_cnt);
+  return hipGetLastError();
+}
+
+hipError_t launch_tp_up_run(const ExtArgs& a, int64_t base, int64_t F, const int32_t* rep,
+                            uint32_t* cnt, hipStream_t st) {
+  if (F == 0) return hipSuccess;
+  k_up_run<true><<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, base, F, rep, cnt);
   return hipGetLastError();
 }
 
@@ -981,8 +1044,9 @@ hipError_t launch_up_run(const ExtArgs& a, int depth, int64_t base, int64_t F, u
 // takes its root's leaves 16 Ki at a time and gives the cycles among them
 // their places after every other vertex's position.
 constexpr int kRotItems = 16;
-__global__ __launch_bounds__(1024) void k_rotations(ExtArgs a, DChains ch, const int32_t* rot,
-                                                    int32_t range_lo, const int64_t* rb,
+__global__ __launch_bounds__(1024) void k_rotations(ExtArgs a, DChains ch, TpTree t,
+                                                    const int32_t* rot, int32_t range_lo,
+                                                    const int64_t* rb,
                                                     uint64_t* leaf, int32_t* pp_len) {
   __shared__ int32_t s_w[16];
   const int x = rot[blockIdx.x];
@@ -1017,10 +1081,12 @@ __global__ __launch_bounds__(1024) void k_rotations(ExtArgs a, DChains ch, const
       if (lf[i] >> 63) {
         const int64_t k = at + __builtin_popcountll(cyc & ((1ull << lane) - 1));
         const int32_t len = pp_len[w0 + 64 * i];
+        const int32_t canon = t.canon ? t.leaf_canon[w0 + 64 * i] : 0;
         for (int j = 1; j < m; ++j) {
           const int64_t r = rb[ch.v[o + j] - range_lo] + k;
           leaf[r] = lf[i] | (uint64_t)j << kLeafStartShift;
           pp_len[r] = len;
+          if (t.canon) t.leaf_canon[r] = canon;
         }
       }
       at += __builtin_popcountll(cyc);
@@ -1029,11 +1095,11 @@ __global__ __launch_bounds__(1024) void k_rotations(ExtArgs a, DChains ch, const
   }
 }
 
-hipError_t launch_rotations(const ExtArgs& a, const DChains& ch, const int32_t* rot, int32_t n_rot,
-                            int32_t range_lo, const int64_t* rb, uint64_t* leaf, int32_t* pp_len,
-                            hipStream_t st) {
+hipError_t launch_rotations(const ExtArgs& a, const DChains& ch, const TpTree& t,
+                            const int32_t* rot, int32_t n_rot, int32_t range_lo, const int64_t* rb,
+                            uint64_t* leaf, int32_t* pp_len, hipStream_t st) {
   if (n_rot <= 0) return hipSuccess;
-  k_rotations<<<(unsigned)n_rot, 1024, 0, st>>>(a, ch, rot, range_lo, rb, leaf, pp_len);
+  k_rotations<<<(unsigned)n_rot, 1024, 0, st>>>(a, ch, t, rot, range_lo, rb, leaf, pp_len);
   return hipGetLastError();
 }
 
@@ -1046,11 +1112,7 @@ hipError_t launch_rotations(const ExtArgs& a, const DChains& ch, const int32_t* 
 // touches few cache lines.  The entries of kPPSeg consecutive depths
 // go to LDS, one row per lane; then the wave stores the rows, kPPSeg lanes
 // per row, so that a store covers a few whole row segments instead of one
-// word in each of 64 lines.  With the BFS tables given, the walk also checks
-// each entry against the BFS parent of the one after it and records the test
-// path's length and where the path leaves the BFS tree, with the entries on
-// either side of that point and the first vertex, from which the test-path
-// keys are built.
+// word in each of 64 lines.
 constexpr int kPPSeg = 16;
 constexpr int kPPRow = kPPSeg + 1;  // LDS row stride (odd: rows fall in different banks)
 
@@ -1062,7 +1124,7 @@ constexpr int kStageVertices = 2048;
 template <bool LDS>
 __global__ __launch_bounds__(kBlock) void k_pp_write(ExtArgs a, DChains ch, int32_t n,
                                                      const uint64_t* leaf, const int64_t* pp_off,
-                                                     int64_t n_pp, int32_t* pp_vtx, PPWriteTp tp) {
+                                                     int64_t n_pp, int32_t* pp_vtx) {
   __shared__ int32_t s_row[kBlock * kPPRow];
   __shared__ int64_t s_lo[kBlock];
   __shared__ int32_t s_len[kBlock];
@@ -1100,15 +1162,10 @@ __global__ __launch_bounds__(kBlock) void k_pp_write(ExtArgs a, DChains ch, int3
     const int32_t y = __shfl_xor(lmax, d, 64);
     lmax = y > lmax ? y : lmax;
   }
-  const bool with_tp = tp.tp_len != nullptr;
   int32_t done = len;  // entries done .. len - 1 are walked
-  int32_t nxt = -1, vk = -1, lead = len;  // the entry after the current one; the last entry
-  int32_t pn = -1;                        // BFS parent of nxt
-  int32_t lw = -1, le = -1;               // the entries at lead - 1 and lead
   int32_t* row = s_row + tid * kPPRow;
   for (int kb = lmax > 0 ? (lmax - 1) / kPPSeg * kPPSeg : -1; kb >= 0; kb -= kPPSeg) {
-    // depths kb + kPPSeg - 1 down to kb: one dependent load per step
-    const int32_t top = done;
+    // depths kb + kPPSeg - 1 down to kb: one dependent load per chain
     int32_t v[kPPSeg];
 #pragma unroll
     for (int m = kPPSeg - 1; m >= 0; --m) {
@@ -1127,30 +1184,6 @@ __global__ __launch_bounds__(kBlock) void k_pp_write(ExtArgs a, DChains ch, int3
     }
 #pragma unroll
     for (int m = 0; m < kPPSeg; ++m) row[m] = v[m];
-    if (with_tp) {
-      // the BFS parents of the round's entries, loaded together, then the
-      // pairs (entry k, entry k + 1) checked from the last one down
-      int32_t pv[kPPSeg];
-#pragma unroll
-      for (int m = 0; m < kPPSeg; ++m) {
-        const int k = kb + m;
-        pv[m] = k >= done && k < top ? tp.parent[v[m]] : -1;
-      }
-#pragma unroll
-      for (int m = kPPSeg - 1; m >= 0; --m) {
-        const int k = kb + m;
-        if (k >= done && k < top) {
-          if (nxt < 0) vk = v[m];
-          else if (pn != v[m]) {
-            lead = k + 1;
-            lw = v[m];
-            le = nxt;
-          }
-          nxt = v[m];
-          pn = pv[m];
-        }
-      }
-    }
     s_done[tid] = done;
     wave_sync();
     // the wave's rows, kPPSeg lanes per row: depths kb .. kb + kPPSeg - 1 of
@@ -1162,24 +1195,17 @@ __global__ __launch_bounds__(kBlock) void k_pp_write(ExtArgs a, DChains ch, int3
     }
     wave_sync();  // the rows are read before the next round writes them
   }
-  if (with_tp && nxt >= 0) {
-    const int32_t v1 = nxt;
-    const int64_t lp = tp.pfx_off[v1 + 1] - tp.pfx_off[v1];
-    tp.tp_len[i] = lp + len + (tp.sfx_off[vk + 1] - tp.sfx_off[vk]);
-    tp.lead[i] = make_int4(lead, lw, le, v1);
-  }
 }
 
 hipError_t launch_pp_write(const ExtArgs& a, const DChains& ch, int32_t n, const uint64_t* leaf,
-                           const int64_t* pp_off, int64_t n_pp, int32_t* pp_vtx,
-                           const PPWriteTp& tp, hipStream_t st) {
+                           const int64_t* pp_off, int64_t n_pp, int32_t* pp_vtx, hipStream_t st) {
   if (n_pp == 0) return hipSuccess;
   const unsigned grid = (unsigned)((n_pp + kBlock - 1) / kBlock);
   if (n <= kStageVertices) {
     const size_t lds = sizeof(uint16_t) * ((size_t)n + a.g.n + 1);
-    k_pp_write<true><<<grid, kBlock, lds, st>>>(a, ch, n, leaf, pp_off, n_pp, pp_vtx, tp);
+    k_pp_write<true><<<grid, kBlock, lds, st>>>(a, ch, n, leaf, pp_off, n_pp, pp_vtx);
   } else {
-    k_pp_write<false><<<grid, kBlock, 0, st>>>(a, ch, n, leaf, pp_off, n_pp, pp_vtx, tp);
+    k_pp_write<false><<<grid, kBlock, 0, st>>>(a, ch, n, leaf, pp_off, n_pp, pp_vtx);
   }
   return hipGetLastError();
 }

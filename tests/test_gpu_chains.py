@@ -109,3 +109,42 @@ def test_streamed_ranges_cut_chains(chunk):
         firsts = c.vertices[c.offsets[:-1]]
         assert ((firsts >= a) & (firsts < b)).all()
     assert st["n_cycles"] == rst["n_cycles"] and st["n_extensions"] == rst["n_extensions"]
+
+
+def _hub(fan, seed):
+    """A switch of `fan` arms in a loop, with arcs between arms and back to
+    the switch from some of them (arcs off the BFS tree at every slot)."""
+    rng = np.random.default_rng(seed)
+    edges = [(0, 1)]
+    for k in range(fan):
+        edges += [(1, 2 + k), (2 + k, 2 + fan)]
+        if rng.random() < 0.3:
+            edges.append((2 + k, 1))
+        if rng.random() < 0.1:
+            edges.append((2 + k, 2 + int(rng.integers(0, fan))))
+    edges += [(2 + fan, 1), (2 + fan, 3 + fan)] if fan < 64 else [(2 + fan, 3 + fan)]
+    return cfggen.from_edges(4 + fan, edges, 0, 3 + fan, f"hub{fan}_{seed}")
+
+
+@pytest.mark.parametrize("fan", [2, 5, 33, 63, 64])
+def test_test_path_order_with_many_arcs(fan):
+    """Test paths in order where one vertex has up to 64 arcs off the BFS
+    tree, alone, with ids shuffled, and as a union of graphs."""
+    graphs = []
+    for seed in range(3):
+        g = _hub(fan, seed)
+        say("case hub", fan, seed)
+        check_tp(g, local=True)
+        check_tp(_shuffled(g, seed + 1), local=True)
+        graphs.append(g)
+    for seed in range(6):
+        graphs.append(cfggen.random_small_cfg(900 + 10 * fan + seed, 8 + 3 * seed, extra=4 + 2 * seed))
+        say("case dense", fan, seed)
+        check_tp(graphs[-1], local=True)
+    res, _ = tpg.batch_test_paths([tpg.load_cfg(g) for g in graphs], ws=ws())
+    for i, g in enumerate(graphs):
+        rp = oracle.prime_paths_local(g, 0, g.n)[0]
+        rt = oracle.test_paths(g, rp)[0]
+        (po, pv), (to, tv) = res.graph(i)
+        assert np.array_equal(po, rp.offsets) and np.array_equal(pv, rp.vertices), g.name
+        assert np.array_equal(to, rt.offsets) and np.array_equal(tv, rt.vertices), g.name
