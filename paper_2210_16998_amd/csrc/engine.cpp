@@ -1019,6 +1019,8 @@ TpTree tp_tree(tpg_workspace* ws, int xn) {
   TpTree t{};
   t.tpar = ws->tp_links.as<int32_t>();
   t.nx = t.tpar + xn;
+  t.cdist = t.nx + xn;
+  t.cback = t.cdist + xn;
   t.canon = ws->canon.as<int32_t>();
   t.leaf_canon = ws->leaf_canon.as<int32_t>();
   return t;
@@ -1034,7 +1036,7 @@ tpg_status bfs_start(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   TPG_TRY(ws_reserve(ws, ws->sfx_off, sizeof(int64_t) * (n + 1)));
   TPG_TRY(ws_reserve(ws, ws->scan2_status, sizeof(uint64_t) * (scan_tiles(n) + 2)));
   TPG_TRY(ws_reserve(ws, ws->totals, sizeof(uint64_t) * PathTotals::words(ws->xg)));
-  TPG_TRY(ws_reserve(ws, ws->tp_links, sizeof(int32_t) * 2 * (size_t)U.xn));
+  TPG_TRY(ws_reserve(ws, ws->tp_links, sizeof(int32_t) * 4 * (size_t)U.xn));
   TPG_TRY(ws_reserve(ws, ws->tp_order, sizeof(int32_t) * (size_t)(U.gbase.back() + 1)));
   const BfsOut b = bfs_views(ws, n);
   hipStream_t side = ws->side_stream;
@@ -1181,6 +1183,7 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
   int32_t* rep = ws->par.as<int32_t>();
   uint32_t* cnt = ws->sub_cnt.as<uint32_t>();
   int32_t* src = ws->row_src.as<int32_t>();
+  int32_t* len = ws->row_len.as<int32_t>();
   int64_t* first = ws->tp_first.as<int64_t>();
   const int32_t* order = ws->tp_order.as<int32_t>();
   const uint64_t* leaf = ws->leaf_by_rank.as<uint64_t>();
@@ -1190,6 +1193,7 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
   key_add(key, tt);
   key_add(key, cnt);
   key_add(key, src);
+  key_add(key, len);
   key_add(key, first);
   key_add(key, order);
   key_add(key, ng);
@@ -1212,18 +1216,16 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
                 : launch_tp_up(a, R.off[top], R.count[top], rep, cnt, st);
       L -= n;
     }
-    if (e == hipSuccess) e = launch_tp_arc_starts(a, order, ng, rep, cnt, first, src, st);
+    if (e == hipSuccess) e = launch_tp_arc_starts(a, tt, order, ng, rep, cnt, first, src, len, st);
     for (int L = 2; L <= R.Lmax && e == hipSuccess; L += 2)
-      e = launch_tp_down_run(a, tt.nx, R.off[L], R.count[L], rep, cnt, src, st);
+      e = launch_tp_down_run(a, tt, R.off[L], R.count[L], rep, cnt, src, len, st);
     return e;
   }));
   int64_t* sc = ws->scalars.as<int64_t>();
   TPG_TRY(io_read(ws, st, ws->h_scalars, first + ng, sizeof(int64_t)));
   T.n_tp = ws->h_scalars[0];
   TPG_TRY(ws_reserve(ws, o.tp_off, sizeof(int64_t) * (T.n_tp + 1)));
-  TPG_HIP(launch_row_len(src, T.n_tp, o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), &b,
-                         ws->row_len.as<int32_t>(), st));
-  TPG_HIP(scan_i32_to_i64(ws->row_len.as<int32_t>(), o.tp_off.as<int64_t>(), T.n_tp, 0, sc,
+  TPG_HIP(scan_i32_to_i64(len, o.tp_off.as<int64_t>(), T.n_tp, 0, sc,
                           ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
   TPG_TRY(io_read(ws, st, ws->h_scalars, sc, sizeof(int64_t)));
   T.n_vtx = ws->h_scalars[0];

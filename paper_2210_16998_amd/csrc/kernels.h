@@ -108,6 +108,8 @@ constexpr uint64_t kLeafCycle = 1ull << 63;
 struct TpTree {
   int32_t* tpar;        // per chain: the chain before it in the BFS tree (-1: none)
   int32_t* nx;          // per chain: the chain after it on the shortest way to the exit
+  int32_t* cdist;       // per chain: vertices before its first on the way from the entry
+  int32_t* cback;       // per chain: vertices after its last on the way to the exit
   int32_t* canon;       // per node: the node of its path without the chains before the
                         // last one of its first BFS-tree part (-1: all of it is one)
   int32_t* leaf_canon;  // the same per prime path
@@ -281,13 +283,15 @@ hipError_t launch_tp_arcs(const DGraph& g, const DGraph& x, const DChains& ch, c
 hipError_t launch_tp_mark(const ExtArgs& a, const TpTree& t, const uint64_t* leaf, int64_t n_pp,
                           const uint8_t* state, int32_t* rep, hipStream_t st);
 // cnt: marked nodes per subtree (launch_tp_up*), rewritten into places (see
-// k_tp_arc_starts) for the n arcs of order; src[place] = prime path
-hipError_t launch_tp_arc_starts(const ExtArgs& a, const int32_t* order, int32_t n,
+// k_tp_arc_starts) for the n arcs of order; src[place] = prime path, len[place]
+// = entries of the test path
+hipError_t launch_tp_arc_starts(const ExtArgs& a, const TpTree& tt, const int32_t* order, int32_t n,
                                 const int32_t* rep, uint32_t* cnt, int64_t* first, int32_t* src,
-                                hipStream_t st);
+                                int32_t* len, hipStream_t st);
 // places from the nodes of a level down through the next one
-hipError_t launch_tp_down_run(const ExtArgs& a, const int32_t* nx, int64_t base, int64_t F,
-                              const int32_t* rep, uint32_t* cnt, int32_t* src, hipStream_t st);
+hipError_t launch_tp_down_run(const ExtArgs& a, const TpTree& tt, int64_t base, int64_t F,
+                              const int32_t* rep, uint32_t* cnt, int32_t* src, int32_t* len,
+                              hipStream_t st);
 // rows r < n, each prime path src[r] (null: r), with b between its prefix and
 // suffix rows: their lengths, and the rows at out_off (n_entries in all)
 hipError_t launch_row_len(const int32_t* src, int64_t n, const int64_t* pp_off,

@@ -679,7 +679,10 @@ __device__ __forceinline__ bool nch_internal(uint8_t k) { return k >= 1 && k < k
 // of the first histogram, summed once, else three or four of the second,
 // summed twice.  Bins are counted in LDS (kept `copies` times, by lane, as a
 // wave's nodes share few lengths) and added to a.tot once per workgroup.
-// Reads 6 bytes a node.
+// Reads 6 bytes a node; the lookups behind a node are a chain of small loads,
+// so a thread takes kLenItems nodes at a time (1.85e8 nodes: 1.02 ms one at a
+// time, 0.58 four).
+constexpr int kLenItems = 4;
 __global__ __launch_bounds__(kBlock) void k_path_lengths(ExtArgs a, int64_t first, int64_t n_nodes,
                                                          int bins, int copies, int lds_roots) {
   extern __shared__ unsigned long long s_hist[];
@@ -699,33 +702,49 @@ __global__ __launch_bounds__(kBlock) void k_path_lengths(ExtArgs a, int64_t firs
   auto add2 = [&](int bin, int x) {
     atomicAdd(&h2[bin * copies + cp], (unsigned long long)(long long)x);
   };
-  const int64_t step = (int64_t)gridDim.x * kBlock;
-  for (int64_t x = first + (int64_t)blockIdx.x * kBlock + tid; x < n_nodes; x += step) {
-    const uint32_t inf = a.t.info[x];
-    const int T = a.t.tl[x];
-    const int v = node_v(inf);
-    const int v1 = v - a.g.loc[v] + node_v1l(inf);
-    const int m1 = a.g.len[v1];
-    if (inf & F_CYC) {
-      atomicAdd(lds_roots ? &s_cyc[v1] : &g_cyc[v1], 1u);
-      if (m1 == 1) {
-        add1(T + 1, 1);
-        add1(T, -1);
+  // kLenItems nodes of a thread in flight together: the lookups behind a node
+  // are a chain of small loads
+  const int64_t step = (int64_t)gridDim.x * kBlock * kLenItems;
+  for (int64_t x0 = first + (int64_t)blockIdx.x * kBlock * kLenItems + tid; x0 < n_nodes;
+       x0 += step) {
+    uint32_t inf[kLenItems];
+    int T[kLenItems], v1[kLenItems], m1[kLenItems], mk[kLenItems];
+#pragma unroll
+    for (int j = 0; j < kLenItems; ++j) {
+      const int64_t x = x0 + j * kBlock;
+      const bool in = x < n_nodes;
+      inf[j] = in ? a.t.info[x] : 0u;
+      T[j] = in ? (int)a.t.tl[x] : -1;
+    }
+#pragma unroll
+    for (int j = 0; j < kLenItems; ++j) {
+      const int v = node_v(inf[j]);
+      v1[j] = v - a.g.loc[v] + node_v1l(inf[j]);
+      mk[j] = a.g.len[v];
+    }
+#pragma unroll
+    for (int j = 0; j < kLenItems; ++j) m1[j] = T[j] < 0 ? 1 : a.g.len[v1[j]];
+#pragma unroll
+    for (int j = 0; j < kLenItems; ++j) {
+      if (T[j] < 0) continue;
+      if (inf[j] & F_CYC) {
+        atomicAdd(lds_roots ? &s_cyc[v1[j]] : &g_cyc[v1[j]], 1u);
+        if (m1[j] == 1) {
+          add1(T[j] + 1, 1);
+          add1(T[j], -1);
+        } else {
+          add2(T[j] + 1, m1[j]);
+          add2(T[j], -(m1[j] + 1));
+          add2(T[j] - m1[j], 1);
+        }
+      } else if (m1[j] == 1) {
+        add1(T[j], 1);
+        add1(T[j] - mk[j], -1);
       } else {
-        add2(T + 1, m1);
-        add2(T, -(m1 + 1));
-        add2(T - m1, 1);
-      }
-    } else {
-      const int mk = a.g.len[v];
-      if (m1 == 1) {
-        add1(T, 1);
-        add1(T - mk, -1);
-      } else {
-        add2(T, 1);
-        add2(T - m1, -1);
-        add2(T - mk, -1);
-        add2(T - m1 - mk, 1);
+        add2(T[j], 1);
+        add2(T[j] - m1[j], -1);
+        add2(T[j] - mk[j], -1);
+        add2(T[j] - m1[j] - mk[j], 1);
       }
     }
   }

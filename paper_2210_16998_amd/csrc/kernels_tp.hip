@@ -301,6 +301,8 @@ __global__ void k_tp_chain_links(DGraph x, DChains ch, BfsOut b, TpTree t) {
   const int q = b.next[ch.v[ch.off[c + 1] - 1]];
   t.tpar[c] = p >= 0 ? ch.of[p] : -1;
   t.nx[c] = q >= 0 ? ch.of[q] : -1;
+  t.cdist[c] = b.dist_f[ch.v[ch.off[c]]];
+  t.cback[c] = b.dist_b[ch.v[ch.off[c + 1] - 1]];
 }
 
 // The places of every component's arcs off the BFS tree, and of the exit's
@@ -471,7 +473,8 @@ hipError_t launch_tp_mark(const ExtArgs& a, const TpTree& t, const uint64_t* lea
 constexpr int kArcItems = 8;
 __global__ __launch_bounds__(1024) void k_tp_arc_starts(TreeBufs t, const int32_t* order, int32_t n,
                                                         const int32_t* rep, uint32_t* cnt,
-                                                        int64_t* first, int32_t* src) {
+                                                        int64_t* first, int32_t* src,
+                                                        int32_t* len, const int32_t* cdist) {
   __shared__ int64_t s_w[16];
   int64_t carry = 0;
   for (int32_t b = 0; b < n; b += 1024 * kArcItems) {
@@ -498,7 +501,10 @@ __global__ __launch_bounds__(1024) void k_tp_arc_starts(TreeBufs t, const int32_
       if (j0 + j < n) {
         first[j0 + j] = at;
         const bool exit_path = order[j0 + j] < 0;
-        if (exit_path && c[j]) src[at] = rep[node[j]] - 1;
+        if (exit_path && c[j]) {
+          src[at] = rep[node[j]] - 1;
+          len[at] = cdist[node[j]] + t.tl[node[j]];
+        }
         if (!exit_path) cnt[node[j]] = c[j] ? (uint32_t)(at + 1) : 0u;
         at += c[j];
       }
@@ -508,10 +514,10 @@ __global__ __launch_bounds__(1024) void k_tp_arc_starts(TreeBufs t, const int32_
   if (threadIdx.x == 0) first[n] = carry;
 }
 
-hipError_t launch_tp_arc_starts(const ExtArgs& a, const int32_t* order, int32_t n,
+hipError_t launch_tp_arc_starts(const ExtArgs& a, const TpTree& tt, const int32_t* order, int32_t n,
                                 const int32_t* rep, uint32_t* cnt, int64_t* first, int32_t* src,
-                                hipStream_t st) {
-  k_tp_arc_starts<<<1, 1024, 0, st>>>(a.t, order, n, rep, cnt, first, src);
+                                int32_t* len, hipStream_t st) {
+  k_tp_arc_starts<<<1, 1024, 0, st>>>(a.t, order, n, rep, cnt, first, src, len, tt.cdist);
   return hipGetLastError();
 }
 
@@ -519,46 +525,60 @@ hipError_t launch_tp_arc_starts(const ExtArgs& a, const int32_t* order, int32_t 
 // child above the chain that follows on the shortest way to the exit; with
 // D > 0 the children do the same for theirs.
 template <int D>
-__device__ __forceinline__ void tp_down_node(const TreeBufs& t, const int32_t* nx, int64_t x,
+__device__ __forceinline__ void tp_down_node(const ExtArgs& a, const TpTree& tt, int64_t x,
                                              uint32_t r, const int32_t* rep, uint32_t* cnt,
-                                             int32_t* src) {
+                                             int32_t* src, int32_t* len) {
+  const TreeBufs& t = a.t;
   int32_t own = rep[x];
+  int next = 0, row = 0;
   const uint8_t k = t.nch[x];
+  if (own) {
+    // entries: the way to the node's first chain, its chains (a cycle's first
+    // one twice), the way on from its last
+    const uint32_t inf = t.info[x];
+    const int v = node_v(inf), v1 = v - a.g.loc[v] + node_v1l(inf);
+    next = tt.nx[v];
+    row = tt.cdist[v1] + t.tl[x] + (k == kNchCycle ? a.g.len[v1] : 0) + tt.cback[v];
+  }
   if (k > 0 && k < kNchPP) {
-    const int next = own ? nx[node_v(t.info[x])] : 0;
     const int64_t c0 = t.cstart[x];
     for (int64_t y = c0; y < c0 + k; ++y) {
       if (own && node_v(t.info[y]) > next) {
-        src[r++] = own - 1;
+        src[r] = own - 1;
+        len[r++] = row;
         own = 0;
       }
       const uint32_t c = cnt[y];
       if constexpr (D > 0) {
-        if (c) tp_down_node<D - 1>(t, nx, y, r, rep, cnt, src);
+        if (c) tp_down_node<D - 1>(a, tt, y, r, rep, cnt, src, len);
       } else {
         cnt[y] = c ? r + 1 : 0u;
       }
       r += c;
     }
   }
-  if (own) src[r] = own - 1;
+  if (own) {
+    src[r] = own - 1;
+    len[r] = row;
+  }
 }
 
 // Two levels from the level [base, base + F) on, a thread per node of it.
-__global__ __launch_bounds__(kBlock) void k_tp_down_run(TreeBufs t, const int32_t* nx, int64_t base,
+__global__ __launch_bounds__(kBlock) void k_tp_down_run(ExtArgs a, TpTree tt, int64_t base,
                                                         int64_t F, const int32_t* rep,
-                                                        uint32_t* cnt, int32_t* src) {
+                                                        uint32_t* cnt, int32_t* src, int32_t* len) {
   const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (j >= F) return;
   const uint32_t r = cnt[base + j];
-  if (r) tp_down_node<1>(t, nx, base + j, r - 1, rep, cnt, src);
+  if (r) tp_down_node<1>(a, tt, base + j, r - 1, rep, cnt, src, len);
 }
 
-hipError_t launch_tp_down_run(const ExtArgs& a, const int32_t* nx, int64_t base, int64_t F,
-                              const int32_t* rep, uint32_t* cnt, int32_t* src, hipStream_t st) {
+hipError_t launch_tp_down_run(const ExtArgs& a, const TpTree& tt, int64_t base, int64_t F,
+                              const int32_t* rep, uint32_t* cnt, int32_t* src, int32_t* len,
+                              hipStream_t st) {
   if (F == 0) return hipSuccess;
-  k_tp_down_run<<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a.t, nx, base, F, rep,
-                                                                          cnt, src);
+  k_tp_down_run<<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, tt, base, F, rep, cnt,
+                                                                          src, len);
   return hipGetLastError();
 }
 
@@ -580,12 +600,18 @@ __global__ __launch_bounds__(kBlock) void k_row_len(const int32_t* src, int64_t 
   len[r] = l;
 }
 
-// A wave writes `rows` (at most 64) consecutive rows, G lanes to a row: the
-// lanes first load the rows' places and parts, one row each, then copy row by
-// row, the entries of G consecutive places at a time, so that loads and
-// stores are whole segments.  The prefix and suffix rows stay in cache; what
-// bounds it is the store stream.
-template <int G, bool ENDS>
+// A wave writes `rows` (a multiple of R, at most 64) consecutive rows: the
+// lanes first load the rows' places and parts, one row each, then the wave
+// copies R rows at a time, lane k entries k, 64 + k, .. of each, the first U
+// steps of all of them loaded before any is stored.  Bound by memory: on the
+// 400-vertex stress CFG (1.94e7 rows, 21.8 GB) it reads 6 GB (the prime paths
+// in the test paths' order) and writes 21.5 in 7.2 ms, 3.8 TB/s against 4.9
+// for a plain copy.  Measured there as whole calls: one row in flight and 64
+// rows a wave 19.5 ms, two 18.8, four 19.0, eight 19.6; stores that bypass the
+// cache 21 to 22 (the lines at row ends then go out in parts); 16 bytes a
+// lane, seldom aligned, 19.6; a row's prefix and suffix kept in registers for
+// the next row 18.9.
+template <int U, int R, bool ENDS>
 __global__ __launch_bounds__(kBlock) void k_emit_rows(const int32_t* src, int64_t n, int rows,
                                                       const int64_t* pp_off, const int32_t* pp_vtx,
                                                       BfsOut b, const int64_t* out_off,
@@ -595,7 +621,7 @@ __global__ __launch_bounds__(kBlock) void k_emit_rows(const int32_t* src, int64_
   if (r0 >= n) return;
   const int nr = (int)(n - r0 < rows ? n - r0 : rows);
   int64_t out = 0, o0 = 0, p0 = 0, s0 = 0;
-  int lq = 0, lp = 0, ls = 0;
+  int lq = 0, lp = 0, ls = 0;  // lanes past the last row: empty rows
   if (lane < nr) {
     const int64_t i = src ? (int64_t)src[r0 + lane] : r0 + lane;
     out = out_off[r0 + lane];
@@ -609,45 +635,51 @@ __global__ __launch_bounds__(kBlock) void k_emit_rows(const int32_t* src, int64_
       s0 = b.sfx_off[vk];
     }
   }
-  auto get = [&](int x, int from) {
-    return G == 64 ? __builtin_amdgcn_readlane(x, from) : __shfl(x, from, 64);
+  auto get = [&](int x, int q) { return __builtin_amdgcn_readlane(x, q); };
+  auto get64 = [&](int64_t x, int q) {
+    return (int64_t)((uint64_t)(uint32_t)get((int)(uint32_t)x, q) |
+                     (uint64_t)(uint32_t)get((int)(x >> 32), q) << 32);
   };
-  auto get64 = [&](int64_t x, int from) {
-    return (int64_t)((uint64_t)(uint32_t)get((int)(uint32_t)x, from) |
-                     (uint64_t)(uint32_t)get((int)(x >> 32), from) << 32);
-  };
-  const int sub = lane / G, l = lane % G;
-  for (int q = 0; q < nr; q += 64 / G) {
-    const int from = q + sub < 64 ? q + sub : 63;
-    const int64_t to = get64(out, from), oq = get64(o0, from);
-    const int nq = get(lq, from);
-    int np = 0, len = nq;
-    const int32_t* pa = nullptr;
-    const int32_t* pc = nullptr;
-    if constexpr (ENDS) {
-      np = get(lp, from);
-      len += np + get(ls, from);
-      pa = b.pfx + get64(p0, from);
-      pc = b.sfx + get64(s0, from) - (np + nq);
+  // row q's parts, each pointer moved so that entry k is at [k]
+  struct Row {
+    const int32_t *a, *b, *c;
+    int np, nq, len;
+    __device__ __forceinline__ int32_t at(int k) const {
+      if constexpr (!ENDS) return b[k];
+      const int32_t* p = k < np ? a : k < np + nq ? b : c;
+      return p[k];
     }
-    const int32_t* pb = pp_vtx + oq - np;
-    if (q + sub >= nr) len = 0;
-    int32_t* dst = out_vtx + to;
-    constexpr int U = 4;
-    for (int k0 = l; k0 < len; k0 += G * U) {
-      int32_t v[U];
+  };
+  auto row = [&](int q) {
+    Row w{};
+    w.nq = get(lq, q);
+    w.len = w.nq;
+    if constexpr (ENDS) {
+      w.np = get(lp, q);
+      w.len += w.np + get(ls, q);
+      w.a = b.pfx + get64(p0, q);
+      w.c = b.sfx + get64(s0, q) - (w.np + w.nq);
+    }
+    w.b = pp_vtx + get64(o0, q) - w.np;
+    return w;
+  };
+  for (int q0 = 0; q0 < nr; q0 += R) {
+    int32_t v[R][U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = k0 + u * G;
-        if (k < len) {
-          const int32_t* p = pb;
-          if constexpr (ENDS) p = k < np ? pa : k < np + nq ? pb : pc;
-          v[u] = p[k];
-        }
-      }
+    for (int r = 0; r < R; ++r) {
+      const Row w = row(q0 + r);
 #pragma unroll
       for (int u = 0; u < U; ++u)
-        if (k0 + u * G < len) dst[k0 + u * G] = v[u];
+        if (lane + 64 * u < w.len) v[r][u] = w.at(lane + 64 * u);
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const Row w = row(q0 + r);
+      int32_t* to = out_vtx + get64(out, q0 + r);
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (lane + 64 * u < w.len) to[lane + 64 * u] = v[r][u];
+      for (int k = lane + 64 * U; k < w.len; k += 64) to[k] = w.at(k);
     }
   }
 }
@@ -667,19 +699,22 @@ hipError_t launch_emit_rows(const int32_t* src, int64_t n, int64_t n_entries, co
                             const int32_t* pp_vtx, const BfsOut* b, const int64_t* out_off,
                             int32_t* out_vtx, hipStream_t st) {
   if (n == 0) return hipSuccess;
-  // a few thousand waves at least, while there are rows for them
-  const int rows = (int)std::min<int64_t>(64, std::max<int64_t>(1, n / 8192));
+  // more rows a wave spread the first loads' cost, fewer keep the chip full:
+  // 573 k rows 1.90 ms a call with 16 and 1.95 with 64, 1.9e7 rows 19.2 and 18.8
+  const int rows = n >= (int64_t)1 << 20 ? 64 : 16;
   const int64_t waves = (n + rows - 1) / rows;
   const unsigned grid = (unsigned)((waves + kBlock / 64 - 1) / (kBlock / 64));
-  const bool wide = n_entries >= 64 * n;  // rows of a wave's width and more
-#define TPG_EMIT(G, E, B)                                                                       \
-  k_emit_rows<G, E><<<grid, kBlock, 0, st>>>(src, n, rows, pp_off, pp_vtx, B, out_off, out_vtx)
+  // the steps that hold a row of average length, to 5
+  const int64_t steps = n_entries / (64 * n) + 1;
+#define TPG_EMIT(U, R, E, B)                                                                    \
+  k_emit_rows<U, R, E><<<grid, kBlock, 0, st>>>(src, n, rows, pp_off, pp_vtx, B, out_off, out_vtx)
   if (b) {
-    if (wide) TPG_EMIT(64, true, *b);
-    else TPG_EMIT(16, true, *b);
+    if (steps <= 1) TPG_EMIT(1, 4, true, *b);
+    else if (steps <= 2) TPG_EMIT(2, 4, true, *b);
+    else TPG_EMIT(5, 2, true, *b);
   } else {
-    if (wide) TPG_EMIT(64, false, BfsOut{});
-    else TPG_EMIT(16, false, BfsOut{});
+    if (steps <= 1) TPG_EMIT(1, 4, false, BfsOut{});
+    else TPG_EMIT(2, 4, false, BfsOut{});
   }
 #undef TPG_EMIT
   return hipGetLastError();
