@@ -37,6 +37,8 @@ struct HostUnion {
   std::vector<int32_t> xsp{0}, xs, xpp{0}, xp, xloc, xlen, xcomp, xcbase{0};
   std::vector<int32_t> choff{0}, chv, chof, chpos;  // see DChains
   std::vector<int32_t> gbase{0};  // arcs off the BFS tree and exit paths, by component
+  std::vector<int32_t> rbase{0};  // entries of the chains' prefix (suffix) rows, by component
+  int32_t max_chains = 1, max_words = 1;  // chains, and graph words (sp, s, pp, p, len), of a component
   std::vector<int32_t> xhead;                       // first vertex of every chain
   std::vector<int32_t> rot;  // chains of two or more vertices, ascending
   std::vector<uint64_t> uids;
@@ -110,6 +112,7 @@ struct tpg_workspace {
   DGraph dg{}, xg{};   // the union, and the union of its chains
   DChains ch{};
   const int32_t* d_gbase = nullptr;  // HostUnion::gbase
+  const int32_t* d_rbase = nullptr;  // HostUnion::rbase
   const int32_t* d_rot = nullptr;    // HostUnion::rot
 
   // path tree
@@ -120,9 +123,8 @@ struct tpg_workspace {
   DevBuf sub_cnt, pp_len, leaf_by_rank, totals;  // totals: see PathTotals
   // scans
   DevBuf scan_status, scan_ctr, scalars;
-  DevBuf scan2_status;  // the side stream's own scan scratch
   // test paths
-  DevBuf bfs_i32, pfx_off, sfx_off, pfx, sfx;
+  DevBuf bfs_i32, pfx, sfx;            // see EndRows
   DevBuf rb0;                         // output positions by first vertex
   DevBuf tp_links, tp_order, tp_first;  // TpTree's chain links, the arcs' order and places
   DevBuf canon, leaf_canon;           // see TpTree
@@ -363,6 +365,9 @@ void add_component(HostUnion& U, const tpg_graph* g, int32_t block = 0) {
   U.xcbase.push_back(U.xn);
   // every chain but the entry's has one BFS-tree arc; the exit's path counts too
   U.gbase.push_back(U.gbase.back() + (int32_t)c.s.size() - (c.n - 1) + 1);
+  U.rbase.push_back(U.rbase.back() + c.n * g->n);  // at most 2^12 * 2^17 in a union
+  U.max_chains = std::max(U.max_chains, c.n);
+  U.max_words = std::max(U.max_words, 3 * c.n + 2 + 2 * (int32_t)c.s.size());
   U.n_comp += 1;
   U.W = std::max(U.W, pow2_words(c.n));
   U.Wu = std::max(U.Wu, (c.n + 63) / 64);
@@ -378,7 +383,7 @@ tpg_status upload_union(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   const std::vector<int32_t>* parts[] = {
       &U.sp, &U.s, &U.pp, &U.p, &U.loc, &U.comp, &U.cbase, &U.centry, &U.cexit,
       &U.xsp, &U.xs, &U.xpp, &U.xp, &U.xloc, &U.xlen, &U.xcomp, &U.xcbase,
-      &U.choff, &U.chv, &U.chof, &U.chpos, &U.gbase, &U.rot};
+      &U.choff, &U.chv, &U.chof, &U.chpos, &U.gbase, &U.rbase, &U.rot};
   constexpr int kParts = sizeof(parts) / sizeof(parts[0]);
   size_t words = 0, at[kParts];
   for (int i = 0; i < kParts; ++i) {
@@ -422,7 +427,8 @@ tpg_status upload_union(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   ws->xg = x;
   ws->ch = DChains{q + at[17], q + at[18], q + at[19], q + at[20]};
   ws->d_gbase = q + at[21];
-  ws->d_rot = q + at[22];
+  ws->d_rbase = q + at[22];
+  ws->d_rot = q + at[23];
   ws->union_uids = U.uids;
   return TPG_OK;
 }
@@ -863,7 +869,7 @@ struct PPResult {
   int64_t n_pp = 0, n_vtx = 0, n_cycles = 0;
 };
 
-BfsOut bfs_views(tpg_workspace* ws, int n);
+EndRows end_rows(tpg_workspace* ws, int n);
 TpTree tp_tree(tpg_workspace* ws, int xn);
 
 // Simple paths by length (index: entries) from the histograms that the device
@@ -931,7 +937,7 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
     if (e == hipSuccess) e = launch_roots(a, ws->ch, range_lo, range_n, sc, rb, st);
     return e;
   }));
-  // the BFS ran beside the extension: its row totals come with the others
+  // the BFS ran beside the extension
   const bool with_tp = ws->bfs_pending;
   if (with_tp) TPG_HIP(hipStreamWaitEvent(st, ws->ev_join, 0));
   TPG_TRY(io_read(ws, st, ws->h_totals, ws->totals.p,
@@ -999,17 +1005,12 @@ struct TPResult {
   int64_t n_spliced = 0, n_tp = 0, n_vtx = 0;
 };
 
-BfsOut bfs_views(tpg_workspace* ws, int n) {
-  BfsOut b{};
-  int32_t* bi = ws->bfs_i32.as<int32_t>();
-  b.dist_f = bi;
-  b.parent = bi + n;
-  b.dist_b = bi + 2 * n;
-  b.next = bi + 3 * n;
-  b.pre = bi + 4 * n;
-  b.pend = bi + 5 * n;
-  b.pfx_off = ws->pfx_off.as<int64_t>();
-  b.sfx_off = ws->sfx_off.as<int64_t>();
+EndRows end_rows(tpg_workspace* ws, int n) {
+  EndRows b{};
+  b.n_pfx = ws->bfs_i32.as<int32_t>();
+  b.n_sfx = b.n_pfx + n;
+  b.pfx_at = b.n_sfx + n;
+  b.sfx_at = b.pfx_at + n;
   b.pfx = ws->pfx.as<int32_t>();
   b.sfx = ws->sfx.as<int32_t>();
   return b;
@@ -1026,30 +1027,20 @@ TpTree tp_tree(tpg_workspace* ws, int xn) {
   return t;
 }
 
-// BFS distances, tree ranks, prefix / suffix row offsets and the arcs'
-// test-path order of the uploaded union, on the side stream after everything
-// already queued on `st`.
+// BFS tree, prefix and suffix rows and the arcs' test-path order of the
+// uploaded union, on the side stream after everything already queued on `st`.
 tpg_status bfs_start(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
-  const int n = U.n;
-  TPG_TRY(ws_reserve(ws, ws->bfs_i32, sizeof(int32_t) * 6 * (size_t)n));
-  TPG_TRY(ws_reserve(ws, ws->pfx_off, sizeof(int64_t) * (n + 1)));
-  TPG_TRY(ws_reserve(ws, ws->sfx_off, sizeof(int64_t) * (n + 1)));
-  TPG_TRY(ws_reserve(ws, ws->scan2_status, sizeof(uint64_t) * (scan_tiles(n) + 2)));
-  TPG_TRY(ws_reserve(ws, ws->totals, sizeof(uint64_t) * PathTotals::words(ws->xg)));
+  TPG_TRY(ws_reserve(ws, ws->bfs_i32, sizeof(int32_t) * 4 * (size_t)U.n));
+  TPG_TRY(ws_reserve(ws, ws->pfx, sizeof(int32_t) * ((size_t)U.rbase.back() + 1)));
+  TPG_TRY(ws_reserve(ws, ws->sfx, sizeof(int32_t) * ((size_t)U.rbase.back() + 1)));
   TPG_TRY(ws_reserve(ws, ws->tp_links, sizeof(int32_t) * 4 * (size_t)U.xn));
   TPG_TRY(ws_reserve(ws, ws->tp_order, sizeof(int32_t) * (size_t)(U.gbase.back() + 1)));
-  const BfsOut b = bfs_views(ws, n);
   hipStream_t side = ws->side_stream;
-  int64_t* tot = ws->totals.as<int64_t>();
   TPG_HIP(hipEventRecord(ws->ev_fork, st));
   TPG_HIP(hipStreamWaitEvent(side, ws->ev_fork, 0));
-  TPG_HIP(launch_bfs_dist(ws->dg, b, side));
-  TPG_HIP(scan_i32_to_i64(b.dist_f, b.pfx_off, n, 0, tot + PathTotals::kPfx, ws->scan2_status.as<uint64_t>(),
-                          nullptr, side));
-  TPG_HIP(scan_i32_to_i64(b.dist_b, b.sfx_off, n, 0, tot + PathTotals::kSfx, ws->scan2_status.as<uint64_t>(),
-                          nullptr, side));
-  TPG_HIP(launch_tp_arcs(ws->dg, ws->xg, ws->ch, b, tp_tree(ws, U.xn), ws->d_gbase,
-                         ws->tp_order.as<int32_t>(), side));
+  TPG_HIP(launch_chain_bfs(ws->dg, ws->xg, ws->ch, tp_tree(ws, U.xn), ws->d_gbase,
+                           ws->tp_order.as<int32_t>(), ws->d_rbase, end_rows(ws, U.n),
+                           U.max_chains, U.max_words, side));
   TPG_HIP(hipEventRecord(ws->ev_join, side));
   ws->bfs_pending = true;
   return TPG_OK;
@@ -1058,7 +1049,7 @@ tpg_status bfs_start(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
 // Longest-first covering (see kernels_cover.hip) over the spliced test paths
 // of all np prime paths: gstate0[i] = 1 for the chosen prime paths.
 tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, int64_t np,
-                         const OutSet& o, const BfsOut& b) {
+                         const OutSet& o, const EndRows& b) {
   const int n = U.n;
   int64_t* sc = ws->scalars.as<int64_t>();
   int64_t* hs = ws->h_scalars;
@@ -1172,10 +1163,7 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
   TPG_TRY(ws_reserve(ws, ws->row_src, sizeof(int32_t) * (np + 1)));
   TPG_TRY(ws_reserve(ws, ws->row_len, sizeof(int32_t) * (np + 1)));
   TPG_TRY(ws_reserve(ws, ws->tp_first, sizeof(int64_t) * (ng + 1)));
-  TPG_TRY(ws_reserve(ws, ws->pfx, sizeof(int32_t) * (ws->h_totals[PathTotals::kPfx] + 1)));
-  TPG_TRY(ws_reserve(ws, ws->sfx, sizeof(int32_t) * (ws->h_totals[PathTotals::kSfx] + 1)));
-  const BfsOut b = bfs_views(ws, U.n);
-  TPG_HIP(launch_bfs_tables(ws->dg, b, st));
+  const EndRows b = end_rows(ws, U.n);
   if (greedy) TPG_TRY(greedy_select(ws, U, st, np, o, b));
   // the prime paths' parents are not read any more: the marks take their place
   const ExtArgs a = make_args(ws);
@@ -1584,11 +1572,11 @@ void tpg_workspace_free(tpg_workspace* ws) {
   DevBuf* bufs[] = {&ws->g_csr, &ws->par, &ws->info, &ws->cstart, &ws->nch, &ws->tl, &ws->mask0,
                     &ws->mask1, &ws->ls, &ws->sub_cnt, &ws->pp_len,
                     &ws->leaf_by_rank, &ws->totals, &ws->scan_status,
-                    &ws->scan_ctr, &ws->scalars, &ws->bfs_i32, &ws->pfx_off, &ws->sfx_off,
+                    &ws->scan_ctr, &ws->scalars, &ws->bfs_i32,
                     &ws->pfx, &ws->sfx, &ws->rb0, &ws->tp_links, &ws->tp_order, &ws->tp_first,
                     &ws->canon, &ws->leaf_canon, &ws->row_src, &ws->row_len, &ws->spl_off,
                     &ws->spl_vtx, &ws->chunk_off, &ws->lvl_comp, &ws->b_pp_off,
-                    &ws->scan2_status, &ws->digest, &ws->grp_key, &ws->grp_hist, &ws->grp_base,
+                    &ws->digest, &ws->grp_key, &ws->grp_hist, &ws->grp_base,
                     &ws->cov_keys, &ws->cov_vals, &ws->cov_misc, &ws->cov_cnt, &ws->cov_at,
                     &ws->pair_p, &ws->pair_q, &ws->cov_pos, &ws->gstate0, &ws->gstate1,
                     &ws->scc_work, &ws->scc_comp, &ws->scc_flags, &ws->scc_misc, &ws->ty_off,

@@ -52,13 +52,12 @@ struct ExtArgs {
   uint64_t* tot;  // PathTotals of this tree, cleared by the seeding
 };
 
-// What the ranking reports of a tree, int64 words: the totals of the prefix
-// and suffix rows (the BFS's, kept by the seeding), the prime paths, the
+// What the ranking reports of a tree, int64 words: the prime paths, the
 // closed cycles, then two histograms of kLenPad + max_comp bins by path
 // length (see k_path_lengths), then one uint32 per chain: the cycles closed
 // in its tree.
 struct PathTotals {
-  static constexpr int kPfx = 0, kSfx = 1, kPP = 2, kCycles = 3, kHist = 4, kLenPad = 2;
+  static constexpr int kPP = 0, kCycles = 1, kHist = 2, kLenPad = 2;
   __host__ __device__ static int64_t bins(const DGraph& g) { return kLenPad + (int64_t)g.max_comp; }
   __host__ __device__ static int64_t host_words(const DGraph& g) { return kHist + 2 * bins(g); }
   __host__ __device__ static int64_t words(const DGraph& g) { return host_words(g) + ((int64_t)g.n + 1) / 2; }
@@ -249,22 +248,20 @@ hipError_t launch_digest(const int64_t* off, const int32_t* vtx, int64_t n, uint
 hipError_t launch_zero_u32(uint32_t* p, int64_t n, hipStream_t st);
 
 // --- test paths --------------------------------------------------------------
-struct BfsOut {
-  int32_t* dist_f;   // [n] arcs from entry
-  int32_t* parent;   // [n] lexicographically smallest shortest-path parent
-  int32_t* dist_b;   // [n] arcs to exit
-  int32_t* next;     // [n] first step of the smallest shortest path to exit
-  int64_t* pfx_off;  // [n+1] prefix table offsets (entries before v)
-  int32_t* pfx;      // [pfx_off[n]]
-  int64_t* sfx_off;  // [n+1] suffix table offsets (entries after v)
-  int32_t* sfx;      // [sfx_off[n]]
-  int32_t* pre;      // [n] graph-wide preorder rank in the BFS tree (children ascending)
-  int32_t* pend;     // [n] end of v's subtree rank range
+// Prefix and suffix of every vertex: n_pfx[v] entries from pfx[pfx_at[v]],
+// n_sfx[v] entries from sfx[sfx_at[v]] (see k_chain_rows).
+struct EndRows {
+  int32_t *n_pfx, *n_sfx, *pfx_at, *sfx_at;  // [n]
+  int32_t *pfx, *sfx;
 };
-// one workgroup per component: dist_f, parent, pre, pend, dist_b, next
-hipError_t launch_bfs_dist(const DGraph& g, const BfsOut& b, hipStream_t st);
-// after pfx_off / sfx_off are scans of dist_f / dist_b: fill pfx / sfx
-hipError_t launch_bfs_tables(const DGraph& g, const BfsOut& b, hipStream_t st);
+// The BFS tree over the chains into t, the arcs' test-path order (gbase[c]:
+// the components' first places, c = 0 .. n_comp), and b's rows (rbase[c]: the
+// components' first entries).  max_chains, max_words: chains, and words of
+// sp, s, pp, p and len, of the largest component.
+constexpr int kArcSlotBits = 6;  // a successor slot; chain ids take 17 bits
+hipError_t launch_chain_bfs(const DGraph& g, const DGraph& x, const DChains& ch, const TpTree& t,
+                            const int32_t* gbase, int32_t* order, const int32_t* rbase,
+                            const EndRows& b, int max_chains, int max_words, hipStream_t st);
 hipError_t launch_localize(const int32_t* loc, int32_t* v, int64_t n, hipStream_t st);
 // per-component output starts: pp_start[c] = rank of the first PP of c and
 // ppv_start[c] = offset of its first entry (after the PP offsets exist; rb:
@@ -272,12 +269,6 @@ hipError_t launch_localize(const int32_t* loc, int32_t* v, int64_t n, hipStream_
 hipError_t launch_comp_pp_starts(const DGraph& g, const int64_t* rb, const int64_t* pp_off,
                                  int64_t* pp_start, int64_t* ppv_start, hipStream_t st);
 
-// The arcs off the BFS tree in test-path order (see k_tp_arc_order) and the
-// chains' links t.tpar, t.nx; gbase[c]: the components' first places there
-// (c = 0 .. n_comp).
-constexpr int kArcSlotBits = 6;  // a successor slot; chain ids take 17 bits
-hipError_t launch_tp_arcs(const DGraph& g, const DGraph& x, const DChains& ch, const BfsOut& b,
-                          const TpTree& t, const int32_t* gbase, int32_t* order, hipStream_t st);
 // rep[node] = prime path + 1 for the node of every test path (state: see
 // k_tp_mark); rep must be zero
 hipError_t launch_tp_mark(const ExtArgs& a, const TpTree& t, const uint64_t* leaf, int64_t n_pp,
@@ -295,9 +286,9 @@ hipError_t launch_tp_down_run(const ExtArgs& a, const TpTree& tt, int64_t base, 
 // rows r < n, each prime path src[r] (null: r), with b between its prefix and
 // suffix rows: their lengths, and the rows at out_off (n_entries in all)
 hipError_t launch_row_len(const int32_t* src, int64_t n, const int64_t* pp_off,
-                          const int32_t* pp_vtx, const BfsOut* b, int32_t* len, hipStream_t st);
+                          const int32_t* pp_vtx, const EndRows* b, int32_t* len, hipStream_t st);
 hipError_t launch_emit_rows(const int32_t* src, int64_t n, int64_t n_entries, const int64_t* pp_off,
-                            const int32_t* pp_vtx, const BfsOut* b, const int64_t* out_off,
+                            const int32_t* pp_vtx, const EndRows* b, const int64_t* out_off,
                             int32_t* out_vtx, hipStream_t st);
 // start[c] / vstart[c] (c = 0 .. n_comp) of the test paths
 hipError_t launch_comp_tp_starts(int n_comp, const int32_t* gbase, const int64_t* first,

@@ -83,7 +83,7 @@ __global__ void k_seed(ExtArgs a, int64_t tot_words) {
     a.t.info[i] = make_info(v, a.g.loc[v], 0);
     a.t.tl[i] = (uint16_t)a.g.len[v];
   }
-  for (int64_t k = PathTotals::kPP + i; k < tot_words; k += (int64_t)gridDim.x * blockDim.x) a.tot[k] = 0;
+  for (int64_t k = i; k < tot_words; k += (int64_t)gridDim.x * blockDim.x) a.tot[k] = 0;
   // visited sets of level 1 (stored, buffer 0): one bit each, at the
   // chain's local id
   const int W = a.t.mask_words;

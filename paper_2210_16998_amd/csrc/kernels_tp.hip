@@ -4,14 +4,9 @@
 // Sec. 7.3, the Ammann-Offutt construction; Problem 1 asks for test paths
 // covering every prime path).  The shortest connection is taken, and among
 // shortest ones the lexicographically smallest, so the result is unique:
-//  * prefix(v): smallest shortest entry -> v path.  A FIFO breadth-first
-//    search that scans successors in ascending order discovers it (each
-//    layer's queue order is the lexicographic order of those paths); the
-//    level-synchronous search here reproduces FIFO discovery order by giving
-//    every vertex the discoverer with the smallest (queue position, successor
-//    slot) key.
-//  * suffix(v): smallest shortest v -> exit path: distances to the exit by a
-//    reverse search, then the smallest successor one step closer.
+//  * prefix(v): smallest shortest entry -> v path; suffix(v): smallest shortest
+//    v -> exit path.  Both are made of whole chains, so they are found on the
+//    graph of chains (k_chain_bfs).
 //  * TP(p) = prefix(v1) without v1 ++ p ++ suffix(vk) without vk.
 //
 // Order and duplicates are read off the path tree; no test path is compared
@@ -19,232 +14,289 @@
 // the tree, two subtree sweeps like the prime paths' give the nodes' places
 // in lexicographic order, and the rows are written where they belong.
 
-#include <climits>
-
 #include "kernels.h"
 
 namespace tpg {
 
-constexpr int kBfsThreads = 256;
 constexpr int kMaxComp = 4096;  // vertices per component
 
-// Exclusive scan of data[0..m) in place (m <= kMaxComp), in chunks of
-// 4 * kBfsThreads; returns the total.
-__device__ int lds_excl_scan(int16_t* data, int m, int32_t* s_w) {
-  int carry = 0;
-  for (int c0 = 0; c0 < m; c0 += 4 * kBfsThreads) {
-    const int b = c0 + (int)threadIdx.x * 4;
-    int v[4];
-    int sum = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      v[k] = (b + k < m) ? (int)data[b + k] : 0;
-      sum += v[k];
+// Shortest paths from the entry and to the exit over one component's chains,
+// the BFS tree (every chain's predecessor on its lexicographically smallest
+// shortest path, the one a first-in first-out search with ascending
+// successors finds) and the test-path order of the arcs off it.  One workgroup
+// per component, everything in LDS:
+//  * distances by relaxing all chains at once until nothing changes (as many
+//    rounds as a shortest path has chains, not vertices);
+//  * where several predecessors are on shortest paths, the two paths are
+//    compared by walking them up, the longer one first, to the chain they
+//    share: the smaller chain after it decides.  The walk uses the tree as
+//    found so far, so it is repeated until no choice changes;
+//  * preorder ranks (children ascending) by sums along the ways up: of ones for
+//    the subtree sizes, then of the sizes of the smaller siblings;
+//  * the arcs' order.  An arc (W, Y) off the tree comes right before W's first
+//    tree child above Y (rank s), or at the end of W's subtree; among arcs at
+//    one rank those that end a subtree come first, deepest first, then W's own
+//    before child s in the order of Y; the exit's path comes last at the exit's
+//    rank.  order[gbase[c] ..) lists the arcs as W << kArcSlotBits | slot of Y
+//    among W's successors, and the exit's chain X as ~X.
+// A search by vertices, one queue layer after the other, took 0.26 ms for 212
+// vertices and 2.5 ms for 1000 (98 and 174 chains), longer than the extension
+// beside it.
+template <int MAXC, int NT, bool STAGE>
+__global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch, TpTree t,
+                                                  const int32_t* gbase, int32_t* order) {
+  __shared__ int32_t s_d[MAXC + 1];  // distance before the chain; later sibling sums, arcs per rank
+  __shared__ int32_t s_b[MAXC + 1];  // distance after it; later subtree sizes, arcs that end one
+  __shared__ int16_t s_par[MAXC];
+  __shared__ int16_t s_pre[MAXC];
+  __shared__ int16_t s_pend[MAXC];
+  __shared__ int32_t s_w[NT / 64];
+  extern __shared__ int32_t s_g[];  // STAGE: the component's sp, s, pp, p, len
+  constexpr int kFar = 1 << 29;
+  const int c = (int)blockIdx.x, tid = (int)threadIdx.x;
+  const int x0 = x.cbase[c], n = x.cbase[c + 1] - x0;
+  const int e0 = x.sp[x0], m = x.sp[x0 + n] - e0, f0 = x.pp[x0];
+  int32_t* const l_sp = s_g;
+  int32_t* const l_s = l_sp + n + 1;
+  int32_t* const l_pp = l_s + m;
+  int32_t* const l_p = l_pp + n + 1;
+  int32_t* const l_len = l_p + m;
+  if constexpr (STAGE) {
+    for (int i = tid; i <= n; i += NT) {
+      l_sp[i] = x.sp[x0 + i] - e0;
+      l_pp[i] = x.pp[x0 + i] - f0;
     }
+    for (int i = tid; i < m; i += NT) {
+      l_s[i] = x.s[e0 + i] - x0;
+      l_p[i] = x.p[f0 + i] - x0;
+    }
+    for (int i = tid; i < n; i += NT) l_len[i] = x.len[x0 + i];
+  }
+  // local ids and arc indices throughout
+  auto sp = [&](int i) { return STAGE ? l_sp[i] : x.sp[x0 + i] - e0; };
+  auto succ = [&](int k) { return STAGE ? l_s[k] : x.s[e0 + k] - x0; };
+  auto pp = [&](int i) { return STAGE ? l_pp[i] : x.pp[x0 + i] - f0; };
+  auto pred = [&](int k) { return STAGE ? l_p[k] : x.p[f0 + k] - x0; };
+  auto len = [&](int i) { return STAGE ? l_len[i] : x.len[x0 + i]; };
+  const int en = ch.of[g.centry[c]] - x0, ex = ch.of[g.cexit[c]] - x0;
+  for (int i = tid; i < n; i += NT) {
+    s_d[i] = i == en ? 0 : kFar;
+    s_b[i] = i == ex ? 0 : kFar;
+  }
+  __syncthreads();
+  int more;
+  do {
+    more = 0;
+    for (int i = tid; i < n; i += NT) {
+      int d = s_d[i], b = s_b[i];
+      for (int k = pp(i); k < pp(i + 1); ++k) d = min(d, s_d[pred(k)] + len(pred(k)));
+      for (int k = sp(i); k < sp(i + 1); ++k) b = min(b, s_b[succ(k)] + len(succ(k)));
+      if (d < s_d[i] || b < s_b[i]) {
+        s_d[i] = d;
+        s_b[i] = b;
+        more = 1;
+      }
+    }
+  } while (__syncthreads_or(more));
+  // a predecessor on a shortest path (the first), the next chain to the exit
+  for (int i = tid; i < n; i += NT) {
+    int par = -1, nx = -1;
+    for (int k = pp(i); k < pp(i + 1) && par < 0; ++k)
+      if (s_d[pred(k)] + len(pred(k)) == s_d[i]) par = pred(k);
+    for (int k = sp(i); k < sp(i + 1) && nx < 0; ++k)
+      if (s_b[succ(k)] + len(succ(k)) == s_b[i]) nx = succ(k);
+    if (i == en) par = -1;
+    if (i == ex) nx = -1;
+    s_par[i] = (int16_t)par;
+    t.nx[x0 + i] = nx < 0 ? -1 : x0 + nx;
+    t.cdist[x0 + i] = s_d[i];
+    t.cback[x0 + i] = s_b[i];
+  }
+  __syncthreads();
+  // whether the tree path to a's end precedes the equally long one to b's;
+  // every step up shortens a path, whatever the tree holds so far
+  auto before = [&](int a, int b) {
+    int ca = a, cb = b;
+    while (a != b && a >= 0 && b >= 0) {
+      const int da = s_d[a], db = s_d[b];
+      if (da >= db) {
+        ca = a;
+        a = s_par[a];
+      }
+      if (db >= da) {
+        cb = b;
+        b = s_par[b];
+      }
+    }
+    return ca < cb;
+  };
+  do {
+    more = 0;
+    for (int i = tid; i < n; i += NT) {
+      if (i == en) continue;
+      int best = -1;
+      for (int k = pp(i); k < pp(i + 1); ++k) {
+        const int p = pred(k);
+        if (s_d[p] + len(p) == s_d[i] && (best < 0 || before(p, best))) best = p;
+      }
+      if (best != s_par[i]) {
+        s_par[i] = (int16_t)best;
+        more = 1;
+      }
+    }
+  } while (__syncthreads_or(more));
+  for (int i = tid; i < n; i += NT) {
+    t.tpar[x0 + i] = s_par[i] < 0 ? -1 : x0 + s_par[i];
+    s_b[i] = 1;
+  }
+  __syncthreads();
+  for (int i = tid; i < n; i += NT)
+    for (int a = s_par[i]; a >= 0; a = s_par[a]) atomicAdd(&s_b[a], 1);
+  __syncthreads();
+  for (int i = tid; i < n; i += NT) {
+    int d = 1;
+    const int p = s_par[i];
+    if (p >= 0)
+      for (int k = sp(p); k < sp(p + 1) && succ(k) < i; ++k)
+        if (s_par[succ(k)] == p) d += s_b[succ(k)];
+    s_d[i] = d;
+  }
+  __syncthreads();
+  for (int i = tid; i < n; i += NT) {
+    int r = 0;
+    for (int a = i; s_par[a] >= 0; a = s_par[a]) r += s_d[a];
+    s_pre[i] = (int16_t)r;
+    s_pend[i] = (int16_t)(r + s_b[i]);
+  }
+  __syncthreads();
+  int32_t* s_at = s_d;   // arcs per rank, then their first place
+  int32_t* s_end = s_b;  // of them, arcs that end a subtree
+  for (int i = tid; i <= n; i += NT) {
+    s_at[i] = 0;
+    s_end[i] = 0;
+  }
+  __syncthreads();
+  auto tree_arc = [&](int w, int k) { return s_par[succ(k)] == w; };
+  // rank at which arc k of w comes
+  auto rank_of = [&](int w, int k, bool& ends) {
+    for (int j = k + 1; j < sp(w + 1); ++j)
+      if (tree_arc(w, j)) {
+        ends = false;
+        return (int)s_pre[succ(j)];
+      }
+    ends = true;
+    return (int)s_pend[w];
+  };
+  for (int w = tid; w < n; w += NT) {
+    for (int k = sp(w); k < sp(w + 1); ++k) {
+      if (tree_arc(w, k)) continue;
+      bool ends;
+      const int r = rank_of(w, k, ends);
+      atomicAdd(&s_at[r], 1);
+      if (ends) atomicAdd(&s_end[r], 1);
+    }
+    if (w == ex) atomicAdd(&s_at[s_pre[w]], 1);
+  }
+  __syncthreads();
+  int carry = gbase[c];
+  for (int k0 = 0; k0 <= n; k0 += NT) {
+    const int k = k0 + tid;
+    const int v = k <= n ? s_at[k] : 0;
     int tot;
-    int pre = block_excl_scan<kBfsThreads, int>(sum, tot, s_w) + carry;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (b + k < m) data[b + k] = (int16_t)pre;
-      pre += v[k];
-    }
+    const int pre = block_excl_scan<NT, int>(v, tot, s_w);
+    if (k <= n) s_at[k] = carry + pre;
     carry += tot;
-    __syncthreads();
-  }
-  return carry;
-}
-
-// One workgroup per component: distances from the entry with the FIFO
-// (smallest discoverer) parent, the BFS tree's preorder (children in
-// ascending order) as rank ranges, distances to the exit, and next[].
-//
-// The forward search keeps one queue in LDS whose layers are contiguous;
-// the children of a vertex form a contiguous ascending block of the next
-// layer, which gives subtree sizes bottom-up and preorder ranks top-down.
-__global__ __launch_bounds__(kBfsThreads) void k_bfs_dist(DGraph g, BfsOut b) {
-  __shared__ int16_t s_df[kMaxComp];
-  __shared__ int16_t s_db[kMaxComp];
-  __shared__ int32_t s_key[kMaxComp];   // smallest discoverer key, then the parent (local id)
-  __shared__ int16_t s_q[kMaxComp];     // forward queue (layers contiguous), then reverse queue
-  __shared__ int16_t s_lb[kMaxComp + 2];  // layer d of the forward queue: [s_lb[d], s_lb[d + 1])
-  __shared__ int16_t s_cnt[kMaxComp];   // per-layer child counts, then preorder ranks
-  __shared__ int32_t s_sz[kMaxComp];    // subtree sizes, then reverse-search marks
-  __shared__ int32_t s_w[kBfsThreads / 64];
-  __shared__ int32_t s_m;
-  const int c = (int)blockIdx.x;
-  const int base = g.cbase[c];
-  const int nc = g.cbase[c + 1] - base;
-  const int tid = (int)threadIdx.x;
-  for (int v = tid; v < nc; v += kBfsThreads) {
-    s_df[v] = -1;
-    s_db[v] = -1;
-    s_key[v] = INT_MAX;
-    s_sz[v] = 1;
-    b.parent[base + v] = -1;
-    b.next[base + v] = -1;
-  }
-  const int el = g.centry[c] - base;
-  if (tid == 0) {
-    s_df[el] = 0;
-    s_key[el] = -1;
-    s_q[0] = (int16_t)el;
-    s_lb[0] = 0;
-    s_lb[1] = 1;
   }
   __syncthreads();
-  int qb = 0, qe = 1, d = 0;
-  while (qe > qb) {
-    const int m = qe - qb;
-    for (int q = tid; q < m; q += kBfsThreads) {
-      const int u = base + s_q[qb + q];
-      for (int k = g.sp[u]; k < g.sp[u + 1]; ++k) {
-        const int wl = g.s[k] - base;
-        if (s_df[wl] == -1) atomicMin(&s_key[wl], q * 64 + (k - g.sp[u]));
-      }
-    }
-    __syncthreads();
-    for (int q = tid; q < m; q += kBfsThreads) {
-      const int u = base + s_q[qb + q];
-      int cnt = 0;
-      for (int k = g.sp[u]; k < g.sp[u + 1]; ++k) {
-        const int wl = g.s[k] - base;
-        if (s_df[wl] == -1 && s_key[wl] == q * 64 + (k - g.sp[u])) ++cnt;
-      }
-      s_cnt[q] = (int16_t)cnt;
-    }
-    __syncthreads();
-    const int m2 = lds_excl_scan(s_cnt, m, s_w);
-    for (int q = tid; q < m; q += kBfsThreads) {
-      const int u = base + s_q[qb + q];
-      int pos = qe + s_cnt[q];
-      for (int k = g.sp[u]; k < g.sp[u + 1]; ++k) {
-        const int wl = g.s[k] - base;
-        if (s_df[wl] == -1 && s_key[wl] == q * 64 + (k - g.sp[u])) {
-          s_q[pos++] = (int16_t)wl;
-          b.parent[base + wl] = u;
+  for (int w = tid; w < n; w += NT) {
+    int deeper = -1;  // arcs that end the subtrees nested in the end of w's
+    int same = 0, last_r = -1;
+    for (int k = sp(w); k < sp(w + 1); ++k) {
+      if (tree_arc(w, k)) continue;
+      bool ends;
+      const int r = rank_of(w, k, ends);
+      same = r == last_r ? same + 1 : 0;  // earlier arcs of w at this rank
+      last_r = r;
+      int ahead = s_end[r];
+      if (ends) {
+        if (deeper < 0) {
+          deeper = 0;
+          for (int y = w;;) {  // down the last tree children
+            int child = -1, tail = 0;
+            for (int j = sp(y + 1) - 1; j >= sp(y) && child < 0; --j) {
+              if (tree_arc(y, j)) child = succ(j);
+              else ++tail;  // an arc after the last tree child: it ends y's subtree
+            }
+            if (y != w) deeper += tail;
+            if (child < 0) break;
+            y = child;
+          }
         }
+        ahead = deeper;
       }
+      order[s_at[r] + ahead + same] = (x0 + w) << kArcSlotBits | (k - sp(w));
     }
-    __syncthreads();
-    for (int i = tid; i < m2; i += kBfsThreads) {
-      const int wl = s_q[qe + i];
-      s_df[wl] = (int16_t)(d + 1);
-      s_key[wl] = s_q[qb + s_key[wl] / 64];
-    }
-    qb = qe;
-    qe += m2;
-    ++d;
-    if (tid == 0) s_lb[d + 1] = (int16_t)qe;
-    __syncthreads();
-  }
-  const int nlayers = d;  // layers 0 .. nlayers - 1
-  // subtree sizes, deepest layer first
-  for (int l = nlayers - 1; l >= 1; --l) {
-    for (int i = s_lb[l] + tid; i < s_lb[l + 1]; i += kBfsThreads) {
-      const int v = s_q[i];
-      atomicAdd(&s_sz[s_key[v]], s_sz[v]);
-    }
-    __syncthreads();
-  }
-  // preorder ranks, top layer first: a vertex follows its parent and the
-  // subtrees of its smaller siblings
-  if (tid == 0) s_cnt[el] = 0;
-  __syncthreads();
-  for (int l = 1; l < nlayers; ++l) {
-    const int lo = s_lb[l];
-    for (int i = lo + tid; i < s_lb[l + 1]; i += kBfsThreads) {
-      const int v = s_q[i];
-      const int p = s_key[v];
-      int acc = 0;
-      for (int j = i - 1; j >= lo && s_key[s_q[j]] == p; --j) acc += s_sz[s_q[j]];
-      s_cnt[v] = (int16_t)(s_cnt[p] + 1 + acc);
-    }
-    __syncthreads();
-  }
-  for (int v = tid; v < nc; v += kBfsThreads) {
-    const bool r = s_df[v] >= 0;
-    b.pre[base + v] = r ? base + s_cnt[v] : -1;
-    b.pend[base + v] = r ? base + s_cnt[v] + s_sz[v] : -1;
-  }
-  __syncthreads();
-  // distances to the exit (reverse search; order does not matter)
-  for (int v = tid; v < nc; v += kBfsThreads) s_sz[v] = 0;
-  __syncthreads();
-  const int xl = g.cexit[c] - base;
-  if (tid == 0) {
-    s_db[xl] = 0;
-    s_q[0] = (int16_t)xl;
-    s_sz[xl] = 1;
-  }
-  __syncthreads();
-  qb = 0;
-  qe = 1;
-  d = 0;
-  while (qe > qb) {
-    if (tid == 0) s_m = 0;
-    __syncthreads();
-    for (int q = qb + tid; q < qe; q += kBfsThreads) {
-      const int u = base + s_q[q];
-      for (int k = g.pp[u]; k < g.pp[u + 1]; ++k) {
-        const int wl = g.p[k] - base;
-        if (atomicExch(&s_sz[wl], 1) == 0) s_q[qe + atomicAdd(&s_m, 1)] = (int16_t)wl;
-      }
-    }
-    __syncthreads();
-    const int m2 = s_m;
-    for (int i = tid; i < m2; i += kBfsThreads) s_db[s_q[qe + i]] = (int16_t)(d + 1);
-    qb = qe;
-    qe += m2;
-    ++d;
-    __syncthreads();
-  }
-  for (int v = tid; v < nc; v += kBfsThreads) {
-    b.dist_f[base + v] = s_df[v];
-    b.dist_b[base + v] = s_db[v];
-    if (v != xl && s_db[v] > 0) {
-      const int u = base + v;
-      for (int k = g.sp[u]; k < g.sp[u + 1]; ++k)
-        if (s_db[g.s[k] - base] == s_db[v] - 1) {
-          b.next[u] = g.s[k];
-          break;
-        }
+    if (w == ex) {
+      const int r = s_pre[w];
+      order[(r < n ? s_at[r + 1] : carry) - 1] = ~(x0 + w);
     }
   }
 }
 
-hipError_t launch_bfs_dist(const DGraph& g, const BfsOut& b, hipStream_t st) {
-  k_bfs_dist<<<(unsigned)g.n_comp, kBfsThreads, 0, st>>>(g, b);
-  return hipGetLastError();
-}
-
-// Prefix / suffix tables (graph-wide ids): entries before v on its
-// smallest shortest path from the entry, entries after v to the exit.
-__global__ void k_bfs_tables(DGraph g, BfsOut b) {
-  const int v = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (v >= g.n) return;
-  const int df = b.dist_f[v], db = b.dist_b[v];
-  if (df > 0) {
-    const int64_t lo = b.pfx_off[v];
-    int64_t pos = lo + df - 1;
-    int x = b.parent[v];
-    while (x >= 0 && pos >= lo) {
-      b.pfx[pos--] = x;
-      x = b.parent[x];
+// The rows that the prefixes and suffixes are cut from, one wave per chain x:
+// the way to x and x itself, x and the way on from it; row x of component c
+// starts at rbase[c] + (x's number there) * (vertices of c), in both.  Then
+// per vertex of x where its prefix and suffix are and how long.
+__global__ __launch_bounds__(64) void k_chain_rows(DGraph g, DGraph x, DChains ch, TpTree t,
+                                                   const int32_t* rbase, EndRows b) {
+  const int c0 = (int)blockIdx.x, lane = lane_id();
+  const int comp = x.comp[c0];
+  const int at = rbase[comp] + (c0 - x.cbase[comp]) * (g.cbase[comp + 1] - g.cbase[comp]);
+  const int o = ch.off[c0], m = ch.off[c0 + 1] - o;
+  const int df = t.cdist[c0], db = t.cback[c0];
+  // both ways in step
+  for (int p = c0, q = c0; p >= 0 || q >= 0;) {
+    if (p >= 0) {
+      const int po = ch.off[p], pm = ch.off[p + 1] - po, pd = t.cdist[p];
+      const int up = t.tpar[p];
+      for (int j = lane; j < pm; j += 64) b.pfx[at + pd + j] = ch.v[po + j];
+      p = up;
+    }
+    if (q >= 0) {
+      const int qo = ch.off[q], qm = ch.off[q + 1] - qo, qd = db + m - t.cback[q] - qm;
+      const int on = t.nx[q];
+      for (int j = lane; j < qm; j += 64) b.sfx[at + qd + j] = ch.v[qo + j];
+      q = on;
     }
   }
-  if (db > 0) {
-    int64_t pos = b.sfx_off[v];
-    const int64_t hi = pos + db;
-    int x = b.next[v];
-    while (x >= 0 && pos < hi) {
-      b.sfx[pos++] = x;
-      x = b.next[x];
-    }
+  for (int j = lane; j < m; j += 64) {
+    const int v = ch.v[o + j];
+    b.n_pfx[v] = df + j;
+    b.n_sfx[v] = db + m - 1 - j;
+    b.pfx_at[v] = at;
+    b.sfx_at[v] = at + j + 1;
   }
 }
 
-hipError_t launch_bfs_tables(const DGraph& g, const BfsOut& b, hipStream_t st) {
-  k_bfs_tables<<<(unsigned)((g.n + kBlock - 1) / kBlock), kBlock, 0, st>>>(g, b);
+hipError_t launch_chain_bfs(const DGraph& g, const DGraph& x, const DChains& ch, const TpTree& t,
+                            const int32_t* gbase, int32_t* order, const int32_t* rbase,
+                            const EndRows& b, int max_chains, int max_words, hipStream_t st) {
+  const unsigned grid = (unsigned)x.n_comp;
+  // staged graphs of up to 16 KiB; a wave per component when there are many
+  const size_t lds = sizeof(int32_t) * (size_t)max_words;
+  const bool stage = lds <= 16384;
+  if (max_chains <= 256) {
+    if (x.n_comp >= 64) {
+      if (stage) k_chain_bfs<256, 64, true><<<grid, 64, lds, st>>>(g, x, ch, t, gbase, order);
+      else k_chain_bfs<256, 64, false><<<grid, 64, 0, st>>>(g, x, ch, t, gbase, order);
+    } else {
+      if (stage) k_chain_bfs<256, 256, true><<<grid, 256, lds, st>>>(g, x, ch, t, gbase, order);
+      else k_chain_bfs<256, 256, false><<<grid, 256, 0, st>>>(g, x, ch, t, gbase, order);
+    }
+  } else {
+    k_chain_bfs<kMaxComp, 256, false><<<grid, 256, 0, st>>>(g, x, ch, t, gbase, order);
+  }
+  k_chain_rows<<<(unsigned)x.n, 64, 0, st>>>(g, x, ch, t, rbase, b);
   return hipGetLastError();
 }
 
@@ -281,7 +333,7 @@ hipError_t launch_localize(const int32_t* loc, int32_t* v, int64_t n, hipStream_
 //    first order of their nodes, the one of an inner node E coming where its
 //    next chain would (no child of E is that chain);
 //  * test paths with different (W, Y) follow the depth-first order of the BFS
-//    tree with the other arcs as leaves (k_tp_arc_order); the one test path
+//    tree with the other arcs as leaves (k_chain_bfs); the one test path
 //    that is a BFS-tree path all along belongs to the exit.
 // So the test paths' nodes are marked (k_tp_mark, with a prime path for each),
 // counted bottom-up, and given their places top-down.  k_down_run finds, for
@@ -291,130 +343,6 @@ hipError_t launch_localize(const int32_t* loc, int32_t* v, int64_t n, hipStream_
 // again: the test-path stage of the 400-vertex stress CFG took 21 ms of a
 // 30.8 ms call, now 11 ms of 19.9 (its rows alone are 21.8 GB); a batch of
 // 4096 CFGs went from 11.1 to 7.6 ms, a 1000-vertex CFG from 6.7 to 4.3.
-
-// First chain of the BFS tree (tpar) and next chain on the shortest way to
-// the exit (nx), -1 for none.  One thread per chain.
-__global__ void k_tp_chain_links(DGraph x, DChains ch, BfsOut b, TpTree t) {
-  const int c = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (c >= x.n) return;
-  const int p = b.parent[ch.v[ch.off[c]]];
-  const int q = b.next[ch.v[ch.off[c + 1] - 1]];
-  t.tpar[c] = p >= 0 ? ch.of[p] : -1;
-  t.nx[c] = q >= 0 ? ch.of[q] : -1;
-  t.cdist[c] = b.dist_f[ch.v[ch.off[c]]];
-  t.cback[c] = b.dist_b[ch.v[ch.off[c + 1] - 1]];
-}
-
-// The places of every component's arcs off the BFS tree, and of the exit's
-// tree path, in test-path order: order[gbase[c] ..) lists the arcs as W <<
-// kArcSlotBits | slot of Y among W's successors, and the exit's chain X as ~X.
-// With the vertices' BFS-tree preorder, an arc (w, e) comes right before the
-// first tree child of w above e (rank s), or at the end of w's subtree; among
-// arcs at the same rank s, those that end a subtree come first, deepest first,
-// then those before child s, w's own in the order of e; the exit's path comes
-// last at the exit's rank.  The arcs that end the subtrees nested in w's end
-// are counted by walking down the last tree children.  One workgroup per
-// component.
-__global__ __launch_bounds__(kBlock) void k_tp_arc_order(DGraph g, DGraph x, DChains ch, BfsOut b,
-                                                         const int32_t* gbase, int32_t* order) {
-  __shared__ int32_t s_at[kMaxComp + 1];   // arcs per rank, then their first place
-  __shared__ int32_t s_end[kMaxComp + 1];  // of them, arcs that end a subtree
-  __shared__ int32_t s_w[kBlock / 64];
-  const int c = (int)blockIdx.x, tid = (int)threadIdx.x;
-  const int base = g.cbase[c], nc = g.cbase[c + 1] - base;
-  const int x0 = x.cbase[c], x1 = x.cbase[c + 1];
-  for (int k = tid; k <= nc; k += kBlock) {
-    s_at[k] = 0;
-    s_end[k] = 0;
-  }
-  __syncthreads();
-  // rank (local) at which arc k out of w comes; the successors ascend
-  auto rank_of = [&](int w, int k, int k1, bool& ends) {
-    int r = b.pend[w] - base;
-    ends = true;
-    for (int j = k + 1; j < k1; ++j) {
-      const int u = ch.v[ch.off[x.s[j]]];
-      if (b.parent[u] == w) {
-        r = b.pre[u] - base;
-        ends = false;
-        break;
-      }
-    }
-    return r;
-  };
-  auto tree_arc = [&](int w, int k) { return b.parent[ch.v[ch.off[x.s[k]]]] == w; };
-  const int xl = g.cexit[c];
-  for (int i = x0 + tid; i < x1; i += kBlock) {
-    const int w = ch.v[ch.off[i + 1] - 1];
-    const int k0 = x.sp[i], k1 = x.sp[i + 1];
-    for (int k = k0; k < k1; ++k) {
-      if (tree_arc(w, k)) continue;
-      bool ends;
-      const int r = rank_of(w, k, k1, ends);
-      atomicAdd(&s_at[r], 1);
-      if (ends) atomicAdd(&s_end[r], 1);
-    }
-    if (w == xl) atomicAdd(&s_at[b.pre[w] - base], 1);
-  }
-  __syncthreads();
-  // first place of every rank
-  int carry = gbase[c];
-  for (int k0 = 0; k0 <= nc; k0 += kBlock) {
-    const int k = k0 + tid;
-    const int v = k <= nc ? s_at[k] : 0;
-    int tot;
-    const int pre = block_excl_scan<kBlock, int>(v, tot, s_w);
-    if (k <= nc) s_at[k] = carry + pre;
-    carry += tot;
-  }
-  __syncthreads();
-  for (int i = x0 + tid; i < x1; i += kBlock) {
-    const int w = ch.v[ch.off[i + 1] - 1];
-    const int k0 = x.sp[i], k1 = x.sp[i + 1];
-    int deeper = -1;  // arcs that end the subtrees nested in the end of w's
-    int same = 0, last_r = -1;
-    for (int k = k0; k < k1; ++k) {
-      if (tree_arc(w, k)) continue;
-      bool ends;
-      const int r = rank_of(w, k, k1, ends);
-      same = r == last_r ? same + 1 : 0;  // earlier arcs of w at this rank
-      last_r = r;
-      int before = s_end[r];
-      if (ends) {
-        if (deeper < 0) {
-          deeper = 0;
-          for (int y = i;;) {  // down the last tree children
-            const int wy = ch.v[ch.off[y + 1] - 1];
-            int child = -1, tail = 0;
-            for (int j = x.sp[y + 1] - 1; j >= x.sp[y]; --j) {
-              if (tree_arc(wy, j)) {
-                child = x.s[j];
-                break;
-              }
-              ++tail;  // an arc after the last tree child: it ends wy's subtree
-            }
-            if (y != i) deeper += tail;
-            if (child < 0) break;
-            y = child;
-          }
-        }
-        before = deeper;
-      }
-      order[s_at[r] + before + same] = i << kArcSlotBits | (k - k0);
-    }
-    if (w == xl) {
-      const int r = b.pre[w] - base;
-      order[(r < nc ? s_at[r + 1] : carry) - 1] = ~i;
-    }
-  }
-}
-
-hipError_t launch_tp_arcs(const DGraph& g, const DGraph& x, const DChains& ch, const BfsOut& b,
-                          const TpTree& t, const int32_t* gbase, int32_t* order, hipStream_t st) {
-  k_tp_chain_links<<<(unsigned)((x.n + kBlock - 1) / kBlock), kBlock, 0, st>>>(x, ch, b, t);
-  k_tp_arc_order<<<(unsigned)g.n_comp, kBlock, 0, st>>>(g, x, ch, b, gbase, order);
-  return hipGetLastError();
-}
 
 // The child of node c labelled chain y (-1: none).
 __device__ __forceinline__ int64_t child_of(const TreeBufs& t, int64_t c, int y) {
@@ -590,13 +518,13 @@ hipError_t launch_tp_down_run(const ExtArgs& a, const TpTree& tt, int64_t base, 
 template <bool ENDS>
 __global__ __launch_bounds__(kBlock) void k_row_len(const int32_t* src, int64_t n,
                                                     const int64_t* pp_off, const int32_t* pp_vtx,
-                                                    BfsOut b, int32_t* len) {
+                                                    EndRows b, int32_t* len) {
   const int64_t r = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (r >= n) return;
   const int64_t i = src ? (int64_t)src[r] : r;
   const int64_t o0 = pp_off[i], o1 = pp_off[i + 1];
   int32_t l = (int32_t)(o1 - o0);
-  if constexpr (ENDS) l += b.dist_f[pp_vtx[o0]] + b.dist_b[pp_vtx[o1 - 1]];
+  if constexpr (ENDS) l += b.n_pfx[pp_vtx[o0]] + b.n_sfx[pp_vtx[o1 - 1]];
   len[r] = l;
 }
 
@@ -614,14 +542,14 @@ __global__ __launch_bounds__(kBlock) void k_row_len(const int32_t* src, int64_t 
 template <int U, int R, bool ENDS>
 __global__ __launch_bounds__(kBlock) void k_emit_rows(const int32_t* src, int64_t n, int rows,
                                                       const int64_t* pp_off, const int32_t* pp_vtx,
-                                                      BfsOut b, const int64_t* out_off,
+                                                      EndRows b, const int64_t* out_off,
                                                       int32_t* out_vtx) {
   const int lane = lane_id();
   const int64_t r0 = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * rows;
   if (r0 >= n) return;
   const int nr = (int)(n - r0 < rows ? n - r0 : rows);
-  int64_t out = 0, o0 = 0, p0 = 0, s0 = 0;
-  int lq = 0, lp = 0, ls = 0;  // lanes past the last row: empty rows
+  int64_t out = 0, o0 = 0;
+  int lq = 0, lp = 0, ls = 0, p0 = 0, s0 = 0;  // lanes past the last row: empty rows
   if (lane < nr) {
     const int64_t i = src ? (int64_t)src[r0 + lane] : r0 + lane;
     out = out_off[r0 + lane];
@@ -629,10 +557,10 @@ __global__ __launch_bounds__(kBlock) void k_emit_rows(const int32_t* src, int64_
     lq = (int)(pp_off[i + 1] - o0);
     if constexpr (ENDS) {
       const int v1 = pp_vtx[o0], vk = pp_vtx[o0 + lq - 1];
-      lp = b.dist_f[v1];
-      ls = b.dist_b[vk];
-      p0 = b.pfx_off[v1];
-      s0 = b.sfx_off[vk];
+      lp = b.n_pfx[v1];
+      ls = b.n_sfx[vk];
+      p0 = b.pfx_at[v1];
+      s0 = b.sfx_at[vk];
     }
   }
   auto get = [&](int x, int q) { return __builtin_amdgcn_readlane(x, q); };
@@ -657,8 +585,8 @@ __global__ __launch_bounds__(kBlock) void k_emit_rows(const int32_t* src, int64_
     if constexpr (ENDS) {
       w.np = get(lp, q);
       w.len += w.np + get(ls, q);
-      w.a = b.pfx + get64(p0, q);
-      w.c = b.sfx + get64(s0, q) - (w.np + w.nq);
+      w.a = b.pfx + get(p0, q);
+      w.c = b.sfx + get(s0, q) - (w.np + w.nq);
     }
     w.b = pp_vtx + get64(o0, q) - w.np;
     return w;
@@ -685,18 +613,18 @@ __global__ __launch_bounds__(kBlock) void k_emit_rows(const int32_t* src, int64_
 }
 
 hipError_t launch_row_len(const int32_t* src, int64_t n, const int64_t* pp_off,
-                          const int32_t* pp_vtx, const BfsOut* b, int32_t* len, hipStream_t st) {
+                          const int32_t* pp_vtx, const EndRows* b, int32_t* len, hipStream_t st) {
   if (n == 0) return hipSuccess;
   const unsigned grid = (unsigned)((n + kBlock - 1) / kBlock);
   if (b)
     k_row_len<true><<<grid, kBlock, 0, st>>>(src, n, pp_off, pp_vtx, *b, len);
   else
-    k_row_len<false><<<grid, kBlock, 0, st>>>(src, n, pp_off, pp_vtx, BfsOut{}, len);
+    k_row_len<false><<<grid, kBlock, 0, st>>>(src, n, pp_off, pp_vtx, EndRows{}, len);
   return hipGetLastError();
 }
 
 hipError_t launch_emit_rows(const int32_t* src, int64_t n, int64_t n_entries, const int64_t* pp_off,
-                            const int32_t* pp_vtx, const BfsOut* b, const int64_t* out_off,
+                            const int32_t* pp_vtx, const EndRows* b, const int64_t* out_off,
                             int32_t* out_vtx, hipStream_t st) {
   if (n == 0) return hipSuccess;
   // more rows a wave spread the first loads' cost, fewer keep the chip full:
@@ -713,8 +641,8 @@ hipError_t launch_emit_rows(const int32_t* src, int64_t n, int64_t n_entries, co
     else if (steps <= 2) TPG_EMIT(2, 4, true, *b);
     else TPG_EMIT(5, 2, true, *b);
   } else {
-    if (steps <= 1) TPG_EMIT(1, 4, false, BfsOut{});
-    else TPG_EMIT(2, 4, false, BfsOut{});
+    if (steps <= 1) TPG_EMIT(1, 4, false, EndRows{});
+    else TPG_EMIT(2, 4, false, EndRows{});
   }
 #undef TPG_EMIT
   return hipGetLastError();

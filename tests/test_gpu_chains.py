@@ -148,3 +148,36 @@ def test_test_path_order_with_many_arcs(fan):
         (po, pv), (to, tv) = res.graph(i)
         assert np.array_equal(po, rp.offsets) and np.array_equal(pv, rp.vertices), g.name
         assert np.array_equal(to, rt.offsets) and np.array_equal(tv, rt.vertices), g.name
+
+
+def _two_level_switch(a, b):
+    """A switch of a arms, each a switch of b arms, some with a way back to
+    their own switch: 2 + a (b + 1) + 1 chains."""
+    edges, n = [], 2 + a * (b + 1) + 1
+    for i in range(a):
+        v = 2 + i * (b + 1)
+        edges.append((1, v))
+        for j in range(1, b + 1):
+            edges += [(v, v + j), (v + j, n - 1)]
+            if (i + j) % 3 == 0:
+                edges.append((v + j, v))
+    return cfggen.from_edges(n, [(0, 1)] + edges, 0, n - 1, f"switch{a}x{b}")
+
+
+def _layers(a, b):
+    """entry -> a vertices -> each of b vertices -> exit."""
+    n = 2 + a + b
+    edges = [(0, 1 + i) for i in range(a)] + [(1 + a + j, n - 1) for j in range(b)]
+    edges += [(1 + i, 1 + a + j) for i in range(a) for j in range(b)]
+    return cfggen.from_edges(n, edges, 0, n - 1, f"layers{a}x{b}")
+
+
+@pytest.mark.parametrize("name", ["switch25x9", "switch30x9", "switch60x30", "layers20x20", "layers60x60"])
+def test_shortest_paths_at_the_kernel_sizes(name):
+    """BFS trees of at most and of more than 256 chains, and graphs on both
+    sides of the staged size."""
+    a, b = (int(x) for x in name.lstrip("switchlayers").split("x"))
+    g = _two_level_switch(a, b) if name.startswith("switch") else _layers(a, b)
+    say("case", name, g.n)
+    check_tp(g, local=True)
+    check_tp(_shuffled(g, 5), local=True)
