@@ -6,13 +6,16 @@
 // predictions size the path pool of the batched form; results never depend on
 // them.
 //
-// Every matrix product is C = A * Bt^T with A (M x K) and Bt (N x K) stored
-// row-major in bf16 (K contiguous), M and N multiples of 64, K a multiple of
-// 32: one workgroup of 4 waves computes a 64 x 64 tile, each wave a 16 x 64
-// strip as four 16x16x32 MFMA accumulators.
+// Rows are independent up to the weight gradients, so one kernel takes 16 rows
+// through everything that belongs to them (k_mlp_rows), a second one forms the
+// weight gradients' products over the rows, split along them (k_mlp_wgrad),
+// and a third one adds the parts up (k_mlp_reduce).  Gradients of 1024 rows,
+// host arrays in and out: 95 us, 950 as a chain of separate products, column
+// sums and copies.
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -41,107 +44,265 @@ static inline uint16_t f2bf_host(float f) {
   return (uint16_t)(u >> 16);
 }
 
-struct GemmArgs {
-  const uint16_t* A;
-  int lda;
-  const uint16_t* Bt;
-  int ldb;
-  int M, N, K;
-  const float* bias;       // [N] or null
-  const float* gate;       // multiply by (gate[row * ld_gate + col] > 0) or null
-  int ld_gate;
-  int relu;                // apply max(0, .)
-  float* C;                // fp32 out or null
-  int ldc;
-  uint16_t* Cb;            // bf16 out (row-major) or null
-  int ldcb;
-  uint16_t* Cbt;           // bf16 out transposed (N x M) or null
-  int ldcbt;
-  int valid_m, valid_n;    // outside: written as 0
+// Operands of one pass over n rows (ld: the transposed arrays' row length).
+struct RowArgs {
+  const float* x;          // [n][32]
+  const float* t;          // [n][65]; null: forward only
+  int n, ld;
+  const float *mean, *stdv;
+  const uint16_t *w1t, *w2t, *w3t;  // W^T, [out][in], rows of 64 / 128 / 128
+  const uint16_t *w2, *w3;          // W, [in][out], rows of 128
+  const float *b1, *b2, *b3;
+  float* y;                // [n][65]
+  // for the weight gradients, bf16, [column][row]
+  uint16_t *xt, *h1t, *h2t, *dyt, *dh2t, *dh1t;
+  // sums over a block's 16 rows: 3 x 128 bias gradients, then the squared error
+  float* part;             // [blocks][kPart]
 };
+constexpr int kRowTile = 16;
+constexpr int kPart = 3 * kHid + 1;
+constexpr int kOutK = 96;  // 65 outputs padded to whole steps of 32
 
-__global__ __launch_bounds__(256) void k_gemm_nt(GemmArgs g) {
+// A 16 x 16 product tile: A rows in LDS (row-major, `lda`), B^T rows in memory
+// (`ldb`), both K contiguous; lane l holds D[4 (l / 16) + j][l % 16].
+template <int K>
+__device__ __forceinline__ f32x4 tile_product(const uint16_t* a, int lda, const uint16_t* bt,
+                                              int ldb) {
+  const int lane = (int)(threadIdx.x & 63), r = lane & 15, kq = (lane >> 4) * 8;
+  f32x4 acc{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int k0 = 0; k0 < K; k0 += 32) {
+    const bf16x8 av = *reinterpret_cast<const bf16x8*>(a + r * lda + kq + k0);
+    const bf16x8 bv = *reinterpret_cast<const bf16x8*>(bt + (size_t)r * ldb + kq + k0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc, 0, 0, 0);
+  }
+  return acc;
+}
+
+// The lane's four values of a tile (rows row0 .., column col), in bf16 to the
+// next product's A rows and, transposed, to `t` (null: not kept).
+__device__ __forceinline__ void tile_put(const f32x4& v, int col, int row0, int block_row,
+                                         uint16_t* a, int lda, uint16_t* t, int ld) {
+  uint16_t h[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    h[j] = f2bf(v[j]);
+    if (a) a[(row0 + j) * lda + col] = h[j];
+  }
+  if (t)
+    *reinterpret_cast<uint2*>(t + (size_t)col * ld + block_row + row0) =
+        make_uint2((uint32_t)h[0] | (uint32_t)h[1] << 16, (uint32_t)h[2] | (uint32_t)h[3] << 16);
+}
+
+// Sum of a column over the tile's 16 rows, to the lanes of its first four.
+__device__ __forceinline__ float tile_colsum(const f32x4& v) {
+  float c = (v[0] + v[1]) + (v[2] + v[3]);
+  c += __shfl_xor(c, 16, 64);
+  c += __shfl_xor(c, 32, 64);
+  return c;
+}
+
+// 16 rows per workgroup, from features to outputs and, with targets, back to
+// the first hidden layer's gradient; four waves share the columns.  Bound by
+// the latency of its seven dependent products (the weights come from L2, the
+// activations stay in LDS): 15 us for 1024 rows.  Separate products and column
+// sums took 0.85 ms, most of it three serial column sums of 222 us.
+__global__ __launch_bounds__(256) void k_mlp_rows(RowArgs g) {
+  constexpr int LX = kIn + 8, LH = kHid + 8, LO = kOutK + 8;  // LDS row strides
+  __shared__ __align__(16) uint16_t s_x[kRowTile * LX];
+  __shared__ __align__(16) uint16_t s_h1[kRowTile * LH];
+  __shared__ __align__(16) uint16_t s_h2[kRowTile * LH];
+  __shared__ __align__(16) uint16_t s_dy[kRowTile * LO];
+  __shared__ float s_sq[4];
+  const int tid = (int)threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int b0 = (int)blockIdx.x * kRowTile;      // first row
+  const int r0 = 4 * (lane >> 4), cl = lane & 15;  // the lane's rows and column in a tile
+  const bool grad = g.t != nullptr;
+  float* part = g.part + (size_t)blockIdx.x * kPart;
+  auto valid = [&](int j) { return b0 + r0 + j < g.n; };
+  for (int i = tid; i < kRowTile * kIn; i += 256) {
+    const int r = i / kIn, f = i % kIn, row = b0 + r;
+    const float v = row < g.n ? (g.x[(size_t)row * kIn + f] - g.mean[f]) / g.stdv[f] : 0.f;
+    const uint16_t h = f2bf(v);
+    s_x[r * LX + f] = h;
+    if (grad) g.xt[(size_t)f * g.ld + row] = h;
+  }
+  for (int i = tid; i < kRowTile * LO; i += 256) s_dy[i] = 0;
+  __syncthreads();
+  // hidden layers: two tiles of 16 columns a wave; on[..]: the unit is active
+  bool on1[2][4], on2[2][4];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int c0 = 16 * (wave + 4 * q), col = c0 + cl;
+    f32x4 v = tile_product<kIn>(s_x, LX, g.w1t + (size_t)c0 * 64, 64);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[j] += g.b1[col];
+      on1[q][j] = v[j] > 0.f && valid(j);
+      v[j] = on1[q][j] ? v[j] : 0.f;
+    }
+    tile_put(v, col, r0, b0, s_h1, LH, grad ? g.h1t : nullptr, g.ld);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int c0 = 16 * (wave + 4 * q), col = c0 + cl;
+    f32x4 v = tile_product<kHid>(s_h1, LH, g.w2t + (size_t)c0 * kHid, kHid);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[j] += g.b2[col];
+      on2[q][j] = v[j] > 0.f && valid(j);
+      v[j] = on2[q][j] ? v[j] : 0.f;
+    }
+    tile_put(v, col, r0, b0, s_h2, LH, grad ? g.h2t : nullptr, g.ld);
+  }
+  __syncthreads();
+  // outputs: five tiles; with targets their gradient and the squared error
+  float sq = 0.f;
+  for (int c0 = 16 * wave; c0 < kOut; c0 += 64) {
+    const int col = c0 + cl;
+    f32x4 v = tile_product<kHid>(s_h2, LH, g.w3t + (size_t)c0 * kHid, kHid);
+    f32x4 d{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (col >= kOut || !valid(j)) continue;
+      const size_t at = (size_t)(b0 + r0 + j) * kOut + col;
+      const float y = v[j] + g.b3[col];
+      if (!grad) {
+        g.y[at] = y;
+        continue;
+      }
+      const float e = y - g.t[at];
+      d[j] = 2.f * e / (float)(g.n * kOut);
+      sq += e * e;
+    }
+    if (grad) {
+      tile_put(d, col, r0, b0, s_dy, LO, g.dyt, g.ld);
+      const float c = tile_colsum(d);
+      if (lane < 16) part[2 * kHid + col] = c;
+    }
+  }
+  if (!grad) return;
+#pragma unroll
+  for (int d = 32; d >= 1; d >>= 1) sq += __shfl_xor(sq, d, 64);
+  if (lane == 0) s_sq[wave] = sq;
+  __syncthreads();
+  if (tid == 0) part[3 * kHid] = (s_sq[0] + s_sq[1]) + (s_sq[2] + s_sq[3]);
+  // dH2 = dY W3^T and dH1 = dH2 W2^T where the units are active; dH2's rows
+  // take the place of H1's, which no product reads any more
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int c0 = 16 * (wave + 4 * q), col = c0 + cl;
+    f32x4 v = tile_product<kOutK>(s_dy, LO, g.w3 + (size_t)c0 * kOutPad, kOutPad);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = on2[q][j] ? v[j] : 0.f;
+    tile_put(v, col, r0, b0, s_h1, LH, g.dh2t, g.ld);
+    const float c = tile_colsum(v);
+    if (lane < 16) part[kHid + col] = c;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    const int c0 = 16 * (wave + 4 * q), col = c0 + cl;
+    f32x4 v = tile_product<kHid>(s_h1, LH, g.w2 + (size_t)c0 * kHid, kHid);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = on1[q][j] ? v[j] : 0.f;
+    tile_put(v, col, r0, b0, nullptr, 0, g.dh1t, g.ld);
+    const float c = tile_colsum(v);
+    if (lane < 16) part[col] = c;
+  }
+}
+
+// Weight gradients dW = A^T dB as C[m][n] = sum over rows of at[m][row]
+// bt[n][row], in 64 x 64 tiles: two for W1 (32 of its 64 rows), four for W2,
+// four for W3 (65 of its 128 columns).  Split z of gridDim.y takes the rows
+// [z * k_split, (z + 1) * k_split) and writes its tile on its own: 4.5 us for
+// 1024 rows in eight splits; in one piece ten workgroups took 17 us a product.
+constexpr int kTiles = 10;
+__global__ __launch_bounds__(256) void k_mlp_wgrad(RowArgs g, int rows, int k_split, float* out) {
+  const int tile = (int)blockIdx.x;
+  const uint16_t *at, *bt;
+  int m0, n0;
+  if (tile < 2) {
+    at = g.xt, bt = g.dh1t, m0 = 0, n0 = 64 * tile;
+  } else {
+    at = tile < 6 ? g.h1t : g.h2t;
+    bt = tile < 6 ? g.dh2t : g.dyt;
+    m0 = 64 * ((tile - 2) / 2 % 2), n0 = 64 * ((tile - 2) % 2);
+  }
   const int wave = (int)(threadIdx.x >> 6), lane = (int)(threadIdx.x & 63);
-  const int m0 = (int)blockIdx.y * 64 + wave * 16;
-  const int n0 = (int)blockIdx.x * 64;
   const int r = lane & 15, kq = (lane >> 4) * 8;
+  const int k0 = (int)blockIdx.y * k_split, k1 = min(rows, k0 + k_split);
   f32x4 acc[4];
 #pragma unroll
   for (int t = 0; t < 4; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const uint16_t* arow = g.A + (size_t)(m0 + r) * g.lda + kq;
-  for (int k0 = 0; k0 < g.K; k0 += 32) {
-    const bf16x8 a = *reinterpret_cast<const bf16x8*>(arow + k0);
+  const uint16_t* arow = at + (size_t)(m0 + wave * 16 + r) * g.ld + kq;
+  for (int k = k0; k < k1; k += 32) {
+    const bf16x8 a = *reinterpret_cast<const bf16x8*>(arow + k);
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-      const bf16x8 b =
-          *reinterpret_cast<const bf16x8*>(g.Bt + (size_t)(n0 + 16 * t + r) * g.ldb + kq + k0);
+      const bf16x8 b = *reinterpret_cast<const bf16x8*>(bt + (size_t)(n0 + 16 * t + r) * g.ld + kq + k);
       acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[t], 0, 0, 0);
     }
   }
-  // lane holds D[4 * (lane / 16) + j][lane % 16] of each 16x16 tile
+  float* o = out + ((size_t)blockIdx.y * kTiles + tile) * 4096;
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < 4; ++t)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = m0 + 4 * (lane >> 4) + j;
-      const int col = n0 + 16 * t + (lane & 15);
-      float v = acc[t][j];
-      if (g.bias) v += g.bias[col];
-      if (g.relu) v = v > 0.f ? v : 0.f;
-      if (g.gate && !(g.gate[(size_t)row * g.ld_gate + col] > 0.f)) v = 0.f;
-      if (row >= g.valid_m || col >= g.valid_n) v = 0.f;
-      if (g.C) g.C[(size_t)row * g.ldc + col] = v;
-      const uint16_t h = f2bf(v);
-      if (g.Cb) g.Cb[(size_t)row * g.ldcb + col] = h;
-      if (g.Cbt) g.Cbt[(size_t)col * g.ldcbt + row] = h;
+    for (int j = 0; j < 4; ++j)
+      o[(wave * 16 + 4 * (lane >> 4) + j) * 64 + 16 * t + (lane & 15)] = acc[t][j];
+}
+
+// fp32 block layout (floats): w1 64 x 128 (rows 32..63 stay 0), b1 128, w2
+// 128 x 128, b2 128, w3 128 x 128, b3 128 (columns 65.. stay 0)
+constexpr size_t oW1 = 0, oB1 = oW1 + 64 * kHid, oW2 = oB1 + kHid, oB2 = oW2 + kHid * kHid,
+                 oW3 = oB2 + kHid, oB3 = oW3 + kHid * kOutPad, oEnd = oB3 + kOutPad;
+
+// Gradients in the block layout and the loss from the parts.  The first
+// kWeightBlocks workgroups take a weight per thread, the others 32 columns of
+// the row pass's parts each, a part in eight per thread: latency of a few
+// dependent loads, 3.8 us for 64 parts (26 with one workgroup for all columns).
+constexpr int kWeightBlocks = (64 * kHid + 2 * kHid * kHid) / 256;
+constexpr int kPartBlocks = (kPart + 31) / 32;
+__global__ __launch_bounds__(256) void k_mlp_reduce(const float* tiles, int splits,
+                                                    const float* part, int blocks, float inv_n,
+                                                    float* grad, float* loss) {
+  const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+  if (blockIdx.x < kWeightBlocks) {
+    int tile, row, col;
+    size_t at;
+    if (i < 64 * kHid) {  // W1
+      row = i / kHid, col = i % kHid, tile = col / 64, at = oW1 + i;
+    } else {
+      const int w = (i - 64 * kHid) / (kHid * kHid);  // 0: W2, 1: W3
+      const int e = (i - 64 * kHid) % (kHid * kHid);
+      row = e / kHid, col = e % kHid;
+      tile = 2 + 4 * w + 2 * (row / 64) + col / 64, at = (w ? oW3 : oW2) + e;
     }
+    const float* p = tiles + (size_t)tile * 4096 + (row % 64) * 64 + col % 64;
+    float s = 0.f;
+    for (int z = 0; z < splits; ++z) s += p[(size_t)z * kTiles * 4096];
+    if ((i < 64 * kHid && row >= kIn) || (at >= oW3 && col >= kOut)) s = 0.f;
+    grad[at] = s;
+    return;
   }
-}
-
-static hipError_t gemm(const GemmArgs& a, hipStream_t st) {
-  if (a.M % 64 || a.N % 64 || a.K % 32) return hipErrorInvalidValue;
-  dim3 grid((unsigned)(a.N / 64), (unsigned)(a.M / 64));
-  k_gemm_nt<<<grid, 256, 0, st>>>(a);
-  return hipGetLastError();
-}
-
-// features -> normalized bf16 rows (and the transposed copy, 64 rows)
-__global__ void k_prep(const float* x, int n, int rows, const float* mean, const float* stdv,
-                       uint16_t* xb, uint16_t* xbt) {
-  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= rows * kIn) return;
-  const int b = i / kIn, f = i % kIn;
-  const float v = b < n ? (x[(size_t)b * kIn + f] - mean[f]) / stdv[f] : 0.f;
-  const uint16_t h = f2bf(v);
-  xb[(size_t)b * kIn + f] = h;
-  xbt[(size_t)f * rows + b] = h;
-}
-
-// d loss / d y for loss = mean over n x 65 of (y - t)^2; loss sum accumulated
-__global__ void k_loss_grad(const float* y, const float* t, int n, int rows, float* dy,
-                            uint16_t* dyb, uint16_t* dybt, float* loss_sum) {
-  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= rows * kOutPad) return;
-  const int b = i / kOutPad, o = i % kOutPad;
-  float g = 0.f, sq = 0.f;
-  if (b < n && o < kOut) {
-    const float e = y[(size_t)b * kOutPad + o] - t[(size_t)b * kOut + o];
-    g = 2.f * e / (float)(n * kOut);
-    sq = e * e;
-  }
-  dy[i] = g;
-  const uint16_t h = f2bf(g);
-  dyb[i] = h;
-  dybt[(size_t)o * rows + b] = h;
-  if (sq != 0.f) atomicAdd(loss_sum, sq);
-}
-
-__global__ void k_colsum(const float* g, int rows, int cols, int valid, float* out) {
-  const int c = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (c >= valid) return;
+  __shared__ float s_sum[256];
+  const int tid = (int)threadIdx.x, c = ((int)blockIdx.x - kWeightBlocks) * 32 + (tid & 31);
+  // columns past the 65th of the output bias are not written by the row pass
+  const int l = c / kHid;
+  const bool live = c < kPart && (l != 2 || c % kHid < kOut);
   float s = 0.f;
-  for (int r = 0; r < rows; ++r) s += g[(size_t)r * cols + c];
-  out[c] = s;
+  if (live)
+#pragma unroll 4
+    for (int b = tid >> 5; b < blocks; b += 8) s += part[(size_t)b * kPart + c];
+  s_sum[tid] = s;
+  __syncthreads();
+  if (tid >= 32 || c >= kPart) return;
+  s = 0.f;
+#pragma unroll
+  for (int q = 0; q < 8; ++q) s += s_sum[q * 32 + tid];
+  if (l < 3) grad[(l == 0 ? oB1 : l == 1 ? oB2 : oB3) + c % kHid] = s;
+  else *loss = s * inv_n;
 }
 
 struct AdamArgs {
@@ -200,23 +361,21 @@ struct tpg_mlp {
   float* mean = nullptr; float* stdv = nullptr;
   float h_mean[kIn], h_std[kIn];
   int64_t step = 0;
-  // activations for up to `rows` rows
+  // arrays for up to `rows` rows (a multiple of 64)
   int rows = 0;
   void* act = nullptr;
-  size_t act_bytes = 0;
-  float *x = nullptr, *t = nullptr, *h1 = nullptr, *h2 = nullptr, *y = nullptr, *dy = nullptr,
-        *dh2 = nullptr, *dh1 = nullptr, *loss = nullptr;
-  uint16_t *xb = nullptr, *xbt = nullptr, *h1b = nullptr, *h1bt = nullptr, *h2b = nullptr,
-           *h2bt = nullptr, *dyb = nullptr, *dybt = nullptr, *dh2b = nullptr, *dh2bt = nullptr,
-           *dh1b = nullptr, *dh1bt = nullptr;
+  float *x = nullptr, *t = nullptr, *y = nullptr, *part = nullptr, *tiles = nullptr;
+  float* loss = nullptr;
+  uint16_t *xt = nullptr, *h1t = nullptr, *h2t = nullptr, *dyt = nullptr, *dh2t = nullptr,
+           *dh1t = nullptr;
+  // pinned host copies of what goes up (features, targets) and comes back
+  // (outputs, or the gradient block and the loss)
+  float* host = nullptr;
+  size_t host_floats = 0;
+  bool busy = false;  // work that uses `host` may not have ended
 };
 
 namespace {
-
-// fp32 block layout (floats): w1 64x128 (rows 32..63 stay 0), b1 128, w2 128x128,
-// b2 128, w3 128x128, b3 128
-constexpr size_t oW1 = 0, oB1 = oW1 + 64 * kHid, oW2 = oB1 + kHid, oB2 = oW2 + kHid * kHid,
-                 oW3 = oB2 + kHid, oB3 = oW3 + kHid * kOutPad, oEnd = oB3 + kOutPad;
 
 tpg_status mlp_alloc(tpg_mlp* m) {
   TPG_HIP(hipSetDevice(m->device));
@@ -250,41 +409,48 @@ tpg_status mlp_alloc(tpg_mlp* m) {
   return TPG_OK;
 }
 
+// Rows a split of the weight gradients takes at least (four matrix steps: less
+// is all reduction), and splits at most (160 workgroups, 2.6 MB of parts).
+constexpr int kSplitRows = 128, kSplits = 16;
+
 tpg_status mlp_rows(tpg_mlp* m, int n) {
   const int rows = ((n + 63) / 64) * 64;
-  if (rows <= m->rows) return TPG_OK;
-  if (m->act) TPG_HIP(hipFree(m->act));
-  m->act = nullptr;
-  const size_t R = (size_t)rows;
-  size_t floats = R * kIn + R * kOut + 2 * R * kHid + 2 * R * kOutPad + 2 * R * kHid + 64;
-  size_t halves = R * kIn + 64 * R + 2 * (2 * R * kHid) + 2 * R * kOutPad + 2 * (2 * R * kHid);
-  m->act_bytes = floats * 4 + halves * 2 + 1024;
-  TPG_HIP(hipMalloc(&m->act, m->act_bytes));
-  TPG_HIP(hipMemset(m->act, 0, m->act_bytes));
-  float* f = (float*)m->act;
-  m->x = f; f += R * kIn;
-  m->t = f; f += R * kOut;
-  m->h1 = f; f += R * kHid;
-  m->h2 = f; f += R * kHid;
-  m->y = f; f += R * kOutPad;
-  m->dy = f; f += R * kOutPad;
-  m->dh2 = f; f += R * kHid;
-  m->dh1 = f; f += R * kHid;
-  m->loss = f; f += 64;
-  uint16_t* h = (uint16_t*)f;
-  m->xb = h; h += R * kIn;
-  m->xbt = h; h += 64 * R;
-  m->h1b = h; h += R * kHid;
-  m->h1bt = h; h += R * kHid;
-  m->h2b = h; h += R * kHid;
-  m->h2bt = h; h += R * kHid;
-  m->dyb = h; h += R * kOutPad;
-  m->dybt = h; h += R * kOutPad;
-  m->dh2b = h; h += R * kHid;
-  m->dh2bt = h; h += R * kHid;
-  m->dh1b = h; h += R * kHid;
-  m->dh1bt = h; h += R * kHid;
-  m->rows = rows;
+  if (rows > m->rows) {
+    if (m->act) TPG_HIP(hipFree(m->act));
+    m->act = nullptr;
+    m->rows = 0;
+    const size_t R = (size_t)rows;
+    const size_t floats = R * kIn + 2 * R * kOut + R / kRowTile * kPart +
+                          (size_t)kSplits * kTiles * 4096 + 64;
+    const size_t halves = R * (64 + 2 * kHid + kOutPad + 2 * kHid);
+    const size_t bytes = floats * 4 + halves * 2 + 1024;
+    TPG_HIP(hipMalloc(&m->act, bytes));
+    // the padding rows of the transposed arrays stay zero
+    TPG_HIP(hipMemset(m->act, 0, bytes));
+    uint16_t* h = (uint16_t*)m->act;
+    m->xt = h; h += 64 * R;
+    m->h1t = h; h += R * kHid;
+    m->h2t = h; h += R * kHid;
+    m->dyt = h; h += R * kOutPad;
+    m->dh2t = h; h += R * kHid;
+    m->dh1t = h; h += R * kHid;
+    float* f = (float*)h;
+    m->tiles = f; f += (size_t)kSplits * kTiles * 4096;
+    m->x = f; f += R * kIn;
+    m->t = f; f += R * kOut;
+    m->y = f; f += R * kOut;
+    m->part = f; f += R / kRowTile * kPart;
+    m->loss = f;
+    m->rows = rows;
+  }
+  const size_t need = (size_t)rows * (kIn + kOut) + std::max((size_t)rows * kOut, oEnd + 1);
+  if (need > m->host_floats) {
+    if (m->host) TPG_HIP(hipHostFree(m->host));
+    m->host = nullptr;
+    m->host_floats = 0;
+    TPG_HIP(hipHostMalloc((void**)&m->host, sizeof(float) * need, hipHostMallocDefault));
+    m->host_floats = need;
+  }
   return TPG_OK;
 }
 
@@ -298,120 +464,69 @@ tpg_status refresh_bf16(tpg_mlp* m) {
   return TPG_OK;
 }
 
-GemmArgs ga(const uint16_t* A, int lda, const uint16_t* Bt, int ldb, int M, int N, int K) {
-  GemmArgs g{};
-  g.A = A;
-  g.lda = lda;
-  g.Bt = Bt;
-  g.ldb = ldb;
-  g.M = M;
-  g.N = N;
-  g.K = K;
-  g.valid_m = M;
-  g.valid_n = N;
-  return g;
-}
-
-tpg_status forward(tpg_mlp* m, int n) {
-  const int R = m->rows;
+// Features and targets (null: forward only) to the device, and the row pass.
+// *back: pinned room for what comes back.
+tpg_status run_rows(tpg_mlp* m, const float* x, const float* t, int n, RowArgs& g, float** back) {
   hipStream_t st = m->st;
-  k_prep<<<(R * kIn + 255) / 256, 256, 0, st>>>(m->x, n, R, m->mean, m->stdv, m->xb, m->xbt);
-  // W1^T as stored is 128 x 64 with ld 64 (columns 32..63 zero): use K = 32
-  GemmArgs g1 = ga(m->xb, kIn, m->w1bt, 64, R, kHid, kIn);
-  g1.bias = m->b1;
-  g1.relu = 1;
-  g1.C = m->h1;
-  g1.ldc = kHid;
-  g1.Cb = m->h1b;
-  g1.ldcb = kHid;
-  g1.Cbt = m->h1bt;
-  g1.ldcbt = R;
-  g1.valid_m = n;
-  TPG_HIP(gemm(g1, st));
-  GemmArgs g2 = ga(m->h1b, kHid, m->w2bt, kHid, R, kHid, kHid);
-  g2.bias = m->b2;
-  g2.relu = 1;
-  g2.C = m->h2;
-  g2.ldc = kHid;
-  g2.Cb = m->h2b;
-  g2.ldcb = kHid;
-  g2.Cbt = m->h2bt;
-  g2.ldcbt = R;
-  g2.valid_m = n;
-  TPG_HIP(gemm(g2, st));
-  GemmArgs g3 = ga(m->h2b, kHid, m->w3bt, kHid, R, kOutPad, kHid);
-  g3.bias = m->b3;
-  g3.C = m->y;
-  g3.ldc = kOutPad;
-  g3.valid_m = n;
-  g3.valid_n = kOut;
-  TPG_HIP(gemm(g3, st));
-  return TPG_OK;
-}
-
-// gradients of the mean squared error into m->grad (fp32 block layout)
-tpg_status backward(tpg_mlp* m, int n) {
-  const int R = m->rows;
-  hipStream_t st = m->st;
-  TPG_HIP(hipMemsetAsync(m->loss, 0, sizeof(float), st));
-  k_loss_grad<<<(R * kOutPad + 255) / 256, 256, 0, st>>>(m->y, m->t, n, R, m->dy, m->dyb, m->dybt,
-                                                         m->loss);
-  float* G = m->grad;
-  // dW3 = H2^T dY  (128 x 128), db3
-  GemmArgs w3 = ga(m->h2bt, R, m->dybt, R, kHid, kOutPad, R);
-  w3.C = G + oW3;
-  w3.ldc = kOutPad;
-  w3.valid_n = kOut;
-  TPG_HIP(gemm(w3, st));
-  k_colsum<<<1, 128, 0, st>>>(m->dy, R, kOutPad, kOutPad, G + oB3);
-  // dH2 = (dY W3^T) * (H2 > 0)
-  GemmArgs h2 = ga(m->dyb, kOutPad, m->w3b, kOutPad, R, kHid, kOutPad);
-  h2.gate = m->h2;
-  h2.ld_gate = kHid;
-  h2.C = m->dh2;
-  h2.ldc = kHid;
-  h2.Cb = m->dh2b;
-  h2.ldcb = kHid;
-  h2.Cbt = m->dh2bt;
-  h2.ldcbt = R;
-  h2.valid_m = n;
-  TPG_HIP(gemm(h2, st));
-  // dW2 = H1^T dH2, db2
-  GemmArgs w2 = ga(m->h1bt, R, m->dh2bt, R, kHid, kHid, R);
-  w2.C = G + oW2;
-  w2.ldc = kHid;
-  TPG_HIP(gemm(w2, st));
-  k_colsum<<<1, 128, 0, st>>>(m->dh2, R, kHid, kHid, G + oB2);
-  // dH1 = (dH2 W2^T) * (H1 > 0)
-  GemmArgs h1 = ga(m->dh2b, kHid, m->w2b, kHid, R, kHid, kHid);
-  h1.gate = m->h1;
-  h1.ld_gate = kHid;
-  h1.C = m->dh1;
-  h1.ldc = kHid;
-  h1.Cbt = m->dh1bt;
-  h1.ldcbt = R;
-  h1.valid_m = n;
-  TPG_HIP(gemm(h1, st));
-  // dW1 = X^T dH1 (64 x 128, rows 32..63 of X^T are zero), db1
-  GemmArgs w1 = ga(m->xbt, R, m->dh1bt, R, 64, kHid, R);
-  w1.C = G + oW1;
-  w1.ldc = kHid;
-  w1.valid_m = kIn;
-  TPG_HIP(gemm(w1, st));
-  k_colsum<<<1, 128, 0, st>>>(m->dh1, R, kHid, kHid, G + oB1);
+  // a training step that returns no loss does not wait for its uploads
+  if (m->busy) TPG_HIP(hipStreamSynchronize(st));
+  m->busy = false;
+  TPG_TRY(mlp_rows(m, n));
+  float* hx = m->host;
+  float* ht = hx + (size_t)n * kIn;
+  memcpy(hx, x, sizeof(float) * kIn * n);
+  if (t) memcpy(ht, t, sizeof(float) * kOut * n);
+  *back = ht + (size_t)n * kOut;
+  m->busy = true;
+  TPG_HIP(hipMemcpyAsync(m->x, hx, sizeof(float) * kIn * n, hipMemcpyHostToDevice, st));
+  if (t) TPG_HIP(hipMemcpyAsync(m->t, ht, sizeof(float) * kOut * n, hipMemcpyHostToDevice, st));
+  g = RowArgs{};
+  g.x = m->x;
+  g.t = t ? m->t : nullptr;
+  g.n = n;
+  g.ld = m->rows;
+  g.mean = m->mean;
+  g.stdv = m->stdv;
+  g.w1t = m->w1bt;
+  g.w2t = m->w2bt;
+  g.w3t = m->w3bt;
+  g.w2 = m->w2b;
+  g.w3 = m->w3b;
+  g.b1 = m->b1;
+  g.b2 = m->b2;
+  g.b3 = m->b3;
+  g.y = m->y;
+  g.xt = m->xt;
+  g.h1t = m->h1t;
+  g.h2t = m->h2t;
+  g.dyt = m->dyt;
+  g.dh2t = m->dh2t;
+  g.dh1t = m->dh1t;
+  g.part = m->part;
+  // whole steps of 32 rows for the weight gradients: rows past n are zero
+  const int blocks = (n + 31) / 32 * 2;
+  k_mlp_rows<<<(unsigned)blocks, 256, 0, st>>>(g);
   TPG_HIP(hipGetLastError());
   return TPG_OK;
 }
 
-tpg_status upload_rows(tpg_mlp* m, const float* x, const float* t, int n) {
-  TPG_TRY(mlp_rows(m, n));
-  TPG_HIP(hipMemcpyAsync(m->x, x, sizeof(float) * kIn * n, hipMemcpyHostToDevice, m->st));
-  if (t) TPG_HIP(hipMemcpyAsync(m->t, t, sizeof(float) * kOut * n, hipMemcpyHostToDevice, m->st));
+// gradients of the mean squared error into m->grad (fp32 block layout), the
+// loss into m->loss
+tpg_status run_backward(tpg_mlp* m, const RowArgs& g) {
+  hipStream_t st = m->st;
+  const int rows = (g.n + 31) / 32 * 32;
+  int split = std::max(kSplitRows, (rows + kSplits - 1) / kSplits);
+  split = (split + 31) / 32 * 32;
+  const int splits = (rows + split - 1) / split;
+  k_mlp_wgrad<<<dim3(kTiles, (unsigned)splits), 256, 0, st>>>(g, rows, split, m->tiles);
+  k_mlp_reduce<<<kWeightBlocks + kPartBlocks, 256, 0, st>>>(
+      m->tiles, splits, m->part, rows / kRowTile, 1.f / (float)(g.n * kOut), m->grad, m->loss);
+  TPG_HIP(hipGetLastError());
   return TPG_OK;
 }
 
 // packed <-> padded fp32 block
-void pack_params(const std::vector<float>& blk, float* p) {
+void pack_params(const float* blk, float* p) {
   size_t q = 0;
   for (int i = 0; i < kIn; ++i)
     for (int j = 0; j < kHid; ++j) p[q++] = blk[oW1 + i * kHid + j];
@@ -496,6 +611,7 @@ void tpg_mlp_free(tpg_mlp* m) {
   if (m->w1b) (void)hipFree(m->w1b);
   if (m->mean) (void)hipFree(m->mean);
   if (m->act) (void)hipFree(m->act);
+  if (m->host) (void)hipHostFree(m->host);
   if (m->st) (void)hipStreamDestroy(m->st);
   delete m;
 }
@@ -518,7 +634,7 @@ tpg_status tpg_mlp_get_params(const tpg_mlp* m, float* params) {
   std::vector<float> blk(oEnd);
   TPG_HIP(hipStreamSynchronize(m->st));
   TPG_HIP(hipMemcpy(blk.data(), m->master, sizeof(float) * oEnd, hipMemcpyDeviceToHost));
-  pack_params(blk, params);
+  pack_params(blk.data(), params);
   return TPG_OK;
 }
 
@@ -536,12 +652,13 @@ tpg_status tpg_mlp_set_normalizer(tpg_mlp* m, const float* mean, const float* st
 tpg_status tpg_mlp_forward(tpg_mlp* m, const float* x, int32_t n, float* y) {
   if (!m || !x || !y || n < 1) return fail(TPG_ERR_INVALID_ARG, "bad argument");
   TPG_HIP(hipSetDevice(m->device));
-  TPG_TRY(upload_rows(m, x, nullptr, n));
-  TPG_TRY(forward(m, n));
-  std::vector<float> yp((size_t)n * kOutPad);
-  TPG_HIP(hipMemcpyAsync(yp.data(), m->y, sizeof(float) * yp.size(), hipMemcpyDeviceToHost, m->st));
+  RowArgs g;
+  float* back;
+  TPG_TRY(run_rows(m, x, nullptr, n, g, &back));
+  TPG_HIP(hipMemcpyAsync(back, m->y, sizeof(float) * kOut * n, hipMemcpyDeviceToHost, m->st));
   TPG_HIP(hipStreamSynchronize(m->st));
-  for (int b = 0; b < n; ++b) memcpy(y + (size_t)b * kOut, yp.data() + (size_t)b * kOutPad, sizeof(float) * kOut);
+  m->busy = false;
+  memcpy(y, back, sizeof(float) * kOut * n);
   return TPG_OK;
 }
 
@@ -549,20 +666,17 @@ tpg_status tpg_mlp_gradients(tpg_mlp* m, const float* x, const float* t, int32_t
                              float* loss) {
   if (!m || !x || !t || n < 1) return fail(TPG_ERR_INVALID_ARG, "bad argument");
   TPG_HIP(hipSetDevice(m->device));
-  TPG_TRY(upload_rows(m, x, t, n));
-  TPG_TRY(forward(m, n));
-  TPG_TRY(backward(m, n));
+  RowArgs g;
+  float* back;
+  TPG_TRY(run_rows(m, x, t, n, g, &back));
+  TPG_TRY(run_backward(m, g));
+  if (grad) TPG_HIP(hipMemcpyAsync(back, m->grad, sizeof(float) * oEnd, hipMemcpyDeviceToHost, m->st));
+  if (loss)
+    TPG_HIP(hipMemcpyAsync(back + oEnd, m->loss, sizeof(float), hipMemcpyDeviceToHost, m->st));
   TPG_HIP(hipStreamSynchronize(m->st));
-  if (grad) {
-    std::vector<float> blk(oEnd);
-    TPG_HIP(hipMemcpy(blk.data(), m->grad, sizeof(float) * oEnd, hipMemcpyDeviceToHost));
-    pack_params(blk, grad);
-  }
-  if (loss) {
-    float s = 0;
-    TPG_HIP(hipMemcpy(&s, m->loss, sizeof(float), hipMemcpyDeviceToHost));
-    *loss = s / (float)(n * kOut);
-  }
+  m->busy = false;
+  if (grad) pack_params(back, grad);
+  if (loss) *loss = back[oEnd];
   return TPG_OK;
 }
 
@@ -570,9 +684,10 @@ tpg_status tpg_mlp_train_step(tpg_mlp* m, const float* x, const float* t, int32_
                               float* loss) {
   if (!m || !x || !t || n < 1) return fail(TPG_ERR_INVALID_ARG, "bad argument");
   TPG_HIP(hipSetDevice(m->device));
-  TPG_TRY(upload_rows(m, x, t, n));
-  TPG_TRY(forward(m, n));
-  TPG_TRY(backward(m, n));
+  RowArgs g;
+  float* back;
+  TPG_TRY(run_rows(m, x, t, n, g, &back));
+  TPG_TRY(run_backward(m, g));
   m->step += 1;
   AdamArgs a{};
   a.w = m->master;
@@ -590,10 +705,10 @@ tpg_status tpg_mlp_train_step(tpg_mlp* m, const float* x, const float* t, int32_
   TPG_HIP(hipGetLastError());
   TPG_TRY(refresh_bf16(m));
   if (loss) {
-    float s = 0;
-    TPG_HIP(hipMemcpyAsync(&s, m->loss, sizeof(float), hipMemcpyDeviceToHost, m->st));
+    TPG_HIP(hipMemcpyAsync(back, m->loss, sizeof(float), hipMemcpyDeviceToHost, m->st));
     TPG_HIP(hipStreamSynchronize(m->st));
-    *loss = s / (float)(n * kOut);
+    m->busy = false;
+    *loss = *back;
   }
   return TPG_OK;
 }
