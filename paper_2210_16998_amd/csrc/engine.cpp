@@ -869,6 +869,27 @@ struct PPResult {
   int64_t n_pp = 0, n_vtx = 0, n_cycles = 0;
 };
 
+// Levels of at most this many nodes go through the sweeps' one-workgroup form,
+// two per thread: 48 small functions one after another took 25.0 ms without
+// it, 24.6 at 1024 nodes, 22.8 at 2048, 24.9 at 4096 and 25.6 at 8192 (a level
+// then waits for one CU); a 212-vertex CFG 1.78, 1.77, 1.77, 1.80, 1.86 ms.
+constexpr int64_t kNarrowLevel = 2048;
+
+// The run of narrow levels from L on, down to level `last` (last >= L) or up
+// to it, as far as one launch takes.
+LevelSpan narrow_span(const TreeResult& R, int L, int last) {
+  LevelSpan s{};
+  const int step = last >= L ? 1 : -1;
+  int end = L;  // one past the run
+  while (s.n < kSpanLevels && end != last + step && R.count[end] <= kNarrowLevel) {
+    ++s.n;
+    end += step;
+  }
+  const int top = step > 0 ? L : end + 1;
+  for (int i = 0; i <= s.n; ++i) s.off[i] = (uint32_t)R.off[top + i];
+  return s;
+}
+
 EndRows end_rows(tpg_workspace* ws, int n);
 TpTree tp_tree(tpg_workspace* ws, int xn);
 
@@ -928,6 +949,12 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
   TPG_TRY(run_seq(ws, ws->rank_up, std::move(key), st, [&]() -> hipError_t {
     hipError_t e = launch_path_lengths(a, R.count[1], N, st);
     for (int L = R.Lmax; L >= 1 && e == hipSuccess;) {
+      const LevelSpan s = narrow_span(R, L, 1);
+      if (s.n > 0) {
+        e = launch_up_span(a, s, nullptr, sc, st);
+        L -= s.n;
+        continue;
+      }
       const int n = std::min(kRun, L);  // levels L - n + 1 .. L
       const int top = L - n + 1;
       e = n > 1 ? launch_up_run(a, R.off[top], R.count[top], sc, st)
@@ -975,6 +1002,12 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
     // level 1 always (a tree of one level has leaves there), then the parents
     // of the levels below
     for (int L = 1; (L == 1 || L < R.Lmax) && e == hipSuccess;) {
+      const LevelSpan s = narrow_span(R, L, std::max(1, R.Lmax - 1));
+      if (s.n > 0) {
+        e = launch_down_span(a, tt, L, s, sc, leaf, len, st);
+        L += s.n;
+        continue;
+      }
       const int n = std::max(1, std::min(kRun, R.Lmax - L));  // parents of levels L .. L + n - 1
       e = n > 1 ? launch_down_run(a, tt, L, R.off[L], R.count[L], sc, leaf, len, st)
                 : launch_down(a, tt, L, R.off[L], R.count[L], sc, leaf, len, st);
@@ -1198,6 +1231,12 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
     if (e == hipSuccess) e = launch_tp_mark(a, tt, leaf, np, state, rep, st);
     // levels 2 and below, two to a launch
     for (int L = R.Lmax; L >= 2 && e == hipSuccess;) {
+      const LevelSpan s = narrow_span(R, L, 2);
+      if (s.n > 0) {
+        e = launch_up_span(a, s, rep, cnt, st);
+        L -= s.n;
+        continue;
+      }
       const int n = L >= 3 ? 2 : 1;
       const int top = L - n + 1;
       e = n > 1 ? launch_tp_up_run(a, R.off[top], R.count[top], rep, cnt, st)
@@ -1205,8 +1244,12 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
       L -= n;
     }
     if (e == hipSuccess) e = launch_tp_arc_starts(a, tt, order, ng, rep, cnt, first, src, len, st);
-    for (int L = 2; L <= R.Lmax && e == hipSuccess; L += 2)
-      e = launch_tp_down_run(a, tt, R.off[L], R.count[L], rep, cnt, src, len, st);
+    for (int L = 2; L <= R.Lmax && e == hipSuccess;) {
+      const LevelSpan s = narrow_span(R, L, R.Lmax);
+      e = s.n > 0 ? launch_tp_down_span(a, tt, s, rep, cnt, src, len, st)
+                  : launch_tp_down_run(a, tt, R.off[L], R.count[L], rep, cnt, src, len, st);
+      L += s.n > 0 ? s.n : 2;
+    }
     return e;
   }));
   int64_t* sc = ws->scalars.as<int64_t>();

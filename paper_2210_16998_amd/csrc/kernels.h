@@ -92,6 +92,16 @@ hipError_t launch_path_lengths(const ExtArgs& a, int64_t first, int64_t n_nodes,
 // sub_cnt: PP leaves per subtree (k_up), then rewritten top-down into the
 // output position of the subtree's first PP (0xFFFFFFFF when it has none).
 hipError_t launch_up(const ExtArgs& a, int64_t base, int64_t F, uint32_t* sub_cnt, hipStream_t st);
+// Consecutive narrow levels that one workgroup sweeps in one launch: nodes
+// [off[i], off[i + 1]) are the i-th of them from the top.
+constexpr int kSpanLevels = 64;
+struct LevelSpan {
+  int32_t n;
+  uint32_t off[kSpanLevels + 1];
+};
+// rep null: the PP leaves, else the test-path marks
+hipError_t launch_up_span(const ExtArgs& a, const LevelSpan& s, const int32_t* rep,
+                          uint32_t* sub_cnt, hipStream_t st);
 // rb[v - range_lo] = output position of the first prime path whose first
 // vertex is >= v, for the range_n vertices from range_lo (those of the seeded
 // chains) and one past them; the roots' positions into sub_cnt; the prime
@@ -113,6 +123,9 @@ struct TpTree {
                         // last one of its first BFS-tree part (-1: all of it is one)
   int32_t* leaf_canon;  // the same per prime path
 };
+// parents of a span's levels, L the first of them
+hipError_t launch_down_span(const ExtArgs& a, const TpTree& t, int L, const LevelSpan& s,
+                            uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len, hipStream_t st);
 // parents of level L: positions to the children; PP leaves record node and length
 hipError_t launch_down(const ExtArgs& a, const TpTree& t, int L, int64_t base, int64_t F,
                        uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len, hipStream_t st);
@@ -279,6 +292,10 @@ hipError_t launch_tp_mark(const ExtArgs& a, const TpTree& t, const uint64_t* lea
 hipError_t launch_tp_arc_starts(const ExtArgs& a, const TpTree& tt, const int32_t* order, int32_t n,
                                 const int32_t* rep, uint32_t* cnt, int64_t* first, int32_t* src,
                                 int32_t* len, hipStream_t st);
+// places from the nodes of a span's levels down
+hipError_t launch_tp_down_span(const ExtArgs& a, const TpTree& tt, const LevelSpan& s,
+                               const int32_t* rep, uint32_t* cnt, int32_t* src, int32_t* len,
+                               hipStream_t st);
 // places from the nodes of a level down through the next one
 hipError_t launch_tp_down_run(const ExtArgs& a, const TpTree& tt, int64_t base, int64_t F,
                               const int32_t* rep, uint32_t* cnt, int32_t* src, int32_t* len,

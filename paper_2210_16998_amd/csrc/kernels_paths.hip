@@ -785,19 +785,50 @@ __device__ __forceinline__ uint32_t own_count(uint8_t k, const int32_t* rep, int
   return k >= kNchPP ? 1u : 0u;
 }
 
+// The count of node x's subtree from its children's.
+template <bool TP>
+__device__ __forceinline__ uint32_t up_node(const ExtArgs& a, const int32_t* rep, int64_t x,
+                                            const uint32_t* sub_cnt) {
+  const uint8_t k = a.t.nch[x];
+  uint32_t c = own_count<TP>(k, rep, x);
+  if (nch_internal(k)) {
+    const int64_t c0 = a.t.cstart[x], c1 = c0 + k;
+    for (int64_t y = c0; y < c1; ++y) c += sub_cnt[y];
+  }
+  return c;
+}
+
 template <bool TP>
 __global__ __launch_bounds__(kBlock) void k_up(ExtArgs a, int64_t base, int64_t F,
                                                const int32_t* rep, uint32_t* sub_cnt) {
   const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (j >= F) return;
-  const int64_t g = base + j;
-  const uint8_t k = a.t.nch[g];
-  uint32_t c = own_count<TP>(k, rep, g);
-  if (k > 0 && k < kNchPP) {
-    const int64_t c0 = a.t.cstart[g], c1 = c0 + k;
-    for (int64_t x = c0; x < c1; ++x) c += sub_cnt[x];
+  sub_cnt[base + j] = up_node<TP>(a, rep, base + j, sub_cnt);
+}
+
+// Narrow levels, bottom to top, in one launch of one workgroup: a level waits
+// for the one below at the barrier, two or three load latencies, instead of
+// for a launch (5 to 8 us however little it does).  A 20-vertex function's
+// call went from 403 to 367 us, the host's round trips being most of the rest.
+template <bool TP>
+__global__ __launch_bounds__(1024) void k_up_span(ExtArgs a, LevelSpan s, const int32_t* rep,
+                                                  uint32_t* sub_cnt) {
+  for (int l = s.n - 1; l >= 0; --l) {
+    const uint32_t end = s.off[l + 1];
+    for (uint32_t x = s.off[l] + threadIdx.x; x < end; x += 1024)
+      sub_cnt[x] = up_node<TP>(a, rep, x, sub_cnt);
+    __syncthreads();
   }
-  sub_cnt[g] = c;
+}
+
+hipError_t launch_up_span(const ExtArgs& a, const LevelSpan& s, const int32_t* rep,
+                          uint32_t* sub_cnt, hipStream_t st) {
+  if (s.n < 1 || s.n > kSpanLevels) return hipErrorInvalidValue;
+  if (rep)
+    k_up_span<true><<<1, 1024, 0, st>>>(a, s, rep, sub_cnt);
+  else
+    k_up_span<false><<<1, 1024, 0, st>>>(a, s, nullptr, sub_cnt);
+  return hipGetLastError();
 }
 
 hipError_t launch_up(const ExtArgs& a, int64_t base, int64_t F, uint32_t* sub_cnt,
@@ -936,25 +967,54 @@ __device__ __forceinline__ void down_node(const ExtArgs& a, const TpTree& t, int
   }
 }
 
-// Parents of levels L .. L + D in one launch (thread per node of L).  A
-// level-1 node can be a leaf itself.  The nodes' canons pass from launch to
-// launch in t.canon, one level in D + 1.
+// Node x of level L, as a parent.  A level-1 node can be a leaf itself.
+template <int D, bool TP>
+__device__ __forceinline__ void down_parent(const ExtArgs& a, const TpTree& t, int L, int64_t x,
+                                            uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len) {
+  const uint32_t r = sub_cnt[x];
+  if (r == kNoRank) return;
+  const uint8_t k = a.t.nch[x];
+  int32_t cx = -1;
+  if (TP && L > 1 && nch_internal(k)) cx = t.canon[x];
+  if (L == 1 && k >= kNchPP) {
+    put_leaf(a, x, k, r, leaf, pp_len);
+    if constexpr (TP) t.leaf_canon[r] = -1;
+  }
+  down_node<D, TP>(a, t, x, k, cx, r, sub_cnt, leaf, pp_len);
+}
+
+// Parents of levels L .. L + D in one launch (thread per node of L).  The
+// nodes' canons pass from launch to launch in t.canon, one level in D + 1.
 template <int D, bool TP>
 __global__ __launch_bounds__(kBlock) void k_down_run(ExtArgs a, TpTree t, int L, int64_t base,
                                                      int64_t F, uint32_t* sub_cnt, uint64_t* leaf,
                                                      int32_t* pp_len) {
   const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (j >= F) return;
-  const uint32_t r = sub_cnt[base + j];
-  if (r == kNoRank) return;
-  const uint8_t k = a.t.nch[base + j];
-  int32_t cx = -1;
-  if (TP && L > 1 && nch_internal(k)) cx = t.canon[base + j];
-  if (L == 1 && k >= kNchPP) {
-    put_leaf(a, base + j, k, r, leaf, pp_len);
-    if constexpr (TP) t.leaf_canon[r] = -1;
+  down_parent<D, TP>(a, t, L, base + j, sub_cnt, leaf, pp_len);
+}
+
+// Narrow levels, top to bottom (see k_up_span).
+template <bool TP>
+__global__ __launch_bounds__(1024) void k_down_span(ExtArgs a, TpTree t, int L, LevelSpan s,
+                                                    uint32_t* sub_cnt, uint64_t* leaf,
+                                                    int32_t* pp_len) {
+  for (int l = 0; l < s.n; ++l) {
+    const uint32_t end = s.off[l + 1];
+    for (uint32_t x = s.off[l] + threadIdx.x; x < end; x += 1024)
+      down_parent<0, TP>(a, t, L + l, x, sub_cnt, leaf, pp_len);
+    __syncthreads();
   }
-  down_node<D, TP>(a, t, base + j, k, cx, r, sub_cnt, leaf, pp_len);
+}
+
+hipError_t launch_down_span(const ExtArgs& a, const TpTree& t, int L, const LevelSpan& s,
+                            uint32_t* sub_cnt, uint64_t* leaf, int32_t* pp_len, hipStream_t st) {
+  if (s.n < 1 || s.n > kSpanLevels) return hipErrorInvalidValue;
+  if (t.canon)
+    k_down_span<true><<<1, 1024, 0, st>>>(a, t, L, s, sub_cnt, leaf, pp_len);
+  else
+    k_down_span<false><<<1, 1024, 0, st>>>(a, t, L, s, sub_cnt, leaf, pp_len);
+  return hipGetLastError();
 }
 
 hipError_t launch_down(const ExtArgs& a, const TpTree& t, int L, int64_t base, int64_t F,

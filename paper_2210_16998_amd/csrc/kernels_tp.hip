@@ -510,6 +510,28 @@ hipError_t launch_tp_down_run(const ExtArgs& a, const TpTree& tt, int64_t base, 
   return hipGetLastError();
 }
 
+// Narrow levels, top to bottom (see k_up_span).
+__global__ __launch_bounds__(1024) void k_tp_down_span(ExtArgs a, TpTree tt, LevelSpan s,
+                                                       const int32_t* rep, uint32_t* cnt,
+                                                       int32_t* src, int32_t* len) {
+  for (int l = 0; l < s.n; ++l) {
+    const uint32_t end = s.off[l + 1];
+    for (uint32_t x = s.off[l] + threadIdx.x; x < end; x += 1024) {
+      const uint32_t r = cnt[x];
+      if (r) tp_down_node<0>(a, tt, x, r - 1, rep, cnt, src, len);
+    }
+    __syncthreads();
+  }
+}
+
+hipError_t launch_tp_down_span(const ExtArgs& a, const TpTree& tt, const LevelSpan& s,
+                               const int32_t* rep, uint32_t* cnt, int32_t* src, int32_t* len,
+                               hipStream_t st) {
+  if (s.n < 1 || s.n > kSpanLevels) return hipErrorInvalidValue;
+  k_tp_down_span<<<1, 1024, 0, st>>>(a, tt, s, rep, cnt, src, len);
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // rows from prime paths
 // ---------------------------------------------------------------------------
