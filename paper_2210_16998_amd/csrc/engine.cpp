@@ -105,7 +105,8 @@ struct tpg_workspace {
   std::vector<uint64_t> union_uids;
   // level count of the last one-pass run on this union (sizes the first batch)
   std::vector<uint64_t> levels_uids;
-  int levels_last = 0;
+  int levels_last = 0;      // its deepest level
+  int levels_launches = 0;  // extension launches it takes
   // unions (by graph uids) whose predicted capacities could not be allocated
   std::vector<std::vector<uint64_t>> pred_failed;
   DevBuf g_csr;
@@ -618,9 +619,11 @@ tpg_status run_seq(tpg_workspace* ws, tpg_workspace::SeqGraph& g, std::vector<ui
   return TPG_OK;
 }
 
-// `len` extension launches (launch li extends level batch_start + li),
-// replayed from a captured HIP graph (launch arguments are baked in; a change
-// of buffers or stream drops the graphs).
+// `len` extension launches.  As with run_seq they are issued directly the first
+// time, captured when the same arguments ask for as many again, and from then
+// on replayed (a change of buffers or stream drops the graphs): capture and
+// instantiation cost some 100 us, which a graph that is not seen again never
+// earns back.
 tpg_status launch_levels_graph(tpg_workspace* ws, const ExtArgs& a, int W, int items,
                                int variant, int grid, int len, hipStream_t st) {
   if (ws->io_mode == 2) {  // inside a whole-call capture: plain launches
@@ -637,11 +640,18 @@ tpg_status launch_levels_graph(tpg_workspace* ws, const ExtArgs& a, int W, int i
     ws->graph_variant = variant;
     ws->graph_stream = st;
   }
+  tpg_workspace::LevelGraph* seen = nullptr;
   for (auto& lg : ws->level_graphs)
-    if (lg.len == len) {
-      TPG_HIP(hipGraphLaunch(lg.exec, st));
-      return TPG_OK;
-    }
+    if (lg.len == len) seen = &lg;
+  if (!seen) {
+    for (int i = 0; i < len; ++i) TPG_HIP(launch_extend(W, items, variant, a, grid, i, st));
+    ws->level_graphs.push_back({len, nullptr});
+    return TPG_OK;
+  }
+  if (seen->exec) {
+    TPG_HIP(hipGraphLaunch(seen->exec, st));
+    return TPG_OK;
+  }
   hipGraph_t graph = nullptr;
   TPG_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
   for (int i = 0; i < len; ++i) {
@@ -654,13 +664,11 @@ tpg_status launch_levels_graph(tpg_workspace* ws, const ExtArgs& a, int W, int i
     }
   }
   TPG_HIP(hipStreamEndCapture(st, &graph));
-  tpg_workspace::LevelGraph lg;
-  lg.len = len;
-  hipError_t e = hipGraphInstantiate(&lg.exec, graph, nullptr, nullptr, 0);
+  hipError_t e = hipGraphInstantiate(&seen->exec, graph, nullptr, nullptr, 0);
   (void)hipGraphDestroy(graph);
+  if (e != hipSuccess) seen->exec = nullptr;
   TPG_HIP(e);
-  ws->level_graphs.push_back(lg);
-  TPG_HIP(hipGraphLaunch(lg.exec, st));
+  TPG_HIP(hipGraphLaunch(seen->exec, st));
   return TPG_OK;
 }
 
@@ -674,7 +682,13 @@ void release_tree(tpg_workspace* ws) {
   drop_level_graphs(ws);
   ws->levels_uids.clear();
   ws->levels_last = 0;
+  ws->levels_launches = 0;
 }
+
+// Levels that a batch of launches takes at most if the tree is not known: their
+// sizes come back in one copy of 1 KB.
+constexpr int kBatchLevels = 128;
+int level_limit(int L0, int span) { return std::min(L0 + span, kMaxLevels - 2); }
 
 // The device side of the one-pass level loop (see sizing.h): buffers of the
 // workspace, extension launches (replayed from captured graphs, or issued
@@ -687,6 +701,8 @@ struct OnePassDev {
   Timer& tm;
   TreeResult& R;
   int W, items, variant, grid;
+  int span = kBatchLevels;  // levels a batch may take
+  int start = 1;            // batch_start on the device, limit start + span (k_seed)
   ExtArgs a{};
   tpg_status err = TPG_OK;
   std::vector<std::pair<hipEvent_t, hipEvent_t>> evs;
@@ -712,10 +728,16 @@ struct OnePassDev {
   }
   bool run(int L0, int len, BatchReport& r) {
     LevelState* dls = ws->ls.as<LevelState>();
-    ws->h_scalars[8] = L0;
-    if (!hip(hipMemcpyAsync(&dls->batch_start, io_src(ws, &ws->h_scalars[8], sizeof(int32_t)),
-                            sizeof(int32_t), hipMemcpyHostToDevice, st), "batch start"))
-      return false;
+    const int limit = level_limit(L0, span);
+    if (L0 != start) {
+      int32_t* at = reinterpret_cast<int32_t*>(&ws->h_scalars[8]);
+      at[0] = L0;
+      at[1] = limit;
+      if (!hip(hipMemcpyAsync(&dls->batch_start, io_src(ws, at, 2 * sizeof(int32_t)),
+                              2 * sizeof(int32_t), hipMemcpyHostToDevice, st), "batch start"))
+        return false;
+      start = L0;
+    }
     evs.clear();
     if (tm.on) {
       for (int b = 0; b < len; ++b) {
@@ -727,29 +749,38 @@ struct OnePassDev {
     } else if (!ok(launch_levels_graph(ws, a, W, items, variant, grid, len, st))) {
       return false;
     }
-    // header + sizes of levels L0 .. L0 + len
-    if (!ok(io_read(ws, st, ws->h_ls, dls, 32)) ||
-        !ok(io_read(ws, st, ws->h_ls->count + L0, dls->count + L0, sizeof(int64_t) * (len + 1))))
+    // header and the sizes of the levels up to the limit
+    if (!ok(io_read(ws, st, ws->h_ls, dls, kLevelHeader + sizeof(int64_t) * (limit + 1))))
       return false;
     const LevelState& h = *ws->h_ls;
     r.overflow = h.overflow != 0;
     r.overflow_level = h.overflow_level;
+    r.extended = (r.overflow ? r.overflow_level + 2 : h.reached) - L0;
     r.count = h.count;
     // kernel time of the launches that extended a level for good
-    const int last_ok = r.overflow ? r.overflow_level - 1 : L0 + len - 1;
-    for (int b = 0; b < (int)evs.size() && L0 + b <= last_ok && h.count[L0 + b] > 0; ++b) {
-      R.ms_kernel += Timer::ms(evs[b].first, evs[b].second);
+    const int last_ok = r.overflow ? r.overflow_level - 1 : h.reached - 1;
+    int L = L0;
+    for (auto& ev : evs) {
+      if (L > last_ok || h.count[L] == 0) break;
+      R.ms_kernel += Timer::ms(ev.first, ev.second);
       R.launches += 1;
+      L = next_launch(h.count, L, limit);
     }
     tm.next = 0;
     return true;
+  }
+  // The level that the launch after the one from level L on extends first.
+  static int next_launch(const int64_t* count, int L, int limit) {
+    if (count[L] > kNarrowExtend) return L + 1;
+    while (L < limit && count[L] > 0 && count[L] <= kNarrowExtend) ++L;
+    return L;
   }
   bool resume(int Lo) { return hip(launch_resume_fix(a, Lo, st), "replay"); }
 };
 
 // Level loop, one-pass device-sized form.  rec0 / msk0: initial capacities
 // (nodes overall / nodes of one level); 0 = what the workspace already has.
-// Levels run in batches of launches (4, 8, ... 64); the host learns the
+// Levels run in batches of launches (1, 4, 8, ... 64); the host learns the
 // sizes of a batch's levels after it, and grows and replays on overflow.
 tpg_status build_tree_onepass(tpg_workspace* ws, const HostUnion& U, hipStream_t st, Timer& tm,
                               TreeResult& R, int64_t rec0, int64_t msk0) {
@@ -763,12 +794,15 @@ tpg_status build_tree_onepass(tpg_workspace* ws, const HostUnion& U, hipStream_t
   const int grid = ws->num_cus * ws->tune_wgs[wi];
   OnePassDev d{ws, U, st, tm, R, W, ws->tune_items[wi], ws->tune_variant[wi], grid};
   d.a = make_args(ws, grid);
-  TPG_HIP(launch_seed(d.a, st));
+  // a union seen before: one batch takes all of its levels; else one launch to
+  // start with, which is enough for a small function (with four the idle ones
+  // cost an SCC pass over 40 components 0.4 of 4.5 ms)
+  const bool known = ws->levels_uids == U.uids && ws->levels_launches > 0;
+  if (known) d.span = std::max(d.span, ws->levels_last + 1);
+  TPG_HIP(launch_seed(d.a, level_limit(1, d.span), st));
   std::vector<int64_t> cnt(kMaxLevels + 1, 0);
   cnt[1] = d.a.seed_n;
-  // a union seen before: one batch covers its levels and the empty one after
-  const int first_batch =
-      (ws->levels_uids == U.uids && ws->levels_last > 0) ? ws->levels_last + 1 : 4;
+  const int first_batch = known ? ws->levels_launches : 1;
   int Lmax = 0;
   LoopFailure why;
   switch (onepass_levels(d, first_batch, kMaxLevels, cnt, Lmax, R.n_overflows, why)) {
@@ -790,6 +824,9 @@ tpg_status build_tree_onepass(tpg_workspace* ws, const HostUnion& U, hipStream_t
   }
   ws->levels_uids = U.uids;
   ws->levels_last = Lmax;
+  ws->levels_launches = 0;
+  for (int L = 1; L <= Lmax; L = OnePassDev::next_launch(cnt.data(), L, Lmax + 1))
+    ++ws->levels_launches;
   R.count.assign(kMaxLevels, 0);
   R.off.assign(kMaxLevels, 0);
   R.Lmax = Lmax;
@@ -813,7 +850,7 @@ tpg_status build_tree_twopass(tpg_workspace* ws, const HostUnion& U, hipStream_t
     msk = std::max<int64_t>(msk, ws->mask_cap * ws->mask_words / U.Wu);
   TPG_TRY(reserve_tree(ws, rec, msk, U.Wu, st, 0, -1, 0));
   ExtArgs a = make_args(ws);
-  TPG_HIP(launch_seed(a, st));
+  TPG_HIP(launch_seed(a, kMaxLevels - 2, st));
   R.count.assign(kMaxLevels, 0);
   R.off.assign(kMaxLevels, 0);
   int L = 1;

@@ -15,16 +15,21 @@ constexpr int kMaxLevels = 4096 + 4;  // path entries <= n + 1
 // other without the host learning their sizes.  The 32-byte header is what
 // the host polls.
 struct LevelState {
-  int32_t batch_start;     // level extended by launch 0 of the running batch
+  int32_t batch_start;     // first level that launch 0 of the running batch extends
+  int32_t limit;           // the batch leaves levels from this one on alone
   int32_t overflow;        // non-zero: the children of overflow_level did not fit
   int32_t overflow_level;
-  int32_t pad;
-  int64_t pad2[2];
+  int32_t reached;         // first level that the last launch has left to the next
+  int32_t pad[3];
   // nodes (paths) per level, cycle closures included; while level L is
   // extended, count[L + 1] is the running claim counter of its tiles
   int64_t count[kMaxLevels];
   int64_t off[kMaxLevels];    // global index of the first node of each level
+  int32_t next[kMaxLevels];   // first level that each launch of the batch extends
 };
+constexpr int kLevelHeader = 32;  // bytes before count
+// Levels of at most this many nodes are extended many to a launch.
+constexpr int kNarrowExtend = 2048;
 
 // Buffers of the path tree and of the frontier.
 struct TreeBufs {
@@ -67,7 +72,7 @@ struct PathTotals {
 };
 
 // --- path tree -------------------------------------------------------------
-hipError_t launch_seed(const ExtArgs& a, hipStream_t st);
+hipError_t launch_seed(const ExtArgs& a, int limit, hipStream_t st);
 // items: most parents per thread (tile <= threads * items); variant: 0
 // load-balanced tiles of 256 threads, 1 / 2 thread-per-parent with 256 /
 // 1024 threads; grid: persistent workgroups; li: index of the launch in its

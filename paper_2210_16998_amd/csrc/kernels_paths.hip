@@ -46,9 +46,9 @@
 //    waits for another one; the order of tile slices inside a level is the
 //    order in which the claims landed, which ranking does not depend on.
 //  * Levels follow each other on the device: per-level counts and offsets
-//    live in device memory; launch li of a batch extends level
-//    batch_start + li and derives its offset from the level before, or
-//    raises the overflow flag when that level's children did not fit; the
+//    live in device memory; a launch extends the level that the one before
+//    it has left (narrow levels many at a time, see LevelCursor), derives
+//    its offset from the level before, or raises the overflow flag when that level's children did not fit; the
 //    host then grows the buffers to the exact size and replays the level.
 //  * The plain two-pass form (count, scan, host-visible size, fill) keeps
 //    children in parent order and serves as the exact reference form.
@@ -63,7 +63,7 @@ namespace tpg {
 // ---------------------------------------------------------------------------
 // level 1
 // ---------------------------------------------------------------------------
-__global__ void k_seed(ExtArgs a, int64_t tot_words) {
+__global__ void k_seed(ExtArgs a, int limit, int64_t tot_words) {
   const int n = a.seed_n;
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   LevelState* ls = a.ls;
@@ -74,6 +74,7 @@ __global__ void k_seed(ExtArgs a, int64_t tot_words) {
   }
   if (i == 0) {
     ls->batch_start = 1;
+    ls->limit = limit;
     ls->overflow = 0;
     ls->overflow_level = 0;
   }
@@ -94,13 +95,14 @@ __global__ void k_seed(ExtArgs a, int64_t tot_words) {
   }
 }
 
-hipError_t launch_seed(const ExtArgs& a, hipStream_t st) {
+hipError_t launch_seed(const ExtArgs& a, int limit, hipStream_t st) {
+  if (limit < 1 || limit > kMaxLevels - 2) return hipErrorInvalidValue;
   if (a.seed_lo < 0 || a.seed_n < 1 || a.seed_lo + a.seed_n > a.g.n) return hipErrorInvalidValue;
   const int64_t work = std::max<int64_t>(kMaxLevels, (int64_t)a.seed_n * a.t.mask_words);
   // one thread at least per seed
   const int64_t grid = std::max<int64_t>((a.seed_n + kBlock - 1) / kBlock,
                                          std::min<int64_t>(1024, (work + kBlock - 1) / kBlock + 1));
-  k_seed<<<(unsigned)grid, kBlock, 0, st>>>(a, PathTotals::words(a.g));
+  k_seed<<<(unsigned)grid, kBlock, 0, st>>>(a, limit, PathTotals::words(a.g));
   return hipGetLastError();
 }
 
@@ -198,12 +200,100 @@ __device__ __forceinline__ void path_mask_own(int L, int vl, uint64_t (&m)[W]) {
 // ---------------------------------------------------------------------------
 // one-pass extension of level L -> L+1 (device-sized, claim per tile)
 // ---------------------------------------------------------------------------
-// Launch `li` of a batch extends level L = batch_start + li.  Its offset is
-// derived from the previous level's final offset and size, so no kernel has
-// to advance a level counter; a level whose nodes did not fit (claimed
-// beyond the capacities by the launch before) raises the overflow flag and
-// ends the batch.
+// Launch `li` of a batch extends the level that the launch before it has left
+// (batch_start for the first).  Its offset is derived from the previous level's
+// final offset and size, so no kernel has to advance a level counter; a level
+// whose nodes did not fit (claimed beyond the capacities by the launch before)
+// raises the overflow flag and ends the batch.
 //
+// A level of at most kNarrowExtend nodes is workgroup 0's alone, which then
+// goes on to the levels after it until one is wide, empty or past the limit: a
+// launch costs 5 to 8 us and the host's look at the sizes some 40, while the
+// workgroup needs 2 to 3 us a level.  48 small functions, none seen
+// just before, took 20.6 ms without it, 17.0 with the line at 1024 nodes and 16.7 from
+// 2048 to 8192; a 212-vertex CFG 1.83, 1.79, 1.79 and from 8192 on 1.82 ms.
+struct LevelCursor {
+  int L, limit;
+  bool narrow;
+  int64_t F, base, prev;
+  int children;  // of a narrow level, so far (< 2^17)
+
+  // Sets the cursor to the launch's first level; false: nothing to extend.
+  __device__ __forceinline__ bool begin(LevelState* ls, int li) {
+    if (ls->overflow) return false;
+    L = li == 0 ? ls->batch_start : ls->next[li];
+    limit = ls->limit;
+    F = L < limit ? ls->count[L] : 0;
+    if (F == 0) {
+      leave(ls, li);
+      return false;
+    }
+    prev = ls->off[L - 1];
+    base = prev + ls->count[L - 1];
+    narrow = F <= kNarrowExtend;
+    return !narrow || blockIdx.x == 0;
+  }
+  __device__ __forceinline__ int64_t step() const { return narrow ? 1 : (int64_t)gridDim.x; }
+  // Parents per thread of a tile.
+  __device__ __forceinline__ int items(int nt, int most, int64_t target) const {
+    const int64_t want = narrow ? 1 : target;
+    int ir = 1;
+    while (ir < most && (F + (int64_t)nt * ir - 1) / ((int64_t)nt * ir) > want) ir <<= 1;
+    return ir;
+  }
+  __device__ __forceinline__ bool has_tile(int nt, int most, int64_t target) const {
+    return (int64_t)blockIdx.x * nt * items(nt, most, target) < F;
+  }
+  // The level's nodes must be there: false (and the overflow raised) if the
+  // children of the level before it did not fit.
+  __device__ __forceinline__ bool open(const ExtArgs& a) {
+    const bool fits = level_fits(L, base, F, a.t.rec_cap, a.t.mask_cap);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      if (fits) {
+        a.ls->off[L] = base;
+      } else {
+        a.ls->overflow_level = L - 1;
+        a.ls->overflow = 1;
+      }
+    }
+    children = 0;
+    return fits;
+  }
+  // The place of a tile's `total` children in the next level (one thread).
+  __device__ __forceinline__ int64_t claim(LevelState* ls, int total) const {
+    if (narrow) return children;
+    if (!total) return 0;
+    return (int64_t)atomicAdd(reinterpret_cast<unsigned long long*>(&ls->count[L + 1]),
+                              (unsigned long long)total);
+  }
+  // total comes from LDS: said to be uniform, or it and all that follows from
+  // it would take vector registers
+  __device__ __forceinline__ void claimed(int total) {
+    children += __builtin_amdgcn_readfirstlane(total);
+  }
+  // After a level: on to the next one, or leaves it to the next launch.
+  __device__ __forceinline__ bool advance(LevelState* ls, int li) {
+    if (narrow && threadIdx.x == 0) ls->count[L + 1] = children;
+    ++L;
+    if (narrow) {
+      prev = base;
+      base += F;
+      F = children;
+    }
+    if (!narrow || F == 0 || F > kNarrowExtend || L >= limit) {
+      leave(ls, li);
+      return false;
+    }
+    return true;
+  }
+  __device__ __forceinline__ void leave(LevelState* ls, int li) const {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      ls->next[li + 1] = L;
+      ls->reached = L;
+    }
+  }
+};
+
 // A tile is 256 * ir consecutive parents (ir <= ITEMS, chosen per level so
 // that large levels need few claims and small ones still spread over the
 // grid); tile t goes to workgroup t mod grid.  Thread tid owns parents
@@ -224,37 +314,13 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 &
   __shared__ int64_t s_prefix;
   extern __shared__ int32_t s_graph[];
 
-  LevelState* ls = a.ls;
-  if (ls->overflow) return;
-  const int L = ls->batch_start + li;
-  if (L < 1 || L + 2 >= kMaxLevels) return;
-  const int64_t F = ls->count[L];
-  if (F == 0) return;
-  const int64_t base = ls->off[L - 1] + ls->count[L - 1];
   const int tid = (int)threadIdx.x;
   const int lane = lane_id(), wave = tid >> 6;
-  if (!level_fits(L, base, F, a.t.rec_cap, a.t.mask_cap)) {
-    // the previous launch's children did not fit: replay that level
-    if (blockIdx.x == 0 && tid == 0) {
-      ls->overflow_level = L - 1;
-      ls->overflow = 1;
-    }
-    return;
-  }
-  if (blockIdx.x == 0 && tid == 0) ls->off[L] = base;
-  const int64_t nbase = base + F;
-  const int64_t prev = ls->off[L - 1];
-  // children's sets are stored when they land on an odd level
-  uint64_t* mnxt = (L & 1) ? nullptr : a.t.mask[mask_buf(L + 1)];
-  unsigned long long* claim = reinterpret_cast<unsigned long long*>(&ls->count[L + 1]);
-
-  int ir = 1;
-  while (ir < ITEMS && (F + (int64_t)NT * ir - 1) / ((int64_t)NT * ir) > a.tiles_target) ir <<= 1;
-  const int64_t TR = (int64_t)NT * ir;
-  const int64_t ntiles = (F + TR - 1) / TR;
+  LevelCursor cur;
+  if (!cur.begin(a.ls, li)) return;
   DGraph g = a.g;
   if constexpr (GL) {
-    if ((int64_t)blockIdx.x >= ntiles) return;
+    if (!cur.has_tile(NT, ITEMS, a.tiles_target)) return;
     for (int i = tid; i < a.g.n_stage; i += NT) s_graph[i] = a.g.sp[i];
     __syncthreads();
     g.sp = s_graph;
@@ -264,103 +330,109 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 &
     g.loc = s_graph + (a.g.loc - a.g.sp);
     g.len = s_graph + (a.g.len - a.g.sp);
   }
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const int64_t tb = t * TR;
-    // records and visited sets of the thread's parents (independent loads;
-    // rows outside the level read parent 0's set and are ignored)
-    uint32_t inf[ITEMS];
-    int tl[ITEMS];
-    uint64_t m[ITEMS][W];
+  do {
+    if (!cur.open(a)) return;
+    const int L = cur.L;
+    const int64_t F = cur.F, base = cur.base, prev = cur.prev;
+    const int64_t nbase = base + F;
+    // children's sets are stored when they land on an odd level
+    uint64_t* mnxt = (L & 1) ? nullptr : a.t.mask[mask_buf(L + 1)];
+    const int ir = cur.items(NT, ITEMS, a.tiles_target);
+    const int64_t TR = (int64_t)NT * ir;
+    const int64_t ntiles = (F + TR - 1) / TR;
+    for (int64_t t = blockIdx.x; t < ntiles; t += cur.step()) {
+      const int64_t tb = t * TR;
+      // records and visited sets of the thread's parents (independent loads;
+      // rows outside the level read parent 0's set and are ignored)
+      uint32_t inf[ITEMS];
+      int tl[ITEMS];
+      uint64_t m[ITEMS][W];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      const int64_t j = tb + i * NT + tid;
-      const bool ok = i < ir && j < F;
-      inf[i] = ok ? a.t.info[base + j] : F_CYC;
-      tl[i] = ok ? a.t.tl[base + j] : 0;
-      path_mask_load<W>(a, L, prev, base + (ok ? j : 0), ok ? j : 0, m[i]);
-    }
-    // choice masks and the terminal filter
-    uint64_t vm[ITEMS];
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      vm[i] = 0;
-      if (!(inf[i] & F_CYC)) {
-        const int v = node_v(inf[i]);
-        const int cb = v - g.loc[v];
-        path_mask_own<W>(L, v - cb, m[i]);
-        vm[i] = choices<W>(g, inf[i], m[i], g.sp[v], g.sp[v + 1], cb);
-        if (vm[i] == 0) {
-          const bool pp = all_preds_on<W>(g, cb, node_v1l(inf[i]), m[i]);
-          inf[i] |= F_TERM | (pp ? F_PP : 0u);  // recorded through nch_code below
-        }
+      for (int i = 0; i < ITEMS; ++i) {
+        const int64_t j = tb + i * NT + tid;
+        const bool ok = i < ir && j < F;
+        inf[i] = ok ? a.t.info[base + j] : F_CYC;
+        tl[i] = ok ? a.t.tl[base + j] : 0;
+        path_mask_load<W>(a, L, prev, base + (ok ? j : 0), ok ? j : 0, m[i]);
       }
-    }
-    // child offsets: item-major, thread order inside an item
-    int excl[ITEMS];
+      // choice masks and the terminal filter
+      uint64_t vm[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      const int c = __builtin_popcountll(vm[i]);
-      const int inc = wave_incl_scan(c);
-      excl[i] = inc - c;
-      if (lane == 63) s_tot[i][wave] = inc;
-    }
-    __syncthreads();
-    int total = 0;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      int before = 0, all = 0;
-#pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const int x = i < ir ? s_tot[i][w] : 0;
-        before += w < wave ? x : 0;
-        all += x;
-      }
-      excl[i] += total + before;
-      total += all;
-    }
-    if (tid == 0) {
-      int64_t pre = 0;
-      if (ntiles == 1) {
-        *claim = (unsigned long long)total;  // the only tile of the level
-      } else if (total) {
-        pre = (int64_t)atomicAdd(claim, (unsigned long long)total);
-      }
-      s_prefix = pre;
-    }
-    __syncthreads();
-    const int64_t prefix = s_prefix;
-    // expansion: each thread writes its parents' children in slot order
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      const int64_t j = tb + i * NT + tid;
-      if (i < ir && j < F) {
-        int64_t cl = prefix + excl[i];
-        a.t.cstart[base + j] = (int32_t)(nbase + cl);
-        a.t.nch[base + j] = nch_code(inf[i], __builtin_popcountll(vm[i]));
-        const int v1l = node_v1l(inf[i]);
-        uint64_t rest = vm[i];
-        const int pv = node_v(inf[i]);
-        const int k0 = rest ? g.sp[pv] : 0;
-        const int cb = rest ? pv - g.loc[pv] : 0;
-        while (rest) {
-          const int slot = __builtin_ctzll(rest);
-          rest &= rest - 1;
-          const int w = g.s[k0 + slot];
-          const int wl = w - cb;
-          const int64_t cg = nbase + cl;
-          if (cg < a.t.rec_cap) {
-            a.t.par[cg] = (int32_t)(base + j);
-            a.t.info[cg] = make_info(w, v1l, wl == v1l ? F_CYC : 0u);
-            a.t.tl[cg] = (uint16_t)(tl[i] + (wl == v1l ? 0 : g.len[w]));
+      for (int i = 0; i < ITEMS; ++i) {
+        vm[i] = 0;
+        if (!(inf[i] & F_CYC)) {
+          const int v = node_v(inf[i]);
+          const int cb = v - g.loc[v];
+          path_mask_own<W>(L, v - cb, m[i]);
+          vm[i] = choices<W>(g, inf[i], m[i], g.sp[v], g.sp[v + 1], cb);
+          if (vm[i] == 0) {
+            const bool pp = all_preds_on<W>(g, cb, node_v1l(inf[i]), m[i]);
+            inf[i] |= F_TERM | (pp ? F_PP : 0u);  // recorded through nch_code below
           }
-          if (mnxt && wl != v1l && cl < a.t.mask_cap)
-            store_child_mask<W>(mnxt, a.t.mask_cap, a.t.mask_words, cl, m[i], wl);
-          ++cl;
         }
       }
+      // child offsets: item-major, thread order inside an item
+      int excl[ITEMS];
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) {
+        const int c = __builtin_popcountll(vm[i]);
+        const int inc = wave_incl_scan(c);
+        excl[i] = inc - c;
+        if (lane == 63) s_tot[i][wave] = inc;
+      }
+      __syncthreads();
+      int total = 0;
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) {
+        int before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+          const int x = i < ir ? s_tot[i][w] : 0;
+          before += w < wave ? x : 0;
+          all += x;
+        }
+        excl[i] += total + before;
+        total += all;
+      }
+      if (tid == 0) {
+        s_prefix = cur.claim(a.ls, total);
+      }
+      __syncthreads();
+      const int64_t prefix = s_prefix;
+      cur.claimed(total);
+      // expansion: each thread writes its parents' children in slot order
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) {
+        const int64_t j = tb + i * NT + tid;
+        if (i < ir && j < F) {
+          int64_t cl = prefix + excl[i];
+          a.t.cstart[base + j] = (int32_t)(nbase + cl);
+          a.t.nch[base + j] = nch_code(inf[i], __builtin_popcountll(vm[i]));
+          const int v1l = node_v1l(inf[i]);
+          uint64_t rest = vm[i];
+          const int pv = node_v(inf[i]);
+          const int k0 = rest ? g.sp[pv] : 0;
+          const int cb = rest ? pv - g.loc[pv] : 0;
+          while (rest) {
+            const int slot = __builtin_ctzll(rest);
+            rest &= rest - 1;
+            const int w = g.s[k0 + slot];
+            const int wl = w - cb;
+            const int64_t cg = nbase + cl;
+            if (cg < a.t.rec_cap) {
+              a.t.par[cg] = (int32_t)(base + j);
+              a.t.info[cg] = make_info(w, v1l, wl == v1l ? F_CYC : 0u);
+              a.t.tl[cg] = (uint16_t)(tl[i] + (wl == v1l ? 0 : g.len[w]));
+            }
+            if (mnxt && wl != v1l && cl < a.t.mask_cap)
+              store_child_mask<W>(mnxt, a.t.mask_cap, a.t.mask_words, cl, m[i], wl);
+            ++cl;
+          }
+        }
+      }
+      __syncthreads();
     }
-    __syncthreads();
-  }
+  } while (cur.advance(a.ls, li));
 }
 
 // Load-balanced form of the same step: the tile's parents are staged in LDS
@@ -379,137 +451,123 @@ __global__ __launch_bounds__(kBlock) void k_extend_lb(ExtArgs a, int li) {
   __shared__ uint64_t s_mask[kLdsMask ? TILE * W : 1];
   __shared__ int32_t s_w[kBlock / 64];
 
-  LevelState* ls = a.ls;
-  if (ls->overflow) return;
-  const int L = ls->batch_start + li;
-  if (L < 1 || L + 2 >= kMaxLevels) return;
-  const int64_t F = ls->count[L];
-  if (F == 0) return;
-  const int64_t base = ls->off[L - 1] + ls->count[L - 1];
   const int tid = (int)threadIdx.x;
-  if (!level_fits(L, base, F, a.t.rec_cap, a.t.mask_cap)) {
-    if (blockIdx.x == 0 && tid == 0) {
-      ls->overflow_level = L - 1;
-      ls->overflow = 1;
-    }
-    return;
-  }
-  if (blockIdx.x == 0 && tid == 0) ls->off[L] = base;
-  const int64_t nbase = base + F;
-  const int64_t prev = ls->off[L - 1];
-  uint64_t* mnxt = (L & 1) ? nullptr : a.t.mask[mask_buf(L + 1)];
-  unsigned long long* claim = reinterpret_cast<unsigned long long*>(&ls->count[L + 1]);
-
-  int ir = 1;
-  while (ir < ITEMS && (F + (int64_t)kBlock * ir - 1) / ((int64_t)kBlock * ir) > a.tiles_target) ir <<= 1;
-  const int TR = kBlock * ir;
-  const int64_t ntiles = (F + TR - 1) / TR;
-  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-    const int64_t tb = t * TR;
-    uint32_t inf[ITEMS];
+  LevelCursor cur;
+  if (!cur.begin(a.ls, li)) return;
+  do {
+    if (!cur.open(a)) return;
+    const int L = cur.L;
+    const int64_t F = cur.F, base = cur.base, prev = cur.prev;
+    const int64_t nbase = base + F;
+    uint64_t* mnxt = (L & 1) ? nullptr : a.t.mask[mask_buf(L + 1)];
+    const int ir = cur.items(kBlock, ITEMS, a.tiles_target);
+    const int TR = kBlock * ir;
+    const int64_t ntiles = (F + TR - 1) / TR;
+    for (int64_t t = blockIdx.x; t < ntiles; t += cur.step()) {
+      const int64_t tb = t * TR;
+      uint32_t inf[ITEMS];
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      const int64_t j = tb + i * kBlock + tid;
-      inf[i] = (i < ir && j < F) ? a.t.info[base + j] : F_CYC;
-    }
+      for (int i = 0; i < ITEMS; ++i) {
+        const int64_t j = tb + i * kBlock + tid;
+        inf[i] = (i < ir && j < F) ? a.t.info[base + j] : F_CYC;
+      }
 #pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      if (i < ir) {
-        const int p = i * kBlock + tid;
-        const int64_t j = tb + p;
-        uint32_t in = inf[i];
-        uint64_t m[W];
+      for (int i = 0; i < ITEMS; ++i) {
+        if (i < ir) {
+          const int p = i * kBlock + tid;
+          const int64_t j = tb + p;
+          uint32_t in = inf[i];
+          uint64_t m[W];
 #pragma unroll
-        for (int q = 0; q < W; ++q) m[q] = 0;
-        uint64_t vm = 0;
-        int k0 = 0;
-        if (!(in & F_CYC)) {
-          const int v = node_v(in);
-          const int cb = v - a.g.loc[v];
-          k0 = a.g.sp[v];
-          path_mask_load<W>(a, L, prev, base + j, j, m);
-          path_mask_own<W>(L, v - cb, m);
-          vm = choices<W>(a.g, in, m, k0, a.g.sp[v + 1], cb);
-          if (vm == 0) {
-            const bool pp = all_preds_on<W>(a.g, cb, node_v1l(in), m);
-            in |= F_TERM | (pp ? F_PP : 0u);  // recorded through nch_code
+          for (int q = 0; q < W; ++q) m[q] = 0;
+          uint64_t vm = 0;
+          int k0 = 0;
+          if (!(in & F_CYC)) {
+            const int v = node_v(in);
+            const int cb = v - a.g.loc[v];
+            k0 = a.g.sp[v];
+            path_mask_load<W>(a, L, prev, base + j, j, m);
+            path_mask_own<W>(L, v - cb, m);
+            vm = choices<W>(a.g, in, m, k0, a.g.sp[v + 1], cb);
+            if (vm == 0) {
+              const bool pp = all_preds_on<W>(a.g, cb, node_v1l(in), m);
+              in |= F_TERM | (pp ? F_PP : 0u);  // recorded through nch_code
+            }
+          }
+          s_off[p] = __builtin_popcountll(vm);
+          s_vm[p] = vm;
+          s_inf[p] = in;
+          s_kk[p] = k0;
+          if constexpr (kLdsMask) {
+#pragma unroll
+            for (int q = 0; q < W; ++q) s_mask[p * W + q] = m[q];
           }
         }
-        s_off[p] = __builtin_popcountll(vm);
-        s_vm[p] = vm;
-        s_inf[p] = in;
-        s_kk[p] = k0;
-        if constexpr (kLdsMask) {
+      }
+      __syncthreads();
+      int c[ITEMS];
+      int sum = 0;
 #pragma unroll
-          for (int q = 0; q < W; ++q) s_mask[p * W + q] = m[q];
+      for (int i = 0; i < ITEMS; ++i) {
+        c[i] = i < ir ? s_off[tid * ir + i] : 0;
+        sum += c[i];
+      }
+      int32_t total32;
+      int32_t run = block_excl_scan<kBlock, int32_t>(sum, total32, s_w);
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) {
+        if (i < ir) s_off[tid * ir + i] = run;
+        run += c[i];
+      }
+      if (tid == 0) {
+        s_prefix = cur.claim(a.ls, total32);
+      }
+      __syncthreads();
+      const int64_t prefix = s_prefix;
+      cur.claimed(total32);
+#pragma unroll
+      for (int i = 0; i < ITEMS; ++i) {
+        const int p = i * kBlock + tid;
+        if (i < ir && tb + p < F) {
+          a.t.cstart[base + tb + p] = (int32_t)(nbase + prefix + s_off[p]);
+          a.t.nch[base + tb + p] = nch_code(s_inf[p], __builtin_popcountll(s_vm[p]));
         }
       }
-    }
-    __syncthreads();
-    int c[ITEMS];
-    int sum = 0;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      c[i] = i < ir ? s_off[tid * ir + i] : 0;
-      sum += c[i];
-    }
-    int32_t total32;
-    int32_t run = block_excl_scan<kBlock, int32_t>(sum, total32, s_w);
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      if (i < ir) s_off[tid * ir + i] = run;
-      run += c[i];
-    }
-    if (tid == 0) {
-      int64_t pre = 0;
-      if (ntiles == 1) *claim = (unsigned long long)total32;
-      else if (total32) pre = (int64_t)atomicAdd(claim, (unsigned long long)total32);
-      s_prefix = pre;
-    }
-    __syncthreads();
-    const int64_t prefix = s_prefix;
-#pragma unroll
-    for (int i = 0; i < ITEMS; ++i) {
-      const int p = i * kBlock + tid;
-      if (i < ir && tb + p < F) {
-        a.t.cstart[base + tb + p] = (int32_t)(nbase + prefix + s_off[p]);
-        a.t.nch[base + tb + p] = nch_code(s_inf[p], __builtin_popcountll(s_vm[p]));
-      }
-    }
-    for (int k = tid; k < total32; k += kBlock) {
-      int lo = 0, hi = TR - 1;
-      while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (s_off[mid] <= k) lo = mid; else hi = mid - 1;
-      }
-      const int o = lo;
-      const int slot = select_bit(s_vm[o], k - s_off[o]);
-      const uint32_t pinf = s_inf[o];
-      const int v1l = node_v1l(pinf);
-      const int pv = node_v(pinf);
-      const int w = a.g.s[s_kk[o] + slot];
-      const int wl = w - (pv - a.g.loc[pv]);
-      const int64_t cl = prefix + k;
-      const int64_t cg = nbase + cl;
-      if (cg < a.t.rec_cap) {
-        a.t.par[cg] = (int32_t)(base + tb + o);
-        a.t.info[cg] = make_info(w, v1l, wl == v1l ? F_CYC : 0u);
-        a.t.tl[cg] = (uint16_t)(a.t.tl[base + tb + o] + (wl == v1l ? 0 : a.g.len[w]));
-      }
-      if (mnxt && wl != v1l && cl < a.t.mask_cap) {
-        uint64_t pm[W];
-        if constexpr (kLdsMask) {
-#pragma unroll
-          for (int q = 0; q < W; ++q) pm[q] = s_mask[o * W + q];
-        } else {
-          path_mask_load<W>(a, L, prev, base + tb + o, tb + o, pm);
-          path_mask_own<W>(L, a.g.loc[pv], pm);
+      for (int k = tid; k < total32; k += kBlock) {
+        int lo = 0, hi = TR - 1;
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (s_off[mid] <= k) lo = mid; else hi = mid - 1;
         }
-        store_child_mask<W>(mnxt, a.t.mask_cap, a.t.mask_words, cl, pm, wl);
+        const int o = lo;
+        const int slot = select_bit(s_vm[o], k - s_off[o]);
+        const uint32_t pinf = s_inf[o];
+        const int v1l = node_v1l(pinf);
+        const int pv = node_v(pinf);
+        const int w = a.g.s[s_kk[o] + slot];
+        const int wl = w - (pv - a.g.loc[pv]);
+        const int64_t cl = prefix + k;
+        const int64_t cg = nbase + cl;
+        if (cg < a.t.rec_cap) {
+          a.t.par[cg] = (int32_t)(base + tb + o);
+          a.t.info[cg] = make_info(w, v1l, wl == v1l ? F_CYC : 0u);
+          a.t.tl[cg] = (uint16_t)(a.t.tl[base + tb + o] + (wl == v1l ? 0 : a.g.len[w]));
+        }
+        if (mnxt && wl != v1l && cl < a.t.mask_cap) {
+          uint64_t pm[W];
+          if constexpr (kLdsMask) {
+#pragma unroll
+            for (int q = 0; q < W; ++q) pm[q] = s_mask[o * W + q];
+          } else {
+            path_mask_load<W>(a, L, prev, base + tb + o, tb + o, pm);
+            path_mask_own<W>(L, a.g.loc[pv], pm);
+          }
+          store_child_mask<W>(mnxt, a.t.mask_cap, a.t.mask_words, cl, pm, wl);
+        }
       }
+      __syncthreads();
     }
-    __syncthreads();
-  }
+  } while (cur.advance(a.ls, li));
 }
 
 // Launch with optional start / stop events recorded by the dispatch itself

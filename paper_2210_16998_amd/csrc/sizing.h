@@ -62,6 +62,9 @@ constexpr int stored_level_read_by(int L) { return (L & 1) ? L : L - 1; }
 struct BatchReport {
   bool overflow = false;
   int overflow_level = 0;
+  // levels taken from L0 on, counting the ones that an overflow took back
+  // (0: as many as launches)
+  int extended = 0;
   const int64_t* count = nullptr;  // indexed by level
 };
 
@@ -98,14 +101,15 @@ LoopEnd onepass_levels(Dev& d, int first_batch, int max_levels, std::vector<int6
     if (len <= 0) return LoopEnd::too_deep;
     BatchReport r;
     if (!d.run(L0, len, r)) return LoopEnd::device_failed;
+    const int got = r.extended > 0 ? r.extended : len;
     const int Lo = r.overflow ? r.overflow_level : -1;
-    if (r.overflow && (Lo < std::max(1, L0 - 1) || Lo > L0 + len - 2)) {
+    if (r.overflow && (Lo < std::max(1, L0 - 1) || Lo > L0 + got - 2)) {
       fail_info.level = Lo;
       return LoopEnd::bad_report;
     }
     // levels extended for good in this batch: L0 .. last_ok
-    const int last_ok = r.overflow ? Lo - 1 : L0 + len - 1;
-    for (int L = L0; L <= std::min(last_ok + 1, L0 + len); ++L) cnt[L] = r.count[L];
+    const int last_ok = r.overflow ? Lo - 1 : L0 + got - 1;
+    for (int L = L0; L <= std::min(last_ok + 1, L0 + got); ++L) cnt[L] = r.count[L];
     if (r.overflow) {
       cnt[Lo + 1] = r.count[Lo + 1];
       int64_t base = 0;
@@ -125,7 +129,7 @@ LoopEnd onepass_levels(Dev& d, int first_batch, int max_levels, std::vector<int6
       continue;
     }
     int empty = -1;
-    for (int L = L0; L <= L0 + len; ++L)
+    for (int L = L0; L <= L0 + got; ++L)
       if (cnt[L] == 0) {
         empty = L;
         break;
@@ -134,7 +138,7 @@ LoopEnd onepass_levels(Dev& d, int first_batch, int max_levels, std::vector<int6
       Lmax = empty - 1;
       return LoopEnd::ok;
     }
-    L0 += len;
+    L0 += got;
     batch = std::max(4, std::min(batch * 2, 64));
   }
 }

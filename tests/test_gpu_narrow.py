@@ -50,6 +50,21 @@ def test_all_paths_of_fans(widths):
         assert st["n_pp"] == st["n_tp"] == n
 
 
+# a new workspace holds 64 nodes a chain and 16 sets a chain to begin with:
+# levels that do not fit on both sides of 2048 nodes, inside a launch that takes
+# several levels and between launches
+@pytest.mark.parametrize("widths", [(2, 2, 2, 2, 2, 2, 2, 2, 2, 2, 2), (16, 16, 8), (32, 32, 32)])
+def test_levels_that_do_not_fit_a_new_workspace(widths):
+    g, cols = _fans(widths)
+    say("case", g.name)
+    w = tpg.Workspace()
+    want = np.array(list(itertools.product(*cols)), np.int32)
+    pp, tp, st = tpg.test_paths(tpg.load_cfg(g), ws=w)
+    assert np.array_equal(np.asarray(pp.vertices).reshape(want.shape), want)
+    assert np.array_equal(np.asarray(tp.vertices).reshape(want.shape), want)
+    assert st["n_pp"] == st["n_tp"] == len(want)
+
+
 @pytest.mark.parametrize("widths", [(3, 4), (9, 10, 9), (12, 12, 2)])
 def test_loops_around_fans(widths):
     g, _ = _fans(widths, back=True)
