@@ -141,6 +141,18 @@ struct tpg_workspace {
   // pinned host mirrors
   LevelState* h_ls = nullptr;
   int64_t* h_scalars = nullptr;
+  // pinned room that results pass through on their way to the caller's arrays
+  // (copy_out), and a streamed chunk's arrays
+  uint8_t* stage = nullptr;
+  size_t stage_cap = 0, stage_used = 0, stage_want = 0;
+  struct Staged {
+    void* dst;
+    const uint8_t* src;
+    size_t bytes;
+  };
+  std::vector<Staged> staged;
+  uint8_t* chunk = nullptr;
+  size_t chunk_cap = 0, chunk_seen = 0;
   int64_t* h_totals = nullptr;  // PathTotals::host_words of the largest graph
 
   std::vector<hipEvent_t> ev_pool;
@@ -904,7 +916,18 @@ tpg_status build_tree_twopass(tpg_workspace* ws, const HostUnion& U, hipStream_t
 
 struct PPResult {
   int64_t n_pp = 0, n_vtx = 0, n_cycles = 0;
+  bool ahead = false;  // n_vtx comes with the test paths' sizes
 };
+
+// Rows of at most `entries` may be written before the host knows their number:
+// a look at the device costs 20 us and more, which only room for a small result
+// is worth, and only if it is there under the pool's cap.
+constexpr int64_t kAheadEntries = (int64_t)4 << 20;
+bool room_ahead(const tpg_workspace* ws, const DevBuf& b, int64_t entries) {
+  const size_t bytes = sizeof(int32_t) * (size_t)(entries + 1);
+  return entries <= kAheadEntries &&
+         (b.cap >= bytes || !ws->cap || ws->bytes - b.cap + bytes + 256 <= ws->cap);
+}
 
 // Levels of at most this many nodes go through the sweeps' one-workgroup form,
 // two per thread: 48 small functions one after another took 25.0 ms without
@@ -955,7 +978,7 @@ void path_counts(const tpg_workspace* ws, const HostUnion& U, const int64_t* his
 }
 
 tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream_t st,
-                                TreeResult& R, PPResult& P, OutSet& o) {
+                                TreeResult& R, PPResult& P, OutSet& o, bool ahead) {
   ExtArgs a = make_args(ws);
   const int64_t N = R.n_nodes;
   TPG_TRY(ws_reserve(ws, ws->sub_cnt, sizeof(uint32_t) * N));
@@ -1061,9 +1084,13 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
     int64_t* cs = o.comp_starts.as<int64_t>();
     TPG_HIP(launch_comp_pp_starts(ws->dg, rb, o.pp_off.as<int64_t>(), cs, cs + (U.n_comp + 1), st));
   }
-  TPG_TRY(io_read(ws, st, ws->h_scalars + 6, scal + 6, sizeof(int64_t)));
-  P.n_vtx = ws->h_scalars[6];
-  TPG_TRY(ws_reserve(ws, o.pp_vtx, sizeof(int32_t) * (P.n_vtx + 1)));
+  const int64_t most = P.n_pp * PathTotals::bins(ws->xg);
+  P.ahead = ahead && room_ahead(ws, o.pp_vtx, most);
+  if (!P.ahead) {
+    TPG_TRY(io_read(ws, st, ws->h_scalars + 6, scal + 6, sizeof(int64_t)));
+    P.n_vtx = ws->h_scalars[6];
+  }
+  TPG_TRY(ws_reserve(ws, o.pp_vtx, sizeof(int32_t) * ((P.ahead ? most : P.n_vtx) + 1)));
   TPG_HIP(launch_pp_write(a, ws->ch, U.n, leaf, o.pp_off.as<int64_t>(), P.n_pp,
                           o.pp_vtx.as<int32_t>(), st));
   o.n_pp = P.n_pp;
@@ -1222,7 +1249,7 @@ tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, 
 // Test paths of the ranked union (rank_and_materialize has filled the canons):
 // marks, places by two sweeps, lengths, rows.
 tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t st,
-                             const TreeResult& R, const PPResult& P, TPResult& T, OutSet& o,
+                             const TreeResult& R, PPResult& P, TPResult& T, OutSet& o,
                              bool greedy = false) {
   const int nc = U.n_comp;
   ws->bfs_pending = false;
@@ -1246,9 +1273,16 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
   const int32_t* order = ws->tp_order.as<int32_t>();
   const uint64_t* leaf = ws->leaf_by_rank.as<uint64_t>();
   const uint8_t* state = greedy ? ws->gstate0.as<uint8_t>() : nullptr;
+  int64_t* sc = ws->scalars.as<int64_t>();
+  // a test path is a prime path between two rows of its graph's vertices
+  const int64_t most = np * 3 * PathTotals::bins(ws->xg);
+  const bool ahead = P.ahead && room_ahead(ws, o.tp_vtx, most);
+  const int64_t room = ahead ? np : 0;
   std::vector<uint8_t> key;
   key_add(key, a);
   key_add(key, tt);
+  key_add(key, room);
+  key_add(key, sc);
   key_add(key, cnt);
   key_add(key, src);
   key_add(key, len);
@@ -1280,7 +1314,8 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
                 : launch_tp_up(a, R.off[top], R.count[top], rep, cnt, st);
       L -= n;
     }
-    if (e == hipSuccess) e = launch_tp_arc_starts(a, tt, order, ng, rep, cnt, first, src, len, st);
+    if (e == hipSuccess) 
+      e = launch_tp_arc_starts(a, tt, order, ng, rep, cnt, first, src, len, room, sc + 7, st);
     for (int L = 2; L <= R.Lmax && e == hipSuccess;) {
       const LevelSpan s = narrow_span(R, L, R.Lmax);
       e = s.n > 0 ? launch_tp_down_span(a, tt, s, rep, cnt, src, len, st)
@@ -1289,17 +1324,32 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
     }
     return e;
   }));
-  int64_t* sc = ws->scalars.as<int64_t>();
-  TPG_TRY(io_read(ws, st, ws->h_scalars, first + ng, sizeof(int64_t)));
-  T.n_tp = ws->h_scalars[0];
-  TPG_TRY(ws_reserve(ws, o.tp_off, sizeof(int64_t) * (T.n_tp + 1)));
-  TPG_HIP(scan_i32_to_i64(len, o.tp_off.as<int64_t>(), T.n_tp, 0, sc,
+  // their number, offsets and rows; the sizes of all of it in one look if there
+  // is room ahead (scalars 6 to 8: prime-path entries, test paths, entries)
+  const int64_t* hs = ws->h_scalars;
+  if (!ahead) {
+    TPG_TRY(io_read(ws, st, ws->h_scalars + 6, sc + 6, 2 * sizeof(int64_t)));
+    T.n_tp = hs[7];
+  }
+  const int64_t rows = ahead ? np : T.n_tp;
+  TPG_TRY(ws_reserve(ws, o.tp_off, sizeof(int64_t) * (rows + 1)));
+  TPG_HIP(scan_i32_to_i64(len, o.tp_off.as<int64_t>(), rows, 0, sc + 8,
                           ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  TPG_TRY(io_read(ws, st, ws->h_scalars, sc, sizeof(int64_t)));
-  T.n_vtx = ws->h_scalars[0];
-  TPG_TRY(ws_reserve(ws, o.tp_vtx, sizeof(int32_t) * (T.n_vtx + 1)));
-  TPG_HIP(launch_emit_rows(src, T.n_tp, T.n_vtx, o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), &b,
-                           o.tp_off.as<int64_t>(), o.tp_vtx.as<int32_t>(), st));
+  if (!ahead) {
+    TPG_TRY(io_read(ws, st, ws->h_scalars + 8, sc + 8, sizeof(int64_t)));
+    T.n_vtx = hs[8];
+  }
+  TPG_TRY(ws_reserve(ws, o.tp_vtx, sizeof(int32_t) * ((ahead ? most : T.n_vtx) + 1)));
+  TPG_HIP(launch_emit_rows(src, rows, ahead ? np * PathTotals::bins(ws->xg) : T.n_vtx,
+                           o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), &b,
+                           o.tp_off.as<int64_t>(), o.tp_vtx.as<int32_t>(), st,
+                           ahead ? sc + 7 : nullptr));
+  if (ahead) {
+    TPG_TRY(io_read(ws, st, ws->h_scalars + 6, sc + 6, 3 * sizeof(int64_t)));
+    T.n_tp = hs[7];
+    T.n_vtx = hs[8];
+  }
+  if (P.ahead) o.n_ppv = P.n_vtx = hs[6];
   if (nc > 1) {
     int64_t* cs = o.comp_starts.as<int64_t>();
     TPG_HIP(launch_comp_tp_starts(nc, ws->d_gbase, first, o.tp_off.as<int64_t>(),
@@ -1310,8 +1360,62 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
   return TPG_OK;
 }
 
-tpg_status export_paths(const DevBuf& off, const DevBuf& vtx, int64_t n, int64_t nv, bool device,
-                        hipStream_t st, tpg_paths* out) {
+// Grows a pinned buffer to hold `bytes`; false (and no buffer) if it cannot.
+bool reserve_pinned(uint8_t*& p, size_t& cap, size_t bytes) {
+  if (bytes <= cap) return true;
+  if (p) (void)hipHostFree(p);
+  p = nullptr;
+  cap = 0;
+  // (pinning costs some 0.3 ms a MB: little to spare where it is large)
+  size_t want = 64 << 10;
+  while (want < bytes) want += want / 2;
+  want = std::min(want, std::max<size_t>(bytes + bytes / 16, 1 << 20));
+  if (hipHostMalloc((void**)&p, want, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    p = nullptr;
+    return false;
+  }
+  cap = want;
+  return true;
+}
+
+// Device arrays to pageable memory of the caller's.  Such a copy waits for
+// itself, 20 to 40 us each; up to kStageBytes go through pinned memory instead
+// and into their places at finish_copies, which waits once for all of them (a
+// 20-vertex function's call with four result arrays: 335 us before this and
+// the sizes' single look, 259 after; 16 MB of it gave nothing more for 6 MB).
+constexpr size_t kStageBytes = (size_t)4 << 20;
+tpg_status copy_out(tpg_workspace* ws, void* dst, const void* dev, size_t bytes, hipStream_t st) {
+  const size_t room = (bytes + 63) & ~(size_t)63;
+  // the first array of a call, which has no copy into the buffer under way,
+  // makes room for more like it, and for what did not fit before
+  if (ws->staged.empty() && room <= kStageBytes)
+    (void)reserve_pinned(ws->stage, ws->stage_cap,
+                         std::min(kStageBytes, std::max(32 * room, ws->stage_want)));
+  if (ws->stage_used + room > ws->stage_cap) {
+    ws->stage_want = std::min(kStageBytes, std::max(ws->stage_want, 2 * (ws->stage_used + room)));
+    TPG_HIP(hipMemcpyAsync(dst, dev, bytes, hipMemcpyDeviceToHost, st));
+    return TPG_OK;
+  }
+  uint8_t* at = ws->stage + ws->stage_used;
+  TPG_HIP(hipMemcpyAsync(at, dev, bytes, hipMemcpyDeviceToHost, st));
+  ws->staged.push_back({dst, at, bytes});
+  ws->stage_used += room;
+  return TPG_OK;
+}
+
+tpg_status finish_copies(tpg_workspace* ws, hipStream_t st) {
+  TPG_HIP(hipStreamSynchronize(st));
+  for (const auto& s : ws->staged) memcpy(s.dst, s.src, s.bytes);
+  ws->staged.clear();
+  ws->stage_used = 0;
+  return TPG_OK;
+}
+
+// wait false: the host arrays are filled at the caller's finish_copies.
+tpg_status export_paths(tpg_workspace* ws, const DevBuf& off, const DevBuf& vtx, int64_t n,
+                        int64_t nv, bool device, hipStream_t st, tpg_paths* out,
+                        bool wait = true) {
   memset(out, 0, sizeof *out);
   out->n_paths = n;
   out->n_vertices = nv;
@@ -1329,11 +1433,9 @@ tpg_status export_paths(const DevBuf& off, const DevBuf& vtx, int64_t n, int64_t
     memset(out, 0, sizeof *out);
     return fail(TPG_ERR_OOM_HOST, "result arrays");
   }
-  TPG_HIP(hipMemcpyAsync(out->offsets, off.p, sizeof(int64_t) * (n + 1), hipMemcpyDeviceToHost, st));
-  if (nv)
-    TPG_HIP(hipMemcpyAsync(out->vertices, vtx.p, sizeof(int32_t) * nv, hipMemcpyDeviceToHost, st));
-  TPG_HIP(hipStreamSynchronize(st));
-  return TPG_OK;
+  TPG_TRY(copy_out(ws, out->offsets, off.p, sizeof(int64_t) * (n + 1), st));
+  if (nv) TPG_TRY(copy_out(ws, out->vertices, vtx.p, sizeof(int32_t) * nv, st));
+  return wait ? finish_copies(ws, st) : TPG_OK;
 }
 
 // The canonical prime paths regrouped by last vertex (stable, so each
@@ -1371,12 +1473,19 @@ tpg_status group_by_last(tpg_workspace* ws, int32_t n_keys, hipStream_t st, OutS
 }
 
 // Digest of paths [0, n) of a device set (see tpg_paths.digest).
-tpg_status digest_set(tpg_workspace* ws, const DevBuf& off, const DevBuf& vtx, int64_t n,
-                      hipStream_t st, uint64_t out[2]) {
+// (h_scalars + 12 once the stream has got there.)
+tpg_status start_digest(tpg_workspace* ws, const DevBuf& off, const DevBuf& vtx, int64_t n,
+                        hipStream_t st) {
   TPG_TRY(ws_reserve(ws, ws->digest, 2 * sizeof(uint64_t)));
   TPG_HIP(launch_digest(off.as<int64_t>(), vtx.as<int32_t>(), n, ws->digest.as<uint64_t>(), st));
   TPG_HIP(hipMemcpyAsync(ws->h_scalars + 12, ws->digest.p, 2 * sizeof(uint64_t),
                          hipMemcpyDeviceToHost, st));
+  return TPG_OK;
+}
+
+tpg_status digest_set(tpg_workspace* ws, const DevBuf& off, const DevBuf& vtx, int64_t n,
+                      hipStream_t st, uint64_t out[2]) {
+  TPG_TRY(start_digest(ws, off, vtx, n, st));
   TPG_HIP(hipStreamSynchronize(st));
   out[0] = (uint64_t)ws->h_scalars[12];
   out[1] = (uint64_t)ws->h_scalars[13];
@@ -1385,7 +1494,8 @@ tpg_status digest_set(tpg_workspace* ws, const DevBuf& off, const DevBuf& vtx, i
 
 // Result set into *out as the flags ask: arrays (host or device), digest.
 tpg_status deliver_set(tpg_workspace* ws, const DevBuf& off, const DevBuf& vtx, int64_t n,
-                       int64_t nv, uint32_t flags, hipStream_t st, tpg_paths* out) {
+                       int64_t nv, uint32_t flags, hipStream_t st, tpg_paths* out,
+                       bool wait = true) {
   uint64_t dg[2] = {0, 0};
   if (flags & (TPG_DIGEST | TPG_DIGEST_ONLY)) TPG_TRY(digest_set(ws, off, vtx, n, st, dg));
   if (flags & TPG_DIGEST_ONLY) {
@@ -1393,7 +1503,7 @@ tpg_status deliver_set(tpg_workspace* ws, const DevBuf& off, const DevBuf& vtx, 
     out->n_paths = n;
     out->n_vertices = nv;
   } else {
-    TPG_TRY(export_paths(off, vtx, n, nv, flags & TPG_OUT_DEVICE, st, out));
+    TPG_TRY(export_paths(ws, off, vtx, n, nv, flags & TPG_OUT_DEVICE, st, out, wait));
   }
   out->digest[0] = dg[0];
   out->digest[1] = dg[1];
@@ -1434,12 +1544,15 @@ tpg_status begin_call(const tpg_opts* opts, CallCtx& c) {
   if (c.ws->out.empty()) c.ws->out.resize(1);
   c.ws->seed_lo = 0;
   c.ws->seed_n = -1;
+  // copies that a call which failed did not finish
+  c.ws->staged.clear();
+  c.ws->stage_used = 0;
   return TPG_OK;
 }
 
 tpg_status run_pp(const HostUnion& U, CallCtx& c, Timer& tm, TreeResult& R, PPResult& P,
                   OutSet& o, hipEvent_t* e_ext, int64_t rec0 = 0, int64_t msk0 = 0,
-                  bool with_bfs = false) {
+                  bool with_bfs = false, bool ahead = false) {
   TPG_TRY(upload_union(c.ws, U, c.st));
   c.ws->bfs_pending = false;
   if (with_bfs) TPG_TRY(bfs_start(c.ws, U, c.st));
@@ -1448,7 +1561,7 @@ tpg_status run_pp(const HostUnion& U, CallCtx& c, Timer& tm, TreeResult& R, PPRe
   else
     TPG_TRY(build_tree_onepass(c.ws, U, c.st, tm, R, rec0, msk0));
   if (e_ext) *e_ext = tm.mark();
-  TPG_TRY(rank_and_materialize(c.ws, U, c.st, R, P, o));
+  TPG_TRY(rank_and_materialize(c.ws, U, c.st, R, P, o, ahead));
   return TPG_OK;
 }
 
@@ -1486,6 +1599,28 @@ tpg_status call_chunk(CallCtx& c, const tpg_paths& chunk, int64_t first, int64_t
   return TPG_OK;
 }
 
+// A chunk's host arrays in the workspace's pinned memory, which the copies
+// reach without passing through the runtime's own (false: too large for it, or
+// the first so large, since pinning it costs as much as two copies).  A
+// 198-vertex CFG's 85 MB, nearly all of it one chunk, took 31 ms through fresh
+// pageable arrays and 11 this way, the caller's copy included.
+constexpr size_t kChunkBytes = (size_t)256 << 20;
+bool chunk_arrays(tpg_workspace* ws, int64_t n, int64_t nv, tpg_paths& chunk) {
+  const size_t head = sizeof(int64_t) * (size_t)(n + 1);
+  const size_t bytes = head + sizeof(int32_t) * (size_t)std::max<int64_t>(nv, 1);
+  if (bytes > ws->chunk_cap && bytes > (size_t)1 << 20 && bytes > 2 * ws->chunk_seen) {
+    ws->chunk_seen = bytes;
+    return false;
+  }
+  if (bytes > kChunkBytes || !reserve_pinned(ws->chunk, ws->chunk_cap, bytes)) return false;
+  memset(&chunk, 0, sizeof chunk);
+  chunk.n_paths = n;
+  chunk.n_vertices = nv;
+  chunk.offsets = reinterpret_cast<int64_t*>(ws->chunk);
+  chunk.vertices = reinterpret_cast<int32_t*>(ws->chunk + head);
+  return true;
+}
+
 // TPG_STREAM for prime paths: the first vertices in ranges of
 // chunk_vertices, each range a fresh path tree (so device memory is bounded
 // by the largest range's tree); prime paths grouped by first vertex are
@@ -1514,16 +1649,26 @@ tpg_status prime_paths_stream(const tpg_graph* g, CallCtx& c, tpg_paths* out) {
     TreeResult R;
     PPResult P;
     TPG_TRY(run_pp(U, c, tm, R, P, o, nullptr));
-    uint64_t cd[2];
-    TPG_TRY(digest_set(c.ws, o.pp_off, o.pp_vtx, P.n_pp, c.st, cd));
-    dg[0] += cd[0];
-    dg[1] ^= cd[1];
+    TPG_TRY(start_digest(c.ws, o.pp_off, o.pp_vtx, P.n_pp, c.st));
     tpg_paths chunk;
-    TPG_TRY(export_paths(o.pp_off, o.pp_vtx, P.n_pp, P.n_vtx, c.flags & TPG_OUT_DEVICE, c.st, &chunk));
-    chunk.digest[0] = cd[0];
-    chunk.digest[1] = cd[1];
+    const bool dev = c.flags & TPG_OUT_DEVICE;
+    const bool ours = !dev && chunk_arrays(c.ws, P.n_pp, P.n_vtx, chunk);
+    if (ours) {
+      TPG_HIP(hipMemcpyAsync(chunk.offsets, o.pp_off.p, sizeof(int64_t) * (P.n_pp + 1),
+                             hipMemcpyDeviceToHost, c.st));
+      if (P.n_vtx)
+        TPG_HIP(hipMemcpyAsync(chunk.vertices, o.pp_vtx.p, sizeof(int32_t) * P.n_vtx,
+                               hipMemcpyDeviceToHost, c.st));
+    } else {
+      TPG_TRY(export_paths(c.ws, o.pp_off, o.pp_vtx, P.n_pp, P.n_vtx, dev, c.st, &chunk));
+    }
+    TPG_HIP(hipStreamSynchronize(c.st));
+    chunk.digest[0] = (uint64_t)c.ws->h_scalars[12];
+    chunk.digest[1] = (uint64_t)c.ws->h_scalars[13];
+    dg[0] += chunk.digest[0];
+    dg[1] ^= chunk.digest[1];
     const tpg_status rc = call_chunk(c, chunk, lo, hi);
-    tpg_paths_free(&chunk);
+    if (!ours) tpg_paths_free(&chunk);
     TPG_TRY(rc);
     out->n_paths += P.n_pp;
     out->n_vertices += P.n_vtx;
@@ -1628,14 +1773,15 @@ tpg_status tpg_workspace_create(int32_t device, tpg_workspace** out) {
     tpg_workspace_free(ws);
     return fail(TPG_ERR_DEVICE, "side stream / events");
   }
-  if (hipHostMalloc((void**)&ws->h_ls, sizeof(LevelState), hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc((void**)&ws->h_scalars, sizeof(int64_t) * 16, hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc((void**)&ws->h_totals,
-                    sizeof(int64_t) * (PathTotals::kHist + 2 * (PathTotals::kLenPad + TPG_MAX_VERTICES)),
+  // one pinned block (an allocation costs some 60 us however small it is)
+  constexpr size_t kTotals = PathTotals::kHist + 2 * (PathTotals::kLenPad + TPG_MAX_VERTICES);
+  if (hipHostMalloc((void**)&ws->h_ls, sizeof(LevelState) + sizeof(int64_t) * (16 + kTotals),
                     hipHostMallocDefault) != hipSuccess) {
     tpg_workspace_free(ws);
     return fail(TPG_ERR_OOM_HOST, "pinned host buffers");
   }
+  ws->h_scalars = reinterpret_cast<int64_t*>(ws->h_ls + 1);
+  ws->h_totals = ws->h_scalars + 16;
   ws->out.resize(1);
   *out = ws;
   return TPG_OK;
@@ -1686,8 +1832,8 @@ void tpg_workspace_free(tpg_workspace* ws) {
   drop_seq_graph(ws->rank_down);
   drop_seq_graph(ws->tp_sweeps);
   if (ws->h_ls) (void)hipHostFree(ws->h_ls);
-  if (ws->h_scalars) (void)hipHostFree(ws->h_scalars);
-  if (ws->h_totals) (void)hipHostFree(ws->h_totals);
+  if (ws->stage) (void)hipHostFree(ws->stage);
+  if (ws->chunk) (void)hipHostFree(ws->chunk);
   if (ws->own_stream) (void)hipStreamDestroy(ws->own_stream);
   if (ws->side_stream) (void)hipStreamDestroy(ws->side_stream);
   if (ws->ev_fork) (void)hipEventDestroy(ws->ev_fork);
@@ -1994,13 +2140,13 @@ struct HostSet {
   int64_t size() const { return (int64_t)off.size() - 1; }
 };
 
-tpg_status fetch_set(const DevBuf& off, const DevBuf& vtx, int64_t n, int64_t nv, hipStream_t st,
-                     HostSet& h) {
+// (there after finish_copies)
+tpg_status fetch_set(tpg_workspace* ws, const DevBuf& off, const DevBuf& vtx, int64_t n, int64_t nv,
+                     hipStream_t st, HostSet& h) {
   h.off.assign(n + 1, 0);
   h.vtx.assign(nv, 0);
-  TPG_HIP(hipMemcpyAsync(h.off.data(), off.p, sizeof(int64_t) * (n + 1), hipMemcpyDeviceToHost, st));
-  if (nv) TPG_HIP(hipMemcpyAsync(h.vtx.data(), vtx.p, sizeof(int32_t) * nv, hipMemcpyDeviceToHost, st));
-  TPG_HIP(hipStreamSynchronize(st));
+  TPG_TRY(copy_out(ws, h.off.data(), off.p, sizeof(int64_t) * (n + 1), st));
+  if (nv) TPG_TRY(copy_out(ws, h.vtx.data(), vtx.p, sizeof(int32_t) * nv, st));
   return TPG_OK;
 }
 
@@ -2102,9 +2248,9 @@ tpg_status tpg_scc_paths(const tpg_graph* g, const tpg_opts* opts, tpg_paths* en
   tpg_paths* outs[3] = {entry_exit, exit_paths, entry_paths};
   for (int s = 0; s < 3; ++s)
     if (outs[s])
-      TPG_TRY(export_paths(c.ws->cx_off[s], c.ws->cx_vtx[s], n[s], nv[s],
-                           (c.flags & TPG_OUT_DEVICE) != 0, c.st, outs[s]));
-  return TPG_OK;
+      TPG_TRY(export_paths(c.ws, c.ws->cx_off[s], c.ws->cx_vtx[s], n[s], nv[s],
+                           (c.flags & TPG_OUT_DEVICE) != 0, c.st, outs[s], false));
+  return finish_copies(c.ws, c.st);
 }
 
 tpg_status tpg_scc_internal_pps(const tpg_graph* g, const tpg_opts* opts, tpg_paths* out) {
@@ -2127,7 +2273,7 @@ tpg_status tpg_scc_internal_pps(const tpg_graph* g, const tpg_opts* opts, tpg_pa
     TPG_TRY(ws_reserve(ws, ooff, sizeof(int64_t)));
     TPG_TRY(ws_reserve(ws, ovtx, sizeof(int32_t)));
     TPG_HIP(launch_zero_u64(ooff.as<uint64_t>(), 1, st));
-    return export_paths(ooff, ovtx, 0, 0, (c.flags & TPG_OUT_DEVICE) != 0, st, out);
+    return export_paths(ws, ooff, ovtx, 0, 0, (c.flags & TPG_OUT_DEVICE) != 0, st, out);
   }
   // the extension on every component alone (one union), then Def. 9
   Timer tm{ws, st, false};
@@ -2168,8 +2314,8 @@ tpg_status tpg_scc_internal_pps(const tpg_graph* g, const tpg_opts* opts, tpg_pa
                             ws->cm_voff.as<int64_t>(), ws->cm_len.as<int32_t>(),
                             ws->cx_orig.as<int32_t>(), ooff.as<int64_t>(), ovtx.as<int32_t>(), st));
   TPG_HIP(launch_set_i64(ooff.as<int64_t>() + k, scal + 3, st));
-  TPG_HIP(hipStreamSynchronize(st));
-  return export_paths(ooff, ovtx, k, kv, (c.flags & TPG_OUT_DEVICE) != 0, st, out);
+  TPG_TRY(export_paths(ws, ooff, ovtx, k, kv, (c.flags & TPG_OUT_DEVICE) != 0, st, out, false));
+  return finish_copies(ws, st);
 }
 
 tpg_status tpg_merged_pps(const tpg_graph* g, const tpg_opts* opts, tpg_paths* complete,
@@ -2189,9 +2335,10 @@ tpg_status tpg_merged_pps(const tpg_graph* g, const tpg_opts* opts, tpg_paths* c
   int64_t n[3], nv[3];
   TPG_TRY(extract_device(c, g, comp, fl, n, nv));
   HostSet ee, ex, en;
-  TPG_TRY(fetch_set(ws->cx_off[0], ws->cx_vtx[0], n[0], nv[0], st, ee));
-  TPG_TRY(fetch_set(ws->cx_off[1], ws->cx_vtx[1], n[1], nv[1], st, ex));
-  TPG_TRY(fetch_set(ws->cx_off[2], ws->cx_vtx[2], n[2], nv[2], st, en));
+  TPG_TRY(fetch_set(ws, ws->cx_off[0], ws->cx_vtx[0], n[0], nv[0], st, ee));
+  TPG_TRY(fetch_set(ws, ws->cx_off[1], ws->cx_vtx[1], n[1], nv[1], st, ex));
+  TPG_TRY(fetch_set(ws, ws->cx_off[2], ws->cx_vtx[2], n[2], nv[2], st, en));
+  TPG_TRY(finish_copies(ws, st));
 
   // The macro graph H (graph preparation on the host): a vertex for every
   // vertex of g outside the components with a cycle; the trie of the
@@ -2349,11 +2496,10 @@ tpg_status tpg_merged_pps(const tpg_graph* g, const tpg_opts* opts, tpg_paths* c
                               ws->cm_vtx[s].as<int32_t>(), st));
     TPG_HIP(launch_set_i64(ws->cm_off[s].as<int64_t>() + k, scal + 3, st));
     if (outs[s])
-      TPG_TRY(export_paths(ws->cm_off[s], ws->cm_vtx[s], k, kv, (c.flags & TPG_OUT_DEVICE) != 0, st,
-                           outs[s]));
+      TPG_TRY(export_paths(ws, ws->cm_off[s], ws->cm_vtx[s], k, kv,
+                           (c.flags & TPG_OUT_DEVICE) != 0, st, outs[s], false));
   }
-  TPG_HIP(hipStreamSynchronize(st));
-  return TPG_OK;
+  return finish_copies(ws, st);
 }
 
 tpg_status tpg_prime_paths_vertex_lists(const tpg_graph* g, const tpg_opts* opts,
@@ -2491,7 +2637,7 @@ tpg_status tpg_test_paths(const tpg_graph* g, const tpg_opts* opts, tpg_paths* p
   TPResult T;
   hipEvent_t ext_done = nullptr;
   OutSet& o = c.ws->out[0];
-  tpg_status s = run_pp(U, c, tm, R, P, o, &ext_done, 0, 0, true);
+  tpg_status s = run_pp(U, c, tm, R, P, o, &ext_done, 0, 0, true, !(c.flags & TPG_TP_GREEDY));
   if (s == TPG_OK && timing) TPG_HIP(hipEventRecord(phase[1], c.st));
   if (s == TPG_OK) s = test_paths_device(c.ws, U, c.st, R, P, T, o, c.flags & TPG_TP_GREEDY);
   if (s == TPG_OK && timing) TPG_HIP(hipEventRecord(phase[2], c.st));
@@ -2502,11 +2648,11 @@ tpg_status tpg_test_paths(const tpg_graph* g, const tpg_opts* opts, tpg_paths* p
   if (s == TPG_OK && grouped) s = group_by_last(c.ws, U.n, c.st, o, P.n_pp, P.n_vtx);
   if (s == TPG_OK && pp_out)
     s = deliver_set(c.ws, grouped ? o.ppg_off : o.pp_off, grouped ? o.ppg_vtx : o.pp_vtx, P.n_pp,
-                    P.n_vtx, fl, c.st, pp_out);
+                    P.n_vtx, fl, c.st, pp_out, false);
   if (s == TPG_OK) s = deliver_set(c.ws, o.tp_off, o.tp_vtx, T.n_tp, T.n_vtx, fl, c.st, tp_out);
   if (s == TPG_OK && (c.flags & TPG_STREAM)) s = test_paths_stream_out(c, o, T.n_tp);
+  if (s == TPG_OK) s = finish_copies(c.ws, c.st);
   if (s == TPG_OK) {
-    TPG_HIP(hipStreamSynchronize(c.st));
     if (c.stats) {
       memset(c.stats, 0, sizeof *c.stats);
       add_stats(c.stats, U, R, P, &T);
@@ -2639,7 +2785,7 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
     TreeResult R;
     PPResult P;
     TPResult T;
-    tpg_status s_pp = run_pp(U, c, tm, R, P, o, nullptr, rec0, msk0, true);
+    tpg_status s_pp = run_pp(U, c, tm, R, P, o, nullptr, rec0, msk0, true, true);
     if (s_pp != TPG_OK && (rec0 || msk0) &&
         (s_pp == TPG_ERR_CAPACITY || s_pp == TPG_ERR_OOM_DEVICE || s_pp == TPG_ERR_UNSUPPORTED)) {
       // the predicted capacities did not fit: size this union exactly, by
@@ -2650,7 +2796,7 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
       release_tree(ws);
       R = TreeResult{};
       P = PPResult{};
-      s_pp = run_pp(U, c, tm, R, P, o, nullptr, 0, 0, true);
+      s_pp = run_pp(U, c, tm, R, P, o, nullptr, 0, 0, true, true);
     }
     TPG_TRY(s_pp);
     TPG_TRY(test_paths_device(ws, U, c.st, R, P, T, o));
@@ -2926,9 +3072,11 @@ tpg_status tpg_batch_test_paths(const tpg_graph* const* graphs, int32_t n_graphs
   const bool dev = c.flags & TPG_OUT_DEVICE;
   if (tm.on) TPG_HIP(hipEventRecord(t1, c.st));
 
-  tpg_status s = export_paths(ws->b_pp_off, ws->b_pp_vtx, pp_first[n_graphs], ppv, dev, c.st, &out->pp);
+  tpg_status s = export_paths(ws, ws->b_pp_off, ws->b_pp_vtx, pp_first[n_graphs], ppv, dev, c.st,
+                              &out->pp, false);
   if (s == TPG_OK)
-    s = export_paths(ws->b_tp_off, ws->b_tp_vtx, tp_first[n_graphs], tpv, dev, c.st, &out->tp);
+    s = export_paths(ws, ws->b_tp_off, ws->b_tp_vtx, tp_first[n_graphs], tpv, dev, c.st, &out->tp,
+                     false);
   if (s == TPG_OK) {
     out->n_graphs = n_graphs;
     out->pp_first = (int64_t*)malloc(sizeof(int64_t) * (n_graphs + 1));
@@ -2940,8 +3088,8 @@ tpg_status tpg_batch_test_paths(const tpg_graph* const* graphs, int32_t n_graphs
       memcpy(out->tp_first, tp_first.data(), sizeof(int64_t) * (n_graphs + 1));
     }
   }
+  if (s == TPG_OK) s = finish_copies(ws, c.st);
   if (s == TPG_OK) {
-    TPG_HIP(hipStreamSynchronize(c.st));
     if (c.stats) {
       c.stats->device_bytes = (int64_t)ws->bytes;
       if (tm.on) c.stats->ms_total = Timer::ms(t0, t1);

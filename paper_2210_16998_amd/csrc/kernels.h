@@ -293,10 +293,11 @@ hipError_t launch_tp_mark(const ExtArgs& a, const TpTree& t, const uint64_t* lea
                           const uint8_t* state, int32_t* rep, hipStream_t st);
 // cnt: marked nodes per subtree (launch_tp_up*), rewritten into places (see
 // k_tp_arc_starts) for the n arcs of order; src[place] = prime path, len[place]
-// = entries of the test path
+// = entries of the test path (0 for the places from their number up to `room`);
+// their number also into *n_out
 hipError_t launch_tp_arc_starts(const ExtArgs& a, const TpTree& tt, const int32_t* order, int32_t n,
                                 const int32_t* rep, uint32_t* cnt, int64_t* first, int32_t* src,
-                                int32_t* len, hipStream_t st);
+                                int32_t* len, int64_t room, int64_t* n_out, hipStream_t st);
 // places from the nodes of a span's levels down
 hipError_t launch_tp_down_span(const ExtArgs& a, const TpTree& tt, const LevelSpan& s,
                                const int32_t* rep, uint32_t* cnt, int32_t* src, int32_t* len,
@@ -306,12 +307,13 @@ hipError_t launch_tp_down_run(const ExtArgs& a, const TpTree& tt, int64_t base, 
                               const int32_t* rep, uint32_t* cnt, int32_t* src, int32_t* len,
                               hipStream_t st);
 // rows r < n, each prime path src[r] (null: r), with b between its prefix and
-// suffix rows: their lengths, and the rows at out_off (n_entries in all)
+// suffix rows: their lengths, and the rows at out_off (n_entries in all; n_dev:
+// where the number of rows is, at most n, if the host does not know it yet)
 hipError_t launch_row_len(const int32_t* src, int64_t n, const int64_t* pp_off,
                           const int32_t* pp_vtx, const EndRows* b, int32_t* len, hipStream_t st);
 hipError_t launch_emit_rows(const int32_t* src, int64_t n, int64_t n_entries, const int64_t* pp_off,
                             const int32_t* pp_vtx, const EndRows* b, const int64_t* out_off,
-                            int32_t* out_vtx, hipStream_t st);
+                            int32_t* out_vtx, hipStream_t st, const int64_t* n_dev = nullptr);
 // start[c] / vstart[c] (c = 0 .. n_comp) of the test paths
 hipError_t launch_comp_tp_starts(int n_comp, const int32_t* gbase, const int64_t* first,
                                  const int64_t* off, int64_t* start, int64_t* vstart,

@@ -402,7 +402,8 @@ constexpr int kArcItems = 8;
 __global__ __launch_bounds__(1024) void k_tp_arc_starts(TreeBufs t, const int32_t* order, int32_t n,
                                                         const int32_t* rep, uint32_t* cnt,
                                                         int64_t* first, int32_t* src,
-                                                        int32_t* len, const int32_t* cdist) {
+                                                        int32_t* len, const int32_t* cdist,
+                                                        int64_t room, int64_t* n_out) {
   __shared__ int64_t s_w[16];
   int64_t carry = 0;
   for (int32_t b = 0; b < n; b += 1024 * kArcItems) {
@@ -439,13 +440,18 @@ __global__ __launch_bounds__(1024) void k_tp_arc_starts(TreeBufs t, const int32_
     }
     carry += tot;
   }
-  if (threadIdx.x == 0) first[n] = carry;
+  for (int64_t r = carry + threadIdx.x; r < room; r += 1024) len[r] = 0;
+  if (threadIdx.x == 0) {
+    first[n] = carry;
+    *n_out = carry;
+  }
 }
 
 hipError_t launch_tp_arc_starts(const ExtArgs& a, const TpTree& tt, const int32_t* order, int32_t n,
                                 const int32_t* rep, uint32_t* cnt, int64_t* first, int32_t* src,
-                                int32_t* len, hipStream_t st) {
-  k_tp_arc_starts<<<1, 1024, 0, st>>>(a.t, order, n, rep, cnt, first, src, len, tt.cdist);
+                                int32_t* len, int64_t room, int64_t* n_out, hipStream_t st) {
+  k_tp_arc_starts<<<1, 1024, 0, st>>>(a.t, order, n, rep, cnt, first, src, len, tt.cdist, room,
+                                      n_out);
   return hipGetLastError();
 }
 
@@ -562,11 +568,13 @@ __global__ __launch_bounds__(kBlock) void k_row_len(const int32_t* src, int64_t 
 // lane, seldom aligned, 19.6; a row's prefix and suffix kept in registers for
 // the next row 18.9.
 template <int U, int R, bool ENDS>
-__global__ __launch_bounds__(kBlock) void k_emit_rows(const int32_t* src, int64_t n, int rows,
+__global__ __launch_bounds__(kBlock) void k_emit_rows(const int32_t* src, int64_t n,
+                                                      const int64_t* n_dev, int rows,
                                                       const int64_t* pp_off, const int32_t* pp_vtx,
                                                       EndRows b, const int64_t* out_off,
                                                       int32_t* out_vtx) {
   const int lane = lane_id();
+  if (n_dev) n = *n_dev < n ? *n_dev : n;
   const int64_t r0 = ((int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * rows;
   if (r0 >= n) return;
   const int nr = (int)(n - r0 < rows ? n - r0 : rows);
@@ -647,7 +655,7 @@ hipError_t launch_row_len(const int32_t* src, int64_t n, const int64_t* pp_off,
 
 hipError_t launch_emit_rows(const int32_t* src, int64_t n, int64_t n_entries, const int64_t* pp_off,
                             const int32_t* pp_vtx, const EndRows* b, const int64_t* out_off,
-                            int32_t* out_vtx, hipStream_t st) {
+                            int32_t* out_vtx, hipStream_t st, const int64_t* n_dev) {
   if (n == 0) return hipSuccess;
   // more rows a wave spread the first loads' cost, fewer keep the chip full:
   // 573 k rows 1.90 ms a call with 16 and 1.95 with 64, 1.9e7 rows 19.2 and 18.8
@@ -657,7 +665,8 @@ hipError_t launch_emit_rows(const int32_t* src, int64_t n, int64_t n_entries, co
   // the steps that hold a row of average length, to 5
   const int64_t steps = n_entries / (64 * n) + 1;
 #define TPG_EMIT(U, R, E, B)                                                                    \
-  k_emit_rows<U, R, E><<<grid, kBlock, 0, st>>>(src, n, rows, pp_off, pp_vtx, B, out_off, out_vtx)
+  k_emit_rows<U, R, E><<<grid, kBlock, 0, st>>>(src, n, n_dev, rows, pp_off, pp_vtx, B, out_off,  \
+                                               out_vtx)
   if (b) {
     if (steps <= 1) TPG_EMIT(1, 4, true, *b);
     else if (steps <= 2) TPG_EMIT(2, 4, true, *b);

@@ -298,21 +298,40 @@ class SetDigest:
         return self.n_paths
 
 
+class _OwnedPaths:
+    """Releases a host result's library-owned arrays with the last array that
+    views them."""
+
+    def __init__(self, p: _Paths) -> None:
+        self._p = p
+
+    def __del__(self):
+        try:
+            lib().tpg_paths_free(ctypes.byref(self._p))
+        except Exception:
+            pass
+
+
+class _HostArray:
+    def __init__(self, ptr: int, n: int, typestr: str, owner) -> None:
+        self.owner = owner
+        self.__array_interface__ = {"shape": (n,), "typestr": typestr,
+                                    "data": (int(ptr), False), "version": 3}
+
+
 class HostPaths:
-    """Host result: offsets int64 [n+1], vertices int32 (copied out of the
-    library-owned arrays, which are then released unless `owned` is False,
-    as for a streamed chunk the library releases itself)."""
+    """Host result: offsets int64 [n+1], vertices int32, the library-owned
+    arrays themselves, released with the arrays (copies of them if `owned` is
+    False, as for a streamed chunk the library releases itself)."""
 
     def __init__(self, p: _Paths, owned: bool = True) -> None:
         n, nv = p.n_paths, p.n_vertices
-        self.offsets = np.ctypeslib.as_array(
-            ctypes.cast(p.offsets, ctypes.POINTER(ctypes.c_int64)), shape=(n + 1,)).copy()
-        self.vertices = (np.ctypeslib.as_array(
-            ctypes.cast(p.vertices, ctypes.POINTER(ctypes.c_int32)), shape=(nv,)).copy()
-            if nv else np.zeros(0, np.int32))
+        get = np.asarray if owned else np.array
+        owner = _OwnedPaths(p) if owned else None
+        self.offsets = get(_HostArray(p.offsets, n + 1, "<i8", owner))
+        self.vertices = (get(_HostArray(p.vertices, nv, "<i4", owner))
+                         if nv else np.zeros(0, np.int32))
         self.digest = (int(p.digest[0]), int(p.digest[1]))
-        if owned:
-            lib().tpg_paths_free(ctypes.byref(p))
 
     def __len__(self) -> int:
         return len(self.offsets) - 1
