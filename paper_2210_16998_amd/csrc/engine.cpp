@@ -130,7 +130,6 @@ struct tpg_workspace {
   DevBuf tp_links, tp_order, tp_first;  // TpTree's chain links, the arcs' order and places
   DevBuf canon, leaf_canon;           // see TpTree
   DevBuf row_src, row_len;            // rows of a reordered set: source path, length
-  DevBuf spl_off, spl_vtx;            // the covering's spliced test paths
   DevBuf chunk_off;                   // rebased offsets of a streamed chunk
   // per-level, per-component counts (batched labels)
   DevBuf lvl_comp;
@@ -180,7 +179,7 @@ struct tpg_workspace {
   DevBuf grp_key, grp_hist, grp_base;  // last-vertex grouping: keys, per-tile histograms, their scan
   // longest-first covering: prime-path hash table, covering pairs, order,
   // coverers per path, round states
-  DevBuf cov_keys, cov_vals, cov_misc, cov_cnt, cov_at, pair_p, pair_q, cov_pos, gstate0, gstate1;
+  DevBuf cov_keys, cov_vals, cov_misc, pair_p, pair_q, gstate0, gstate1;
   // components and prime-path types: Tarjan scratch, labels, flags, counters
   // (n_comp int32 at 0, type counts u64 at 64), a host path set's copy, types
   DevBuf scc_work, scc_comp, scc_flags, scc_misc, ty_off, ty_vtx, ty_types;
@@ -1147,85 +1146,55 @@ tpg_status bfs_start(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
 // of all np prime paths: gstate0[i] = 1 for the chosen prime paths.
 tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, int64_t np,
                          const OutSet& o, const EndRows& b) {
-  const int n = U.n;
-  int64_t* sc = ws->scalars.as<int64_t>();
-  int64_t* hs = ws->h_scalars;
+  int64_t* hs = ws->h_scalars + 10;
   TPG_TRY(ws_reserve(ws, ws->cov_misc, sizeof(uint64_t) * 4));
-  uint64_t* misc = ws->cov_misc.as<uint64_t>();  // [0] shared hashes, [1] missing windows, [2] undecided
-  // the spliced test paths, in the prime paths' order
-  TPG_TRY(ws_reserve(ws, ws->row_len, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->spl_off, sizeof(int64_t) * (np + 1)));
-  TPG_HIP(launch_row_len(nullptr, np, o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), &b,
-                         ws->row_len.as<int32_t>(), st));
-  TPG_HIP(scan_i32_to_i64(ws->row_len.as<int32_t>(), ws->spl_off.as<int64_t>(), np, 0, sc + 12,
-                          ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  TPG_HIP(hipMemcpyAsync(hs + 10, sc + 12, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  TPG_HIP(hipStreamSynchronize(st));
-  TPG_TRY(ws_reserve(ws, ws->spl_vtx, sizeof(int32_t) * (hs[10] + 1)));
-  TPG_HIP(launch_emit_rows(nullptr, np, hs[10], o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), &b,
-                           ws->spl_off.as<int64_t>(), ws->spl_vtx.as<int32_t>(), st));
+  // [0] shared hashes, [1] missing windows, [2] pairs, [3] undecided paths
+  uint64_t* misc = ws->cov_misc.as<uint64_t>();
   // hash table of the prime paths, load factor <= 1/2
   int64_t slots = 1024;
   while (slots < 2 * np) slots <<= 1;
   TPG_TRY(ws_reserve(ws, ws->cov_keys, sizeof(uint64_t) * slots));
   TPG_TRY(ws_reserve(ws, ws->cov_vals, sizeof(int32_t) * slots));
-  uint64_t mul = 0;
-  for (int attempt = 0;; ++attempt) {
-    if (attempt == 4) return fail(TPG_ERR_UNSUPPORTED, "prime-path hashes collide for 4 multipliers");
-    mul = cover_hash_mul(attempt);
-    TPG_HIP(launch_zero_u64(ws->cov_keys.as<uint64_t>(), slots, st));
-    TPG_HIP(launch_zero_u64(misc, 4, st));
-    TPG_HIP(launch_pp_hash_insert(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np, mul,
-                                  ws->cov_keys.as<uint64_t>(), ws->cov_vals.as<int32_t>(), slots - 1,
-                                  misc, st));
-    TPG_HIP(hipMemcpyAsync(hs + 10, misc, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
-    TPG_HIP(hipStreamSynchronize(st));
-    if (hs[10] == 0) break;
+  // room for the pairs: what is there, or twice the paths; more once their
+  // number is known (642294 for the 376808 paths of a 182-vertex CFG)
+  const size_t guess = sizeof(int32_t) * (size_t)(2 * np + 1);
+  if (!ws->cap || ws->bytes + 2 * guess + 1024 <= ws->cap) {
+    TPG_TRY(ws_reserve(ws, ws->pair_p, guess));
+    TPG_TRY(ws_reserve(ws, ws->pair_q, guess));
   }
-  // covering pairs: count, offsets, write
-  const int64_t* tp_off = ws->spl_off.as<int64_t>();
-  const int32_t* tp_vtx = ws->spl_vtx.as<int32_t>();
-  TPG_TRY(ws_reserve(ws, ws->cov_cnt, sizeof(int64_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->cov_at, sizeof(int64_t) * (np + 1)));
-  int64_t* cnt = ws->cov_cnt.as<int64_t>();
-  int64_t* at = ws->cov_at.as<int64_t>();
-  TPG_HIP(launch_cover(pow2_words(U.max_comp), ws->dg, tp_off, tp_vtx, np, mul, ws->cov_keys.as<uint64_t>(),
-                       ws->cov_vals.as<int32_t>(), slots - 1, cnt, at, nullptr, nullptr, 0, misc + 1,
-                       st));
-  TPG_HIP(scan_i64(cnt, at, np, 0, sc + 12, ws->scan_status.as<uint64_t>(),
-                   ws->scan_ctr.as<uint32_t>(), st));
-  TPG_HIP(hipMemcpyAsync(hs + 10, sc + 12, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  TPG_HIP(hipStreamSynchronize(st));
-  const int64_t npairs = hs[10];
-  TPG_TRY(ws_reserve(ws, ws->pair_p, sizeof(int32_t) * (npairs + 1)));
-  TPG_TRY(ws_reserve(ws, ws->pair_q, sizeof(int32_t) * (npairs + 1)));
-  TPG_HIP(launch_cover(pow2_words(U.max_comp), ws->dg, tp_off, tp_vtx, np, mul, ws->cov_keys.as<uint64_t>(),
-                       ws->cov_vals.as<int32_t>(), slots - 1, cnt, at, ws->pair_p.as<int32_t>(),
-                       ws->pair_q.as<int32_t>(), 1, misc + 1, st));
-  TPG_HIP(hipMemcpyAsync(hs + 11, misc + 1, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
-  TPG_HIP(hipStreamSynchronize(st));
-  if (hs[11] != 0)
-    return fail(TPG_ERR_DEVICE, "%lld accepted windows are not prime paths", (long long)hs[11]);
-  // order: decreasing length, canonical order among equal lengths
-  const int64_t nt = group_tiles(np);
-  const int64_t nkeys = (int64_t)n + 2;
-  const int64_t nh = nkeys * std::max<int64_t>(nt, 1);
-  TPG_TRY(ws_reserve(ws, ws->grp_key, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->grp_hist, sizeof(int64_t) * (nh + 1)));
-  TPG_TRY(ws_reserve(ws, ws->grp_base, sizeof(int64_t) * (nh + 1)));
-  TPG_TRY(ws_reserve(ws, ws->row_src, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->cov_pos, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(reserve_scan(ws, std::max(np, nh)));
-  int32_t* key = ws->grp_key.as<int32_t>();
-  int32_t* perm = ws->row_src.as<int32_t>();
-  TPG_HIP(launch_len_key(o.pp_off.as<int64_t>(), np, (int64_t)n + 1, key, st));
-  TPG_HIP(launch_zero_u64(ws->grp_hist.as<uint64_t>(), nh, st));
-  TPG_HIP(launch_key_hist(key, np, nt, ws->grp_hist.as<uint64_t>(), st));
-  TPG_HIP(scan_i64(ws->grp_hist.as<int64_t>(), ws->grp_base.as<int64_t>(), nh, 0, sc + 13,
-                   ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  TPG_HIP(launch_last_place(key, np, nt, ws->grp_base.as<int64_t>(), perm, st));
-  TPG_HIP(launch_invert(perm, np, ws->cov_pos.as<int32_t>(), st));
-  // rounds until every path is decided
+  int64_t npairs = 0;
+  for (int attempt = 0, grown = 0;;) {
+    if (attempt == 4) return fail(TPG_ERR_UNSUPPORTED, "prime-path hashes collide for 4 multipliers");
+    const uint64_t mul = cover_hash_mul(attempt);
+    if (!grown) {
+      TPG_HIP(launch_zero_u64(ws->cov_keys.as<uint64_t>(), slots, st));
+      TPG_HIP(launch_zero_u64(misc, 4, st));
+      TPG_HIP(launch_pp_hash_insert(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np, mul,
+                                    ws->cov_keys.as<uint64_t>(), ws->cov_vals.as<int32_t>(),
+                                    slots - 1, misc, st));
+    }
+    const int64_t cap = (int64_t)(std::min(ws->pair_p.cap, ws->pair_q.cap) / sizeof(int32_t));
+    TPG_HIP(launch_cover(ws->dg, U.n, o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np, b, mul,
+                         ws->cov_keys.as<uint64_t>(), ws->cov_vals.as<int32_t>(), slots - 1,
+                         ws->pair_p.as<int32_t>(), ws->pair_q.as<int32_t>(), cap, misc + 2,
+                         misc + 1, ws->num_cus, st));
+    TPG_HIP(hipMemcpyAsync(hs, misc, 3 * sizeof(uint64_t), hipMemcpyDeviceToHost, st));
+    TPG_HIP(hipStreamSynchronize(st));
+    if (hs[0] != 0) {
+      ++attempt;
+      continue;
+    }
+    if (hs[1] != 0)
+      return fail(TPG_ERR_DEVICE, "%lld accepted windows are not prime paths", (long long)hs[1]);
+    npairs = hs[2];
+    if (npairs <= cap) break;
+    if (grown++) return fail(TPG_ERR_DEVICE, "covering pairs changed their number");
+    TPG_TRY(ws_reserve(ws, ws->pair_p, sizeof(int32_t) * npairs));
+    TPG_TRY(ws_reserve(ws, ws->pair_q, sizeof(int32_t) * npairs));
+    TPG_HIP(launch_zero_u64(misc, 4, st));
+  }
+  // rounds until every path is decided, four to a look (a round after the last
+  // changes nothing)
   TPG_TRY(ws_reserve(ws, ws->gstate0, (size_t)np + 8));
   TPG_TRY(ws_reserve(ws, ws->gstate1, (size_t)2 * np + 16));
   uint8_t* state = ws->gstate0.as<uint8_t>();
@@ -1233,15 +1202,18 @@ tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, 
   uint8_t* block = drop + np + 8;
   TPG_HIP(launch_zero_u32(reinterpret_cast<uint32_t*>(state), (np + 4) / 4, st));
   TPG_HIP(launch_zero_u32(reinterpret_cast<uint32_t*>(drop), (2 * np + 16) / 4, st));
-  for (int64_t round = 0;; ++round) {
-    if (round > np + 1) return fail(TPG_ERR_DEVICE, "covering rounds did not settle");
-    TPG_HIP(launch_zero_u64(misc + 2, 1, st));
-    TPG_HIP(launch_round_pairs(ws->pair_p.as<int32_t>(), ws->pair_q.as<int32_t>(), npairs,
-                               ws->cov_pos.as<int32_t>(), state, drop, block, st));
-    TPG_HIP(launch_round_decide(np, state, drop, block, misc + 2, st));
-    TPG_HIP(hipMemcpyAsync(hs + 10, misc + 2, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
+  constexpr int kRounds = 4;
+  for (int64_t round = 0;; round += kRounds) {
+    if (round > np + kRounds) return fail(TPG_ERR_DEVICE, "covering rounds did not settle");
+    TPG_HIP(launch_zero_u64(misc + 3, 1, st));
+    for (int r = 0; r < kRounds; ++r) {
+      TPG_HIP(launch_round_pairs(ws->pair_p.as<int32_t>(), ws->pair_q.as<int32_t>(), npairs, state,
+                                 drop, block, st));
+      TPG_HIP(launch_round_decide(np, state, drop, block, r + 1 < kRounds ? nullptr : misc + 3, st));
+    }
+    TPG_HIP(hipMemcpyAsync(hs, misc + 3, sizeof(uint64_t), hipMemcpyDeviceToHost, st));
     TPG_HIP(hipStreamSynchronize(st));
-    if (hs[10] == 0) break;
+    if (hs[0] == 0) break;
   }
   return TPG_OK;
 }
@@ -1800,11 +1772,10 @@ void tpg_workspace_free(tpg_workspace* ws) {
                     &ws->leaf_by_rank, &ws->totals, &ws->scan_status,
                     &ws->scan_ctr, &ws->scalars, &ws->bfs_i32,
                     &ws->pfx, &ws->sfx, &ws->rb0, &ws->tp_links, &ws->tp_order, &ws->tp_first,
-                    &ws->canon, &ws->leaf_canon, &ws->row_src, &ws->row_len, &ws->spl_off,
-                    &ws->spl_vtx, &ws->chunk_off, &ws->lvl_comp, &ws->b_pp_off,
+                    &ws->canon, &ws->leaf_canon, &ws->row_src, &ws->row_len, &ws->chunk_off, &ws->lvl_comp, &ws->b_pp_off,
                     &ws->digest, &ws->grp_key, &ws->grp_hist, &ws->grp_base,
-                    &ws->cov_keys, &ws->cov_vals, &ws->cov_misc, &ws->cov_cnt, &ws->cov_at,
-                    &ws->pair_p, &ws->pair_q, &ws->cov_pos, &ws->gstate0, &ws->gstate1,
+                    &ws->cov_keys, &ws->cov_vals, &ws->cov_misc, &ws->pair_p,
+                    &ws->pair_q, &ws->gstate0, &ws->gstate1,
                     &ws->scc_work, &ws->scc_comp, &ws->scc_flags, &ws->scc_misc, &ws->ty_off,
                     &ws->ty_vtx, &ws->ty_types, &ws->cg_cnt, &ws->cg_off, &ws->cg_src,
                     &ws->cg_dst, &ws->cx_qb, &ws->cx_cnt0, &ws->cx_cnt1, &ws->cx_node,

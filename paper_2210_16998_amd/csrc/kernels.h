@@ -230,6 +230,7 @@ hipError_t launch_last_hist(const int64_t* off, const int32_t* vtx, int64_t n, i
 // tile's earlier paths with the same key (base: exclusive scan of hist)
 hipError_t launch_last_place(const int32_t* key, int64_t n, int64_t ntiles, const int64_t* base,
                              int32_t* perm, hipStream_t st);
+struct EndRows;
 // --- test paths by longest-first covering (kernels_cover.hip) ----------------
 // Hash table of the prime paths (keys / vals of mask + 1 slots, keys zeroed);
 // dups counts hashes shared by two prime paths (then retry with another mul).
@@ -237,25 +238,22 @@ uint64_t cover_hash_mul(int attempt);
 hipError_t launch_pp_hash_insert(const int64_t* off, const int32_t* vtx, int64_t n, uint64_t mul,
                                  uint64_t* keys, int32_t* vals, int64_t mask, uint64_t* dups,
                                  hipStream_t st);
-// Prime paths contained in each spliced test path p: pass 0 writes cnt[p],
-// pass 1 the pairs (p, q) at at[p] (exclusive scan of cnt); missing counts
-// accepted windows absent from the table (never, unless the input is bad).
-hipError_t launch_cover(int W, const DGraph& g, const int64_t* tp_off, const int32_t* tp_vtx,
-                        int64_t n, uint64_t mul, const uint64_t* keys, const int32_t* vals,
-                        int64_t mask, int64_t* cnt, const int64_t* at, int32_t* pair_p,
-                        int32_t* pair_q, int pass, uint64_t* missing, hipStream_t st);
-// key[i] = max_len - length of path i (decreasing length first)
-hipError_t launch_len_key(const int64_t* off, int64_t n, int64_t max_len, int32_t* key,
-                          hipStream_t st);
-hipError_t launch_key_hist(const int32_t* key, int64_t n, int64_t ntiles, uint64_t* hist,
-                           hipStream_t st);
-hipError_t launch_invert(const int32_t* perm, int64_t n, int32_t* pos, hipStream_t st);
+// Pairs (p, q) of prime paths (at most cap of them written, all counted): q is
+// contained in the test path that b's rows make of p and comes after p in the
+// order of decreasing length, then of index; missing counts accepted windows
+// absent from the table (never, unless the input is bad).  One graph of n
+// vertices, np prime paths.
+hipError_t launch_cover(const DGraph& g, int n, const int64_t* pp_off, const int32_t* pp_vtx,
+                        int64_t np, const EndRows& b, uint64_t mul, const uint64_t* keys,
+                        const int32_t* vals, int64_t mask, int32_t* pair_p, int32_t* pair_q,
+                        int64_t cap, uint64_t* count, uint64_t* missing, int num_cus,
+                        hipStream_t st);
 // A round of the covering decision: pass over the pairs (drop / block
 // flags, state read only), then decide every undecided path (state 0 ->
-// 1 chosen, 2 dropped) and count the ones left (undecided must be zeroed).
+// 1 chosen, 2 dropped) and add the ones left to *undecided (may be null).
 hipError_t launch_round_pairs(const int32_t* pair_p, const int32_t* pair_q, int64_t np,
-                              const int32_t* pos, const uint8_t* state, uint8_t* drop,
-                              uint8_t* block, hipStream_t st);
+                              const uint8_t* state, uint8_t* drop, uint8_t* block,
+                              hipStream_t st);
 hipError_t launch_round_decide(int64_t n, uint8_t* state, uint8_t* drop, uint8_t* block,
                                uint64_t* undecided, hipStream_t st);
 // Set digest of paths [0, n) (offsets off, entries vtx): out[0] = sum and

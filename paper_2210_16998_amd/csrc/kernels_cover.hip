@@ -8,15 +8,20 @@
 //  * every spliced test path t finds the prime paths it contains.  A prime
 //    path is a simple path that cannot be extended either way, or a simple
 //    cycle, so among the windows of t starting at position i only the
-//    longest simple one, t[i..j), can be a prime path (a shorter simple
-//    window is extended by t's next entry), or the cycle t[i..j] when
-//    t[j] = t[i].  A two-pointer sweep with the window's vertex set in
-//    registers visits these candidates in O(|t|), the local prime rule
-//    (no successor of the last vertex outside the window or equal to the
-//    first; every predecessor of the first vertex inside) accepts them, and
-//    a hash table of the prime paths gives the accepted window's index.  The
+//    longest simple one, t[i..j(i)), can be a prime path (a shorter simple
+//    window is extended by t's next entry), or the cycle t[i..j(i)] when
+//    t[j(i)] = t[i].  If the longest window of i - 1 ends where that of i
+//    does, it extends it backward; so an acyclic candidate starts at 0 or
+//    right after the start of a cycle.  The local prime rule (no successor of
+//    the last vertex outside the window or equal to the first; every
+//    predecessor of the first vertex inside) accepts the candidates, and a
+//    hash table of the prime paths gives the accepted window's index.  The
 //    table is exact for these lookups: an accepted window is a prime path,
 //    and the table is built only when no two prime paths share a hash.
+//  * t is a prefix, the prime path and a suffix, each of them simple (or the
+//    path a cycle), so a vertex has at most one place in each, and the next
+//    place of t[k] after k is a table entry; j(i) is the least of them from i
+//    on, a scan.  One wave takes a path, its lanes the positions.
 //  * The sequential rule "chosen iff no earlier chooser covers it" is
 //    resolved in rounds: a path with a chosen earlier coverer is dropped, a
 //    path whose earlier coverers are all dropped is chosen.  The first
@@ -34,20 +39,59 @@ namespace {
 
 constexpr uint64_t kHashMul = 0x9E3779B97F4A7C15ull;  // odd multiplier of the polynomial hash
 
-// Polynomial hash of a vertex sequence: h = h * mul + (v + 1), never 0.
-__device__ __forceinline__ uint64_t seq_hash_step(uint64_t h, int32_t v, uint64_t mul) {
-  return h * mul + (uint64_t)(v + 1);
-}
+// Polynomial hash of a vertex sequence v_0 .. v_(k-1): the sum of
+// (v_i + 1) mul^(k - 1 - i), never 0.
 __device__ __forceinline__ uint64_t seq_hash_fix(uint64_t h) { return h ? h : 1ull; }
 
+// mul^(2^b) and mul^-(2^b): exponents below 2^14 (rows of 3 * 4096 + 1)
+constexpr int kPowers = 14;
+struct HashPowers {
+  uint64_t pow[kPowers], inv[kPowers];
+};
+
+HashPowers hash_powers(uint64_t mul) {
+  HashPowers w;
+  uint64_t inv = mul;  // Newton's iteration for the inverse of an odd number mod 2^64
+  for (int r = 0; r < 6; ++r) inv *= 2 - mul * inv;
+  for (int b = 0; b < kPowers; ++b, mul *= mul, inv *= inv) {
+    w.pow[b] = mul;
+    w.inv[b] = inv;
+  }
+  return w;
+}
+
+__device__ __forceinline__ uint64_t shfl64(uint64_t x, int from) {
+  return (uint64_t)(uint32_t)__shfl((int)(uint32_t)x, from, 64) |
+         (uint64_t)(uint32_t)__shfl((int)(x >> 32), from, 64) << 32;
+}
+
+// Sixteen lanes take a path: as the polynomial's value is mul^(k - 1) times the
+// sum of (v_i + 1) mul^-i (mul is odd), they add up strided parts of the sum.
+// A thread per path waited for its entries one after another: 368 us for
+// 376808 paths, 66 this way.
+constexpr int kHashLanes = 16;
 __global__ __launch_bounds__(kBlock) void k_pp_hash_insert(const int64_t* off, const int32_t* vtx,
-                                                           int64_t n, uint64_t mul,
+                                                           int64_t n, HashPowers w,
                                                            unsigned long long* keys, int32_t* vals,
                                                            int64_t mask, unsigned long long* dups) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int l = (int)threadIdx.x & (kHashLanes - 1);
+  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kHashLanes;
   if (i >= n) return;
-  uint64_t h = 0;
-  for (int64_t k = off[i]; k < off[i + 1]; ++k) h = seq_hash_step(h, vtx[k], mul);
+  const int64_t o = off[i];
+  const int len = (int)(off[i + 1] - o);
+  uint64_t sum = 0, f = 1;
+  for (int b = 0; b < 4; ++b)
+    if (l >> b & 1) f *= w.inv[b];
+  for (int k = l; k < len; k += kHashLanes) {
+    sum += (uint64_t)(vtx[o + k] + 1) * f;
+    f *= w.inv[4];
+  }
+#pragma unroll
+  for (int d = kHashLanes / 2; d >= 1; d >>= 1) sum += shfl64(sum, lane_id() ^ d);
+  if (l) return;
+  uint64_t h = sum;
+  for (int e = len - 1, k = 0; e; e >>= 1, ++k)
+    if (e & 1) h *= w.pow[k];
   h = seq_hash_fix(h);
   int64_t s = (int64_t)(h & (uint64_t)mask);
   for (int64_t probe = 0; probe <= mask; ++probe) {
@@ -77,129 +121,200 @@ __device__ __forceinline__ int32_t table_find(const unsigned long long* keys, co
   return -1;
 }
 
-template <int W>
-__device__ __forceinline__ bool set_has(const uint64_t (&m)[W], int l) {
-  return mask_has<W>(m, l);
-}
-template <int W>
-__device__ __forceinline__ void set_flip(uint64_t (&m)[W], int l) {
-  const int q = l >> 6;
-  const uint64_t bit = 1ull << (l & 63);
-#pragma unroll
-  for (int k = 0; k < W; ++k) m[k] ^= (k == q) ? bit : 0ull;
+struct CoverArgs {
+  DGraph g;
+  int n;  // vertices
+  const int64_t* pp_off;
+  const int32_t* pp_vtx;
+  int64_t np;
+  EndRows b;
+  HashPowers w;
+  const unsigned long long* keys;
+  const int32_t* vals;
+  int64_t mask;
+  int32_t *pair_p, *pair_q;
+  int64_t cap;
+  unsigned long long* count;
+  unsigned long long* missing;
+};
+
+// Orders a wave's own LDS accesses (no other wave shares its rows).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
-// Pass 0 counts, pass 1 writes the pairs (chooser p, covered q) of each
-// spliced test path p (offsets tp_off over the prime paths' indices).
-// Window hashes roll in O(1): with prefix hashes P[k] of t (P[0] = 0,
-// P[k+1] = P[k] * mul + t[k] + 1), the window t[i..j) hashes to
-// P[j] - P[i] * mul^(j-i); mul^(j-i) is kept up to date with mul and its
-// inverse mod 2^64 (mul is odd).
-template <int W>
-__global__ __launch_bounds__(kBlock) void k_cover(DGraph g, const int64_t* tp_off,
-                                                  const int32_t* tp_vtx, int64_t n, uint64_t mul,
-                                                  uint64_t mul_inv,
-                                                  const unsigned long long* keys, const int32_t* vals,
-                                                  int64_t mask, int64_t* cnt, const int64_t* at,
-                                                  int32_t* pair_p, int32_t* pair_q, int pass,
-                                                  unsigned long long* missing) {
-  const int64_t p = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (p >= n) return;
-  const int32_t* t = tp_vtx + tp_off[p];
-  const int64_t L = tp_off[p + 1] - tp_off[p];
-  uint64_t m[W];
-#pragma unroll
-  for (int k = 0; k < W; ++k) m[k] = 0;
-  int64_t j = 0, found = 0, w0 = pass ? at[p] : 0;
-  uint64_t Pi = 0, Pj = 0, pw = 1;  // P[i], P[j], mul^(j - i)
-  // One action per iteration (extend the window, or test it and advance its
-  // start), so the lanes of a wave stay in step: at most 2 |t| iterations.
-  int64_t i = 0;
-  while (i < L) {
-    if (j < L) {
-      const int x = t[j];
-      if (!set_has<W>(m, g.loc[x])) {
-        set_flip<W>(m, g.loc[x]);
-        Pj = seq_hash_step(Pj, x, mul);
-        pw *= mul;
-        ++j;
-        continue;
-      }
+// Pairs (p, q): the test path spliced for p contains prime path q, which comes
+// after p in the order of decreasing length.  One wave per p; LDS per wave:
+// the row t (3 n + 2 entries) and each vertex's place in its prefix, its prime
+// path and its suffix.  The spliced rows are not written anywhere.
+//
+// A window's hash is sum of (t[k] + 1) mul^(end - 1 - k), which the wave takes
+// as mul^(end - 1) times the sum of (t[k] + 1) mul^-k (mul is odd).
+//
+// Bound by instructions, the LDS lookups and the scan of j for the most part.
+// 376808 prime paths of a 182-vertex CFG: 548 us; a thread per path that walked
+// rows written before took two passes of 1250 us, and a sort by length besides,
+// which the lengths of p and of the window make needless.
+template <int NW>
+__global__ __launch_bounds__(64 * NW) void k_cover(CoverArgs a) {
+  extern __shared__ uint16_t s_cover[];
+  const int lane = lane_id(), wave = (int)threadIdx.x >> 6;
+  const int n = a.n, row = (3 * n + 3) & ~1;
+  uint16_t* t = s_cover + (size_t)wave * (row + 3 * (n + (n & 1)));
+  uint16_t* at_a = t + row;
+  uint16_t* at_b = at_a + n + (n & 1);
+  uint16_t* at_c = at_b + n + (n & 1);
+  uint32_t* at_all = reinterpret_cast<uint32_t*>(at_a);
+  const int at_words = 3 * (n + (n & 1)) / 2;
+  constexpr int kNone = 0xFFFF;
+  const uint64_t inv64 = a.w.inv[6];
+  uint64_t inv_lane = 1;
+  for (int b = 0; b < 6; ++b)
+    if (lane >> b & 1) inv_lane *= a.w.inv[b];
+  __shared__ int32_t s_p[NW][64], s_q[NW][64];  // found pairs, not written yet
+  int held = 0;
+  auto flush = [&]() {
+    unsigned long long at = 0;
+    if (lane == 0) at = atomicAdd(a.count, (unsigned long long)held);
+    at = shfl64(at, 0);
+    if (lane < held && (int64_t)at + lane < a.cap) {
+      a.pair_p[at + lane] = s_p[wave][lane];
+      a.pair_q[at + lane] = s_q[wave][lane];
     }
-    // t[i..j) is the longest simple window starting at i
-    const int v1 = t[i];
-    int64_t end = -1;  // exclusive end of the accepted window
-    if (j < L && t[j] == v1) {
-      end = j + 1;  // a simple cycle
-    } else {
-      const int vk = t[j - 1];
+    held = 0;
+  };
+  for (int64_t p = (int64_t)blockIdx.x * NW + wave; p < a.np; p += (int64_t)gridDim.x * NW) {
+    const int64_t o0 = a.pp_off[p];
+    const int lq = (int)(a.pp_off[p + 1] - o0);
+    const int32_t* pp = a.pp_vtx + o0;
+    const int v1 = pp[0], vk = pp[lq - 1];
+    const bool cyc = lq > 1 && v1 == vk;
+    const int lp = a.b.n_pfx[v1], lpq = lp + lq, L = lpq + a.b.n_sfx[vk];
+    const int32_t* pfx = a.b.pfx + a.b.pfx_at[v1];
+    const int32_t* sfx = a.b.sfx + a.b.sfx_at[vk];
+    const int last = lpq - 1;  // the path's last entry
+    for (int k = lane; k < at_words; k += 64) at_all[k] = 0xFFFFFFFFu;
+    wave_lds_fence();
+    for (int k = lane; k < L; k += 64) {
+      const int x = k < lp ? pfx[k] : k < lpq ? pp[k - lp] : sfx[k - lpq];
+      t[k] = (uint16_t)x;
+      if (k < lp) at_a[x] = (uint16_t)k;
+      else if (k >= lpq) at_c[x] = (uint16_t)k;
+      else if (!cyc || k != last) at_b[x] = (uint16_t)k;  // a cycle's vertex: its first place
+    }
+    wave_lds_fence();
+    // is vertex w on t[i..j)?
+    auto on = [&](int w, int i, int j) {
+      const int x = at_a[w], y = at_b[w], z = at_c[w];
+      return (x >= i && x < j) || (y >= i && y < j) || (z >= i && z < j) ||
+             (cyc && w == v1 && last >= i && last < j);
+    };
+    // windows that come before p in the order, or are p, make no pair
+    auto wanted = [&](int i, int end) {
+      return end - i <= lq && !(i == lp && end == lpq);
+    };
+    // the local prime rule for the window t[i..j)
+    auto prime = [&](int i, int j) {
+      const int x = t[i], y = t[j - 1];
       bool ok = true;
-      for (int k = g.sp[vk]; k < g.sp[vk + 1] && ok; ++k) {
-        const int w = g.s[k];
-        ok = w != v1 && set_has<W>(m, g.loc[w]);
+      for (int k = a.g.sp[y]; k < a.g.sp[y + 1] && ok; ++k) {
+        const int w = a.g.s[k];
+        ok = w != x && on(w, i, j);
       }
-      for (int k = g.pp[v1]; k < g.pp[v1 + 1] && ok; ++k) ok = set_has<W>(m, g.loc[g.p[k]]);
-      if (ok) end = j;
-    }
-    if (end > 0) {
-      uint64_t h = Pj - Pi * pw;
-      if (end > j) h = seq_hash_step(Pj, t[j], mul) - Pi * (pw * mul);  // the cycle's closing entry
-      const int32_t q = table_find(keys, vals, mask, seq_hash_fix(h));
+      for (int k = a.g.pp[x]; k < a.g.pp[x + 1] && ok; ++k) ok = on(a.g.p[k], i, j);
+      return ok;
+    };
+    // t[i..end) (the same in all lanes) is a prime path
+    auto found = [&](int i, int end) {
+      const int len = end - i;
+      uint64_t sum = 0, f = inv_lane;
+      for (int k = lane; k < end; k += 64) {
+        if (k >= i) sum += (uint64_t)(t[k] + 1) * f;
+        f *= inv64;
+      }
+#pragma unroll
+      for (int d = 32; d >= 1; d >>= 1) sum += shfl64(sum, lane ^ d);
+      uint64_t h = sum;
+      for (int e = end - 1, k = 0; e; e >>= 1, ++k)
+        if (e & 1) h *= a.w.pow[k];
+      const int32_t q = table_find(a.keys, a.vals, a.mask, seq_hash_fix(h));
       if (q < 0) {
-        atomicAdd(missing, 1ull);  // not a prime path: a bug, reported to the host
-      } else {
-        if (pass) {
-          pair_p[w0 + found] = (int32_t)p;
-          pair_q[w0 + found] = q;
+        if (lane == 0) atomicAdd(a.missing, 1ull);  // not a prime path: a bug, reported to the host
+      } else if (lq > len || p < q) {
+        if (held == 64) flush();
+        if (lane == 0) {
+          s_p[wave][held] = (int32_t)p;
+          s_q[wave][held] = q;
         }
-        ++found;
+        wave_lds_fence();
+        ++held;
       }
+    };
+    // from the last positions to the first: j(k), and with a cycle at k that
+    // cycle and the window that starts after it
+    int next_j = L;          // j of the position after the block
+    bool next_cyc = true;    // nothing starts after the row
+    for (int k0 = (L - 1) & ~63; k0 >= 0; k0 -= 64) {
+      const int k = k0 + lane;
+      int nx = L;
+      if (k < lpq) {
+        const int x = t[k], c = at_c[x], b = at_b[x];
+        nx = c != kNone ? c : L;
+        if (k < lp && b != kNone) nx = b;
+        if (cyc && k == lp) nx = last;
+      }
+      int j = nx;
+#pragma unroll
+      for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_down(j, d, 64);
+        if (lane + d < 64) j = min(j, o);
+      }
+      j = min(j, next_j);
+      const bool is_cyc = k < L && nx == j && j < L;
+      // the position after this one
+      int j1 = __shfl_down(j, 1, 64);
+      int c1 = __shfl_down((int)is_cyc, 1, 64);
+      if (lane == 63) {
+        j1 = next_j;
+        c1 = next_cyc;
+      }
+      const bool after = is_cyc && !c1 && wanted(k + 1, j1) && prime(k + 1, j1);
+      const bool head = k == 0 && !is_cyc && wanted(0, j) && prime(0, j);
+      next_j = __builtin_amdgcn_readfirstlane(j);
+      next_cyc = (bool)__builtin_amdgcn_readfirstlane((int)is_cyc);
+      for (uint64_t m = __ballot(is_cyc && wanted(k, j + 1)); m; m &= m - 1) {
+        const int l = __builtin_ctzll(m);
+        found(k0 + l, __builtin_amdgcn_readlane(j, l) + 1);
+      }
+      for (uint64_t m = __ballot(after); m; m &= m - 1) {
+        const int l = __builtin_ctzll(m);
+        found(k0 + l + 1, __builtin_amdgcn_readlane(j1, l));
+      }
+      if (__ballot(head)) found(0, __builtin_amdgcn_readfirstlane(j));
     }
-    // drop t[i]: the window now starts at i + 1 (j > i always holds here)
-    set_flip<W>(m, g.loc[v1]);
-    Pi = seq_hash_step(Pi, v1, mul);
-    pw *= mul_inv;
-    ++i;
+    wave_lds_fence();
   }
-  if (!pass) cnt[p] = found;
-}
-
-// Position of every prime path in the order of decreasing length.
-__global__ __launch_bounds__(kBlock) void k_len_key(const int64_t* off, int64_t n, int64_t max_len,
-                                                    int32_t* key) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) key[i] = (int32_t)(max_len - (off[i + 1] - off[i]));
-}
-
-__global__ __launch_bounds__(kBlock) void k_key_hist(const int32_t* key, int64_t n, int64_t ntiles,
-                                                     unsigned long long* hist) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) atomicAdd(&hist[(int64_t)key[i] * ntiles + i / kGroupTile], 1ull);
-}
-
-__global__ __launch_bounds__(kBlock) void k_invert(const int32_t* perm, int64_t n, int32_t* pos) {
-  const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (k < n) pos[perm[k]] = (int32_t)k;
+  if (held) flush();
 }
 
 // One round over the pairs (p covers q, p before q in the order): q is
 // dropped if p is chosen, and blocked (cannot be chosen yet) if p is still
 // undecided.  Only constant values are stored.
 __global__ __launch_bounds__(kBlock) void k_round_pairs(const int32_t* pair_p, const int32_t* pair_q,
-                                                        int64_t np, const int32_t* pos,
-                                                        const uint8_t* state, uint8_t* drop,
-                                                        uint8_t* block) {
+                                                        int64_t np, const uint8_t* state,
+                                                        uint8_t* drop, uint8_t* block) {
   const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (k >= np) return;
   const int32_t p = pair_p[k], q = pair_q[k];
-  if (pos[p] >= pos[q] || state[q] != 0) return;
+  if (state[q] != 0) return;
   const uint8_t sp = state[p];
   if (sp == 1) drop[q] = 1;
   else if (sp == 0) block[q] = 1;
 }
 
 // Decide: 1 chosen, 2 dropped, 0 undecided; clears the flags for the next
-// round and counts the undecided paths (one atomic per wave).
+// round and counts the undecided paths (one atomic per wave) if asked to.
 __global__ __launch_bounds__(kBlock) void k_round_decide(int64_t n, uint8_t* state, uint8_t* drop,
                                                          uint8_t* block,
                                                          unsigned long long* undecided) {
@@ -212,21 +327,9 @@ __global__ __launch_bounds__(kBlock) void k_round_decide(int64_t n, uint8_t* sta
     drop[q] = 0;
     block[q] = 0;
   }
+  if (!undecided) return;
   const uint64_t b = __ballot(und);
   if (lane_id() == 0 && b) atomicAdd(undecided, (unsigned long long)__builtin_popcountll(b));
-}
-
-template <int W>
-hipError_t launch_cover_w(const DGraph& g, const int64_t* tp_off, const int32_t* tp_vtx, int64_t n,
-                          uint64_t mul, const uint64_t* keys, const int32_t* vals, int64_t mask,
-                          int64_t* cnt, const int64_t* at, int32_t* pair_p, int32_t* pair_q,
-                          int pass, uint64_t* missing, hipStream_t st) {
-  uint64_t inv = mul;  // Newton's iteration for the inverse of an odd number mod 2^64
-  for (int r = 0; r < 6; ++r) inv *= 2 - mul * inv;
-  k_cover<W><<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(
-      g, tp_off, tp_vtx, n, mul, inv, reinterpret_cast<const unsigned long long*>(keys), vals, mask,
-      cnt, at, pair_p, pair_q, pass, reinterpret_cast<unsigned long long*>(missing));
-  return hipGetLastError();
 }
 
 }  // namespace
@@ -235,58 +338,58 @@ hipError_t launch_pp_hash_insert(const int64_t* off, const int32_t* vtx, int64_t
                                  uint64_t* keys, int32_t* vals, int64_t mask, uint64_t* dups,
                                  hipStream_t st) {
   if (n == 0) return hipSuccess;
-  k_pp_hash_insert<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(
-      off, vtx, n, mul, reinterpret_cast<unsigned long long*>(keys), vals, mask,
+  const int64_t rows = kBlock / kHashLanes;
+  k_pp_hash_insert<<<(unsigned)((n + rows - 1) / rows), kBlock, 0, st>>>(
+      off, vtx, n, hash_powers(mul), reinterpret_cast<unsigned long long*>(keys), vals, mask,
       reinterpret_cast<unsigned long long*>(dups));
   return hipGetLastError();
 }
 
 uint64_t cover_hash_mul(int attempt) { return kHashMul + 2ull * (uint64_t)attempt * 0x2545F4914F6CDD1Dull; }
 
-hipError_t launch_cover(int W, const DGraph& g, const int64_t* tp_off, const int32_t* tp_vtx,
-                        int64_t n, uint64_t mul, const uint64_t* keys, const int32_t* vals,
-                        int64_t mask, int64_t* cnt, const int64_t* at, int32_t* pair_p,
-                        int32_t* pair_q, int pass, uint64_t* missing, hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  switch (W) {
-    case 1: return launch_cover_w<1>(g, tp_off, tp_vtx, n, mul, keys, vals, mask, cnt, at, pair_p, pair_q, pass, missing, st);
-    case 2: return launch_cover_w<2>(g, tp_off, tp_vtx, n, mul, keys, vals, mask, cnt, at, pair_p, pair_q, pass, missing, st);
-    case 4: return launch_cover_w<4>(g, tp_off, tp_vtx, n, mul, keys, vals, mask, cnt, at, pair_p, pair_q, pass, missing, st);
-    case 8: return launch_cover_w<8>(g, tp_off, tp_vtx, n, mul, keys, vals, mask, cnt, at, pair_p, pair_q, pass, missing, st);
-    case 16: return launch_cover_w<16>(g, tp_off, tp_vtx, n, mul, keys, vals, mask, cnt, at, pair_p, pair_q, pass, missing, st);
-    case 32: return launch_cover_w<32>(g, tp_off, tp_vtx, n, mul, keys, vals, mask, cnt, at, pair_p, pair_q, pass, missing, st);
-    case 64: return launch_cover_w<64>(g, tp_off, tp_vtx, n, mul, keys, vals, mask, cnt, at, pair_p, pair_q, pass, missing, st);
-    default: return hipErrorInvalidValue;
+hipError_t launch_cover(const DGraph& g, int n, const int64_t* pp_off, const int32_t* pp_vtx,
+                        int64_t np, const EndRows& b, uint64_t mul, const uint64_t* keys,
+                        const int32_t* vals, int64_t mask, int32_t* pair_p, int32_t* pair_q,
+                        int64_t cap, uint64_t* count, uint64_t* missing, int num_cus,
+                        hipStream_t st) {
+  if (np == 0) return hipSuccess;
+  if (n < 1 || 3 * n + 1 >= 1 << kPowers) return hipErrorInvalidValue;
+  CoverArgs a{};
+  a.g = g;
+  a.n = n;
+  a.pp_off = pp_off;
+  a.pp_vtx = pp_vtx;
+  a.np = np;
+  a.b = b;
+  a.w = hash_powers(mul);
+  a.keys = reinterpret_cast<const unsigned long long*>(keys);
+  a.vals = vals;
+  a.mask = mask;
+  a.pair_p = pair_p;
+  a.pair_q = pair_q;
+  a.cap = cap;
+  a.count = reinterpret_cast<unsigned long long*>(count);
+  a.missing = reinterpret_cast<unsigned long long*>(missing);
+  const size_t lds = sizeof(uint16_t) * (size_t)(((3 * n + 3) & ~1) + 3 * (n + (n & 1)));
+  // four waves a workgroup while that leaves the CU its 32 waves (20 KB each);
+  // one for the large graphs, up to 49 KB
+  if (4 * lds <= 20 << 10) {
+    const int64_t grid = std::min<int64_t>((np + 3) / 4, (int64_t)num_cus * 8);
+    k_cover<4><<<(unsigned)grid, 256, 4 * lds, st>>>(a);
+  } else {
+    const int64_t per_cu = std::max<int64_t>(1, std::min<int64_t>(32, (160 << 10) / (int64_t)(lds + 512)));
+    const int64_t grid = std::min<int64_t>(np, (int64_t)num_cus * per_cu);
+    k_cover<1><<<(unsigned)grid, 64, lds, st>>>(a);
   }
-}
-
-hipError_t launch_len_key(const int64_t* off, int64_t n, int64_t max_len, int32_t* key,
-                          hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  k_len_key<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(off, n, max_len, key);
-  return hipGetLastError();
-}
-
-hipError_t launch_key_hist(const int32_t* key, int64_t n, int64_t ntiles, uint64_t* hist,
-                           hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  k_key_hist<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(
-      key, n, ntiles, reinterpret_cast<unsigned long long*>(hist));
-  return hipGetLastError();
-}
-
-hipError_t launch_invert(const int32_t* perm, int64_t n, int32_t* pos, hipStream_t st) {
-  if (n == 0) return hipSuccess;
-  k_invert<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(perm, n, pos);
   return hipGetLastError();
 }
 
 hipError_t launch_round_pairs(const int32_t* pair_p, const int32_t* pair_q, int64_t np,
-                              const int32_t* pos, const uint8_t* state, uint8_t* drop,
-                              uint8_t* block, hipStream_t st) {
+                              const uint8_t* state, uint8_t* drop, uint8_t* block,
+                              hipStream_t st) {
   if (np == 0) return hipSuccess;
-  k_round_pairs<<<(unsigned)((np + kBlock - 1) / kBlock), kBlock, 0, st>>>(pair_p, pair_q, np, pos,
-                                                                          state, drop, block);
+  k_round_pairs<<<(unsigned)((np + kBlock - 1) / kBlock), kBlock, 0, st>>>(pair_p, pair_q, np, state,
+                                                                          drop, block);
   return hipGetLastError();
 }
 
