@@ -1429,14 +1429,12 @@ tpg_status group_by_last(tpg_workspace* ws, int32_t n_keys, hipStream_t st, OutS
   uint64_t* hist = ws->grp_hist.as<uint64_t>();
   int64_t* base = ws->grp_base.as<int64_t>();  // the scanned histograms
   int32_t* perm = ws->row_src.as<int32_t>();
-  TPG_HIP(launch_zero_u64(hist, nh, st));
-  TPG_HIP(launch_last_hist(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np, nt,
-                           ws->grp_key.as<int32_t>(), hist, st));
+  TPG_HIP(launch_last_rank(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np, nt, n_keys,
+                           ws->grp_key.as<uint32_t>(), hist, st));
   TPG_HIP(scan_i64(reinterpret_cast<const int64_t*>(hist), base, nh, 0, sc + 10,
                    ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  TPG_HIP(launch_last_place(ws->grp_key.as<int32_t>(), np, nt, base, perm, st));
-  TPG_HIP(launch_row_len(perm, np, o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), nullptr,
-                         ws->row_len.as<int32_t>(), st));
+  TPG_HIP(launch_last_place(ws->grp_key.as<uint32_t>(), np, nt, base, o.pp_off.as<int64_t>(), perm,
+                            ws->row_len.as<int32_t>(), st));
   TPG_HIP(scan_i32_to_i64(ws->row_len.as<int32_t>(), o.ppg_off.as<int64_t>(), np, 0, sc + 11,
                           ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
   TPG_HIP(launch_emit_rows(perm, np, nv, o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), nullptr,

@@ -218,18 +218,19 @@ hipError_t launch_merge_emit(const int64_t* off, const int32_t* vtx, int64_t n, 
 hipError_t launch_pp_types(const DGraph& g, const int32_t* comp, const uint8_t* flags,
                            const int64_t* off, const int32_t* vtx, int64_t n_pp, uint8_t* types,
                            unsigned long long* counts, hipStream_t st);
-// --- stable counting sorts by a small integer key (tiles of kGroupTile) -------
-constexpr int kGroupTile = 1024;
 // --- prime paths grouped by last vertex (stable counting sort) ---------------
-// key[i] = last vertex of path i; hist[key * ntiles + tile] counts (hist must
-// be zero, nkeys * ntiles entries, tile = group_tiles granularity)
+constexpr int kGroupTile = 1024;
+constexpr int kGroupKeyBits = 13;  // keys below 2^13, ranks in a tile above them
 int64_t group_tiles(int64_t n);
-hipError_t launch_last_hist(const int64_t* off, const int32_t* vtx, int64_t n, int64_t ntiles,
-                            int32_t* key, uint64_t* hist, hipStream_t st);
-// perm[slot] = path index, slot = base[key * ntiles + tile] + rank among the
-// tile's earlier paths with the same key (base: exclusive scan of hist)
-hipError_t launch_last_place(const int32_t* key, int64_t n, int64_t ntiles, const int64_t* base,
-                             int32_t* perm, hipStream_t st);
+// key_rank[i] = last vertex of path i and the number of its tile's earlier paths
+// with the same one; hist[key * ntiles + tile] their counts (n_keys * ntiles)
+hipError_t launch_last_rank(const int64_t* off, const int32_t* vtx, int64_t n, int64_t ntiles,
+                            int n_keys, uint32_t* key_rank, uint64_t* hist, hipStream_t st);
+// perm[slot] = path index and len[slot] its entries, slot = base[key * ntiles +
+// tile] + rank (base: exclusive scan of hist)
+hipError_t launch_last_place(const uint32_t* key_rank, int64_t n, int64_t ntiles,
+                             const int64_t* base, const int64_t* off, int32_t* perm, int32_t* len,
+                             hipStream_t st);
 struct EndRows;
 // --- test paths by longest-first covering (kernels_cover.hip) ----------------
 // Hash table of the prime paths (keys / vals of mask + 1 slots, keys zeroed);
@@ -304,11 +305,9 @@ hipError_t launch_tp_down_span(const ExtArgs& a, const TpTree& tt, const LevelSp
 hipError_t launch_tp_down_run(const ExtArgs& a, const TpTree& tt, int64_t base, int64_t F,
                               const int32_t* rep, uint32_t* cnt, int32_t* src, int32_t* len,
                               hipStream_t st);
-// rows r < n, each prime path src[r] (null: r), with b between its prefix and
-// suffix rows: their lengths, and the rows at out_off (n_entries in all; n_dev:
-// where the number of rows is, at most n, if the host does not know it yet)
-hipError_t launch_row_len(const int32_t* src, int64_t n, const int64_t* pp_off,
-                          const int32_t* pp_vtx, const EndRows* b, int32_t* len, hipStream_t st);
+// rows r < n, each prime path src[r], with b between its prefix and suffix rows,
+// at out_off (n_entries in all; n_dev: where the number of rows is, at most n, if
+// the host does not know it yet)
 hipError_t launch_emit_rows(const int32_t* src, int64_t n, int64_t n_entries, const int64_t* pp_off,
                             const int32_t* pp_vtx, const EndRows* b, const int64_t* out_off,
                             int32_t* out_vtx, hipStream_t st, const int64_t* n_dev = nullptr);
