@@ -1869,7 +1869,7 @@ tpg_status scc_device(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   TPG_TRY(ws_reserve(ws, ws->scc_comp, sizeof(int32_t) * n));
   TPG_TRY(ws_reserve(ws, ws->scc_flags, n));
   TPG_TRY(ws_reserve(ws, ws->scc_misc, 64 + sizeof(uint64_t) * kPpTypes));
-  TPG_HIP(launch_scc(ws->dg, (int32_t)U.s.size(), ws->scc_work.as<int32_t>(),
+  TPG_HIP(launch_scc(ws->dg, ws->xg, ws->ch, (int32_t)U.s.size(), ws->scc_work.as<int32_t>(),
                      ws->scc_comp.as<int32_t>(),
                      ws->scc_flags.as<uint8_t>(), ws->scc_misc.as<int32_t>(), st));
   return TPG_OK;
@@ -2067,9 +2067,16 @@ tpg_status extract_device(CallCtx& c, const tpg_graph* g, const std::vector<int3
     const ExtArgs a = make_args(ws);
     uint8_t* qb = ws->cx_qb.as<uint8_t>();
     uint32_t* cnt[2] = {ws->cx_cnt0.as<uint32_t>(), ws->cx_cnt1.as<uint32_t>()};
-    for (int L = R.Lmax; L >= 1; --L)
-      TPG_HIP(launch_ex_up(a, R.off[L], R.count[L], ws->cx_vfl.as<uint8_t>(), rev, qb, cnt[0],
-                           nsets > 1 ? cnt[1] : nullptr, st));
+    uint32_t* cnt1 = nsets > 1 ? cnt[1] : nullptr;
+    for (int L = R.Lmax; L >= 1;) {
+      const LevelSpan s = narrow_span(R, L, 1);
+      if (s.n > 0)
+        TPG_HIP(launch_ex_up_span(a, s, ws->cx_vfl.as<uint8_t>(), rev, qb, cnt[0], cnt1, st));
+      else
+        TPG_HIP(launch_ex_up(a, R.off[L], R.count[L], ws->cx_vfl.as<uint8_t>(), rev, qb, cnt[0],
+                             cnt1, st));
+      L -= std::max(1, s.n);
+    }
     for (int s = 0; s < nsets; ++s) {
       TPG_HIP(launch_ex_roots(cnt[s], R.count[1], scal, st));
       TPG_HIP(hipMemcpyAsync(ws->h_scalars, scal, sizeof(int64_t), hipMemcpyDeviceToHost, st));
@@ -2077,9 +2084,16 @@ tpg_status extract_device(CallCtx& c, const tpg_graph* g, const std::vector<int3
       const int64_t np = ws->h_scalars[0];
       TPG_TRY(ws_reserve(ws, ws->cx_node, sizeof(int64_t) * (np + 1)));
       TPG_TRY(ws_reserve(ws, ws->cx_len, sizeof(int32_t) * (np + 1)));
-      for (int L = 1; L <= R.Lmax; ++L)
-        TPG_HIP(launch_ex_down(a, L, R.off[L], R.count[L], qb, cnt[s], rev, s,
-                               ws->cx_node.as<int64_t>(), ws->cx_len.as<int32_t>(), st));
+      for (int L = 1; L <= R.Lmax;) {
+        const LevelSpan sp = narrow_span(R, L, R.Lmax);
+        if (sp.n > 0)
+          TPG_HIP(launch_ex_down_span(a, L, sp, qb, cnt[s], rev, s, ws->cx_node.as<int64_t>(),
+                                      ws->cx_len.as<int32_t>(), st));
+        else
+          TPG_HIP(launch_ex_down(a, L, R.off[L], R.count[L], qb, cnt[s], rev, s,
+                                 ws->cx_node.as<int64_t>(), ws->cx_len.as<int32_t>(), st));
+        L += std::max(1, sp.n);
+      }
       DevBuf& off = ws->cx_off[slot[s]];
       TPG_TRY(ws_reserve(ws, off, sizeof(int64_t) * (np + 1)));
       TPG_TRY(reserve_scan(ws, std::max<int64_t>(np, 16)));

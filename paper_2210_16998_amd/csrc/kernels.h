@@ -173,9 +173,11 @@ constexpr uint8_t kPpComplete = 1, kPpSccInternal = 2, kPpSccExit = 3, kPpSccEnt
                   kPpOther = 5;
 constexpr int kPpTypes = 6;  // counts are indexed by type (index 0 unused)
 // comp[v] = smallest vertex of v's component, flags[v], n_comp[0] = number of
-// components; m: arcs of the union; work: 6 n int32 of scratch
-hipError_t launch_scc(const DGraph& g, int32_t m, int32_t* work, int32_t* comp, uint8_t* flags,
-                      int32_t* n_comp, hipStream_t st);
+// components; x, ch: the graph of its chains (empty: not at hand); m: arcs of the
+// union; work: 6 n int32 of scratch
+hipError_t launch_scc(const DGraph& g, const DGraph& x, const DChains& ch, int32_t m,
+                      int32_t* work, int32_t* comp, uint8_t* flags, int32_t* n_comp,
+                      hipStream_t st);
 // --- the paper's per-vertex schedule (comparison variant) ------------------
 hipError_t launch_pv_init(int n, int64_t* voff, int32_t* rows, hipStream_t st);
 hipError_t launch_pv_count(const DGraph& g, int L, const int64_t* voff, const int32_t* rows,
@@ -197,6 +199,12 @@ hipError_t launch_ccfg_write(const DGraph& g, const int32_t* comp, const int64_t
 // paths); mode 1: tree of the reversed components (set 0 exit paths)
 hipError_t launch_ex_up(const ExtArgs& a, int64_t base, int64_t F, const uint8_t* vfl, int mode,
                         uint8_t* qb, uint32_t* cnt0, uint32_t* cnt1, hipStream_t st);
+// the same for the levels of a span (L: its first)
+hipError_t launch_ex_up_span(const ExtArgs& a, const LevelSpan& s, const uint8_t* vfl, int mode,
+                             uint8_t* qb, uint32_t* cnt0, uint32_t* cnt1, hipStream_t st);
+hipError_t launch_ex_down_span(const ExtArgs& a, int L, const LevelSpan& s, const uint8_t* qb,
+                               uint32_t* cnt, int mode, int set, int64_t* out_node,
+                               int32_t* out_len, hipStream_t st);
 hipError_t launch_ex_roots(uint32_t* cnt, int64_t n_roots, int64_t* total, hipStream_t st);
 hipError_t launch_ex_down(const ExtArgs& a, int L, int64_t base, int64_t F, const uint8_t* qb,
                           uint32_t* cnt, int mode, int set, int64_t* out_node, int32_t* out_len,

@@ -91,12 +91,8 @@ __device__ __forceinline__ uint32_t ex_emit(uint8_t qb, int mode, int set) {
 }
 
 // Level L, bottom-up (its children's marks exist): marks and emitted counts.
-__global__ __launch_bounds__(kBlock) void k_ex_up(ExtArgs a, int64_t base, int64_t F,
-                                                  const uint8_t* vfl, int mode, uint8_t* qb,
-                                                  uint32_t* cnt0, uint32_t* cnt1) {
-  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (j >= F) return;
-  const int64_t x = base + j;
+__device__ __forceinline__ void ex_up_node(const ExtArgs& a, int64_t x, const uint8_t* vfl,
+                                           int mode, uint8_t* qb, uint32_t* cnt0, uint32_t* cnt1) {
   const uint8_t k = a.t.nch[x];
   uint8_t below = 0;
   uint32_t c0 = 0, c1 = 0;
@@ -113,6 +109,26 @@ __global__ __launch_bounds__(kBlock) void k_ex_up(ExtArgs a, int64_t base, int64
   qb[x] = q;
   cnt0[x] = c0 + ex_emit(q, mode, 0);
   if (cnt1) cnt1[x] = c1 + ex_emit(q, mode, 1);
+}
+
+__global__ __launch_bounds__(kBlock) void k_ex_up(ExtArgs a, int64_t base, int64_t F,
+                                                  const uint8_t* vfl, int mode, uint8_t* qb,
+                                                  uint32_t* cnt0, uint32_t* cnt1) {
+  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (j < F) ex_up_node(a, base + j, vfl, mode, qb, cnt0, cnt1);
+}
+
+// Narrow levels, bottom to top, by one workgroup (see k_up_span): a 218-vertex
+// CFG's extractions made 190 launches of single levels, most of them narrow.
+__global__ __launch_bounds__(1024) void k_ex_up_span(ExtArgs a, LevelSpan s, const uint8_t* vfl,
+                                                     int mode, uint8_t* qb, uint32_t* cnt0,
+                                                     uint32_t* cnt1) {
+  for (int l = s.n - 1; l >= 0; --l) {
+    const uint32_t end = s.off[l + 1];
+    for (uint32_t x = s.off[l] + threadIdx.x; x < end; x += 1024)
+      ex_up_node(a, x, vfl, mode, qb, cnt0, cnt1);
+    __syncthreads();
+  }
 }
 
 constexpr uint32_t kExNoRank = 0xFFFFFFFFu;
@@ -137,12 +153,9 @@ __global__ __launch_bounds__(1024) void k_ex_roots(uint32_t* cnt, int64_t n_root
 
 // Level L, top-down: a node with a rank records itself when emitted and
 // hands ranks to its children in slot order (cnt becomes ranks in place).
-__global__ __launch_bounds__(kBlock) void k_ex_down(ExtArgs a, int L, int64_t base, int64_t F,
-                                                    const uint8_t* qb, uint32_t* cnt, int mode,
-                                                    int set, int64_t* out_node, int32_t* out_len) {
-  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (j >= F) return;
-  const int64_t x = base + j;
+__device__ __forceinline__ void ex_down_node(const ExtArgs& a, int L, int64_t x, const uint8_t* qb,
+                                             uint32_t* cnt, int mode, int set, int64_t* out_node,
+                                             int32_t* out_len) {
   uint32_t r = cnt[x];
   if (r == kExNoRank) return;
   if (ex_emit(qb[x], mode, set)) {
@@ -157,6 +170,25 @@ __global__ __launch_bounds__(kBlock) void k_ex_down(ExtArgs a, int L, int64_t ba
     const uint32_t cc = cnt[y];
     cnt[y] = cc ? r : kExNoRank;
     r += cc;
+  }
+}
+
+__global__ __launch_bounds__(kBlock) void k_ex_down(ExtArgs a, int L, int64_t base, int64_t F,
+                                                    const uint8_t* qb, uint32_t* cnt, int mode,
+                                                    int set, int64_t* out_node, int32_t* out_len) {
+  const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (j < F) ex_down_node(a, L, base + j, qb, cnt, mode, set, out_node, out_len);
+}
+
+__global__ __launch_bounds__(1024) void k_ex_down_span(ExtArgs a, int L, LevelSpan s,
+                                                       const uint8_t* qb, uint32_t* cnt, int mode,
+                                                       int set, int64_t* out_node,
+                                                       int32_t* out_len) {
+  for (int l = 0; l < s.n; ++l) {
+    const uint32_t end = s.off[l + 1];
+    for (uint32_t x = s.off[l] + threadIdx.x; x < end; x += 1024)
+      ex_down_node(a, L + l, x, qb, cnt, mode, set, out_node, out_len);
+    __syncthreads();
   }
 }
 
@@ -182,6 +214,21 @@ hipError_t launch_ex_up(const ExtArgs& a, int64_t base, int64_t F, const uint8_t
   if (F == 0) return hipSuccess;
   k_ex_up<<<(unsigned)((F + kBlock - 1) / kBlock), kBlock, 0, st>>>(a, base, F, vfl, mode, qb,
                                                                     cnt0, cnt1);
+  return hipGetLastError();
+}
+
+hipError_t launch_ex_up_span(const ExtArgs& a, const LevelSpan& s, const uint8_t* vfl, int mode,
+                             uint8_t* qb, uint32_t* cnt0, uint32_t* cnt1, hipStream_t st) {
+  if (s.n < 1 || s.n > kSpanLevels) return hipErrorInvalidValue;
+  k_ex_up_span<<<1, 1024, 0, st>>>(a, s, vfl, mode, qb, cnt0, cnt1);
+  return hipGetLastError();
+}
+
+hipError_t launch_ex_down_span(const ExtArgs& a, int L, const LevelSpan& s, const uint8_t* qb,
+                               uint32_t* cnt, int mode, int set, int64_t* out_node,
+                               int32_t* out_len, hipStream_t st) {
+  if (s.n < 1 || s.n > kSpanLevels) return hipErrorInvalidValue;
+  k_ex_down_span<<<1, 1024, 0, st>>>(a, L, s, qb, cnt, mode, set, out_node, out_len);
   return hipGetLastError();
 }
 
@@ -264,17 +311,21 @@ __global__ __launch_bounds__(kBlock) void k_merge_class(const int64_t* off, cons
 }
 
 // Paths of class c, in order: entries mapped to g's vertices (pos: exclusive
-// scan of the class flags, voff: of the lengths of the class's paths).
+// scan of the class flags, voff: of the lengths of the class's paths).  Sixteen
+// lanes a path, for whole lines of its row: 71 to 22 us for the largest set of a
+// 218-vertex CFG.
+constexpr int kEmitLanes = 16;
 __global__ __launch_bounds__(kBlock) void k_merge_emit(const int64_t* off, const int32_t* vtx,
                                                        int64_t n, const uint8_t* cls, int c,
                                                        const int64_t* pos, const int64_t* voff,
                                                        const int32_t* len, const int32_t* horig,
                                                        int64_t* out_off, int32_t* out_vtx) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kEmitLanes;
+  const int l = (int)threadIdx.x & (kEmitLanes - 1);
   if (i >= n || cls[i] != c) return;
   const int64_t o0 = off[i], d0 = voff[i];
-  out_off[pos[i]] = d0;
-  for (int32_t k = 0; k < len[i]; ++k) out_vtx[d0 + k] = horig[vtx[o0 + k]];
+  if (l == 0) out_off[pos[i]] = d0;
+  for (int32_t k = l; k < len[i]; k += kEmitLanes) out_vtx[d0 + k] = horig[vtx[o0 + k]];
 }
 
 // Prime paths of the components with a cycle, each taken alone (union ids,
@@ -332,7 +383,8 @@ hipError_t launch_merge_emit(const int64_t* off, const int32_t* vtx, int64_t n, 
                              const int32_t* horig, int64_t* out_off, int32_t* out_vtx,
                              hipStream_t st) {
   if (n == 0) return hipSuccess;
-  k_merge_emit<<<(unsigned)((n + kBlock - 1) / kBlock), kBlock, 0, st>>>(
+  const int64_t rows = kBlock / kEmitLanes;
+  k_merge_emit<<<(unsigned)((n + rows - 1) / rows), kBlock, 0, st>>>(
       off, vtx, n, cls, c, pos, voff, len, horig, out_off, out_vtx);
   return hipGetLastError();
 }

@@ -142,7 +142,7 @@ extern "C" tpg_status tpg_prime_path_types_noalloc(const tpg_graph* g, const int
   uint8_t* flags = b + off_flags;
   int32_t* n_comp = (int32_t*)(b + off_misc);
   unsigned long long* d_cnt = (unsigned long long*)(b + off_misc + 64);
-  TPG_HIP(launch_scc(d, (int32_t)m, work, comp, flags, n_comp, st));
+  TPG_HIP(launch_scc(d, DGraph{}, DChains{}, (int32_t)m, work, comp, flags, n_comp, st));
   TPG_HIP(launch_pp_types(d, comp, flags, d_offsets, d_vertices, n_paths, d_types, d_cnt, st));
   if (counts) {
     // pageable destination: the copy returns once the counters are read
