@@ -129,6 +129,7 @@ struct tpg_workspace {
   DevBuf rb0;                         // output positions by first vertex
   DevBuf tp_links, tp_order, tp_first;  // TpTree's chain links, the arcs' order and places
   DevBuf canon, leaf_canon;           // see TpTree
+  DevBuf seq_num;                     // counts that a scan turns into positions
   DevBuf row_src, row_len;            // rows of a reordered set: source path, length
   DevBuf chunk_off;                   // rebased offsets of a streamed chunk
   // per-level, per-component counts (batched labels)
@@ -996,6 +997,12 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
   key_add(key, rb);
   key_add(key, range_lo);
   key_add(key, range_n);
+  TPG_TRY(ws_reserve(ws, ws->seq_num, sizeof(int32_t) * (size_t)(range_n + 1)));
+  TPG_TRY(reserve_scan(ws, range_n));
+  int32_t* num = ws->seq_num.as<int32_t>();
+  uint64_t* status = ws->scan_status.as<uint64_t>();
+  key_add(key, num);
+  key_add(key, status);
   key_add(key, R.Lmax);
   for (int L = 1; L <= R.Lmax; ++L) {
     key_add(key, R.off[L]);
@@ -1020,7 +1027,7 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
                 : launch_up(a, R.off[top], R.count[top], sc, st);
       L -= n;
     }
-    if (e == hipSuccess) e = launch_roots(a, ws->ch, range_lo, range_n, sc, rb, st);
+    if (e == hipSuccess) e = launch_roots(a, ws->ch, range_lo, range_n, sc, rb, num, status, st);
     return e;
   }));
   // the BFS ran beside the extension
@@ -1228,9 +1235,10 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
   const int64_t np = P.n_pp;
   T.n_spliced = np;
   const int32_t ng = U.gbase.back();
-  TPG_TRY(reserve_scan(ws, np));
+  TPG_TRY(reserve_scan(ws, std::max<int64_t>(np, ng)));
   TPG_TRY(ws_reserve(ws, ws->row_src, sizeof(int32_t) * (np + 1)));
   TPG_TRY(ws_reserve(ws, ws->row_len, sizeof(int32_t) * (np + 1)));
+  TPG_TRY(ws_reserve(ws, ws->seq_num, sizeof(int32_t) * (size_t)(ng + 1)));
   TPG_TRY(ws_reserve(ws, ws->tp_first, sizeof(int64_t) * (ng + 1)));
   const EndRows b = end_rows(ws, U.n);
   if (greedy) TPG_TRY(greedy_select(ws, U, st, np, o, b));
@@ -1253,6 +1261,10 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
   std::vector<uint8_t> key;
   key_add(key, a);
   key_add(key, tt);
+  int32_t* num = ws->seq_num.as<int32_t>();
+  uint64_t* status = ws->scan_status.as<uint64_t>();
+  key_add(key, num);
+  key_add(key, status);
   key_add(key, room);
   key_add(key, sc);
   key_add(key, cnt);
@@ -1287,7 +1299,8 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
       L -= n;
     }
     if (e == hipSuccess) 
-      e = launch_tp_arc_starts(a, tt, order, ng, rep, cnt, first, src, len, room, sc + 7, st);
+      e = launch_tp_arc_starts(a, tt, order, ng, rep, cnt, first, src, len, room, sc + 7, num, status,
+                               st);
     for (int L = 2; L <= R.Lmax && e == hipSuccess;) {
       const LevelSpan s = narrow_span(R, L, R.Lmax);
       e = s.n > 0 ? launch_tp_down_span(a, tt, s, rep, cnt, src, len, st)
@@ -1770,7 +1783,7 @@ void tpg_workspace_free(tpg_workspace* ws) {
                     &ws->leaf_by_rank, &ws->totals, &ws->scan_status,
                     &ws->scan_ctr, &ws->scalars, &ws->bfs_i32,
                     &ws->pfx, &ws->sfx, &ws->rb0, &ws->tp_links, &ws->tp_order, &ws->tp_first,
-                    &ws->canon, &ws->leaf_canon, &ws->row_src, &ws->row_len, &ws->chunk_off, &ws->lvl_comp, &ws->b_pp_off,
+                    &ws->canon, &ws->leaf_canon, &ws->seq_num, &ws->row_src, &ws->row_len, &ws->chunk_off, &ws->lvl_comp, &ws->b_pp_off,
                     &ws->digest, &ws->grp_key, &ws->grp_hist, &ws->grp_base,
                     &ws->cov_keys, &ws->cov_vals, &ws->cov_misc, &ws->pair_p,
                     &ws->pair_q, &ws->gstate0, &ws->gstate1,
@@ -2711,6 +2724,7 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
 
   std::vector<int32_t> g_union(n_graphs), g_comp(n_graphs);
   std::vector<std::vector<int64_t>> starts(unions.size());
+  std::vector<std::vector<int32_t>> bases(unions.size());  // first vertex id of each graph
   for (size_t u = 0; u < unions.size(); ++u) {
     HostUnion U;
     for (size_t k = 0; k < unions[u].size(); ++k) {
@@ -2798,9 +2812,8 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
         memcpy(c.opts->level_counts + (size_t)64 * unions[u][k], h.data() + 64 * k,
                sizeof(int64_t) * 64);
     }
-    // graph-wide ids -> ids of each graph; per-graph output starts
-    TPG_HIP(launch_localize(ws->dg.loc, o.pp_vtx.as<int32_t>(), o.n_ppv, c.st));
-    TPG_HIP(launch_localize(ws->dg.loc, o.tp_vtx.as<int32_t>(), o.n_tpv, c.st));
+    // per-graph output starts
+    bases[u] = U.cbase;
     starts[u].assign((size_t)4 * (nc + 1), 0);
     if (nc == 1) {
       starts[u] = {0, o.n_pp, 0, o.n_ppv, 0, o.n_tp, 0, o.n_tpv};
@@ -2838,8 +2851,8 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
     // graphs of a union are in caller order, so segment k of the union is graph i
     PackDesc& dp = desc[at[2 * u] + k];
     PackDesc& dt = desc[at[2 * u + 1] + k];
-    dp = PackDesc{p0, p1 - p0, v0, v1 - v0, pp_first[i], ppv, 0, 0};
-    dt = PackDesc{q0, q1 - q0, w0, w1 - w0, tp_first[i], tpv, 0, 0};
+    dp = PackDesc{p0, p1 - p0, v0, v1 - v0, pp_first[i], ppv, 0, bases[u][k]};
+    dt = PackDesc{q0, q1 - q0, w0, w1 - w0, tp_first[i], tpv, 0, bases[u][k]};
     pp_first[i + 1] = pp_first[i] + (p1 - p0);
     tp_first[i + 1] = tp_first[i] + (q1 - q0);
     ppv += v1 - v0;

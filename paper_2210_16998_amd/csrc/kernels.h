@@ -110,9 +110,10 @@ hipError_t launch_up_span(const ExtArgs& a, const LevelSpan& s, const int32_t* r
 // rb[v - range_lo] = output position of the first prime path whose first
 // vertex is >= v, for the range_n vertices from range_lo (those of the seeded
 // chains) and one past them; the roots' positions into sub_cnt; the prime
-// paths and the closed cycles into a.tot.
+// paths and the closed cycles into a.tot.  cnt: scratch, range_n entries.
 hipError_t launch_roots(const ExtArgs& a, const DChains& ch, int32_t range_lo, int32_t range_n,
-                        uint32_t* sub_cnt, int64_t* rb, hipStream_t st);
+                        uint32_t* sub_cnt, int64_t* rb, int32_t* cnt, uint64_t* scan_status,
+                        hipStream_t st);
 // A prime path's leaf: its node (bits 0-31), the place in its first chain
 // where it starts (bits 32-44), and bit 63 when it is a cycle.
 constexpr int kLeafStartShift = 32;
@@ -287,7 +288,6 @@ constexpr int kArcSlotBits = 6;  // a successor slot; chain ids take 17 bits
 hipError_t launch_chain_bfs(const DGraph& g, const DGraph& x, const DChains& ch, const TpTree& t,
                             const int32_t* gbase, int32_t* order, const int32_t* rbase,
                             const EndRows& b, int max_chains, int max_words, hipStream_t st);
-hipError_t launch_localize(const int32_t* loc, int32_t* v, int64_t n, hipStream_t st);
 // per-component output starts: pp_start[c] = rank of the first PP of c and
 // ppv_start[c] = offset of its first entry (after the PP offsets exist; rb:
 // see launch_roots, over all vertices; c = n_comp: the totals)
@@ -301,10 +301,11 @@ hipError_t launch_tp_mark(const ExtArgs& a, const TpTree& t, const uint64_t* lea
 // cnt: marked nodes per subtree (launch_tp_up*), rewritten into places (see
 // k_tp_arc_starts) for the n arcs of order; src[place] = prime path, len[place]
 // = entries of the test path (0 for the places from their number up to `room`);
-// their number also into *n_out
+// their number also into *n_out.  num: scratch, n entries
 hipError_t launch_tp_arc_starts(const ExtArgs& a, const TpTree& tt, const int32_t* order, int32_t n,
                                 const int32_t* rep, uint32_t* cnt, int64_t* first, int32_t* src,
-                                int32_t* len, int64_t room, int64_t* n_out, hipStream_t st);
+                                int32_t* len, int64_t room, int64_t* n_out, int32_t* num,
+                                uint64_t* scan_status, hipStream_t st);
 // places from the nodes of a span's levels down
 hipError_t launch_tp_down_span(const ExtArgs& a, const TpTree& tt, const LevelSpan& s,
                                const int32_t* rep, uint32_t* cnt, int32_t* src, int32_t* len,
@@ -337,7 +338,7 @@ struct PackDesc {
   int64_t src_path, n_paths, src_v0, n_v;
   int64_t dst_path, dst_v;
   int64_t chunk0;
-  int64_t pad;
+  int64_t base;  // the graph's first vertex id in the union
 };
 inline int64_t pack_chunks(const PackDesc& e) {
   return (e.n_paths + kPackPaths - 1) / kPackPaths + (e.n_v + kPackVtx - 1) / kPackVtx;

@@ -956,8 +956,52 @@ __global__ __launch_bounds__(1024) void k_roots(ExtArgs a, DChains ch, int32_t r
   }
 }
 
+// The same for a large union, around a scan over the chip: its numbers, then
+// the roots' positions.  100 k vertices of 4096 CFGs took one workgroup 170 to
+// 210 us, about 35 this way; up to kOneRoots its two steps are as fast.
+constexpr int32_t kOneRoots = 2 * 1024 * kRootItems;
+__global__ __launch_bounds__(kBlock) void k_root_counts(ExtArgs a, DChains ch, int32_t range_lo,
+                                                        int32_t range_n, const uint32_t* sub_cnt,
+                                                        int32_t* cnt) {
+  const int32_t i = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
+  uint32_t cx = 0;
+  if (i < range_n) {
+    const int v = range_lo + i, x = ch.of[v];
+    cx = PathTotals::root_cycles(a.g, a.tot)[x];
+    cnt[i] = (int32_t)(ch.pos[v] == 0 ? sub_cnt[x - a.seed_lo] : cx);
+  }
+  __shared__ int64_t s_w[kBlock / 64];
+  int64_t cycles;
+  (void)block_excl_scan<kBlock, int64_t>(cx, cycles, s_w);
+  if (threadIdx.x == 0 && cycles)
+    atomicAdd(reinterpret_cast<unsigned long long*>(a.tot) + PathTotals::kCycles,
+              (unsigned long long)cycles);
+}
+
+__global__ __launch_bounds__(kBlock) void k_root_places(ExtArgs a, DChains ch, int32_t range_lo,
+                                                        int32_t range_n, const int32_t* cnt,
+                                                        const int64_t* rb, uint32_t* sub_cnt) {
+  const int32_t i = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
+  if (i >= range_n) return;
+  const int v = range_lo + i;
+  if (ch.pos[v] == 0) sub_cnt[ch.of[v] - a.seed_lo] = cnt[i] ? (uint32_t)rb[i] : kNoRank;
+}
+
 hipError_t launch_roots(const ExtArgs& a, const DChains& ch, int32_t range_lo, int32_t range_n,
-                        uint32_t* sub_cnt, int64_t* rb, hipStream_t st) {
+                        uint32_t* sub_cnt, int64_t* rb, int32_t* cnt, uint64_t* scan_status,
+                        hipStream_t st) {
+  if (range_n > kOneRoots) {
+    const unsigned grid = (unsigned)((range_n + kBlock - 1) / kBlock);
+    k_root_counts<<<grid, kBlock, 0, st>>>(a, ch, range_lo, range_n, sub_cnt, cnt);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess)
+      e = scan_i32_to_i64(cnt, rb, range_n, 0,
+                          reinterpret_cast<int64_t*>(a.tot) + PathTotals::kPP, scan_status,
+                          nullptr, st);
+    if (e != hipSuccess) return e;
+    k_root_places<<<grid, kBlock, 0, st>>>(a, ch, range_lo, range_n, cnt, rb, sub_cnt);
+    return hipGetLastError();
+  }
   k_roots<<<1, 1024, 0, st>>>(a, ch, range_lo, range_n, sub_cnt, rb);
   return hipGetLastError();
 }
@@ -1178,14 +1222,19 @@ hipError_t launch_tp_up_run(const ExtArgs& a, int64_t base, int64_t F, const int
 // from each of x's other vertices too: the j-th vertex's prime paths are the
 // root's cycles, in the same order (they pass the rest of x, then differ
 // where the root's do).  One workgroup per chain of two or more vertices
-// takes its root's leaves 16 Ki at a time and gives the cycles among them
+// takes its root's leaves 16 a thread at a time and gives the cycles among them
 // their places after every other vertex's position.
+// Unions of many graphs have many such chains with few leaves each: 256 threads
+// and a quarter of the leaves a step then (4096 CFGs: 163 us a union with 1024,
+// 32 with 256).
 constexpr int kRotItems = 16;
-__global__ __launch_bounds__(1024) void k_rotations(ExtArgs a, DChains ch, TpTree t,
+constexpr int32_t kManyRot = 1024;
+template <int NT>
+__global__ __launch_bounds__(NT) void k_rotations(ExtArgs a, DChains ch, TpTree t,
                                                     const int32_t* rot, int32_t range_lo,
                                                     const int64_t* rb,
                                                     uint64_t* leaf, int32_t* pp_len) {
-  __shared__ int32_t s_w[16];
+  __shared__ int32_t s_w[NT / 64];
   const int x = rot[blockIdx.x];
   if (PathTotals::root_cycles(a.g, a.tot)[x] == 0) return;
   const int o = ch.off[x], m = ch.off[x + 1] - o;
@@ -1193,7 +1242,7 @@ __global__ __launch_bounds__(1024) void k_rotations(ExtArgs a, DChains ch, TpTre
   const int64_t p0 = rb[head], p1 = rb[head + 1];
   const int tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
   int64_t carry = 0;
-  for (int64_t b = p0; b < p1; b += 1024 * kRotItems) {
+  for (int64_t b = p0; b < p1; b += NT * kRotItems) {
     // a wave's leaves are consecutive: 64 at a time
     const int64_t w0 = b + (int64_t)wave * 64 * kRotItems + lane;
     uint64_t lf[kRotItems];
@@ -1207,7 +1256,7 @@ __global__ __launch_bounds__(1024) void k_rotations(ExtArgs a, DChains ch, TpTre
     int64_t at = carry;
     int all = 0;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) {
+    for (int w = 0; w < NT / 64; ++w) {
       at += w < wave ? s_w[w] : 0;
       all += s_w[w];
     }
@@ -1236,7 +1285,10 @@ hipError_t launch_rotations(const ExtArgs& a, const DChains& ch, const TpTree& t
                             const int32_t* rot, int32_t n_rot, int32_t range_lo, const int64_t* rb,
                             uint64_t* leaf, int32_t* pp_len, hipStream_t st) {
   if (n_rot <= 0) return hipSuccess;
-  k_rotations<<<(unsigned)n_rot, 1024, 0, st>>>(a, ch, t, rot, range_lo, rb, leaf, pp_len);
+  if (n_rot >= kManyRot)
+    k_rotations<256><<<(unsigned)n_rot, 256, 0, st>>>(a, ch, t, rot, range_lo, rb, leaf, pp_len);
+  else
+    k_rotations<1024><<<(unsigned)n_rot, 1024, 0, st>>>(a, ch, t, rot, range_lo, rb, leaf, pp_len);
   return hipGetLastError();
 }
 

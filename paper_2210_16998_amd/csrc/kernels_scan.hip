@@ -170,11 +170,11 @@ __global__ __launch_bounds__(kBlock) void k_scan_down(const Tin* in, Tout* out, 
 }
 
 // Up to kScanSmall items: one workgroup, kSmallItems consecutive items per
-// thread and step.  Three launches cost more than four steps of it: 48 small
-// functions took 24.7 ms with the line anywhere from 8192 items to 131072,
-// 26.0 without it.
+// thread and step.  Three launches cost more than two steps of it (7 us): 48
+// small functions took 24.7 ms with it, 26.0 without.  25 k items took it 20 to
+// 30 us, three launches 25 with the gaps between them.
 constexpr int kSmallItems = 8;
-constexpr int64_t kScanSmall = 32768;
+constexpr int64_t kScanSmall = 16384;
 template <class Tin, class Tout>
 __global__ __launch_bounds__(1024) void k_scan_small(const Tin* in, Tout* out, int32_t n,
                                                      int64_t add, int64_t* total) {

@@ -300,19 +300,6 @@ hipError_t launch_chain_bfs(const DGraph& g, const DGraph& x, const DChains& ch,
   return hipGetLastError();
 }
 
-// Graph-wide ids -> ids local to each component (batched output).
-__global__ void k_localize(const int32_t* loc, int32_t* v, int64_t n) {
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (int64_t)gridDim.x * blockDim.x)
-    v[i] = loc[v[i]];
-}
-
-hipError_t launch_localize(const int32_t* loc, int32_t* v, int64_t n, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  k_localize<<<(unsigned)std::min<int64_t>(4096, (n + kBlock - 1) / kBlock), kBlock, 0, st>>>(loc, v, n);
-  return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // test-path order from the path tree
 // ---------------------------------------------------------------------------
@@ -393,6 +380,12 @@ hipError_t launch_tp_mark(const ExtArgs& a, const TpTree& t, const uint64_t* lea
   return hipGetLastError();
 }
 
+// The node of an arc of the order (the exit's own path: its root).
+__device__ __forceinline__ int64_t arc_node(const TreeBufs& t, int32_t g) {
+  return g < 0 ? (int64_t)~g
+               : (int64_t)t.cstart[g >> kArcSlotBits] + (g & ((1 << kArcSlotBits) - 1));
+}
+
 // Places of the arcs' test paths: a scan of the marked nodes below each arc's
 // node in the arcs' order.  cnt: place + 1 of the subtree's first test path
 // (0: it has none), as k_tp_down reads it; first[j] = the place of arc j's
@@ -417,8 +410,7 @@ __global__ __launch_bounds__(1024) void k_tp_arc_starts(TreeBufs t, const int32_
       c[j] = 0;
       if (j0 + j < n) {
         const int32_t g = order[j0 + j];
-        node[j] = g < 0 ? (int64_t)~g
-                        : (int64_t)t.cstart[g >> kArcSlotBits] + (g & ((1 << kArcSlotBits) - 1));
+        node[j] = arc_node(t, g);
         c[j] = g < 0 ? (rep[node[j]] != 0 ? 1u : 0u) : cnt[node[j]];
         sum += c[j];
       }
@@ -447,9 +439,51 @@ __global__ __launch_bounds__(1024) void k_tp_arc_starts(TreeBufs t, const int32_
   }
 }
 
+// The same for a large union, around a scan over the chip (see k_root_counts):
+// 4096 CFGs took one workgroup 97 us a union, about 35 this way.
+constexpr int32_t kOneArcs = 2 * 1024 * kArcItems;
+__global__ __launch_bounds__(kBlock) void k_arc_counts(TreeBufs t, const int32_t* order, int32_t n,
+                                                       const int32_t* rep, const uint32_t* cnt,
+                                                       int32_t* out) {
+  const int32_t j = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
+  if (j >= n) return;
+  const int32_t g = order[j];
+  const int64_t x = arc_node(t, g);
+  out[j] = g < 0 ? (rep[x] != 0 ? 1 : 0) : (int32_t)cnt[x];
+}
+
+__global__ __launch_bounds__(kBlock) void k_arc_places(TreeBufs t, const int32_t* order, int32_t n,
+                                                       const int32_t* rep, uint32_t* cnt,
+                                                       const int32_t* num, const int64_t* first,
+                                                       int32_t* src, int32_t* len,
+                                                       const int32_t* cdist) {
+  const int32_t j = (int32_t)(blockIdx.x * kBlock + threadIdx.x);
+  if (j >= n) return;
+  const int32_t g = order[j], c = num[j];
+  const int64_t x = arc_node(t, g), at = first[j];
+  if (g >= 0) {
+    cnt[x] = c ? (uint32_t)(at + 1) : 0u;
+  } else if (c) {
+    src[at] = rep[x] - 1;
+    len[at] = cdist[x] + t.tl[x];
+  }
+}
+
 hipError_t launch_tp_arc_starts(const ExtArgs& a, const TpTree& tt, const int32_t* order, int32_t n,
                                 const int32_t* rep, uint32_t* cnt, int64_t* first, int32_t* src,
-                                int32_t* len, int64_t room, int64_t* n_out, hipStream_t st) {
+                                int32_t* len, int64_t room, int64_t* n_out, int32_t* num,
+                                uint64_t* scan_status, hipStream_t st) {
+  if (n > kOneArcs) {
+    const unsigned grid = (unsigned)((n + kBlock - 1) / kBlock);
+    hipError_t e = launch_zero_u32(reinterpret_cast<uint32_t*>(len), room, st);
+    if (e != hipSuccess) return e;
+    k_arc_counts<<<grid, kBlock, 0, st>>>(a.t, order, n, rep, cnt, num);
+    e = hipGetLastError();
+    if (e == hipSuccess) e = scan_i32_to_i64(num, first, n, 0, n_out, scan_status, nullptr, st);
+    if (e != hipSuccess) return e;
+    k_arc_places<<<grid, kBlock, 0, st>>>(a.t, order, n, rep, cnt, num, first, src, len, tt.cdist);
+    return hipGetLastError();
+  }
   k_tp_arc_starts<<<1, 1024, 0, st>>>(a.t, order, n, rep, cnt, first, src, len, tt.cdist, room,
                                       n_out);
   return hipGetLastError();
@@ -760,7 +794,8 @@ int64_t group_tiles(int64_t n) { return (n + kGroupTile - 1) / kGroupTile; }
 // One workgroup per chunk of a union's segments: the chunk's segment is the
 // last descriptor whose first chunk is at or before it (a segment with no
 // chunks shares its first chunk with the next one, which wins the search).
-// Fixed-size chunks keep the largest graphs of a batch from leaving one
+// Vertices become ids of their graph on the way (in passes of their own before
+// it took 380 us of 1030 for 651 MB).  Fixed-size chunks keep the largest graphs of a batch from leaving one
 // workgroup copying long after the others are done.
 __global__ __launch_bounds__(kBlock) void k_pack(const int64_t* src_off, const int32_t* src_vtx,
                                                  const PackDesc* d, int32_t n_desc,
@@ -783,7 +818,7 @@ __global__ __launch_bounds__(kBlock) void k_pack(const int64_t* src_off, const i
   } else {
     const int64_t q0 = (c - n_oc) * kPackVtx, q1 = min(e.n_v, q0 + kPackVtx);
     for (int64_t q = q0 + threadIdx.x; q < q1; q += kBlock)
-      dst_vtx[e.dst_v + q] = src_vtx[e.src_v0 + q];
+      dst_vtx[e.dst_v + q] = src_vtx[e.src_v0 + q] - e.base;
   }
 }
 

@@ -1,7 +1,7 @@
 """Level and row counts around the one-workgroup forms: levels of the path tree
 on both sides of 2048 nodes (swept by one workgroup, or by a launch for two
 levels) in one call, more narrow levels than one launch takes (64), and scans
-of lengths around 8192 (one step) and 32768 (the last length that one
+of lengths around 8192 (one step) and 16384 (the last length that one
 workgroup takes)."""
 import itertools
 
@@ -34,7 +34,8 @@ def _fans(widths, back=False):
 
 # prime paths, all of equal length: 8192 +- 256, 32768 and its neighbours; level
 # sizes from 2 to the same
-@pytest.mark.parametrize("widths", [(2,), (32, 32, 2), (31, 33, 2), (33, 32, 2), (32, 8, 31),
+@pytest.mark.parametrize("widths", [(2,), (32, 32, 2), (31, 33, 2), (33, 32, 2), (32, 8, 31), (33, 31, 16),
+                                    (32, 16, 32), (31, 32, 17),
                                     (8, 32, 32), (32, 32, 8), (31, 32, 33), (32, 32, 32),
                                     (32, 32, 33), (2, 2, 2, 32, 32, 4)])
 def test_all_paths_of_fans(widths):
