@@ -55,6 +55,8 @@
 
 #include <hip/hip_ext.h>
 
+#include <type_traits>
+
 #include "kernels.h"
 #include "sizing.h"
 
@@ -1302,19 +1304,25 @@ hipError_t launch_rotations(const ExtArgs& a, const DChains& ch, const TpTree& t
 // go to LDS, one row per lane; then the wave stores the rows, kPPSeg lanes
 // per row, so that a store covers a few whole row segments instead of one
 // word in each of 64 lines.
-constexpr int kPPSeg = 16;
-constexpr int kPPRow = kPPSeg + 1;  // LDS row stride (odd: rows fall in different banks)
 
 // LDS: the chains' rows (off, v) are staged as 16-bit words (the union has at
 // most kStageVertices vertices), so that a step inside a chain costs an LDS
-// read; only a step to the parent's chain loads from the tree.
+// read; only a step to the parent's chain loads from the tree.  The rows are
+// 16-bit words there too, which makes room for segments of 32 depths: the
+// stress CFG's 3.5 GB took 2.58 ms in segments of 16 (5.4 GB written, since a
+// segment's ends share their lines with its neighbours', written at another
+// time), 2.05 in segments of 32, 2.4 in 64; windows shifted so that a segment
+// is a whole line take the lanes off their common depth and cost more, 2.9.
 constexpr int kStageVertices = 2048;
 
 template <bool LDS>
 __global__ __launch_bounds__(kBlock) void k_pp_write(ExtArgs a, DChains ch, int32_t n,
                                                      const uint64_t* leaf, const int64_t* pp_off,
                                                      int64_t n_pp, int32_t* pp_vtx) {
-  __shared__ int32_t s_row[kBlock * kPPRow];
+  using Entry = std::conditional_t<LDS, uint16_t, int32_t>;
+  constexpr int kPPSeg = LDS ? 32 : 16;
+  constexpr int kPPRow = kPPSeg + 4 / (int)sizeof(Entry);  // odd in words: rows in different banks
+  __shared__ Entry s_row[kBlock * kPPRow];
   __shared__ int64_t s_lo[kBlock];
   __shared__ int32_t s_len[kBlock];
   __shared__ int32_t s_done[kBlock];
@@ -1352,16 +1360,16 @@ __global__ __launch_bounds__(kBlock) void k_pp_write(ExtArgs a, DChains ch, int3
     lmax = y > lmax ? y : lmax;
   }
   int32_t done = len;  // entries done .. len - 1 are walked
-  int32_t* row = s_row + tid * kPPRow;
+  Entry* row = s_row + tid * kPPRow;
   for (int kb = lmax > 0 ? (lmax - 1) / kPPSeg * kPPSeg : -1; kb >= 0; kb -= kPPSeg) {
     // depths kb + kPPSeg - 1 down to kb: one dependent load per chain
-    int32_t v[kPPSeg];
+    Entry v[kPPSeg];
 #pragma unroll
     for (int m = kPPSeg - 1; m >= 0; --m) {
       const int k = kb + m;
-      v[m] = -1;
+      v[m] = 0;
       if (k < len) {
-        v[m] = vertex(at);
+        v[m] = (Entry)vertex(at);
         done = k;
         if (--at < c0 && up >= 0) {  // on to the parent's chain
           const int c = node_v(a.t.info[up]);
