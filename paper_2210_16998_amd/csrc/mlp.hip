@@ -420,8 +420,8 @@ tpg_status mlp_rows(tpg_mlp* m, int n) {
     m->act = nullptr;
     m->rows = 0;
     const size_t R = (size_t)rows;
-    const size_t floats = R * kIn + 2 * R * kOut + R / kRowTile * kPart +
-                          (size_t)kSplits * kTiles * 4096 + 64;
+    const size_t tiles = (size_t)std::min(kSplits, (rows + kSplitRows - 1) / kSplitRows) * kTiles * 4096;
+    const size_t floats = R * kIn + 2 * R * kOut + R / kRowTile * kPart + tiles + 64;
     const size_t halves = R * (64 + 2 * kHid + kOutPad + 2 * kHid);
     const size_t bytes = floats * 4 + halves * 2 + 1024;
     TPG_HIP(hipMalloc(&m->act, bytes));
@@ -435,7 +435,7 @@ tpg_status mlp_rows(tpg_mlp* m, int n) {
     m->dh2t = h; h += R * kHid;
     m->dh1t = h; h += R * kHid;
     float* f = (float*)h;
-    m->tiles = f; f += (size_t)kSplits * kTiles * 4096;
+    m->tiles = f; f += tiles;
     m->x = f; f += R * kIn;
     m->t = f; f += R * kOut;
     m->y = f; f += R * kOut;
