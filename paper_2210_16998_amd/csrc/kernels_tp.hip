@@ -328,8 +328,9 @@ hipError_t launch_chain_bfs(const DGraph& g, const DGraph& x, const DChains& ch,
 // BFS-tree part dropped, from its parent's.  Before, every test path was
 // spliced packed, sorted by merge rounds that compared them and unpacked
 // again: the test-path stage of the 400-vertex stress CFG took 21 ms of a
-// 30.8 ms call, now 11 ms of 19.9 (its rows alone are 21.8 GB); a batch of
-// 4096 CFGs went from 11.1 to 7.6 ms, a 1000-vertex CFG from 6.7 to 4.3.
+// 30.8 ms call, with this order 11 ms of 19.9, and 9.3 of 17.8 since (its rows
+// alone are 21.8 GB, 7.2 ms); a batch of 4096 CFGs went from 11.1 to 7.6 ms, a
+// 1000-vertex CFG from 6.7 to 4.3.
 
 // The child of node c labelled chain y (-1: none).
 __device__ __forceinline__ int64_t child_of(const TreeBufs& t, int64_t c, int y) {
