@@ -76,7 +76,7 @@ hipError_t launch_seed(const ExtArgs& a, int limit, hipStream_t st);
 // items: most parents per thread (tile <= threads * items); variant: 0
 // load-balanced tiles of 256 threads, 1 / 2 thread-per-parent with 256 /
 // 1024 threads; grid: persistent workgroups; li: index of the launch in its
-// batch (it extends level batch_start + li)
+// batch (it goes on from the level that the launch before it has left)
 // e0 / e1 (optional): events recorded at the kernel's own start and end
 hipError_t launch_extend(int W, int items, int variant, const ExtArgs& a, int grid, int li,
                          hipStream_t st, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
