@@ -78,7 +78,7 @@ struct tpg_workspace {
   // joined before the splice, so they overlap the extension
   hipStream_t side_stream = nullptr;
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  bool bfs_pending = false;
+  bool bfs_pending = false;  // forked, and its tables are not used up yet
   int num_cus = 256;
   size_t bytes = 0;
   uint64_t cap = 0;  // pool cap of the running call (0: none)
@@ -1142,11 +1142,12 @@ tpg_status bfs_start(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   hipStream_t side = ws->side_stream;
   TPG_HIP(hipEventRecord(ws->ev_fork, st));
   TPG_HIP(hipStreamWaitEvent(side, ws->ev_fork, 0));
-  TPG_HIP(launch_chain_bfs(ws->dg, ws->xg, ws->ch, tp_tree(ws, U.xn), ws->d_gbase,
-                           ws->tp_order.as<int32_t>(), ws->d_rbase, end_rows(ws, U.n),
-                           U.max_chains, U.max_words, side));
-  TPG_HIP(hipEventRecord(ws->ev_join, side));
   ws->bfs_pending = true;
+  const hipError_t e = launch_chain_bfs(ws->dg, ws->xg, ws->ch, tp_tree(ws, U.xn), ws->d_gbase,
+                                        ws->tp_order.as<int32_t>(), ws->d_rbase,
+                                        end_rows(ws, U.n), U.max_chains, U.max_words, side);
+  TPG_HIP(hipEventRecord(ws->ev_join, side));
+  TPG_HIP(e);
   return TPG_OK;
 }
 
@@ -1520,6 +1521,10 @@ tpg_status begin_call(const tpg_opts* opts, CallCtx& c) {
     c.own_ws = true;
   }
   TPG_HIP(hipSetDevice(c.ws->device));
+  // a call that failed before it joined the side stream: the search there still
+  // reads the union's arrays, which the next upload overwrites
+  if (c.ws->bfs_pending) TPG_HIP(hipStreamSynchronize(c.ws->side_stream));
+  c.ws->bfs_pending = false;
   c.st = (opts && opts->stream) ? (hipStream_t)opts->stream : c.ws->own_stream;
   c.ws->cap = opts ? opts->pool_cap_bytes : 0;
   if (c.ws->cap && c.ws->bytes > c.ws->cap)
@@ -1537,8 +1542,10 @@ tpg_status begin_call(const tpg_opts* opts, CallCtx& c) {
 tpg_status run_pp(const HostUnion& U, CallCtx& c, Timer& tm, TreeResult& R, PPResult& P,
                   OutSet& o, hipEvent_t* e_ext, int64_t rec0 = 0, int64_t msk0 = 0,
                   bool with_bfs = false, bool ahead = false) {
-  TPG_TRY(upload_union(c.ws, U, c.st));
+  // the search of a run that failed before (see begin_call)
+  if (c.ws->bfs_pending) TPG_HIP(hipStreamWaitEvent(c.st, c.ws->ev_join, 0));
   c.ws->bfs_pending = false;
+  TPG_TRY(upload_union(c.ws, U, c.st));
   if (with_bfs) TPG_TRY(bfs_start(c.ws, U, c.st));
   if (c.flags & TPG_FORCE_TWO_PASS)
     TPG_TRY(build_tree_twopass(c.ws, U, c.st, tm, R));
@@ -2991,6 +2998,7 @@ tpg_status tpg_batch_test_paths(const tpg_graph* const* graphs, int32_t n_graphs
         cg.failed = true;
       }
       if (graph) (void)hipGraphDestroy(graph);
+      ws->bfs_pending = false;  // what was captured has not run
       ws->io_mode = 0;
       ws->io_rec = nullptr;
       (void)hipGetLastError();
