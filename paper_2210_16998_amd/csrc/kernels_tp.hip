@@ -24,36 +24,52 @@ constexpr int kMaxComp = 4096;  // vertices per component
 // the BFS tree (every chain's predecessor on its lexicographically smallest
 // shortest path, the one a first-in first-out search with ascending
 // successors finds) and the test-path order of the arcs off it.  One workgroup
-// per component, everything in LDS:
-//  * distances by relaxing all chains at once until nothing changes (as many
-//    rounds as a shortest path has chains, not vertices);
+// per component, everything in LDS.  No step walks a chain's ancestors or all
+// arcs once per level, so a deep graph (early exits: 1000 vertices, 1000
+// levels) costs a barrier per level and not a pass over the graph:
+//  * distances by relaxing the arcs of the chains whose distance fell in the
+//    round before (a bit per chain), both ways in the same rounds; a chain of
+//    more than kBusy predecessors is a wave's;
 //  * where several predecessors are on shortest paths, the two paths are
 //    compared by walking them up, the longer one first, to the chain they
 //    share: the smaller chain after it decides.  The walk uses the tree as
-//    found so far, so it is repeated until no choice changes;
-//  * preorder ranks (children ascending) by sums along the ways up: of ones for
-//    the subtree sizes, then of the sizes of the smaller siblings;
+//    found so far, so it is repeated until no choice changes.  Two walks
+//    mostly meet after a few chains; where they do not, or the choices do not
+//    settle, one thread searches depth-first along the shortest
+//    paths' arcs, successors ascending, which meets every chain first on its
+//    smallest shortest path;
+//  * subtree sizes, preorder ranks (children ascending) and the arcs that end
+//    the subtrees along last children, by doubling the distance over which
+//    they are summed;
 //  * the arcs' order.  An arc (W, Y) off the tree comes right before W's first
 //    tree child above Y (rank s), or at the end of W's subtree; among arcs at
 //    one rank those that end a subtree come first, deepest first, then W's own
 //    before child s in the order of Y; the exit's path comes last at the exit's
 //    rank.  order[gbase[c] ..) lists the arcs as W << kArcSlotBits | slot of Y
 //    among W's successors, and the exit's chain X as ~X.
-// A search by vertices, one queue layer after the other, took 0.26 ms for 212
-// vertices and 2.5 ms for 1000 (98 and 174 chains), longer than the extension
-// beside it.
+// Bound by the LDS latencies of the rounds, a few hundred ns each: 51 us for
+// 212 vertices (98 chains), 82 for 1000 (174 chains), 1.06 ms for 1000 early
+// exits.  A search by vertices, one queue layer after the other, took 0.26 and
+// 2.5 ms for the first two; relaxing all arcs in every round, and walking up and
+// down the tree for the sums, 68 us, 129 us and 98 ms, and 0.85 ms for a switch of
+// 30 switches of 30 (0.06 now).
+constexpr int kBusy = 64;
 template <int MAXC, int NT, bool STAGE>
 __global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch, TpTree t,
                                                   const int32_t* gbase, int32_t* order) {
-  __shared__ int32_t s_d[MAXC + 1];  // distance before the chain; later sibling sums, arcs per rank
+  constexpr int Q = (MAXC + NT - 1) / NT;  // chains per thread: tid, tid + NT, ..
+  constexpr int kWords = MAXC / 32;
+  __shared__ int32_t s_d[MAXC + 1];  // distance before the chain; later arcs along last children, arcs per rank
   __shared__ int32_t s_b[MAXC + 1];  // distance after it; later subtree sizes, arcs that end one
   __shared__ int16_t s_par[MAXC];
-  __shared__ int16_t s_pre[MAXC];
-  __shared__ int16_t s_pend[MAXC];
+  __shared__ int16_t s_pre[MAXC];    // busy chains; later a step of the doublings, preorder ranks
+  __shared__ int16_t s_pend[MAXC];   // sibling sums; later ranks past the subtrees
+  __shared__ uint32_t s_f[3][2][kWords];  // chains to relax, from the entry and to the exit
   __shared__ int32_t s_w[NT / 64];
+  __shared__ int32_t s_nb[3], s_nbusy;
   extern __shared__ int32_t s_g[];  // STAGE: the component's sp, s, pp, p, len
   constexpr int kFar = 1 << 29;
-  const int c = (int)blockIdx.x, tid = (int)threadIdx.x;
+  const int c = (int)blockIdx.x, tid = (int)threadIdx.x, lane = lane_id(), wave = tid >> 6;
   const int x0 = x.cbase[c], n = x.cbase[c + 1] - x0;
   const int e0 = x.sp[x0], m = x.sp[x0 + n] - e0, f0 = x.pp[x0];
   int32_t* const l_sp = s_g;
@@ -83,26 +99,67 @@ __global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch
     s_d[i] = i == en ? 0 : kFar;
     s_b[i] = i == ex ? 0 : kFar;
   }
+  for (int i = tid; i < 6 * kWords; i += NT) (&s_f[0][0][0])[i] = 0;
+  if (tid == 0) s_nb[0] = s_nb[1] = s_nb[2] = s_nbusy = 0;
   __syncthreads();
-  int more;
-  do {
+  if (tid == 0) {
+    s_f[0][0][en >> 5] = 1u << (en & 31);
+    s_f[0][1][ex >> 5] = 1u << (ex & 31);
+  }
+  __syncthreads();
+  int more, any;
+  for (int cur = 0;;) {
+    const int nxt = cur == 2 ? 0 : cur + 1, old = cur == 0 ? 2 : cur - 1;
+    for (int i = tid; i < 2 * kWords; i += NT) (&s_f[old][0][0])[i] = 0;
+    if (tid == 0) s_nb[nxt] = 0;  // read two rounds ago
     more = 0;
-    for (int i = tid; i < n; i += NT) {
-      int d = s_d[i], b = s_b[i];
-      for (int k = pp(i); k < pp(i + 1); ++k) d = min(d, s_d[pred(k)] + len(pred(k)));
-      for (int k = sp(i); k < sp(i + 1); ++k) b = min(b, s_b[succ(k)] + len(succ(k)));
-      if (d < s_d[i] || b < s_b[i]) {
-        s_d[i] = d;
-        s_b[i] = b;
+    // chain y is d away over an arc
+    auto relax = [&](int dir, int y, int d) {
+      if (atomicMin(dir ? &s_b[y] : &s_d[y], d) > d) {
+        atomicOr(&s_f[nxt][dir][y >> 5], 1u << (y & 31));
         more = 1;
       }
+    };
+    for (int q = 0; q < Q; ++q) {
+      const int i = tid + q * NT;
+      if (i >= n) break;
+      if (s_f[cur][0][i >> 5] >> (i & 31) & 1) {
+        const int d = s_d[i] + len(i), k1 = sp(i + 1);
+        for (int k = sp(i); k < k1; ++k) relax(0, succ(k), d);
+      }
+      if (s_f[cur][1][i >> 5] >> (i & 31) & 1) {
+        const int b = s_b[i] + len(i), k0 = pp(i), k1 = pp(i + 1);
+        if (k1 - k0 > kBusy) {
+          s_pre[atomicAdd(&s_nb[cur], 1)] = (int16_t)i;
+          more = 1;
+        } else {
+          for (int k = k0; k < k1; ++k) relax(1, pred(k), b);
+        }
+      }
     }
-  } while (__syncthreads_or(more));
+    any = __syncthreads_or(more);
+    const int nb = s_nb[cur];
+    if (nb) {
+      for (int j = wave; j < nb; j += NT / 64) {
+        const int i = s_pre[j], b = s_b[i] + len(i), k1 = pp(i + 1);
+        for (int k = pp(i) + lane; k < k1; k += 64) relax(1, pred(k), b);
+      }
+      __syncthreads();
+    }
+    if (!any) break;
+    cur = nxt;
+  }
   // a predecessor on a shortest path (the first), the next chain to the exit
+  auto tight = [&](int p, int i) { return s_d[p] + len(p) == s_d[i]; };
   for (int i = tid; i < n; i += NT) {
     int par = -1, nx = -1;
-    for (int k = pp(i); k < pp(i + 1) && par < 0; ++k)
-      if (s_d[pred(k)] + len(pred(k)) == s_d[i]) par = pred(k);
+    const int k0 = pp(i), k1 = pp(i + 1);
+    if (k1 - k0 > kBusy) {
+      s_pre[atomicAdd(&s_nbusy, 1)] = (int16_t)i;
+    } else {
+      for (int k = k0; k < k1 && par < 0; ++k)
+        if (tight(pred(k), i)) par = pred(k);
+    }
     for (int k = sp(i); k < sp(i + 1) && nx < 0; ++k)
       if (s_b[succ(k)] + len(succ(k)) == s_b[i]) nx = succ(k);
     if (i == en) par = -1;
@@ -113,8 +170,21 @@ __global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch
     t.cback[x0 + i] = s_b[i];
   }
   __syncthreads();
+  const int nbusy = s_nbusy;
+  for (int j = wave; j < nbusy; j += NT / 64) {
+    const int i = s_pre[j], k1 = pp(i + 1);
+    for (int k0 = pp(i); k0 < k1; k0 += 64) {
+      const int p = k0 + lane < k1 ? pred(k0 + lane) : -1;
+      const uint64_t on = __ballot(p >= 0 && tight(p, i));
+      if (!on) continue;
+      if (lane == 0) s_par[i] = (int16_t)pred(k0 + __builtin_ctzll(on));
+      break;
+    }
+  }
+  __syncthreads();
   // whether the tree path to a's end precedes the equally long one to b's;
   // every step up shortens a path, whatever the tree holds so far
+  int steps = 0;
   auto before = [&](int a, int b) {
     int ca = a, cb = b;
     while (a != b && a >= 0 && b >= 0) {
@@ -127,46 +197,178 @@ __global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch
         cb = b;
         b = s_par[b];
       }
+      ++steps;
     }
     return ca < cb;
   };
-  do {
+  // steps of a thread's walks before the search takes over, which needs about
+  // as many for n chains
+  const int walks = 4 * n + 256;
+  bool over = false;
+  auto chosen = [&](int i, int best) {
+    if (best != s_par[i]) {
+      s_par[i] = (int16_t)best;
+      more = 1;
+    }
+  };
+  for (int round = 0;; ++round) {
     more = 0;
-    for (int i = tid; i < n; i += NT) {
-      if (i == en) continue;
+    for (int i = tid; i < n && steps <= walks; i += NT) {
+      const int k0 = pp(i), k1 = pp(i + 1);
+      if (i == en || k1 - k0 > kBusy) continue;
       int best = -1;
-      for (int k = pp(i); k < pp(i + 1); ++k) {
+      for (int k = k0; k < k1 && steps <= walks; ++k) {
         const int p = pred(k);
-        if (s_d[p] + len(p) == s_d[i] && (best < 0 || before(p, best))) best = p;
+        if (tight(p, i) && (best < 0 || before(p, best))) best = p;
       }
-      if (best != s_par[i]) {
-        s_par[i] = (int16_t)best;
-        more = 1;
+      chosen(i, best);
+    }
+    for (int j = wave; j < nbusy; j += NT / 64) {
+      const int i = s_pre[j], k1 = pp(i + 1);
+      int best = -1;
+      for (int k = pp(i) + lane; k < k1 && steps <= walks; k += 64) {
+        const int p = pred(k);
+        if (tight(p, i) && (best < 0 || before(p, best))) best = p;
       }
+      for (int d = 32; d >= 1; d >>= 1) {
+        const int o = __shfl_xor(best, d, 64);
+        if (o >= 0 && (best < 0 || before(o, best))) best = o;
+      }
+      if (lane == 0) chosen(i, best);
+    }
+    any = __syncthreads_or(more);
+    over = __syncthreads_or(steps > walks || (more && round == 16));
+    if (!any || over) break;
+  }
+  if (over) {
+    for (int i = tid; i < n; i += NT) {
+      s_pre[i] = i == en;  // seen
+      s_pend[i] = 0;       // arcs looked at
+    }
+    __syncthreads();
+    if (tid == 0) {
+      for (int u = en; u >= 0;) {
+        const int k = sp(u) + s_pend[u];
+        if (k == sp(u + 1)) {
+          u = s_par[u];
+          continue;
+        }
+        ++s_pend[u];
+        const int y = succ(k);
+        if (s_pre[y] || !tight(u, y)) continue;
+        s_pre[y] = 1;
+        s_par[y] = (int16_t)u;
+        u = y;
+      }
+    }
+    __syncthreads();
+  }
+  for (int i = tid; i < n; i += NT) t.tpar[x0 + i] = s_par[i] < 0 ? -1 : x0 + s_par[i];
+  // One step of a doubling: link (2^k steps up or down) goes on to its link's
+  // link, and `add` gets the sum held where it led.
+  auto tree_arc = [&](int w, int k) { return s_par[succ(k)] == w; };
+  for (int i = tid; i < n; i += NT) {
+    s_b[i] = 1;
+    s_pre[i] = s_par[i];
+  }
+  __syncthreads();
+  // subtree sizes: s_b[i] of the descendants less than 2^k below
+  do {
+    int16_t up[Q], on[Q];
+    int32_t v[Q];
+    more = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int i = tid + q * NT;
+      up[q] = i < n ? s_pre[i] : (int16_t)-1;
+      v[q] = i < n ? s_b[i] : 0;
+      on[q] = up[q] >= 0 ? s_pre[up[q]] : (int16_t)-1;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      if (up[q] < 0) continue;
+      atomicAdd(&s_b[up[q]], v[q]);
+      s_pre[tid + q * NT] = on[q];
+      more |= on[q] >= 0;
+    }
+  } while (__syncthreads_or(more));
+  // per chain: its tree children's sibling sums, its last tree child (s_pre),
+  // the arcs after it (s_d)
+  int32_t tail[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int w = tid + q * NT;
+    tail[q] = 0;
+    if (w >= n) continue;
+    int last = -1, sum = 1;
+    for (int k = sp(w); k < sp(w + 1); ++k) {
+      ++tail[q];
+      if (!tree_arc(w, k)) continue;
+      tail[q] = 0;
+      last = succ(k);
+      s_pend[last] = (int16_t)sum;
+      sum += s_b[last];
+    }
+    if (w == en) s_pend[w] = 0;
+    s_pre[w] = (int16_t)last;
+    s_d[w] = tail[q];
+  }
+  __syncthreads();
+  // arcs that end the subtrees along the last tree children below w
+  do {
+    int16_t on[Q];
+    int32_t v[Q];
+    more = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int i = tid + q * NT;
+      const int l = i < n ? s_pre[i] : -1;
+      v[q] = l >= 0 ? s_d[l] : 0;
+      on[q] = l >= 0 ? s_pre[l] : (int16_t)-1;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int i = tid + q * NT;
+      if (i >= n) continue;
+      s_d[i] += v[q];
+      s_pre[i] = on[q];
+      more |= on[q] >= 0;
+    }
+  } while (__syncthreads_or(more));
+  int32_t deeper[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = tid + q * NT;
+    deeper[q] = i < n ? s_d[i] - tail[q] : 0;
+    if (i < n) s_pre[i] = s_par[i];
+  }
+  __syncthreads();
+  // preorder ranks: sibling sums along the way up
+  do {
+    int16_t on[Q], v[Q];
+    more = 0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int i = tid + q * NT;
+      const int u = i < n ? s_pre[i] : -1;
+      v[q] = u >= 0 ? s_pend[u] : (int16_t)0;
+      on[q] = u >= 0 ? s_pre[u] : (int16_t)-1;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int i = tid + q * NT;
+      if (i >= n) continue;
+      s_pend[i] += v[q];
+      s_pre[i] = on[q];
+      more |= on[q] >= 0;
     }
   } while (__syncthreads_or(more));
   for (int i = tid; i < n; i += NT) {
-    t.tpar[x0 + i] = s_par[i] < 0 ? -1 : x0 + s_par[i];
-    s_b[i] = 1;
-  }
-  __syncthreads();
-  for (int i = tid; i < n; i += NT)
-    for (int a = s_par[i]; a >= 0; a = s_par[a]) atomicAdd(&s_b[a], 1);
-  __syncthreads();
-  for (int i = tid; i < n; i += NT) {
-    int d = 1;
-    const int p = s_par[i];
-    if (p >= 0)
-      for (int k = sp(p); k < sp(p + 1) && succ(k) < i; ++k)
-        if (s_par[succ(k)] == p) d += s_b[succ(k)];
-    s_d[i] = d;
-  }
-  __syncthreads();
-  for (int i = tid; i < n; i += NT) {
-    int r = 0;
-    for (int a = i; s_par[a] >= 0; a = s_par[a]) r += s_d[a];
-    s_pre[i] = (int16_t)r;
-    s_pend[i] = (int16_t)(r + s_b[i]);
+    s_pre[i] = s_pend[i];
+    s_pend[i] = (int16_t)(s_pend[i] + s_b[i]);
   }
   __syncthreads();
   int32_t* s_at = s_d;   // arcs per rank, then their first place
@@ -176,25 +378,21 @@ __global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch
     s_end[i] = 0;
   }
   __syncthreads();
-  auto tree_arc = [&](int w, int k) { return s_par[succ(k)] == w; };
-  // rank at which arc k of w comes
-  auto rank_of = [&](int w, int k, bool& ends) {
-    for (int j = k + 1; j < sp(w + 1); ++j)
-      if (tree_arc(w, j)) {
-        ends = false;
-        return (int)s_pre[succ(j)];
-      }
-    ends = true;
-    return (int)s_pend[w];
+  // w's arcs off the tree in runs [k, j) of one rank
+  auto runs = [&](int w, auto&& f) {
+    const int k1 = sp(w + 1);
+    for (int k = sp(w); k < k1;) {
+      int j = k;
+      while (j < k1 && !tree_arc(w, j)) ++j;
+      if (j > k) f(k, j, j == k1, j == k1 ? (int)s_pend[w] : (int)s_pre[succ(j)]);
+      k = j + 1;
+    }
   };
   for (int w = tid; w < n; w += NT) {
-    for (int k = sp(w); k < sp(w + 1); ++k) {
-      if (tree_arc(w, k)) continue;
-      bool ends;
-      const int r = rank_of(w, k, ends);
-      atomicAdd(&s_at[r], 1);
-      if (ends) atomicAdd(&s_end[r], 1);
-    }
+    runs(w, [&](int k, int j, bool ends, int r) {
+      atomicAdd(&s_at[r], j - k);
+      if (ends) atomicAdd(&s_end[r], j - k);
+    });
     if (w == ex) atomicAdd(&s_at[s_pre[w]], 1);
   }
   __syncthreads();
@@ -208,34 +406,14 @@ __global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch
     carry += tot;
   }
   __syncthreads();
-  for (int w = tid; w < n; w += NT) {
-    int deeper = -1;  // arcs that end the subtrees nested in the end of w's
-    int same = 0, last_r = -1;
-    for (int k = sp(w); k < sp(w + 1); ++k) {
-      if (tree_arc(w, k)) continue;
-      bool ends;
-      const int r = rank_of(w, k, ends);
-      same = r == last_r ? same + 1 : 0;  // earlier arcs of w at this rank
-      last_r = r;
-      int ahead = s_end[r];
-      if (ends) {
-        if (deeper < 0) {
-          deeper = 0;
-          for (int y = w;;) {  // down the last tree children
-            int child = -1, tail = 0;
-            for (int j = sp(y + 1) - 1; j >= sp(y) && child < 0; --j) {
-              if (tree_arc(y, j)) child = succ(j);
-              else ++tail;  // an arc after the last tree child: it ends y's subtree
-            }
-            if (y != w) deeper += tail;
-            if (child < 0) break;
-            y = child;
-          }
-        }
-        ahead = deeper;
-      }
-      order[s_at[r] + ahead + same] = (x0 + w) << kArcSlotBits | (k - sp(w));
-    }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int w = tid + q * NT;
+    if (w >= n) continue;
+    runs(w, [&](int k, int j, bool ends, int r) {
+      int at = s_at[r] + (ends ? deeper[q] : s_end[r]);
+      for (int i = k; i < j; ++i) order[at++] = (x0 + w) << kArcSlotBits | (i - sp(w));
+    });
     if (w == ex) {
       const int r = s_pre[w];
       order[(r < n ? s_at[r + 1] : carry) - 1] = ~(x0 + w);
@@ -282,20 +460,22 @@ hipError_t launch_chain_bfs(const DGraph& g, const DGraph& x, const DChains& ch,
                             const int32_t* gbase, int32_t* order, const int32_t* rbase,
                             const EndRows& b, int max_chains, int max_words, hipStream_t st) {
   const unsigned grid = (unsigned)x.n_comp;
-  // staged graphs of up to 16 KiB; a wave per component when there are many
+  // staged graphs of up to 16 KiB (40 KiB from 257 chains on, which are seldom
+  // many at a time); a wave per component when there are many (18 chains alone
+  // take four waves 22 us and one 21)
   const size_t lds = sizeof(int32_t) * (size_t)max_words;
-  const bool stage = lds <= 16384;
-  if (max_chains <= 256) {
-    if (x.n_comp >= 64) {
-      if (stage) k_chain_bfs<256, 64, true><<<grid, 64, lds, st>>>(g, x, ch, t, gbase, order);
-      else k_chain_bfs<256, 64, false><<<grid, 64, 0, st>>>(g, x, ch, t, gbase, order);
-    } else {
-      if (stage) k_chain_bfs<256, 256, true><<<grid, 256, lds, st>>>(g, x, ch, t, gbase, order);
-      else k_chain_bfs<256, 256, false><<<grid, 256, 0, st>>>(g, x, ch, t, gbase, order);
-    }
-  } else {
-    k_chain_bfs<kMaxComp, 256, false><<<grid, 256, 0, st>>>(g, x, ch, t, gbase, order);
-  }
+  auto run = [&](auto staged, auto plain, int threads, size_t most) {
+    if (lds <= most) staged<<<grid, threads, lds, st>>>(g, x, ch, t, gbase, order);
+    else plain<<<grid, threads, 0, st>>>(g, x, ch, t, gbase, order);
+  };
+  if (max_chains <= 256 && x.n_comp >= 64)
+    run(k_chain_bfs<256, 64, true>, k_chain_bfs<256, 64, false>, 64, 16384);
+  else if (max_chains <= 256)
+    run(k_chain_bfs<256, 256, true>, k_chain_bfs<256, 256, false>, 256, 16384);
+  else if (max_chains <= 1024)
+    run(k_chain_bfs<1024, 256, true>, k_chain_bfs<1024, 256, false>, 256, 40960);
+  else
+    k_chain_bfs<kMaxComp, 1024, false><<<grid, 1024, 0, st>>>(g, x, ch, t, gbase, order);
   k_chain_rows<<<(unsigned)x.n, 64, 0, st>>>(g, x, ch, t, rbase, b);
   return hipGetLastError();
 }
