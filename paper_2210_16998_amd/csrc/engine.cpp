@@ -38,6 +38,7 @@ struct HostUnion {
   std::vector<int32_t> choff{0}, chv, chof, chpos;  // see DChains
   std::vector<int32_t> gbase{0};  // arcs off the BFS tree and exit paths, by component
   std::vector<int32_t> rbase{0};  // entries of the chains' prefix (suffix) rows, by component
+  int32_t max_deg = 0;                    // most successors of a vertex
   int32_t max_chains = 1, max_words = 1;  // chains, and graph words (sp, s, pp, p, len), of a component
   std::vector<int32_t> xhead;                       // first vertex of every chain
   std::vector<int32_t> rot;  // chains of two or more vertices, ascending
@@ -380,6 +381,7 @@ void add_component(HostUnion& U, const tpg_graph* g, int32_t block = 0) {
   // every chain but the entry's has one BFS-tree arc; the exit's path counts too
   U.gbase.push_back(U.gbase.back() + (int32_t)c.s.size() - (c.n - 1) + 1);
   U.rbase.push_back(U.rbase.back() + c.n * g->n);  // at most 2^12 * 2^17 in a union
+  U.max_deg = std::max(U.max_deg, g->max_out_degree);
   U.max_chains = std::max(U.max_chains, c.n);
   U.max_words = std::max(U.max_words, 3 * c.n + 2 + 2 * (int32_t)c.s.size());
   U.n_comp += 1;
@@ -1010,9 +1012,13 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
     key_add(key, R.count[L]);
   }
   std::vector<uint8_t> key_down = key;
-  // both sweeps take up to kRun levels per launch (a launch costs ~7 us
-  // however little it does)
-  constexpr int kRun = 2;  // 3 measured slower: deeper per-thread chains
+  // both sweeps take two levels per launch (a launch costs ~7 us however little
+  // it does; three measured slower: deeper per-thread chains) unless a vertex
+  // has many successors, all of whose children are then one thread's: a switch
+  // of 64 switches of 62 took 2.21 ms with two and takes 0.78 with one; up to
+  // eight successors two are as fast or faster (fans of 12 0.42 and 0.40 ms, of 8
+  // 0.41 and 0.42, of 4 0.48 and 0.50, a 212-vertex CFG 1.74 and 1.78)
+  const int kRun = U.max_deg <= 8 ? 2 : 1;
   TPG_TRY(run_seq(ws, ws->rank_up, std::move(key), st, [&]() -> hipError_t {
     hipError_t e = launch_path_lengths(a, R.count[1], N, st);
     for (int L = R.Lmax; L >= 1 && e == hipSuccess;) {

@@ -1027,8 +1027,9 @@ __device__ __forceinline__ int32_t canon_child(const ExtArgs& a, const TpTree& t
   if (cx < 0) {
     const int vx = node_v(a.t.info[x]), vy = node_v(a.t.info[y]);
     if (t.tpar[vy] == vx) return -1;
-    // the first arc off the BFS tree: the child of vx's root (root k is chain k)
-    int s = 0;
+    // the first arc off the BFS tree: the child of vx's root (root k is chain
+    // k), whose children are all of vx's successors
+    int s = slot;
     const int s0 = a.g.sp[vx], s1 = a.g.sp[vx + 1];
     while (s0 + s + 1 < s1 && a.g.s[s0 + s] != vy) ++s;
     return a.t.cstart[vx] + s;

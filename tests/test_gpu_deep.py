@@ -9,6 +9,7 @@ import pytest
 import oracle
 from paper_2210_16998_amd import cfggen, tpg
 from tests.gpu_util import check_tp, say, ws
+from tests.test_gpu_narrow import _fans
 
 pytestmark = pytest.mark.gpu
 
@@ -58,6 +59,18 @@ def test_early_exits(n, flip):
 def test_switches_into_one_exit(a, b):
     say("case", a, b)
     check_tp(_switches(a, b), local=True)
+
+
+# levels of more than 2048 nodes, swept one or two to a launch: eight successors
+# and nine; odd and even numbers of such levels
+@pytest.mark.parametrize("widths", [(8, 8, 8, 8), (9, 9, 9, 4), (8, 8, 8, 8, 3), (9, 3, 9, 9, 3), (9, 9, 9)])
+@pytest.mark.parametrize("back", [False, True])
+def test_wide_levels_by_successors(widths, back):
+    if back:
+        widths = widths[:3]  # and the loop's paths
+    g, _ = _fans(widths, back)
+    say("case", g.name, back)
+    check_tp(g, local=True)
 
 
 # fan 31: 63 predecessors, one thread's; 34: a wave's.  The thread's walks pass
