@@ -37,7 +37,7 @@ struct HostUnion {
   std::vector<int32_t> xsp{0}, xs, xpp{0}, xp, xloc, xlen, xcomp, xcbase{0};
   std::vector<int32_t> choff{0}, chv, chof, chpos;  // see DChains
   std::vector<int32_t> gbase{0};  // arcs off the BFS tree and exit paths, by component
-  std::vector<int32_t> rbase{0};  // entries of the chains' prefix (suffix) rows, by component
+  std::vector<int32_t> pbase{0}, sbase{0};  // entries of the chains' prefix (suffix) rows, by component
   int32_t max_deg = 0;                    // most successors of a vertex
   int32_t max_chains = 1, max_words = 1;  // chains, and graph words (sp, s, pp, p, len), of a component
   std::vector<int32_t> xhead;                       // first vertex of every chain
@@ -114,7 +114,7 @@ struct tpg_workspace {
   DGraph dg{}, xg{};   // the union, and the union of its chains
   DChains ch{};
   const int32_t* d_gbase = nullptr;  // HostUnion::gbase
-  const int32_t* d_rbase = nullptr;  // HostUnion::rbase
+  const int32_t *d_pbase = nullptr, *d_sbase = nullptr;  // HostUnion::pbase, sbase
   const int32_t* d_rot = nullptr;    // HostUnion::rot
 
   // path tree
@@ -380,7 +380,9 @@ void add_component(HostUnion& U, const tpg_graph* g, int32_t block = 0) {
   U.xcbase.push_back(U.xn);
   // every chain but the entry's has one BFS-tree arc; the exit's path counts too
   U.gbase.push_back(U.gbase.back() + (int32_t)c.s.size() - (c.n - 1) + 1);
-  U.rbase.push_back(U.rbase.back() + c.n * g->n);  // at most 2^12 * 2^17 in a union
+  // at most 2^12 * 2^17 in a union
+  U.pbase.push_back(U.pbase.back() + c.pfx_entries);
+  U.sbase.push_back(U.sbase.back() + c.sfx_entries);
   U.max_deg = std::max(U.max_deg, g->max_out_degree);
   U.max_chains = std::max(U.max_chains, c.n);
   U.max_words = std::max(U.max_words, 3 * c.n + 2 + 2 * (int32_t)c.s.size());
@@ -399,7 +401,7 @@ tpg_status upload_union(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   const std::vector<int32_t>* parts[] = {
       &U.sp, &U.s, &U.pp, &U.p, &U.loc, &U.comp, &U.cbase, &U.centry, &U.cexit,
       &U.xsp, &U.xs, &U.xpp, &U.xp, &U.xloc, &U.xlen, &U.xcomp, &U.xcbase,
-      &U.choff, &U.chv, &U.chof, &U.chpos, &U.gbase, &U.rbase, &U.rot};
+      &U.choff, &U.chv, &U.chof, &U.chpos, &U.gbase, &U.pbase, &U.sbase, &U.rot};
   constexpr int kParts = sizeof(parts) / sizeof(parts[0]);
   size_t words = 0, at[kParts];
   for (int i = 0; i < kParts; ++i) {
@@ -443,8 +445,9 @@ tpg_status upload_union(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   ws->xg = x;
   ws->ch = DChains{q + at[17], q + at[18], q + at[19], q + at[20]};
   ws->d_gbase = q + at[21];
-  ws->d_rbase = q + at[22];
-  ws->d_rot = q + at[23];
+  ws->d_pbase = q + at[22];
+  ws->d_sbase = q + at[23];
+  ws->d_rot = q + at[24];
   ws->union_uids = U.uids;
   return TPG_OK;
 }
@@ -1132,6 +1135,8 @@ TpTree tp_tree(tpg_workspace* ws, int xn) {
   t.nx = t.tpar + xn;
   t.cdist = t.nx + xn;
   t.cback = t.cdist + xn;
+  t.prow = t.cback + xn;
+  t.srow = t.prow + xn;
   t.canon = ws->canon.as<int32_t>();
   t.leaf_canon = ws->leaf_canon.as<int32_t>();
   return t;
@@ -1141,16 +1146,16 @@ TpTree tp_tree(tpg_workspace* ws, int xn) {
 // uploaded union, on the side stream after everything already queued on `st`.
 tpg_status bfs_start(tpg_workspace* ws, const HostUnion& U, hipStream_t st) {
   TPG_TRY(ws_reserve(ws, ws->bfs_i32, sizeof(int32_t) * 4 * (size_t)U.n));
-  TPG_TRY(ws_reserve(ws, ws->pfx, sizeof(int32_t) * ((size_t)U.rbase.back() + 1)));
-  TPG_TRY(ws_reserve(ws, ws->sfx, sizeof(int32_t) * ((size_t)U.rbase.back() + 1)));
-  TPG_TRY(ws_reserve(ws, ws->tp_links, sizeof(int32_t) * 4 * (size_t)U.xn));
+  TPG_TRY(ws_reserve(ws, ws->pfx, sizeof(int32_t) * ((size_t)U.pbase.back() + 1)));
+  TPG_TRY(ws_reserve(ws, ws->sfx, sizeof(int32_t) * ((size_t)U.sbase.back() + 1)));
+  TPG_TRY(ws_reserve(ws, ws->tp_links, sizeof(int32_t) * 6 * (size_t)U.xn));
   TPG_TRY(ws_reserve(ws, ws->tp_order, sizeof(int32_t) * (size_t)(U.gbase.back() + 1)));
   hipStream_t side = ws->side_stream;
   TPG_HIP(hipEventRecord(ws->ev_fork, st));
   TPG_HIP(hipStreamWaitEvent(side, ws->ev_fork, 0));
   ws->bfs_pending = true;
   const hipError_t e = launch_chain_bfs(ws->dg, ws->xg, ws->ch, tp_tree(ws, U.xn), ws->d_gbase,
-                                        ws->tp_order.as<int32_t>(), ws->d_rbase,
+                                        ws->tp_order.as<int32_t>(), ws->d_pbase, ws->d_sbase,
                                         end_rows(ws, U.n), U.max_chains, U.max_words, side);
   TPG_HIP(hipEventRecord(ws->ev_join, side));
   TPG_HIP(e);

@@ -223,6 +223,7 @@ tpg_status tpg_load_cfg_csr(int32_t n, const int64_t* row_ptr, const int32_t* co
       for (int32_t k = g->succ_ptr[v]; k < g->succ_ptr[v + 1]; ++k)
         g->pred[fill[g->succ[k]]++] = v;
   }
+  std::vector<int32_t> dist, back;  // empty for any digraph
   if (!(load_flags & TPG_LOAD_ANY_DIGRAPH)) {
     if (g->pred_ptr[entry + 1] != g->pred_ptr[entry]) {
       delete g;
@@ -232,29 +233,29 @@ tpg_status tpg_load_cfg_csr(int32_t n, const int64_t* row_ptr, const int32_t* co
       delete g;
       return fail(TPG_ERR_BAD_ENTRY_EXIT, "exit %d has successors", exit);
     }
-    std::vector<char> seen(n, 0);
+    dist.assign(n, -1);  // vertices before it on a shortest path
     std::deque<int32_t> q{entry};
-    seen[entry] = 1;
+    dist[entry] = 0;
     while (!q.empty()) {
       int32_t u = q.front();
       q.pop_front();
       for (int32_t k = g->succ_ptr[u]; k < g->succ_ptr[u + 1]; ++k)
-        if (!seen[g->succ[k]]) seen[g->succ[k]] = 1, q.push_back(g->succ[k]);
+        if (dist[g->succ[k]] < 0) dist[g->succ[k]] = dist[u] + 1, q.push_back(g->succ[k]);
     }
-    std::vector<char> back(n, 0);
+    back.assign(n, -1);  // vertices after it
     q.push_back(exit);
-    back[exit] = 1;
+    back[exit] = 0;
     while (!q.empty()) {
       int32_t u = q.front();
       q.pop_front();
       for (int32_t k = g->pred_ptr[u]; k < g->pred_ptr[u + 1]; ++k)
-        if (!back[g->pred[k]]) back[g->pred[k]] = 1, q.push_back(g->pred[k]);
+        if (back[g->pred[k]] < 0) back[g->pred[k]] = back[u] + 1, q.push_back(g->pred[k]);
     }
     for (int32_t v = 0; v < n; ++v)
-      if (!seen[v] || !back[v]) {
+      if (dist[v] < 0 || back[v] < 0) {
         delete g;
         return fail(TPG_ERR_UNREACHABLE, "vertex %d is %s", v,
-                    !seen[v] ? "unreachable from entry" : "unable to reach exit");
+                    dist[v] < 0 ? "unreachable from entry" : "unable to reach exit");
       }
   }
   try {
@@ -262,6 +263,14 @@ tpg_status tpg_load_cfg_csr(int32_t n, const int64_t* row_ptr, const int32_t* co
   } catch (const std::bad_alloc&) {
     delete g;
     return fail(TPG_ERR_OOM_HOST, "graph handle");
+  }
+  if (!dist.empty()) {
+    Chains& c = g->chains;
+    for (int32_t x = 0; x < c.n; ++x) {
+      const int32_t len = c.off[x + 1] - c.off[x];
+      c.pfx_entries += dist[c.v[c.off[x]]] + len;
+      c.sfx_entries += len + back[c.v[c.off[x + 1] - 1]];
+    }
   }
   *out = g;
   return TPG_OK;

@@ -27,6 +27,10 @@ struct Chains {
   std::vector<int32_t> off, v;   // vertices of chain x, in order: v[off[x] .. off[x + 1])
   std::vector<int32_t> of, pos;  // per vertex: its chain and its place there
   std::vector<int32_t> sp, s, pp, p;  // contracted CSR and its reverse (rows ascending)
+  // Entries of the rows that the test paths' prefixes (suffixes) are cut from:
+  // every chain behind the shortest way to it (before the one on to the exit);
+  // 0 without an entry and an exit.
+  int32_t pfx_entries = 0, sfx_entries = 0;
 };
 
 }  // namespace tpg

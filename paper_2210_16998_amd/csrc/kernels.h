@@ -125,6 +125,7 @@ struct TpTree {
   int32_t* nx;          // per chain: the chain after it on the shortest way to the exit
   int32_t* cdist;       // per chain: vertices before its first on the way from the entry
   int32_t* cback;       // per chain: vertices after its last on the way to the exit
+  int32_t *prow, *srow; // per chain: its row among the prefix (suffix) rows
   int32_t* canon;       // per node: the node of its path without the chains before the
                         // last one of its first BFS-tree part (-1: all of it is one)
   int32_t* leaf_canon;  // the same per prime path
@@ -281,13 +282,14 @@ struct EndRows {
   int32_t *pfx, *sfx;
 };
 // The BFS tree over the chains into t, the arcs' test-path order (gbase[c]:
-// the components' first places, c = 0 .. n_comp), and b's rows (rbase[c]: the
-// components' first entries).  max_chains, max_words: chains, and words of
+// the components' first places, c = 0 .. n_comp), and b's rows (pbase[c],
+// sbase[c]: the components' first entries).  max_chains, max_words: chains, and words of
 // sp, s, pp, p and len, of the largest component.
 constexpr int kArcSlotBits = 6;  // a successor slot; chain ids take 17 bits
 hipError_t launch_chain_bfs(const DGraph& g, const DGraph& x, const DChains& ch, const TpTree& t,
-                            const int32_t* gbase, int32_t* order, const int32_t* rbase,
-                            const EndRows& b, int max_chains, int max_words, hipStream_t st);
+                            const int32_t* gbase, int32_t* order, const int32_t* pbase,
+                            const int32_t* sbase, const EndRows& b, int max_chains, int max_words,
+                            hipStream_t st);
 // per-component output starts: pp_start[c] = rank of the first PP of c and
 // ppv_start[c] = offset of its first entry (after the PP offsets exist; rb:
 // see launch_roots, over all vertices; c = n_comp: the totals)

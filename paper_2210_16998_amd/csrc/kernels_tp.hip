@@ -56,7 +56,8 @@ constexpr int kMaxComp = 4096;  // vertices per component
 constexpr int kBusy = 64;
 template <int MAXC, int NT, bool STAGE>
 __global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch, TpTree t,
-                                                  const int32_t* gbase, int32_t* order) {
+                                                  const int32_t* gbase, int32_t* order,
+                                                  const int32_t* pbase, const int32_t* sbase) {
   constexpr int Q = (MAXC + NT - 1) / NT;  // chains per thread: tid, tid + NT, ..
   constexpr int kWords = MAXC / 32;
   __shared__ int32_t s_d[MAXC + 1];  // distance before the chain; later arcs along last children, arcs per rank
@@ -65,7 +66,7 @@ __global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch
   __shared__ int16_t s_pre[MAXC];    // busy chains; later a step of the doublings, preorder ranks
   __shared__ int16_t s_pend[MAXC];   // sibling sums; later ranks past the subtrees
   __shared__ uint32_t s_f[3][2][kWords];  // chains to relax, from the entry and to the exit
-  __shared__ int32_t s_w[NT / 64];
+  __shared__ int64_t s_w[NT / 64];
   __shared__ int32_t s_nb[3], s_nbusy;
   extern __shared__ int32_t s_g[];  // STAGE: the component's sp, s, pp, p, len
   constexpr int kFar = 1 << 29;
@@ -170,6 +171,19 @@ __global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch
     t.cback[x0 + i] = s_b[i];
   }
   __syncthreads();
+  // the chains' rows one after another, prefixes in the low half of the sums
+  int64_t at = (int64_t)sbase[c] << 32 | pbase[c];
+  for (int k0 = 0; k0 < n; k0 += NT) {
+    const int i = k0 + tid;
+    const int64_t v = i < n ? (int64_t)(s_b[i] + len(i)) << 32 | (s_d[i] + len(i)) : 0;
+    int64_t tot;
+    const int64_t to = at + block_excl_scan<NT, int64_t>(v, tot, s_w);
+    if (i < n) {
+      t.prow[x0 + i] = (int32_t)to;
+      t.srow[x0 + i] = (int32_t)(to >> 32);
+    }
+    at += tot;
+  }
   const int nbusy = s_nbusy;
   for (int j = wave; j < nbusy; j += NT / 64) {
     const int i = s_pre[j], k1 = pp(i + 1);
@@ -400,10 +414,10 @@ __global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch
   for (int k0 = 0; k0 <= n; k0 += NT) {
     const int k = k0 + tid;
     const int v = k <= n ? s_at[k] : 0;
-    int tot;
-    const int pre = block_excl_scan<NT, int>(v, tot, s_w);
+    int64_t tot;
+    const int pre = (int)block_excl_scan<NT, int64_t>(v, tot, s_w);
     if (k <= n) s_at[k] = carry + pre;
-    carry += tot;
+    carry += (int)tot;
   }
   __syncthreads();
 #pragma unroll
@@ -422,14 +436,11 @@ __global__ __launch_bounds__(NT) void k_chain_bfs(DGraph g, DGraph x, DChains ch
 }
 
 // The rows that the prefixes and suffixes are cut from, one wave per chain x:
-// the way to x and x itself, x and the way on from it; row x of component c
-// starts at rbase[c] + (x's number there) * (vertices of c), in both.  Then
-// per vertex of x where its prefix and suffix are and how long.
-__global__ __launch_bounds__(64) void k_chain_rows(DGraph g, DGraph x, DChains ch, TpTree t,
-                                                   const int32_t* rbase, EndRows b) {
+// the way to x and x itself, x and the way on from it.  Then per vertex of x
+// where its prefix and suffix are and how long.
+__global__ __launch_bounds__(64) void k_chain_rows(DChains ch, TpTree t, EndRows b) {
   const int c0 = (int)blockIdx.x, lane = lane_id();
-  const int comp = x.comp[c0];
-  const int at = rbase[comp] + (c0 - x.cbase[comp]) * (g.cbase[comp + 1] - g.cbase[comp]);
+  const int pat = t.prow[c0], sat = t.srow[c0];
   const int o = ch.off[c0], m = ch.off[c0 + 1] - o;
   const int df = t.cdist[c0], db = t.cback[c0];
   // both ways in step
@@ -437,13 +448,13 @@ __global__ __launch_bounds__(64) void k_chain_rows(DGraph g, DGraph x, DChains c
     if (p >= 0) {
       const int po = ch.off[p], pm = ch.off[p + 1] - po, pd = t.cdist[p];
       const int up = t.tpar[p];
-      for (int j = lane; j < pm; j += 64) b.pfx[at + pd + j] = ch.v[po + j];
+      for (int j = lane; j < pm; j += 64) b.pfx[pat + pd + j] = ch.v[po + j];
       p = up;
     }
     if (q >= 0) {
       const int qo = ch.off[q], qm = ch.off[q + 1] - qo, qd = db + m - t.cback[q] - qm;
       const int on = t.nx[q];
-      for (int j = lane; j < qm; j += 64) b.sfx[at + qd + j] = ch.v[qo + j];
+      for (int j = lane; j < qm; j += 64) b.sfx[sat + qd + j] = ch.v[qo + j];
       q = on;
     }
   }
@@ -451,22 +462,23 @@ __global__ __launch_bounds__(64) void k_chain_rows(DGraph g, DGraph x, DChains c
     const int v = ch.v[o + j];
     b.n_pfx[v] = df + j;
     b.n_sfx[v] = db + m - 1 - j;
-    b.pfx_at[v] = at;
-    b.sfx_at[v] = at + j + 1;
+    b.pfx_at[v] = pat;
+    b.sfx_at[v] = sat + j + 1;
   }
 }
 
 hipError_t launch_chain_bfs(const DGraph& g, const DGraph& x, const DChains& ch, const TpTree& t,
-                            const int32_t* gbase, int32_t* order, const int32_t* rbase,
-                            const EndRows& b, int max_chains, int max_words, hipStream_t st) {
+                            const int32_t* gbase, int32_t* order, const int32_t* pbase,
+                            const int32_t* sbase, const EndRows& b, int max_chains, int max_words,
+                            hipStream_t st) {
   const unsigned grid = (unsigned)x.n_comp;
   // staged graphs of up to 16 KiB (40 KiB from 257 chains on, which are seldom
   // many at a time); a wave per component when there are many (18 chains alone
   // take four waves 22 us and one 21)
   const size_t lds = sizeof(int32_t) * (size_t)max_words;
   auto run = [&](auto staged, auto plain, int threads, size_t most) {
-    if (lds <= most) staged<<<grid, threads, lds, st>>>(g, x, ch, t, gbase, order);
-    else plain<<<grid, threads, 0, st>>>(g, x, ch, t, gbase, order);
+    if (lds <= most) staged<<<grid, threads, lds, st>>>(g, x, ch, t, gbase, order, pbase, sbase);
+    else plain<<<grid, threads, 0, st>>>(g, x, ch, t, gbase, order, pbase, sbase);
   };
   if (max_chains <= 256 && x.n_comp >= 64)
     run(k_chain_bfs<256, 64, true>, k_chain_bfs<256, 64, false>, 64, 16384);
@@ -475,8 +487,9 @@ hipError_t launch_chain_bfs(const DGraph& g, const DGraph& x, const DChains& ch,
   else if (max_chains <= 1024)
     run(k_chain_bfs<1024, 256, true>, k_chain_bfs<1024, 256, false>, 256, 40960);
   else
-    k_chain_bfs<kMaxComp, 1024, false><<<grid, 1024, 0, st>>>(g, x, ch, t, gbase, order);
-  k_chain_rows<<<(unsigned)x.n, 64, 0, st>>>(g, x, ch, t, rbase, b);
+    k_chain_bfs<kMaxComp, 1024, false><<<grid, 1024, 0, st>>>(g, x, ch, t, gbase, order, pbase,
+                                                              sbase);
+  k_chain_rows<<<(unsigned)x.n, 64, 0, st>>>(ch, t, b);
   return hipGetLastError();
 }
 
