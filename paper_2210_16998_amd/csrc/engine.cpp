@@ -1018,10 +1018,13 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
   // both sweeps take two levels per launch (a launch costs ~7 us however little
   // it does; three measured slower: deeper per-thread chains) unless a vertex
   // has many successors, all of whose children are then one thread's: a switch
-  // of 64 switches of 62 took 2.21 ms with two and takes 0.78 with one; up to
-  // eight successors two are as fast or faster (fans of 12 0.42 and 0.40 ms, of 8
-  // 0.41 and 0.42, of 4 0.48 and 0.50, a 212-vertex CFG 1.74 and 1.78)
-  const int kRun = U.max_deg <= 8 ? 2 : 1;
+  // of 64 switches of 62 took 2.21 ms with two and takes 0.78 with one.  At 16
+  // successors it is even (two and one level: the 400-vertex stress CFG 17.3
+  // and 17.6 ms, 12 switches of 16 of 16 0.74 and 0.68, fans of 16 0.55 and 0.53),
+  // below it two are as fast or faster (fans of 8 0.41 and 0.42, of 4 0.48 and
+  // 0.50, a 212-vertex CFG 1.74 and 1.78), above it one is (fans of 32 0.70 and
+  // 0.63, 4 switches of 30 of 30 0.83 and 0.74)
+  const int kRun = U.max_deg <= 16 ? 2 : 1;
   TPG_TRY(run_seq(ws, ws->rank_up, std::move(key), st, [&]() -> hipError_t {
     hipError_t e = launch_path_lengths(a, R.count[1], N, st);
     for (int L = R.Lmax; L >= 1 && e == hipSuccess;) {

@@ -61,9 +61,9 @@ def test_switches_into_one_exit(a, b):
     check_tp(_switches(a, b), local=True)
 
 
-# levels of more than 2048 nodes, swept one or two to a launch: eight successors
-# and nine; odd and even numbers of such levels
-@pytest.mark.parametrize("widths", [(8, 8, 8, 8), (9, 9, 9, 4), (8, 8, 8, 8, 3), (9, 3, 9, 9, 3), (9, 9, 9)])
+# levels of more than 2048 nodes, swept one or two to a launch: 16 successors and
+# 17, and fewer; odd and even numbers of such levels
+@pytest.mark.parametrize("widths", [(16, 16, 16), (17, 17, 8), (16, 16, 16, 3), (17, 3, 17, 17), (9, 9, 9, 4)])
 @pytest.mark.parametrize("back", [False, True])
 def test_wide_levels_by_successors(widths, back):
     if back:
