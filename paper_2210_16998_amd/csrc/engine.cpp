@@ -204,8 +204,10 @@ struct tpg_workspace {
   // register width W): parents per thread (tile = threads * items, one output
   // claim per tile), persistent workgroups per CU and kernel variant;
   // defaults from sweeps on MI355X (one-word sets with two parents a thread took
-  // 48 small functions 13.1 ms and a batch of 4096 5.65, with one 12.8 and 5.53)
-  int tune_items[7] = {1, 1, 1, 1, 2, 1, 1};
+  // 48 small functions 13.1 ms and a batch of 4096 5.65, with one 12.8 and 5.53;
+  // 16-word sets spill with two: 1000 early exits 18.8 and 14.7 ms, 2.6 million
+  // nodes over 547 chains 7.7 and 5.4)
+  int tune_items[7] = {1, 1, 1, 1, 1, 1, 1};
   int tune_wgs[7] = {2, 2, 2, 4, 2, 2, 4};
   int tune_variant[7] = {2, 2, 2, 2, 2, 2, 0};
   double tune_ms[7] = {0, 0, 0, 0, 0, 0, 0};
@@ -782,15 +784,15 @@ struct OnePassDev {
       if (L > last_ok || h.count[L] == 0) break;
       R.ms_kernel += Timer::ms(ev.first, ev.second);
       R.launches += 1;
-      L = next_launch(h.count, L, limit);
+      L = next_launch(h.count, L, limit, U.Wu);
     }
     tm.next = 0;
     return true;
   }
   // The level that the launch after the one from level L on extends first.
-  static int next_launch(const int64_t* count, int L, int limit) {
-    if (count[L] > kNarrowExtend) return L + 1;
-    while (L < limit && count[L] > 0 && count[L] <= kNarrowExtend) ++L;
+  static int next_launch(const int64_t* count, int L, int limit, int words) {
+    if (!narrow_level(count[L], words)) return L + 1;
+    while (L < limit && count[L] > 0 && narrow_level(count[L], words)) ++L;
     return L;
   }
   bool resume(int Lo) { return hip(launch_resume_fix(a, Lo, st), "replay"); }
@@ -843,7 +845,7 @@ tpg_status build_tree_onepass(tpg_workspace* ws, const HostUnion& U, hipStream_t
   ws->levels_uids = U.uids;
   ws->levels_last = Lmax;
   ws->levels_launches = 0;
-  for (int L = 1; L <= Lmax; L = OnePassDev::next_launch(cnt.data(), L, Lmax + 1))
+  for (int L = 1; L <= Lmax; L = OnePassDev::next_launch(cnt.data(), L, Lmax + 1, U.Wu))
     ++ws->levels_launches;
   R.count.assign(kMaxLevels, 0);
   R.off.assign(kMaxLevels, 0);

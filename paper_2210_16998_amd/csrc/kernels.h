@@ -28,8 +28,12 @@ struct LevelState {
   int32_t next[kMaxLevels];   // first level that each launch of the batch extends
 };
 constexpr int kLevelHeader = 32;  // bytes before count
-// Levels of at most this many nodes are extended many to a launch.
-constexpr int kNarrowExtend = 2048;
+// Levels of at most this many nodes, with at most this many words of visited
+// sets, are extended many to a launch.
+constexpr int kNarrowExtend = 2048, kNarrowWords = 16384;
+__host__ __device__ inline bool narrow_level(int64_t nodes, int set_words) {
+  return nodes <= kNarrowExtend && (int)nodes * set_words <= kNarrowWords;
+}
 
 // Buffers of the path tree and of the frontier.
 struct TreeBufs {

@@ -208,12 +208,15 @@ __device__ __forceinline__ void path_mask_own(int L, int vl, uint64_t (&m)[W]) {
 // whose nodes did not fit (claimed beyond the capacities by the launch before)
 // raises the overflow flag and ends the batch.
 //
-// A level of at most kNarrowExtend nodes is workgroup 0's alone, which then
+// A narrow level (kNarrowExtend, kNarrowWords) is workgroup 0's alone, which then
 // goes on to the levels after it until one is wide, empty or past the limit: a
 // launch costs 5 to 8 us and the host's look at the sizes some 40, while the
 // workgroup needs 2 to 3 us a level.  48 small functions, none seen
 // just before, took 20.6 ms without it, 17.0 with the line at 1024 nodes and 16.7 from
-// 2048 to 8192; a 212-vertex CFG 1.83, 1.79, 1.79 and from 8192 on 1.82 ms.
+// 2048 to 8192; a 212-vertex CFG 1.83, 1.79, 1.79 and from 8192 on 1.82 ms.  One
+// CU is soon busy with wide sets: 4000 early exits (63 words) took 140 ms
+// without a line on the words, 103 with 65536, 94.6 with 32768, 93.2 with 16384 and
+// less; 1000 (16 words) 14.7, 14.7, 14.7, 13.2, and 14.8 without any narrow level.
 struct LevelCursor {
   int L, limit;
   bool narrow;
@@ -221,7 +224,8 @@ struct LevelCursor {
   int children;  // of a narrow level, so far (< 2^17)
 
   // Sets the cursor to the launch's first level; false: nothing to extend.
-  __device__ __forceinline__ bool begin(LevelState* ls, int li) {
+  __device__ __forceinline__ bool begin(const ExtArgs& a, int li) {
+    LevelState* ls = a.ls;
     if (ls->overflow) return false;
     L = li == 0 ? ls->batch_start : ls->next[li];
     limit = ls->limit;
@@ -232,7 +236,7 @@ struct LevelCursor {
     }
     prev = ls->off[L - 1];
     base = prev + ls->count[L - 1];
-    narrow = F <= kNarrowExtend;
+    narrow = narrow_level(F, a.t.mask_words);
     return !narrow || blockIdx.x == 0;
   }
   __device__ __forceinline__ int64_t step() const { return narrow ? 1 : (int64_t)gridDim.x; }
@@ -274,7 +278,8 @@ struct LevelCursor {
     children += __builtin_amdgcn_readfirstlane(total);
   }
   // After a level: on to the next one, or leaves it to the next launch.
-  __device__ __forceinline__ bool advance(LevelState* ls, int li) {
+  __device__ __forceinline__ bool advance(const ExtArgs& a, int li) {
+    LevelState* ls = a.ls;
     if (narrow && threadIdx.x == 0) ls->count[L + 1] = children;
     ++L;
     if (narrow) {
@@ -282,7 +287,7 @@ struct LevelCursor {
       base += F;
       F = children;
     }
-    if (!narrow || F == 0 || F > kNarrowExtend || L >= limit) {
+    if (!narrow || F == 0 || !narrow_level(F, a.t.mask_words) || L >= limit) {
       leave(ls, li);
       return false;
     }
@@ -319,7 +324,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 &
   const int tid = (int)threadIdx.x;
   const int lane = lane_id(), wave = tid >> 6;
   LevelCursor cur;
-  if (!cur.begin(a.ls, li)) return;
+  if (!cur.begin(a, li)) return;
   DGraph g = a.g;
   if constexpr (GL) {
     if (!cur.has_tile(NT, ITEMS, a.tiles_target)) return;
@@ -434,7 +439,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 &
       }
       __syncthreads();
     }
-  } while (cur.advance(a.ls, li));
+  } while (cur.advance(a, li));
 }
 
 // Load-balanced form of the same step: the tile's parents are staged in LDS
@@ -455,7 +460,7 @@ __global__ __launch_bounds__(kBlock) void k_extend_lb(ExtArgs a, int li) {
 
   const int tid = (int)threadIdx.x;
   LevelCursor cur;
-  if (!cur.begin(a.ls, li)) return;
+  if (!cur.begin(a, li)) return;
   do {
     if (!cur.open(a)) return;
     const int L = cur.L;
@@ -569,7 +574,7 @@ __global__ __launch_bounds__(kBlock) void k_extend_lb(ExtArgs a, int li) {
       }
       __syncthreads();
     }
-  } while (cur.advance(a.ls, li));
+  } while (cur.advance(a, li));
 }
 
 // Launch with optional start / stop events recorded by the dispatch itself

@@ -110,3 +110,18 @@ def test_deep_graph_costs_no_pass_per_level():
     pp, tp = ms(tpg.prime_paths), ms(tpg.test_paths)
     say("prime paths", pp, "ms, test paths", tp, "ms")
     assert tp < 2.0 * pp
+
+
+# narrow levels by the words of their sets: 2048 nodes up to 8 words, 1024 at 16,
+# 512 at 32, 256 at 64 words
+@pytest.mark.parametrize("widths,exits", [((44, 46), 280), ((31, 33), 600), ((22, 23), 1400), ((15, 17), 2100)])
+def test_narrow_levels_by_words(widths, exits):
+    """Fans and, from the entry, a row of vertices that may all leave to the
+    exit: levels of the row's length and fewer, and more where the fans end."""
+    g, _ = _fans(widths)
+    n, end = g.n, g.n + exits
+    edges = g.edges() + [(n - 1, end), (0, n)] + [(v, v + 1) for v in range(n, end)]
+    edges = sorted(set(edges) | {(v, end) for v in range(n, end)})
+    g = cfggen.from_edges(end + 1, edges, name=f"{g.name}_{exits}")
+    say("case", g.name, g.n)
+    check_tp(g, local=True)
