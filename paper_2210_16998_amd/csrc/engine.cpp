@@ -206,10 +206,12 @@ struct tpg_workspace {
   // defaults from sweeps on MI355X (one-word sets with two parents a thread took
   // 48 small functions 13.1 ms and a batch of 4096 5.65, with one 12.8 and 5.53;
   // 16-word sets spill with two: 1000 early exits 18.8 and 14.7 ms, 2.6 million
-  // nodes over 547 chains 7.7 and 5.4)
+  // nodes over 547 chains 7.7 and 5.4; 32-word sets with 1024 threads, two
+  // workgroups per CU, take 2000 early exits 39.8 ms and the same nodes over 1347
+  // chains 24.1, with 256 threads, four per CU, 30.9 and 21.7)
   int tune_items[7] = {1, 1, 1, 1, 1, 1, 1};
-  int tune_wgs[7] = {2, 2, 2, 4, 2, 2, 4};
-  int tune_variant[7] = {2, 2, 2, 2, 2, 2, 0};
+  int tune_wgs[7] = {2, 2, 2, 4, 2, 4, 4};
+  int tune_variant[7] = {2, 2, 2, 2, 2, 1, 0};
   double tune_ms[7] = {0, 0, 0, 0, 0, 0, 0};
 };
 
