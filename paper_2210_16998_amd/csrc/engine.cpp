@@ -83,6 +83,10 @@ struct tpg_workspace {
   int num_cus = 256;
   size_t bytes = 0;
   uint64_t cap = 0;  // pool cap of the running call (0: none)
+  // the running call sizes its buffers with nothing to spare (see within_cap);
+  // calls under a cap of at most tight_cap do so from the start
+  bool tight = false;
+  uint64_t tight_cap = 0;
 
   // Host <-> device traffic of a call whose device work may be captured
   // into one graph: io_mode 0 an ordinary call; 1 an ordinary call that
@@ -226,7 +230,7 @@ tpg_status ws_reserve(tpg_workspace* ws, DevBuf& b, size_t bytes, bool keep = fa
     return fail(TPG_ERR_UNSUPPORTED, "the captured call needed a larger buffer");
   }
   ws->alloc_gen += 1;
-  size_t want = std::max(bytes, b.cap + b.cap / 2);
+  size_t want = ws->tight ? bytes : std::max(bytes, b.cap + b.cap / 2);
   want = (want + 255) & ~(size_t)255;
   if (ws->cap && ws->bytes - b.cap + want > ws->cap) {
     want = (bytes + 255) & ~(size_t)255;
@@ -480,7 +484,8 @@ tpg_status reserve_tree(tpg_workspace* ws, int64_t rec, int64_t msk, int W, hipS
   // kept level is copied to the new stride when they grow.
   const size_t need = sizeof(uint64_t) * (size_t)msk * W;
   if (ws->mask0.cap < need || ws->mask1.cap < need) {
-    size_t want = std::max(need, std::max(ws->mask0.cap, ws->mask1.cap) * 3 / 2);
+    size_t want = ws->tight ? need
+                            : std::max(need, std::max(ws->mask0.cap, ws->mask1.cap) * 3 / 2);
     want = (want + 255) & ~(size_t)255;
     const bool keep = keep_mask > 0 && keep_parity >= 0 && ws->mask_words == W;
     DevBuf& kb = keep_parity == 1 ? ws->mask1 : ws->mask0;
@@ -694,6 +699,14 @@ tpg_status launch_levels_graph(tpg_workspace* ws, const ExtArgs& a, int W, int i
   return TPG_OK;
 }
 
+// No level is extended any more: the visited sets go if there is nothing to spare.
+void tree_done(tpg_workspace* ws) {
+  if (!ws->tight) return;
+  ws_release(ws, ws->mask0);
+  ws_release(ws, ws->mask1);
+  ws->mask_cap = 0;
+}
+
 // Frees the path tree and the visited-set buffers (capacities back to zero).
 void release_tree(tpg_workspace* ws) {
   for (DevBuf* b : {&ws->par, &ws->info, &ws->cstart, &ws->nch, &ws->tl, &ws->mask0, &ws->mask1})
@@ -809,7 +822,7 @@ tpg_status build_tree_onepass(tpg_workspace* ws, const HostUnion& U, hipStream_t
   const int W = U.W;
   const int64_t held_msk =
       (ws->mask_words && ws->mask_cap) ? ws->mask_cap * ws->mask_words / U.Wu : 0;
-  const TreeCaps first = onepass_first_caps(ws->rec_cap, held_msk, U.xn, rec0, msk0);
+  const TreeCaps first = onepass_first_caps(ws->rec_cap, held_msk, U.xn, rec0, msk0, ws->tight);
   TPG_TRY(reserve_tree(ws, first.rec, first.msk, U.Wu, st, 0, -1, 0));
   int wi = 0;
   while ((1 << wi) < W) ++wi;
@@ -827,7 +840,7 @@ tpg_status build_tree_onepass(tpg_workspace* ws, const HostUnion& U, hipStream_t
   const int first_batch = known ? ws->levels_launches : 1;
   int Lmax = 0;
   LoopFailure why;
-  switch (onepass_levels(d, first_batch, kMaxLevels, cnt, Lmax, R.n_overflows, why)) {
+  switch (onepass_levels(d, first_batch, kMaxLevels, cnt, Lmax, R.n_overflows, why, ws->tight)) {
     case LoopEnd::ok:
       break;
     case LoopEnd::device_failed:
@@ -899,9 +912,10 @@ tpg_status build_tree_twopass(tpg_workspace* ws, const HostUnion& U, hipStream_t
     if (base + F + total + 1 > ws->rec_cap || (store_next && total > ws->mask_cap)) {
       const int64_t need = base + F + total + 1;
       const int Ls = (L & 1) ? L : L - 1;  // the stored level the fill reads
-      TPG_TRY(reserve_tree(ws, std::max(need, std::min(std::max<int64_t>(ws->rec_cap, need + need / 2),
+      const int part = ws->tight ? 16 : 2;
+      TPG_TRY(reserve_tree(ws, std::max(need, std::min(std::max<int64_t>(ws->rec_cap, need + need / part),
                                                        kMaxTreeNodes)),
-                           store_next ? std::max<int64_t>(ws->mask_cap, total + total / 2) : ws->mask_cap,
+                           store_next ? std::max<int64_t>(ws->mask_cap, total + total / part) : ws->mask_cap,
                            U.Wu, st, base + F + 1, mask_buf_host(Ls), R.count[Ls]));
       a = make_args(ws);
     }
@@ -935,7 +949,7 @@ struct PPResult {
 constexpr int64_t kAheadEntries = (int64_t)4 << 20;
 bool room_ahead(const tpg_workspace* ws, const DevBuf& b, int64_t entries) {
   const size_t bytes = sizeof(int32_t) * (size_t)(entries + 1);
-  return entries <= kAheadEntries &&
+  return entries <= kAheadEntries && !ws->tight &&
          (b.cap >= bytes || !ws->cap || ws->bytes - b.cap + bytes + 256 <= ws->cap);
 }
 
@@ -989,6 +1003,7 @@ void path_counts(const tpg_workspace* ws, const HostUnion& U, const int64_t* his
 
 tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream_t st,
                                 TreeResult& R, PPResult& P, OutSet& o, bool ahead) {
+  tree_done(ws);
   ExtArgs a = make_args(ws);
   const int64_t N = R.n_nodes;
   TPG_TRY(ws_reserve(ws, ws->sub_cnt, sizeof(uint32_t) * N));
@@ -1185,7 +1200,7 @@ tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, 
   // room for the pairs: what is there, or twice the paths; more once their
   // number is known (642294 for the 376808 paths of a 182-vertex CFG)
   const size_t guess = sizeof(int32_t) * (size_t)(2 * np + 1);
-  if (!ws->cap || ws->bytes + 2 * guess + 1024 <= ws->cap) {
+  if (!ws->tight && (!ws->cap || ws->bytes + 2 * guess + 1024 <= ws->cap)) {
     TPG_TRY(ws_reserve(ws, ws->pair_p, guess));
     TPG_TRY(ws_reserve(ws, ws->pair_q, guess));
   }
@@ -1254,6 +1269,7 @@ tpg_status test_paths_device(tpg_workspace* ws, const HostUnion& U, hipStream_t 
   ws->bfs_pending = false;
   const int64_t np = P.n_pp;
   T.n_spliced = np;
+  if (ws->tight) ws_release(ws, ws->canon);  // the leaves have theirs
   const int32_t ng = U.gbase.back();
   TPG_TRY(reserve_scan(ws, std::max<int64_t>(np, ng)));
   TPG_TRY(ws_reserve(ws, ws->row_src, sizeof(int32_t) * (np + 1)));
@@ -1545,6 +1561,7 @@ tpg_status begin_call(const tpg_opts* opts, CallCtx& c) {
   c.ws->bfs_pending = false;
   c.st = (opts && opts->stream) ? (hipStream_t)opts->stream : c.ws->own_stream;
   c.ws->cap = opts ? opts->pool_cap_bytes : 0;
+  c.ws->tight = c.ws->cap && c.ws->cap <= c.ws->tight_cap;
   if (c.ws->cap && c.ws->bytes > c.ws->cap)
     return fail(TPG_ERR_CAPACITY, "workspace already holds %zu bytes (cap %llu)", c.ws->bytes,
                 (unsigned long long)c.ws->cap);
@@ -1555,6 +1572,64 @@ tpg_status begin_call(const tpg_opts* opts, CallCtx& c) {
   c.ws->staged.clear();
   c.ws->stage_used = 0;
   return TPG_OK;
+}
+
+// Frees all device memory of the workspace, and the graphs that point into it.
+void release_all(tpg_workspace* ws) {
+  DevBuf* bufs[] = {&ws->g_csr, &ws->par, &ws->info, &ws->cstart, &ws->nch, &ws->tl, &ws->mask0,
+                    &ws->mask1, &ws->ls, &ws->sub_cnt, &ws->pp_len,
+                    &ws->leaf_by_rank, &ws->totals, &ws->scan_status,
+                    &ws->scan_ctr, &ws->scalars, &ws->bfs_i32,
+                    &ws->pfx, &ws->sfx, &ws->rb0, &ws->tp_links, &ws->tp_order, &ws->tp_first,
+                    &ws->canon, &ws->leaf_canon, &ws->seq_num, &ws->row_src, &ws->row_len, &ws->chunk_off, &ws->lvl_comp, &ws->b_pp_off,
+                    &ws->digest, &ws->grp_key, &ws->grp_hist, &ws->grp_base,
+                    &ws->cov_keys, &ws->cov_vals, &ws->cov_misc, &ws->pair_p,
+                    &ws->pair_q, &ws->gstate0, &ws->gstate1,
+                    &ws->scc_work, &ws->scc_comp, &ws->scc_flags, &ws->scc_misc, &ws->ty_off,
+                    &ws->ty_vtx, &ws->ty_types, &ws->cg_cnt, &ws->cg_off, &ws->cg_src,
+                    &ws->cg_dst, &ws->cx_qb, &ws->cx_cnt0, &ws->cx_cnt1, &ws->cx_node,
+                    &ws->cx_len, &ws->cx_vfl, &ws->cx_orig, &ws->cx_off[0], &ws->cx_off[1],
+                    &ws->cx_off[2], &ws->cx_vtx[0], &ws->cx_vtx[1], &ws->cx_vtx[2],
+                    &ws->cm_kind, &ws->cm_orig, &ws->cm_cls, &ws->cm_len, &ws->cm_flag,
+                    &ws->cm_lens, &ws->cm_pos, &ws->cm_voff, &ws->cm_off[0], &ws->cm_off[1],
+                    &ws->cm_off[2], &ws->cm_vtx[0], &ws->cm_vtx[1], &ws->cm_vtx[2],
+                    &ws->pv_rows0, &ws->pv_rows1, &ws->pv_voff0, &ws->pv_voff1, &ws->pv_ext,
+                    &ws->pv_cnt, &ws->pv_flag, &ws->pv_pos,
+                    &ws->b_pp_vtx, &ws->b_tp_off, &ws->b_tp_vtx, &ws->b_desc};
+  for (DevBuf* b : bufs) ws_release(ws, *b);
+  for (OutSet& o : ws->out)
+    for (DevBuf* b : {&o.pp_off, &o.pp_vtx, &o.tp_off, &o.tp_vtx, &o.ppg_off, &o.ppg_vtx,
+                      &o.comp_starts})
+      ws_release(ws, *b);
+  ws->rec_cap = ws->mask_cap = 0;
+  ws->mask_words = 0;
+  ws->union_uids.clear();
+  ws->levels_uids.clear();
+  drop_level_graphs(ws);
+  drop_seq_graph(ws->rank_up);
+  drop_seq_graph(ws->rank_down);
+  drop_seq_graph(ws->tp_sweeps);
+}
+
+// Runs a call that may be under a pool cap.  Buffers are usually sized with
+// room to spare: growth by a quarter, rows written before their number is known,
+// a guess at the covering pairs.  A call that its cap refuses for that is run
+// once more from empty buffers without any of it, and those under the same cap
+// or a smaller one after it begin that way.
+template <class F>
+tpg_status within_cap(CallCtx& c, F&& body) {
+  tpg_workspace* ws = c.ws;
+  const tpg_status s = body();
+  if (s != TPG_ERR_CAPACITY || !ws->cap || ws->tight) return s;
+  TPG_HIP(hipStreamSynchronize(c.st));
+  TPG_HIP(hipStreamSynchronize(ws->side_stream));
+  ws->bfs_pending = false;
+  ws->staged.clear();
+  ws->stage_used = 0;
+  release_all(ws);
+  ws->tight = true;
+  ws->tight_cap = std::max(ws->tight_cap, ws->cap);
+  return body();
 }
 
 tpg_status run_pp(const HostUnion& U, CallCtx& c, Timer& tm, TreeResult& R, PPResult& P,
@@ -1657,8 +1732,12 @@ tpg_status prime_paths_stream(const tpg_graph* g, CallCtx& c, tpg_paths* out) {
     c.ws->range_n = hi - lo;
     TreeResult R;
     PPResult P;
-    TPG_TRY(run_pp(U, c, tm, R, P, o, nullptr));
-    TPG_TRY(start_digest(c.ws, o.pp_off, o.pp_vtx, P.n_pp, c.st));
+    TPG_TRY(within_cap(c, [&]() -> tpg_status {
+      R = TreeResult{};
+      P = PPResult{};
+      TPG_TRY(run_pp(U, c, tm, R, P, o, nullptr));
+      return start_digest(c.ws, o.pp_off, o.pp_vtx, P.n_pp, c.st);
+    }));
     tpg_paths chunk;
     const bool dev = c.flags & TPG_OUT_DEVICE;
     const bool ours = !dev && chunk_arrays(c.ws, P.n_pp, P.n_vtx, chunk);
@@ -1804,41 +1883,8 @@ void tpg_workspace_free(tpg_workspace* ws) {
   if (ws->cg.exec) (void)hipGraphExecDestroy(ws->cg.exec);
   if (ws->io_check) (void)hipHostFree(ws->io_check);
   if (ws->io_stage) (void)hipHostFree(ws->io_stage);
-  DevBuf* bufs[] = {&ws->g_csr, &ws->par, &ws->info, &ws->cstart, &ws->nch, &ws->tl, &ws->mask0,
-                    &ws->mask1, &ws->ls, &ws->sub_cnt, &ws->pp_len,
-                    &ws->leaf_by_rank, &ws->totals, &ws->scan_status,
-                    &ws->scan_ctr, &ws->scalars, &ws->bfs_i32,
-                    &ws->pfx, &ws->sfx, &ws->rb0, &ws->tp_links, &ws->tp_order, &ws->tp_first,
-                    &ws->canon, &ws->leaf_canon, &ws->seq_num, &ws->row_src, &ws->row_len, &ws->chunk_off, &ws->lvl_comp, &ws->b_pp_off,
-                    &ws->digest, &ws->grp_key, &ws->grp_hist, &ws->grp_base,
-                    &ws->cov_keys, &ws->cov_vals, &ws->cov_misc, &ws->pair_p,
-                    &ws->pair_q, &ws->gstate0, &ws->gstate1,
-                    &ws->scc_work, &ws->scc_comp, &ws->scc_flags, &ws->scc_misc, &ws->ty_off,
-                    &ws->ty_vtx, &ws->ty_types, &ws->cg_cnt, &ws->cg_off, &ws->cg_src,
-                    &ws->cg_dst, &ws->cx_qb, &ws->cx_cnt0, &ws->cx_cnt1, &ws->cx_node,
-                    &ws->cx_len, &ws->cx_vfl, &ws->cx_orig, &ws->cx_off[0], &ws->cx_off[1],
-                    &ws->cx_off[2], &ws->cx_vtx[0], &ws->cx_vtx[1], &ws->cx_vtx[2],
-                    &ws->cm_kind, &ws->cm_orig, &ws->cm_cls, &ws->cm_len, &ws->cm_flag,
-                    &ws->cm_lens, &ws->cm_pos, &ws->cm_voff, &ws->cm_off[0], &ws->cm_off[1],
-                    &ws->cm_off[2], &ws->cm_vtx[0], &ws->cm_vtx[1], &ws->cm_vtx[2],
-                    &ws->pv_rows0, &ws->pv_rows1, &ws->pv_voff0, &ws->pv_voff1, &ws->pv_ext,
-                    &ws->pv_cnt, &ws->pv_flag, &ws->pv_pos,
-                    &ws->b_pp_vtx, &ws->b_tp_off, &ws->b_tp_vtx, &ws->b_desc};
-  for (DevBuf* b : bufs) ws_release(ws, *b);
-  for (OutSet& o : ws->out) {
-    ws_release(ws, o.pp_off);
-    ws_release(ws, o.pp_vtx);
-    ws_release(ws, o.tp_off);
-    ws_release(ws, o.tp_vtx);
-    ws_release(ws, o.ppg_off);
-    ws_release(ws, o.ppg_vtx);
-    ws_release(ws, o.comp_starts);
-  }
+  release_all(ws);
   for (hipEvent_t e : ws->ev_pool) (void)hipEventDestroy(e);
-  drop_level_graphs(ws);
-  drop_seq_graph(ws->rank_up);
-  drop_seq_graph(ws->rank_down);
-  drop_seq_graph(ws->tp_sweeps);
   if (ws->h_ls) (void)hipHostFree(ws->h_ls);
   if (ws->stage) (void)hipHostFree(ws->stage);
   if (ws->chunk) (void)hipHostFree(ws->chunk);
@@ -1873,8 +1919,13 @@ tpg_status tpg_prime_paths(const tpg_graph* g, const tpg_opts* opts, tpg_paths* 
   PPResult P;
   hipEvent_t ext_done = nullptr;
   OutSet& o = c.ws->out[0];
-  tpg_status s = run_pp(U, c, tm, R, P, o, &ext_done);
-  if (s == TPG_OK && (c.flags & TPG_ORDER_BY_LAST)) s = group_by_last(c.ws, U.n, c.st, o, P.n_pp, P.n_vtx);
+  tpg_status s = within_cap(c, [&]() -> tpg_status {
+    R = TreeResult{};
+    P = PPResult{};
+    TPG_TRY(run_pp(U, c, tm, R, P, o, &ext_done));
+    if (c.flags & TPG_ORDER_BY_LAST) TPG_TRY(group_by_last(c.ws, U.n, c.st, o, P.n_pp, P.n_vtx));
+    return TPG_OK;
+  });
   if (s == TPG_OK && timing) TPG_HIP(hipEventRecord(phase[1], c.st));
   const bool grouped = c.flags & TPG_ORDER_BY_LAST;
   if (s == TPG_OK)
@@ -2094,6 +2145,7 @@ tpg_status extract_device(CallCtx& c, const tpg_graph* g, const std::vector<int3
       TPG_TRY(build_tree_twopass(ws, U, st, tm, R));
     else
       TPG_TRY(build_tree_onepass(ws, U, st, tm, R, 0, 0));
+    tree_done(ws);
     const int64_t N = R.n_nodes;
     TPG_TRY(ws_reserve(ws, ws->cx_qb, (size_t)N + 1));
     TPG_TRY(ws_reserve(ws, ws->cx_cnt0, sizeof(uint32_t) * (N + 1)));
@@ -2262,17 +2314,21 @@ tpg_status tpg_scc_paths(const tpg_graph* g, const tpg_opts* opts, tpg_paths* en
   TPG_TRY(check_graph(g));
   CallCtx c;
   TPG_TRY(begin_call(opts, c));
-  std::vector<int32_t> comp;
-  std::vector<uint8_t> fl;
-  TPG_TRY(components_host(c, g, comp, fl));
-  int64_t n[3], nv[3];
-  TPG_TRY(extract_device(c, g, comp, fl, n, nv));
   tpg_paths* outs[3] = {entry_exit, exit_paths, entry_paths};
-  for (int s = 0; s < 3; ++s)
-    if (outs[s])
-      TPG_TRY(export_paths(c.ws, c.ws->cx_off[s], c.ws->cx_vtx[s], n[s], nv[s],
-                           (c.flags & TPG_OUT_DEVICE) != 0, c.st, outs[s], false));
-  return finish_copies(c.ws, c.st);
+  return within_cap(c, [&]() -> tpg_status {
+    for (tpg_paths* p : outs)
+      if (p) tpg_paths_free(p);
+    std::vector<int32_t> comp;
+    std::vector<uint8_t> fl;
+    TPG_TRY(components_host(c, g, comp, fl));
+    int64_t n[3], nv[3];
+    TPG_TRY(extract_device(c, g, comp, fl, n, nv));
+    for (int s = 0; s < 3; ++s)
+      if (outs[s])
+        TPG_TRY(export_paths(c.ws, c.ws->cx_off[s], c.ws->cx_vtx[s], n[s], nv[s],
+                             (c.flags & TPG_OUT_DEVICE) != 0, c.st, outs[s], false));
+    return finish_copies(c.ws, c.st);
+  });
 }
 
 tpg_status tpg_scc_internal_pps(const tpg_graph* g, const tpg_opts* opts, tpg_paths* out) {
@@ -2283,61 +2339,64 @@ tpg_status tpg_scc_internal_pps(const tpg_graph* g, const tpg_opts* opts, tpg_pa
   TPG_TRY(begin_call(opts, c));
   tpg_workspace* ws = c.ws;
   hipStream_t st = c.st;
-  std::vector<int32_t> comp;
-  std::vector<uint8_t> fl;
-  TPG_TRY(components_host(c, g, comp, fl));
-  ComponentUnion S;
-  HostUnion U;
-  TPG_TRY(component_union(g, comp, fl, false, 0, S, U));
-  DevBuf& ooff = ws->cm_off[0];
-  DevBuf& ovtx = ws->cm_vtx[0];
-  if (U.n == 0) {
-    TPG_TRY(ws_reserve(ws, ooff, sizeof(int64_t)));
-    TPG_TRY(ws_reserve(ws, ovtx, sizeof(int32_t)));
-    TPG_HIP(launch_zero_u64(ooff.as<uint64_t>(), 1, st));
-    return export_paths(ws, ooff, ovtx, 0, 0, (c.flags & TPG_OUT_DEVICE) != 0, st, out);
-  }
-  // the extension on every component alone (one union), then Def. 9
-  Timer tm{ws, st, false};
-  TreeResult R;
-  PPResult P;
-  OutSet& o = ws->out[0];
-  TPG_TRY(run_pp(U, c, tm, R, P, o, nullptr));
-  const int64_t np = P.n_pp;
-  TPG_TRY(ws_reserve(ws, ws->cx_vfl, (size_t)U.n));
-  TPG_TRY(ws_reserve(ws, ws->cx_orig, sizeof(int32_t) * U.n));
-  TPG_HIP(hipMemcpyAsync(ws->cx_vfl.p, S.vfl.data(), U.n, hipMemcpyHostToDevice, st));
-  TPG_HIP(hipMemcpyAsync(ws->cx_orig.p, S.orig.data(), sizeof(int32_t) * U.n,
-                         hipMemcpyHostToDevice, st));
-  TPG_TRY(ws_reserve(ws, ws->cm_cls, (size_t)np + 1));
-  TPG_TRY(ws_reserve(ws, ws->cm_len, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->cm_flag, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->cm_lens, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->cm_pos, sizeof(int64_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->cm_voff, sizeof(int64_t) * (np + 1)));
-  TPG_HIP(launch_internal_class(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np,
-                                ws->cx_vfl.as<uint8_t>(), ws->cm_cls.as<uint8_t>(),
-                                ws->cm_len.as<int32_t>(), st));
-  TPG_TRY(reserve_scan(ws, std::max<int64_t>(np, 16)));
-  int64_t* scal = ws->scalars.as<int64_t>();
-  TPG_HIP(launch_merge_sel(ws->cm_cls.as<uint8_t>(), ws->cm_len.as<int32_t>(), np, 1,
-                           ws->cm_flag.as<int32_t>(), ws->cm_lens.as<int32_t>(), st));
-  TPG_HIP(scan_i32_to_i64(ws->cm_flag.as<int32_t>(), ws->cm_pos.as<int64_t>(), np, 0, scal + 2,
-                          ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  TPG_HIP(scan_i32_to_i64(ws->cm_lens.as<int32_t>(), ws->cm_voff.as<int64_t>(), np, 0, scal + 3,
-                          ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-  TPG_HIP(hipMemcpyAsync(ws->h_scalars + 2, scal + 2, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
-  TPG_HIP(hipStreamSynchronize(st));
-  const int64_t k = ws->h_scalars[2], kv = ws->h_scalars[3];
-  TPG_TRY(ws_reserve(ws, ooff, sizeof(int64_t) * (k + 1)));
-  TPG_TRY(ws_reserve(ws, ovtx, sizeof(int32_t) * (kv + 1)));
-  TPG_HIP(launch_merge_emit(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np,
-                            ws->cm_cls.as<uint8_t>(), 1, ws->cm_pos.as<int64_t>(),
-                            ws->cm_voff.as<int64_t>(), ws->cm_len.as<int32_t>(),
-                            ws->cx_orig.as<int32_t>(), ooff.as<int64_t>(), ovtx.as<int32_t>(), st));
-  TPG_HIP(launch_set_i64(ooff.as<int64_t>() + k, scal + 3, st));
-  TPG_TRY(export_paths(ws, ooff, ovtx, k, kv, (c.flags & TPG_OUT_DEVICE) != 0, st, out, false));
-  return finish_copies(ws, st);
+  return within_cap(c, [&]() -> tpg_status {
+    tpg_paths_free(out);
+    std::vector<int32_t> comp;
+    std::vector<uint8_t> fl;
+    TPG_TRY(components_host(c, g, comp, fl));
+    ComponentUnion S;
+    HostUnion U;
+    TPG_TRY(component_union(g, comp, fl, false, 0, S, U));
+    DevBuf& ooff = ws->cm_off[0];
+    DevBuf& ovtx = ws->cm_vtx[0];
+    if (U.n == 0) {
+      TPG_TRY(ws_reserve(ws, ooff, sizeof(int64_t)));
+      TPG_TRY(ws_reserve(ws, ovtx, sizeof(int32_t)));
+      TPG_HIP(launch_zero_u64(ooff.as<uint64_t>(), 1, st));
+      return export_paths(ws, ooff, ovtx, 0, 0, (c.flags & TPG_OUT_DEVICE) != 0, st, out);
+    }
+    // the extension on every component alone (one union), then Def. 9
+    Timer tm{ws, st, false};
+    TreeResult R;
+    PPResult P;
+    OutSet& o = ws->out[0];
+    TPG_TRY(run_pp(U, c, tm, R, P, o, nullptr));
+    const int64_t np = P.n_pp;
+    TPG_TRY(ws_reserve(ws, ws->cx_vfl, (size_t)U.n));
+    TPG_TRY(ws_reserve(ws, ws->cx_orig, sizeof(int32_t) * U.n));
+    TPG_HIP(hipMemcpyAsync(ws->cx_vfl.p, S.vfl.data(), U.n, hipMemcpyHostToDevice, st));
+    TPG_HIP(hipMemcpyAsync(ws->cx_orig.p, S.orig.data(), sizeof(int32_t) * U.n,
+                           hipMemcpyHostToDevice, st));
+    TPG_TRY(ws_reserve(ws, ws->cm_cls, (size_t)np + 1));
+    TPG_TRY(ws_reserve(ws, ws->cm_len, sizeof(int32_t) * (np + 1)));
+    TPG_TRY(ws_reserve(ws, ws->cm_flag, sizeof(int32_t) * (np + 1)));
+    TPG_TRY(ws_reserve(ws, ws->cm_lens, sizeof(int32_t) * (np + 1)));
+    TPG_TRY(ws_reserve(ws, ws->cm_pos, sizeof(int64_t) * (np + 1)));
+    TPG_TRY(ws_reserve(ws, ws->cm_voff, sizeof(int64_t) * (np + 1)));
+    TPG_HIP(launch_internal_class(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np,
+                                  ws->cx_vfl.as<uint8_t>(), ws->cm_cls.as<uint8_t>(),
+                                  ws->cm_len.as<int32_t>(), st));
+    TPG_TRY(reserve_scan(ws, std::max<int64_t>(np, 16)));
+    int64_t* scal = ws->scalars.as<int64_t>();
+    TPG_HIP(launch_merge_sel(ws->cm_cls.as<uint8_t>(), ws->cm_len.as<int32_t>(), np, 1,
+                             ws->cm_flag.as<int32_t>(), ws->cm_lens.as<int32_t>(), st));
+    TPG_HIP(scan_i32_to_i64(ws->cm_flag.as<int32_t>(), ws->cm_pos.as<int64_t>(), np, 0, scal + 2,
+                            ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
+    TPG_HIP(scan_i32_to_i64(ws->cm_lens.as<int32_t>(), ws->cm_voff.as<int64_t>(), np, 0, scal + 3,
+                            ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
+    TPG_HIP(hipMemcpyAsync(ws->h_scalars + 2, scal + 2, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    TPG_HIP(hipStreamSynchronize(st));
+    const int64_t k = ws->h_scalars[2], kv = ws->h_scalars[3];
+    TPG_TRY(ws_reserve(ws, ooff, sizeof(int64_t) * (k + 1)));
+    TPG_TRY(ws_reserve(ws, ovtx, sizeof(int32_t) * (kv + 1)));
+    TPG_HIP(launch_merge_emit(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np,
+                              ws->cm_cls.as<uint8_t>(), 1, ws->cm_pos.as<int64_t>(),
+                              ws->cm_voff.as<int64_t>(), ws->cm_len.as<int32_t>(),
+                              ws->cx_orig.as<int32_t>(), ooff.as<int64_t>(), ovtx.as<int32_t>(), st));
+    TPG_HIP(launch_set_i64(ooff.as<int64_t>() + k, scal + 3, st));
+    TPG_TRY(export_paths(ws, ooff, ovtx, k, kv, (c.flags & TPG_OUT_DEVICE) != 0, st, out, false));
+    return finish_copies(ws, st);
+  });
 }
 
 tpg_status tpg_merged_pps(const tpg_graph* g, const tpg_opts* opts, tpg_paths* complete,
@@ -2351,177 +2410,181 @@ tpg_status tpg_merged_pps(const tpg_graph* g, const tpg_opts* opts, tpg_paths* c
   TPG_TRY(begin_call(opts, c));
   tpg_workspace* ws = c.ws;
   hipStream_t st = c.st;
-  std::vector<int32_t> comp;
-  std::vector<uint8_t> fl;
-  TPG_TRY(components_host(c, g, comp, fl));
-  int64_t n[3], nv[3];
-  TPG_TRY(extract_device(c, g, comp, fl, n, nv));
-  HostSet ee, ex, en;
-  TPG_TRY(fetch_set(ws, ws->cx_off[0], ws->cx_vtx[0], n[0], nv[0], st, ee));
-  TPG_TRY(fetch_set(ws, ws->cx_off[1], ws->cx_vtx[1], n[1], nv[1], st, ex));
-  TPG_TRY(fetch_set(ws, ws->cx_off[2], ws->cx_vtx[2], n[2], nv[2], st, en));
-  TPG_TRY(finish_copies(ws, st));
-
-  // The macro graph H (graph preparation on the host): a vertex for every
-  // vertex of g outside the components with a cycle; the trie of the
-  // SccEntryExitPaths and SccEntryPaths (they start at SccEntryVertices); the
-  // trie of the SccExitPaths; a terminal mark after every node where an
-  // SccEntryPath ends.  Arcs: g's arcs out of the vertices outside the
-  // components, trie arcs, and g's arcs that leave a component out of every
-  // node where an SccEntryExitPath or an SccExitPath ends; an arc into a
-  // component lands on the trie root of the vertex it enters.  H is acyclic
-  // and its prime paths are the merged candidates: from the entry to the
-  // exit (complete), from an exit-path trie root to the exit, from the entry
-  // to a terminal mark.  H's ids follow g's vertex order (terminal marks
-  // first), and the successors of an H vertex are distinct vertices of g, so
-  // the lexicographic order of H's paths is that of the paths in g.
-  PathTrie tin, tex;
-  tin.add(ee, 1);
-  tin.add(en, 2);
-  tex.add(ex, 4);
-  const int32_t n0 = g->n;
-  const int32_t b_in = n0, b_ex = b_in + (int32_t)tin.v.size();
-  const int32_t b_mk = b_ex + (int32_t)tex.v.size();
-  std::vector<int32_t> mark_of(tin.v.size(), -1);
-  int32_t nh = b_mk;
-  for (size_t x = 0; x < tin.v.size(); ++x)
-    if (tin.end[x] & 2) mark_of[x] = nh++;
-  std::vector<uint8_t> kind(nh, 0);
-  std::vector<int32_t> horig(nh, -1);
-  for (int32_t v = 0; v < n0; ++v) horig[v] = v;  // ids of cyclic vertices stay unused
-  for (size_t x = 0; x < tin.v.size(); ++x) {
-    kind[b_in + x] = 1;
-    horig[b_in + x] = tin.v[x];
-  }
-  for (size_t x = 0; x < tex.v.size(); ++x) {
-    kind[b_ex + x] = 2;
-    horig[b_ex + x] = tex.v[x];
-  }
-  for (int32_t h = b_mk; h < nh; ++h) kind[h] = 3;
-  auto target = [&](int32_t w) -> int32_t {
-    if (!(fl[w] & kSccCyclic)) return w;
-    const int32_t r = tin.root(w);
-    return r < 0 ? -1 : b_in + r;
-  };
-  std::vector<std::vector<int32_t>> adj(nh);
-  std::vector<uint8_t> live(nh, 1);
-  for (int32_t v = 0; v < n0; ++v) {
-    if (fl[v] & kSccCyclic) {
-      live[v] = 0;
-      continue;
-    }
-    for (int32_t e = g->succ_ptr[v]; e < g->succ_ptr[v + 1]; ++e) {
-      const int32_t t = target(g->succ[e]);
-      if (t >= 0) adj[v].push_back(t);
-    }
-  }
-  auto leave_arcs = [&](int32_t h, int32_t a) {
-    for (int32_t e = g->succ_ptr[a]; e < g->succ_ptr[a + 1]; ++e) {
-      const int32_t w = g->succ[e];
-      if (comp[w] == comp[a]) continue;
-      const int32_t t = target(w);
-      if (t >= 0) adj[h].push_back(t);
-    }
-  };
-  for (size_t x = 0; x < tin.v.size(); ++x) {
-    const int32_t h = b_in + (int32_t)x;
-    for (int32_t k : tin.kids[x]) adj[h].push_back(b_in + k);
-    if (tin.end[x] & 1) leave_arcs(h, tin.v[x]);
-    if (tin.end[x] & 2) adj[h].push_back(mark_of[x]);
-  }
-  for (size_t x = 0; x < tex.v.size(); ++x) {
-    const int32_t h = b_ex + (int32_t)x;
-    for (int32_t k : tex.kids[x]) adj[h].push_back(b_ex + k);
-    if (tex.end[x] & 4) leave_arcs(h, tex.v[x]);
-  }
-  // renumber: live vertices by (vertex of g, kind, id); terminal marks first
-  std::vector<int32_t> order;
-  for (int32_t h = 0; h < nh; ++h)
-    if (live[h]) order.push_back(h);
-  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
-    if (horig[x] != horig[y]) return horig[x] < horig[y];
-    return kind[x] < kind[y];
-  });
-  const int32_t nH = (int32_t)order.size();
-  if (nH > TPG_MAX_VERTICES)
-    return fail(TPG_ERR_UNSUPPORTED, "the merge graph has %d vertices (at most %d)", nH,
-                TPG_MAX_VERTICES);
-  std::vector<int32_t> nid(nh, -1);
-  for (int32_t i = 0; i < nH; ++i) nid[order[i]] = i;
-  std::vector<int64_t> rp(nH + 1, 0);
-  std::vector<int32_t> ci;
-  std::vector<uint8_t> hk(nH);
-  std::vector<int32_t> ho(nH);
-  for (int32_t i = 0; i < nH; ++i) {
-    const int32_t h = order[i];
-    for (int32_t t : adj[h]) ci.push_back(nid[t]);
-    rp[i + 1] = (int64_t)ci.size();
-    hk[i] = kind[h];
-    ho[i] = horig[h];
-  }
-  if (ci.empty()) ci.push_back(0);
-  tpg_graph* H = nullptr;
-  TPG_TRY(tpg_load_cfg_csr(nH, rp.data(), ci.data(), nid[g->entry], nid[g->exit],
-                           TPG_LOAD_ANY_DIGRAPH, &H));
-  struct Free {
-    tpg_graph* h;
-    ~Free() { tpg_graph_free(h); }
-  } free_h{H};
-  // prime paths of H on the device
-  HostUnion UH;
-  add_component(UH, H);
-  Timer tm{ws, st, false};
-  TreeResult R;
-  PPResult P;
-  OutSet& o = ws->out[0];
-  TPG_TRY(run_pp(UH, c, tm, R, P, o, nullptr));
-  // classify them in g (its CSR back on the device), keep the prime ones
-  HostUnion UG;
-  add_component(UG, g);
-  TPG_TRY(upload_union(ws, UG, st));
-  const int64_t np = P.n_pp;
-  TPG_TRY(ws_reserve(ws, ws->cm_kind, (size_t)nH));
-  TPG_TRY(ws_reserve(ws, ws->cm_orig, sizeof(int32_t) * nH));
-  TPG_TRY(ws_reserve(ws, ws->cm_cls, (size_t)np + 1));
-  TPG_TRY(ws_reserve(ws, ws->cm_len, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->cm_flag, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->cm_lens, sizeof(int32_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->cm_pos, sizeof(int64_t) * (np + 1)));
-  TPG_TRY(ws_reserve(ws, ws->cm_voff, sizeof(int64_t) * (np + 1)));
-  TPG_HIP(hipMemcpyAsync(ws->cm_kind.p, hk.data(), nH, hipMemcpyHostToDevice, st));
-  TPG_HIP(hipMemcpyAsync(ws->cm_orig.p, ho.data(), sizeof(int32_t) * nH, hipMemcpyHostToDevice, st));
-  TPG_HIP(launch_merge_class(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np,
-                             ws->cm_kind.as<uint8_t>(), ws->cm_orig.as<int32_t>(), ws->dg,
-                             nid[g->entry], nid[g->exit], ws->cm_cls.as<uint8_t>(),
-                             ws->cm_len.as<int32_t>(), st));
-  TPG_TRY(reserve_scan(ws, std::max<int64_t>(np, 16)));
-  int64_t* scal = ws->scalars.as<int64_t>();
-  const int cls_of[3] = {1, 3, 4};
   tpg_paths* outs[3] = {complete, exit_pps, entry_pps};
-  for (int s = 0; s < 3; ++s) {
-    TPG_HIP(launch_merge_sel(ws->cm_cls.as<uint8_t>(), ws->cm_len.as<int32_t>(), np, cls_of[s],
-                             ws->cm_flag.as<int32_t>(), ws->cm_lens.as<int32_t>(), st));
-    TPG_HIP(scan_i32_to_i64(ws->cm_flag.as<int32_t>(), ws->cm_pos.as<int64_t>(), np, 0, scal + 2,
-                            ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-    TPG_HIP(scan_i32_to_i64(ws->cm_lens.as<int32_t>(), ws->cm_voff.as<int64_t>(), np, 0, scal + 3,
-                            ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
-    TPG_HIP(hipMemcpyAsync(ws->h_scalars + 2, scal + 2, 2 * sizeof(int64_t), hipMemcpyDeviceToHost,
-                           st));
-    TPG_HIP(hipStreamSynchronize(st));
-    const int64_t k = ws->h_scalars[2], kv = ws->h_scalars[3];
-    TPG_TRY(ws_reserve(ws, ws->cm_off[s], sizeof(int64_t) * (k + 1)));
-    TPG_TRY(ws_reserve(ws, ws->cm_vtx[s], sizeof(int32_t) * (kv + 1)));
-    TPG_HIP(launch_merge_emit(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np,
-                              ws->cm_cls.as<uint8_t>(), cls_of[s], ws->cm_pos.as<int64_t>(),
-                              ws->cm_voff.as<int64_t>(), ws->cm_len.as<int32_t>(),
-                              ws->cm_orig.as<int32_t>(), ws->cm_off[s].as<int64_t>(),
-                              ws->cm_vtx[s].as<int32_t>(), st));
-    TPG_HIP(launch_set_i64(ws->cm_off[s].as<int64_t>() + k, scal + 3, st));
-    if (outs[s])
-      TPG_TRY(export_paths(ws, ws->cm_off[s], ws->cm_vtx[s], k, kv,
-                           (c.flags & TPG_OUT_DEVICE) != 0, st, outs[s], false));
-  }
-  return finish_copies(ws, st);
+  return within_cap(c, [&]() -> tpg_status {
+    for (tpg_paths* p : outs)
+      if (p) tpg_paths_free(p);
+    std::vector<int32_t> comp;
+    std::vector<uint8_t> fl;
+    TPG_TRY(components_host(c, g, comp, fl));
+    int64_t n[3], nv[3];
+    TPG_TRY(extract_device(c, g, comp, fl, n, nv));
+    HostSet ee, ex, en;
+    TPG_TRY(fetch_set(ws, ws->cx_off[0], ws->cx_vtx[0], n[0], nv[0], st, ee));
+    TPG_TRY(fetch_set(ws, ws->cx_off[1], ws->cx_vtx[1], n[1], nv[1], st, ex));
+    TPG_TRY(fetch_set(ws, ws->cx_off[2], ws->cx_vtx[2], n[2], nv[2], st, en));
+    TPG_TRY(finish_copies(ws, st));
+
+    // The macro graph H (graph preparation on the host): a vertex for every
+    // vertex of g outside the components with a cycle; the trie of the
+    // SccEntryExitPaths and SccEntryPaths (they start at SccEntryVertices); the
+    // trie of the SccExitPaths; a terminal mark after every node where an
+    // SccEntryPath ends.  Arcs: g's arcs out of the vertices outside the
+    // components, trie arcs, and g's arcs that leave a component out of every
+    // node where an SccEntryExitPath or an SccExitPath ends; an arc into a
+    // component lands on the trie root of the vertex it enters.  H is acyclic
+    // and its prime paths are the merged candidates: from the entry to the
+    // exit (complete), from an exit-path trie root to the exit, from the entry
+    // to a terminal mark.  H's ids follow g's vertex order (terminal marks
+    // first), and the successors of an H vertex are distinct vertices of g, so
+    // the lexicographic order of H's paths is that of the paths in g.
+    PathTrie tin, tex;
+    tin.add(ee, 1);
+    tin.add(en, 2);
+    tex.add(ex, 4);
+    const int32_t n0 = g->n;
+    const int32_t b_in = n0, b_ex = b_in + (int32_t)tin.v.size();
+    const int32_t b_mk = b_ex + (int32_t)tex.v.size();
+    std::vector<int32_t> mark_of(tin.v.size(), -1);
+    int32_t nh = b_mk;
+    for (size_t x = 0; x < tin.v.size(); ++x)
+      if (tin.end[x] & 2) mark_of[x] = nh++;
+    std::vector<uint8_t> kind(nh, 0);
+    std::vector<int32_t> horig(nh, -1);
+    for (int32_t v = 0; v < n0; ++v) horig[v] = v;  // ids of cyclic vertices stay unused
+    for (size_t x = 0; x < tin.v.size(); ++x) {
+      kind[b_in + x] = 1;
+      horig[b_in + x] = tin.v[x];
+    }
+    for (size_t x = 0; x < tex.v.size(); ++x) {
+      kind[b_ex + x] = 2;
+      horig[b_ex + x] = tex.v[x];
+    }
+    for (int32_t h = b_mk; h < nh; ++h) kind[h] = 3;
+    auto target = [&](int32_t w) -> int32_t {
+      if (!(fl[w] & kSccCyclic)) return w;
+      const int32_t r = tin.root(w);
+      return r < 0 ? -1 : b_in + r;
+    };
+    std::vector<std::vector<int32_t>> adj(nh);
+    std::vector<uint8_t> live(nh, 1);
+    for (int32_t v = 0; v < n0; ++v) {
+      if (fl[v] & kSccCyclic) {
+        live[v] = 0;
+        continue;
+      }
+      for (int32_t e = g->succ_ptr[v]; e < g->succ_ptr[v + 1]; ++e) {
+        const int32_t t = target(g->succ[e]);
+        if (t >= 0) adj[v].push_back(t);
+      }
+    }
+    auto leave_arcs = [&](int32_t h, int32_t a) {
+      for (int32_t e = g->succ_ptr[a]; e < g->succ_ptr[a + 1]; ++e) {
+        const int32_t w = g->succ[e];
+        if (comp[w] == comp[a]) continue;
+        const int32_t t = target(w);
+        if (t >= 0) adj[h].push_back(t);
+      }
+    };
+    for (size_t x = 0; x < tin.v.size(); ++x) {
+      const int32_t h = b_in + (int32_t)x;
+      for (int32_t k : tin.kids[x]) adj[h].push_back(b_in + k);
+      if (tin.end[x] & 1) leave_arcs(h, tin.v[x]);
+      if (tin.end[x] & 2) adj[h].push_back(mark_of[x]);
+    }
+    for (size_t x = 0; x < tex.v.size(); ++x) {
+      const int32_t h = b_ex + (int32_t)x;
+      for (int32_t k : tex.kids[x]) adj[h].push_back(b_ex + k);
+      if (tex.end[x] & 4) leave_arcs(h, tex.v[x]);
+    }
+    // renumber: live vertices by (vertex of g, kind, id); terminal marks first
+    std::vector<int32_t> order;
+    for (int32_t h = 0; h < nh; ++h)
+      if (live[h]) order.push_back(h);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+      if (horig[x] != horig[y]) return horig[x] < horig[y];
+      return kind[x] < kind[y];
+    });
+    const int32_t nH = (int32_t)order.size();
+    if (nH > TPG_MAX_VERTICES)
+      return fail(TPG_ERR_UNSUPPORTED, "the merge graph has %d vertices (at most %d)", nH,
+                  TPG_MAX_VERTICES);
+    std::vector<int32_t> nid(nh, -1);
+    for (int32_t i = 0; i < nH; ++i) nid[order[i]] = i;
+    std::vector<int64_t> rp(nH + 1, 0);
+    std::vector<int32_t> ci;
+    std::vector<uint8_t> hk(nH);
+    std::vector<int32_t> ho(nH);
+    for (int32_t i = 0; i < nH; ++i) {
+      const int32_t h = order[i];
+      for (int32_t t : adj[h]) ci.push_back(nid[t]);
+      rp[i + 1] = (int64_t)ci.size();
+      hk[i] = kind[h];
+      ho[i] = horig[h];
+    }
+    if (ci.empty()) ci.push_back(0);
+    tpg_graph* H = nullptr;
+    TPG_TRY(tpg_load_cfg_csr(nH, rp.data(), ci.data(), nid[g->entry], nid[g->exit],
+                             TPG_LOAD_ANY_DIGRAPH, &H));
+    struct Free {
+      tpg_graph* h;
+      ~Free() { tpg_graph_free(h); }
+    } free_h{H};
+    // prime paths of H on the device
+    HostUnion UH;
+    add_component(UH, H);
+    Timer tm{ws, st, false};
+    TreeResult R;
+    PPResult P;
+    OutSet& o = ws->out[0];
+    TPG_TRY(run_pp(UH, c, tm, R, P, o, nullptr));
+    // classify them in g (its CSR back on the device), keep the prime ones
+    HostUnion UG;
+    add_component(UG, g);
+    TPG_TRY(upload_union(ws, UG, st));
+    const int64_t np = P.n_pp;
+    TPG_TRY(ws_reserve(ws, ws->cm_kind, (size_t)nH));
+    TPG_TRY(ws_reserve(ws, ws->cm_orig, sizeof(int32_t) * nH));
+    TPG_TRY(ws_reserve(ws, ws->cm_cls, (size_t)np + 1));
+    TPG_TRY(ws_reserve(ws, ws->cm_len, sizeof(int32_t) * (np + 1)));
+    TPG_TRY(ws_reserve(ws, ws->cm_flag, sizeof(int32_t) * (np + 1)));
+    TPG_TRY(ws_reserve(ws, ws->cm_lens, sizeof(int32_t) * (np + 1)));
+    TPG_TRY(ws_reserve(ws, ws->cm_pos, sizeof(int64_t) * (np + 1)));
+    TPG_TRY(ws_reserve(ws, ws->cm_voff, sizeof(int64_t) * (np + 1)));
+    TPG_HIP(hipMemcpyAsync(ws->cm_kind.p, hk.data(), nH, hipMemcpyHostToDevice, st));
+    TPG_HIP(hipMemcpyAsync(ws->cm_orig.p, ho.data(), sizeof(int32_t) * nH, hipMemcpyHostToDevice, st));
+    TPG_HIP(launch_merge_class(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np,
+                               ws->cm_kind.as<uint8_t>(), ws->cm_orig.as<int32_t>(), ws->dg,
+                               nid[g->entry], nid[g->exit], ws->cm_cls.as<uint8_t>(),
+                               ws->cm_len.as<int32_t>(), st));
+    TPG_TRY(reserve_scan(ws, std::max<int64_t>(np, 16)));
+    int64_t* scal = ws->scalars.as<int64_t>();
+    const int cls_of[3] = {1, 3, 4};
+    for (int s = 0; s < 3; ++s) {
+      TPG_HIP(launch_merge_sel(ws->cm_cls.as<uint8_t>(), ws->cm_len.as<int32_t>(), np, cls_of[s],
+                               ws->cm_flag.as<int32_t>(), ws->cm_lens.as<int32_t>(), st));
+      TPG_HIP(scan_i32_to_i64(ws->cm_flag.as<int32_t>(), ws->cm_pos.as<int64_t>(), np, 0, scal + 2,
+                              ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
+      TPG_HIP(scan_i32_to_i64(ws->cm_lens.as<int32_t>(), ws->cm_voff.as<int64_t>(), np, 0, scal + 3,
+                              ws->scan_status.as<uint64_t>(), ws->scan_ctr.as<uint32_t>(), st));
+      TPG_HIP(hipMemcpyAsync(ws->h_scalars + 2, scal + 2, 2 * sizeof(int64_t), hipMemcpyDeviceToHost,
+                             st));
+      TPG_HIP(hipStreamSynchronize(st));
+      const int64_t k = ws->h_scalars[2], kv = ws->h_scalars[3];
+      TPG_TRY(ws_reserve(ws, ws->cm_off[s], sizeof(int64_t) * (k + 1)));
+      TPG_TRY(ws_reserve(ws, ws->cm_vtx[s], sizeof(int32_t) * (kv + 1)));
+      TPG_HIP(launch_merge_emit(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np,
+                                ws->cm_cls.as<uint8_t>(), cls_of[s], ws->cm_pos.as<int64_t>(),
+                                ws->cm_voff.as<int64_t>(), ws->cm_len.as<int32_t>(),
+                                ws->cm_orig.as<int32_t>(), ws->cm_off[s].as<int64_t>(),
+                                ws->cm_vtx[s].as<int32_t>(), st));
+      TPG_HIP(launch_set_i64(ws->cm_off[s].as<int64_t>() + k, scal + 3, st));
+      if (outs[s])
+        TPG_TRY(export_paths(ws, ws->cm_off[s], ws->cm_vtx[s], k, kv,
+                             (c.flags & TPG_OUT_DEVICE) != 0, st, outs[s], false));
+    }
+    return finish_copies(ws, st);
+  });
 }
 
 tpg_status tpg_prime_paths_vertex_lists(const tpg_graph* g, const tpg_opts* opts,
@@ -2659,15 +2722,22 @@ tpg_status tpg_test_paths(const tpg_graph* g, const tpg_opts* opts, tpg_paths* p
   TPResult T;
   hipEvent_t ext_done = nullptr;
   OutSet& o = c.ws->out[0];
-  tpg_status s = run_pp(U, c, tm, R, P, o, &ext_done, 0, 0, true, !(c.flags & TPG_TP_GREEDY));
-  if (s == TPG_OK && timing) TPG_HIP(hipEventRecord(phase[1], c.st));
-  if (s == TPG_OK) s = test_paths_device(c.ws, U, c.st, R, P, T, o, c.flags & TPG_TP_GREEDY);
-  if (s == TPG_OK && timing) TPG_HIP(hipEventRecord(phase[2], c.st));
+  const bool grouped = pp_out && (c.flags & TPG_ORDER_BY_LAST);
+  tpg_status s = within_cap(c, [&]() -> tpg_status {
+    R = TreeResult{};
+    P = PPResult{};
+    T = TPResult{};
+    const bool greedy = c.flags & TPG_TP_GREEDY;
+    TPG_TRY(run_pp(U, c, tm, R, P, o, &ext_done, 0, 0, true, !greedy));
+    if (timing) TPG_HIP(hipEventRecord(phase[1], c.st));
+    TPG_TRY(test_paths_device(c.ws, U, c.st, R, P, T, o, greedy));
+    if (timing) TPG_HIP(hipEventRecord(phase[2], c.st));
+    if (grouped) TPG_TRY(group_by_last(c.ws, U.n, c.st, o, P.n_pp, P.n_vtx));
+    return TPG_OK;
+  });
   // with TPG_STREAM the sets come back as counts and digests and the test
   // paths go through on_chunk
   const uint32_t fl = (c.flags & TPG_STREAM) ? (c.flags | TPG_DIGEST_ONLY) : c.flags;
-  const bool grouped = pp_out && (c.flags & TPG_ORDER_BY_LAST);
-  if (s == TPG_OK && grouped) s = group_by_last(c.ws, U.n, c.st, o, P.n_pp, P.n_vtx);
   if (s == TPG_OK && pp_out)
     s = deliver_set(c.ws, grouped ? o.ppg_off : o.pp_off, grouped ? o.ppg_vtx : o.pp_vtx, P.n_pp,
                     P.n_vtx, fl, c.st, pp_out, false);
@@ -2761,7 +2831,7 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
     }
     int64_t rec0 = 0, msk0 = 0;
     const bool use_pred =
-        predicted &&
+        predicted && !ws->tight &&
         std::find(ws->pred_failed.begin(), ws->pred_failed.end(), U.uids) == ws->pred_failed.end();
     if (use_pred) {
       // capacities from the predicted per-level path counts, 25% margin;
@@ -3050,11 +3120,14 @@ tpg_status tpg_batch_test_paths(const tpg_graph* const* graphs, int32_t n_graphs
       cg.exec = nullptr;
     }
     ws->io_mode = graphable ? 1 : 0;
-    ws->io_vals.clear();
-    ws->io_stage_used = 0;
     const uint64_t gen0 = ws->alloc_gen;
-    const tpg_status bs = batch_body(c, graphs, n_graphs, predicted, want_levels, tm, pp_first,
-                                     tp_first, ppv, tpv);
+    const tpg_status bs = within_cap(c, [&]() -> tpg_status {
+      ws->io_vals.clear();
+      ws->io_stage_used = 0;
+      if (c.stats) memset(c.stats, 0, sizeof *c.stats);
+      return batch_body(c, graphs, n_graphs, predicted, want_levels, tm, pp_first, tp_first, ppv,
+                        tpv);
+    });
     ws->io_mode = 0;
     TPG_TRY(bs);
     if (c.stats) c.stats->n_allocs = (int64_t)(ws->alloc_gen - gen0);

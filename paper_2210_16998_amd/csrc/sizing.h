@@ -35,21 +35,25 @@ constexpr int64_t kMaxTreeNodes = (int64_t)INT32_MAX - 2;
 
 // First request of a run: what the workspace already holds (held_rec, and
 // held_msk slots at the run's set width), a floor from the vertex count, and
-// the caller's predicted sizes (0: none).
+// the caller's predicted sizes (0: none).  tight: with little to spare.
 constexpr TreeCaps onepass_first_caps(int64_t held_rec, int64_t held_msk, int n, int64_t rec0,
-                                      int64_t msk0) {
-  return TreeCaps{std::min(std::max({held_rec, (int64_t)n * 64 + 4096, rec0}), kMaxTreeNodes),
-                  std::max({(int64_t)n * 16 + 1024, msk0, held_msk})};
+                                      int64_t msk0, bool tight = false) {
+  return TreeCaps{std::min(std::max({held_rec, tight ? (int64_t)n * 8 + 512 : (int64_t)n * 64 + 4096,
+                                     rec0}),
+                           kMaxTreeNodes),
+                  std::max({tight ? (int64_t)n * 2 + 64 : (int64_t)n * 16 + 1024, msk0, held_msk})};
 }
 
 // After level Lo (F paths from node base) claimed nxt children that did not
-// fit: room for every node up to the end of level Lo + 1 with 25% to spare,
-// and when Lo + 1 is odd (its sets are stored) room for its nxt sets.
+// fit: room for every node up to the end of level Lo + 1 with 25% to spare
+// (tight: 6%), and when Lo + 1 is odd (its sets are stored) room for its nxt
+// sets.
 constexpr TreeCaps onepass_grown_caps(int64_t rec_cap, int64_t mask_cap, int Lo, int64_t base,
-                                      int64_t F, int64_t nxt) {
-  const int64_t need = base + F + nxt + 1;
-  return TreeCaps{std::max(need, std::min(std::max(rec_cap, need + need / 4), kMaxTreeNodes)),
-                  ((Lo + 1) & 1) ? std::max(mask_cap, nxt + nxt / 4 + 1024) : mask_cap};
+                                      int64_t F, int64_t nxt, bool tight = false) {
+  const int64_t need = base + F + nxt + 1, part = tight ? 16 : 4;
+  return TreeCaps{std::max(need, std::min(std::max(rec_cap, need + need / part), kMaxTreeNodes)),
+                  ((Lo + 1) & 1) ? std::max(mask_cap, nxt + nxt / part + (tight ? 64 : 1024))
+                                 : mask_cap};
 }
 
 // Stored level whose sets the extension of level L reads (L itself when odd,
@@ -91,7 +95,8 @@ struct LoopFailure {
 // repeated_overflow instead of replaying it again.
 template <class Dev>
 LoopEnd onepass_levels(Dev& d, int first_batch, int max_levels, std::vector<int64_t>& cnt,
-                       int& Lmax, int64_t& n_overflows, LoopFailure& fail_info) {
+                       int& Lmax, int64_t& n_overflows, LoopFailure& fail_info,
+                       bool tight = false) {
   if ((int)cnt.size() < max_levels + 1) cnt.resize(max_levels + 1, 0);
   std::vector<uint8_t> overflowed(max_levels + 1, 0);
   int L0 = 1;
@@ -120,7 +125,7 @@ LoopEnd onepass_levels(Dev& d, int first_batch, int max_levels, std::vector<int6
         return LoopEnd::repeated_overflow;
       }
       overflowed[Lo] = 1;
-      const TreeCaps c = onepass_grown_caps(d.rec_cap(), d.mask_cap(), Lo, base, F, nxt);
+      const TreeCaps c = onepass_grown_caps(d.rec_cap(), d.mask_cap(), Lo, base, F, nxt, tight);
       const int Ls = stored_level_read_by(Lo);
       if (!d.reserve(c, base + F, Ls, cnt[Ls])) return LoopEnd::device_failed;
       if (!d.resume(Lo)) return LoopEnd::device_failed;
