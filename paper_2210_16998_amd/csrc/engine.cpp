@@ -1674,10 +1674,22 @@ tpg_status check_graph(const tpg_graph* g) {
   return TPG_OK;
 }
 
-// Hands one chunk to the caller: host copies (freed right after the call)
-// or device pointers.
+// Hands one chunk to the caller: host arrays or device pointers.  on_chunk may
+// make calls of its own on the workspace: it does not find the chunk's room
+// there, and what the running call has set is set again.
 tpg_status call_chunk(CallCtx& c, const tpg_paths& chunk, int64_t first, int64_t end) {
+  tpg_workspace* ws = c.ws;
+  uint8_t* const room = ws->chunk;
+  const size_t room_cap = ws->chunk_cap;
+  const uint64_t cap = ws->cap;
+  ws->chunk = nullptr;
+  ws->chunk_cap = 0;
   const int32_t r = c.opts->on_chunk(c.opts->chunk_ctx, &chunk, first, end);
+  if (ws->chunk) (void)hipHostFree(ws->chunk);
+  ws->chunk = room;
+  ws->chunk_cap = room_cap;
+  ws->cap = cap;
+  ws->tight = cap && cap <= ws->tight_cap;
   if (r != 0) return fail(TPG_ERR_CALLBACK, "on_chunk returned %d for [%lld, %lld)", r,
                           (long long)first, (long long)end);
   return TPG_OK;
@@ -1722,8 +1734,8 @@ tpg_status prime_paths_stream(const tpg_graph* g, CallCtx& c, tpg_paths* out) {
   tpg_stats acc{};
   std::vector<int64_t> levels;
   uint64_t dg[2] = {0, 0};
-  OutSet& o = c.ws->out[0];
   for (int32_t lo = 0; lo < U.n; lo += cv) {
+    OutSet& o = c.ws->out[0];
     const int32_t hi = std::min(lo + cv, U.n);
     const int32_t* xl = U.xhead.data();
     c.ws->seed_lo = (int32_t)(std::lower_bound(xl, xl + U.xn, lo) - xl);
