@@ -368,10 +368,11 @@ struct tpg_mlp {
   float* loss = nullptr;
   uint16_t *xt = nullptr, *h1t = nullptr, *h2t = nullptr, *dyt = nullptr, *dh2t = nullptr,
            *dh1t = nullptr;
-  // pinned host copies of what goes up (features, targets) and comes back
-  // (outputs, or the gradient block and the loss)
+  // pinned room that arrays pass through on their way up (features, targets) and
+  // back (outputs, or the gradient block and the loss)
   float* host = nullptr;
-  size_t host_floats = 0;
+  size_t host_floats = 0, host_used = 0;
+  bool seen = false;  // a call has been made
   bool busy = false;  // work that uses `host` may not have ended
 };
 
@@ -443,13 +444,72 @@ tpg_status mlp_rows(tpg_mlp* m, int n) {
     m->loss = f;
     m->rows = rows;
   }
-  const size_t need = (size_t)rows * (kIn + kOut) + std::max((size_t)rows * kOut, oEnd + 1);
-  if (need > m->host_floats) {
-    if (m->host) TPG_HIP(hipHostFree(m->host));
-    m->host = nullptr;
-    m->host_floats = 0;
-    TPG_HIP(hipHostMalloc((void**)&m->host, sizeof(float) * need, hipHostMallocDefault));
+  return TPG_OK;
+}
+
+// Room for a call of n rows, up to kRoomFloats.  Pinning costs some 0.3 ms a MB,
+// so a handle's first call, which may be its only one, goes without (a first
+// forward of 1024 rows: 0.68 ms with it, 0.40 without), and larger arrays pass
+// through in pieces.  Without room the copies take the caller's arrays as they
+// are.
+constexpr size_t kRoomFloats = (size_t)4 << 20;
+void mlp_room(tpg_mlp* m, int n) {
+  const size_t need = std::min(kRoomFloats, (size_t)n * (kIn + kOut) +
+                                                std::max((size_t)n * kOut, oEnd + 1));
+  m->host_used = 0;
+  if (m->seen && need > m->host_floats) {
+    if (m->host) (void)hipHostFree(m->host);
     m->host_floats = need;
+    if (hipHostMalloc((void**)&m->host, sizeof(float) * need, hipHostMallocDefault) != hipSuccess) {
+      (void)hipGetLastError();
+      m->host = nullptr;
+      m->host_floats = 0;
+    }
+  }
+  m->seen = true;
+}
+
+// Room for `floats` of it (null: there is none so large), all of it if need be.
+tpg_status mlp_take(tpg_mlp* m, size_t floats, float** at) {
+  *at = nullptr;
+  if (floats > m->host_floats) return TPG_OK;
+  if (floats > m->host_floats - m->host_used) {
+    TPG_HIP(hipStreamSynchronize(m->st));
+    m->host_used = 0;
+  }
+  *at = m->host + m->host_used;
+  m->host_used += floats;
+  return TPG_OK;
+}
+
+tpg_status mlp_up(tpg_mlp* m, float* dev, const float* src, size_t floats) {
+  while (floats > 0) {
+    const size_t left = m->host_floats - m->host_used;
+    const size_t k = m->host ? std::min(floats, left ? left : m->host_floats) : floats;
+    float* at = nullptr;
+    TPG_TRY(mlp_take(m, k, &at));
+    if (at) memcpy(at, src, sizeof(float) * k);
+    TPG_HIP(hipMemcpyAsync(dev, at ? at : src, sizeof(float) * k, hipMemcpyHostToDevice, m->st));
+    if (!at) TPG_HIP(hipStreamSynchronize(m->st));  // the caller's array is its own again
+    dev += k;
+    src += k;
+    floats -= k;
+  }
+  return TPG_OK;
+}
+
+// (dst holds the array when it returns)
+tpg_status mlp_down(tpg_mlp* m, float* dst, const float* dev, size_t floats) {
+  while (floats > 0) {
+    const size_t k = m->host ? std::min(floats, m->host_floats) : floats;
+    float* at = nullptr;
+    TPG_TRY(mlp_take(m, k, &at));
+    TPG_HIP(hipMemcpyAsync(at ? at : dst, dev, sizeof(float) * k, hipMemcpyDeviceToHost, m->st));
+    TPG_HIP(hipStreamSynchronize(m->st));
+    if (at) memcpy(dst, at, sizeof(float) * k);
+    dst += k;
+    dev += k;
+    floats -= k;
   }
   return TPG_OK;
 }
@@ -465,21 +525,16 @@ tpg_status refresh_bf16(tpg_mlp* m) {
 }
 
 // Features and targets (null: forward only) to the device, and the row pass.
-// *back: pinned room for what comes back.
-tpg_status run_rows(tpg_mlp* m, const float* x, const float* t, int n, RowArgs& g, float** back) {
+tpg_status run_rows(tpg_mlp* m, const float* x, const float* t, int n, RowArgs& g) {
   hipStream_t st = m->st;
   // a training step that returns no loss does not wait for its uploads
   if (m->busy) TPG_HIP(hipStreamSynchronize(st));
   m->busy = false;
   TPG_TRY(mlp_rows(m, n));
-  float* hx = m->host;
-  float* ht = hx + (size_t)n * kIn;
-  memcpy(hx, x, sizeof(float) * kIn * n);
-  if (t) memcpy(ht, t, sizeof(float) * kOut * n);
-  *back = ht + (size_t)n * kOut;
+  mlp_room(m, n);
   m->busy = true;
-  TPG_HIP(hipMemcpyAsync(m->x, hx, sizeof(float) * kIn * n, hipMemcpyHostToDevice, st));
-  if (t) TPG_HIP(hipMemcpyAsync(m->t, ht, sizeof(float) * kOut * n, hipMemcpyHostToDevice, st));
+  TPG_TRY(mlp_up(m, m->x, x, (size_t)n * kIn));
+  if (t) TPG_TRY(mlp_up(m, m->t, t, (size_t)n * kOut));
   g = RowArgs{};
   g.x = m->x;
   g.t = t ? m->t : nullptr;
@@ -653,12 +708,9 @@ tpg_status tpg_mlp_forward(tpg_mlp* m, const float* x, int32_t n, float* y) {
   if (!m || !x || !y || n < 1) return fail(TPG_ERR_INVALID_ARG, "bad argument");
   TPG_HIP(hipSetDevice(m->device));
   RowArgs g;
-  float* back;
-  TPG_TRY(run_rows(m, x, nullptr, n, g, &back));
-  TPG_HIP(hipMemcpyAsync(back, m->y, sizeof(float) * kOut * n, hipMemcpyDeviceToHost, m->st));
-  TPG_HIP(hipStreamSynchronize(m->st));
+  TPG_TRY(run_rows(m, x, nullptr, n, g));
+  TPG_TRY(mlp_down(m, y, m->y, (size_t)n * kOut));
   m->busy = false;
-  memcpy(y, back, sizeof(float) * kOut * n);
   return TPG_OK;
 }
 
@@ -667,9 +719,15 @@ tpg_status tpg_mlp_gradients(tpg_mlp* m, const float* x, const float* t, int32_t
   if (!m || !x || !t || n < 1) return fail(TPG_ERR_INVALID_ARG, "bad argument");
   TPG_HIP(hipSetDevice(m->device));
   RowArgs g;
-  float* back;
-  TPG_TRY(run_rows(m, x, t, n, g, &back));
+  TPG_TRY(run_rows(m, x, t, n, g));
   TPG_TRY(run_backward(m, g));
+  float* back = nullptr;
+  TPG_TRY(mlp_take(m, oEnd + 1, &back));
+  std::vector<float> own;
+  if (!back) {
+    own.resize(oEnd + 1);
+    back = own.data();
+  }
   if (grad) TPG_HIP(hipMemcpyAsync(back, m->grad, sizeof(float) * oEnd, hipMemcpyDeviceToHost, m->st));
   if (loss)
     TPG_HIP(hipMemcpyAsync(back + oEnd, m->loss, sizeof(float), hipMemcpyDeviceToHost, m->st));
@@ -685,8 +743,7 @@ tpg_status tpg_mlp_train_step(tpg_mlp* m, const float* x, const float* t, int32_
   if (!m || !x || !t || n < 1) return fail(TPG_ERR_INVALID_ARG, "bad argument");
   TPG_HIP(hipSetDevice(m->device));
   RowArgs g;
-  float* back;
-  TPG_TRY(run_rows(m, x, t, n, g, &back));
+  TPG_TRY(run_rows(m, x, t, n, g));
   TPG_TRY(run_backward(m, g));
   m->step += 1;
   AdamArgs a{};
@@ -705,10 +762,8 @@ tpg_status tpg_mlp_train_step(tpg_mlp* m, const float* x, const float* t, int32_
   TPG_HIP(hipGetLastError());
   TPG_TRY(refresh_bf16(m));
   if (loss) {
-    TPG_HIP(hipMemcpyAsync(back, m->loss, sizeof(float), hipMemcpyDeviceToHost, m->st));
-    TPG_HIP(hipStreamSynchronize(m->st));
+    TPG_TRY(mlp_down(m, loss, m->loss, 1));
     m->busy = false;
-    *loss = *back;
   }
   return TPG_OK;
 }
