@@ -383,7 +383,7 @@ tpg_status mlp_alloc(tpg_mlp* m) {
   TPG_HIP(hipStreamCreateWithFlags(&m->st, hipStreamNonBlocking));
   m->n_master = oEnd;
   TPG_HIP(hipMalloc(&m->master, sizeof(float) * oEnd * 4));  // w, m, v, grad
-  TPG_HIP(hipMemset(m->master, 0, sizeof(float) * oEnd * 4));
+  TPG_HIP(hipMemsetAsync(m->master, 0, sizeof(float) * oEnd * 4, m->st));
   m->w1 = m->master + oW1;
   m->b1 = m->master + oB1;
   m->w2 = m->master + oW2;
@@ -395,7 +395,7 @@ tpg_status mlp_alloc(tpg_mlp* m) {
   uint16_t* bb = nullptr;
   const size_t nb = 2 * (64 * kHid + kHid * kHid + kHid * kOutPad);
   TPG_HIP(hipMalloc(&bb, sizeof(uint16_t) * nb));
-  TPG_HIP(hipMemset(bb, 0, sizeof(uint16_t) * nb));
+  TPG_HIP(hipMemsetAsync(bb, 0, sizeof(uint16_t) * nb, m->st));
   m->w1b = bb;
   m->w1bt = m->w1b + 64 * kHid;
   m->w2b = m->w1bt + 64 * kHid;
@@ -427,7 +427,7 @@ tpg_status mlp_rows(tpg_mlp* m, int n) {
     const size_t bytes = floats * 4 + halves * 2 + 1024;
     TPG_HIP(hipMalloc(&m->act, bytes));
     // the padding rows of the transposed arrays stay zero
-    TPG_HIP(hipMemset(m->act, 0, bytes));
+    TPG_HIP(hipMemsetAsync(m->act, 0, bytes, m->st));
     uint16_t* h = (uint16_t*)m->act;
     m->xt = h; h += 64 * R;
     m->h1t = h; h += R * kHid;
@@ -676,8 +676,10 @@ tpg_status tpg_mlp_set_params(tpg_mlp* m, const float* params) {
   std::vector<float> blk;
   unpack_params(params, blk);
   TPG_HIP(hipSetDevice(m->device));
+  // a step that returned no loss may still be at work on the parameters
+  TPG_HIP(hipStreamSynchronize(m->st));
   TPG_HIP(hipMemcpy(m->master, blk.data(), sizeof(float) * oEnd, hipMemcpyHostToDevice));
-  TPG_HIP(hipMemset(m->mom, 0, sizeof(float) * 2 * oEnd));
+  TPG_HIP(hipMemsetAsync(m->mom, 0, sizeof(float) * 2 * oEnd, m->st));
   m->step = 0;
   TPG_TRY(refresh_bf16(m));
   TPG_HIP(hipStreamSynchronize(m->st));
@@ -699,6 +701,7 @@ tpg_status tpg_mlp_set_normalizer(tpg_mlp* m, const float* mean, const float* st
     m->h_mean[i] = mean[i];
     m->h_std[i] = stdv[i] > 1e-12f ? stdv[i] : 1.f;
   }
+  TPG_HIP(hipStreamSynchronize(m->st));  // as for the parameters
   TPG_HIP(hipMemcpy(m->mean, m->h_mean, sizeof(float) * kIn, hipMemcpyHostToDevice));
   TPG_HIP(hipMemcpy(m->stdv, m->h_std, sizeof(float) * kIn, hipMemcpyHostToDevice));
   return TPG_OK;

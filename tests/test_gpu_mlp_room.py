@@ -51,3 +51,19 @@ def test_steps_without_a_loss():
         x[:], t[:] = 0, 0  # the caller's arrays are its own again
         b.train_step(x0, t0, 1e-3)
     assert np.array_equal(a.params(), b.params())
+
+
+def test_parameters_set_after_a_step_without_a_loss():
+    """The step is still at work when the parameters and the normalizer change:
+    it takes the old ones and leaves the new ones alone."""
+    rng = np.random.default_rng(11)
+    n = 60000
+    x = rng.normal(0, 2, (n, R.IN)).astype(np.float32)
+    t = rng.normal(0, 1, (n, R.OUT)).astype(np.float32)
+    a, b = tpg.MLP(seed=3), tpg.MLP(seed=4)
+    for _ in range(5):
+        tpg._check(tpg.lib().tpg_mlp_train_step(a._h, x.ctypes.data, t.ctypes.data, n, 0.5, None))
+        a.set_params(b.params())
+        a.set_normalizer(np.zeros(R.IN, np.float32), np.ones(R.IN, np.float32))
+        assert np.array_equal(a.params(), b.params())
+        assert np.array_equal(a.forward(x[:99]), b.forward(x[:99]))
