@@ -2791,10 +2791,13 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
                       std::vector<int64_t>& pp_first, std::vector<int64_t>& tp_first,
                       int64_t& ppv, int64_t& tpv) {
   tpg_workspace* ws = c.ws;
-  // unions: one per visited-set width class, with the graphs of at most 64
-  // vertices apart (a graph's test-path runs are padded to those of the
-  // union's largest); split at 2^17 vertices and, with predictions and a pool
-  // cap, at half the cap of predicted footprint
+  // unions: one per visited-set width, with the graphs of at most 64 vertices
+  // apart: a batch too large for one union then has the deep trees in one of them
+  // and not in all (4096 functions 5.5 ms, 6.0 without), though a small one
+  // makes two rounds of launches of what could be one (64 functions 2.0 and
+  // 1.3 ms); split at 2^17 vertices and, with predictions and a pool cap, at
+  // half the cap of predicted footprint (24 bytes a path: its node's 15, count
+  // and canon)
   std::vector<std::vector<int32_t>> unions;
   {
     std::vector<std::vector<int32_t>> cls(8);  // 0: at most 64 vertices; 1 + log2(words)
@@ -2849,22 +2852,34 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
       // capacities from the predicted per-level path counts, 25% margin;
       // index 63 pools every deeper level, so it sizes the total but not the
       // largest single level
-      std::vector<double> lv(64, 0.0);
-      for (int32_t i : unions[u])
-        for (int L = 0; L < 64; ++L) lv[L] += predicted_paths(predicted, i, L);
-      double tot = 0, peak = 0;
+      // The predictions count simple paths; nodes are paths of chains, of which
+      // both ends' choices shrink with the share of chains among the graph's
+      // vertices (levels are fewer too, so a single one shrinks with one end's
+      // only).  The graphs with most paths have more lines than the others: of
+      // 862 functions of more than 64 vertices the nodes were over-estimated
+      // 2.2 times by the union's share and 1.8 by each graph's own.
+      std::vector<double> lv(64, 0.0), sets(64, 0.0);
+      double tot = 0, peak = 0, nodes = 0, level = 0;
+      for (int32_t i : unions[u]) {
+        const double share = (double)graphs[i]->chains.n / (double)graphs[i]->n;
+        for (int L = 0; L < 64; ++L) {
+          const double p = predicted_paths(predicted, i, L);
+          lv[L] += p;
+          sets[L] += share * p;
+          nodes += share * share * p;
+        }
+      }
       for (int L = 0; L < 64; ++L) {
         tot += lv[L];
-        if (L < 63) peak = std::max(peak, lv[L]);
+        if (L < 63) {
+          peak = std::max(peak, lv[L]);
+          level = std::max(level, sets[L]);
+        }
       }
       // never more than the record limit, the pool cap or half the free
       // device memory: an over-prediction costs capacity, not the call
       double rec_lim = (double)INT32_MAX - 2, msk_lim = (double)INT32_MAX - 2;
       const double node_b = 15.0, set_b = 2.0 * 8.0 * U.Wu;
-      // The predictions count simple paths; nodes are paths of chains, of which
-      // both ends' choices shrink with the share of chains among the vertices
-      // (levels are fewer too, so a single one shrinks with one end's only).
-      const double share = (double)U.xn / (double)U.n;
       size_t free_b = 0, total_b = 0;
       if (ws->io_mode != 2 && hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b > 0) {
         rec_lim = std::min(rec_lim, 0.5 * (double)free_b / node_b);
@@ -2876,8 +2891,8 @@ static tpg_status batch_body(CallCtx& c, const tpg_graph* const* graphs, int32_t
         rec_lim = std::min(rec_lim, 0.5 * (double)ws->cap / node_b);
         msk_lim = std::min(msk_lim, 0.25 * (double)ws->cap / set_b);
       }
-      rec0 = (int64_t)std::min(1.25 * share * share * tot + U.n + 1024, rec_lim);
-      msk0 = (int64_t)std::min(1.25 * share * peak + 1024, msk_lim);
+      rec0 = (int64_t)std::min(1.25 * nodes + U.n + 1024, rec_lim);
+      msk0 = (int64_t)std::min(1.25 * level + 1024, msk_lim);
       io_value(ws, rec0);  // free device memory may differ between calls
       io_value(ws, msk0);
       if (c.stats) {
