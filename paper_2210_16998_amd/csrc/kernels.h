@@ -326,6 +326,10 @@ hipError_t launch_tp_down_run(const ExtArgs& a, const TpTree& tt, int64_t base, 
 hipError_t launch_emit_rows(const int32_t* src, int64_t n, int64_t n_entries, const int64_t* pp_off,
                             const int32_t* pp_vtx, const EndRows* b, const int64_t* out_off,
                             int32_t* out_vtx, hipStream_t st, const int64_t* n_dev = nullptr);
+// the n rows at off (off[n]: their entries, at most n_entries) and their offsets,
+// both arrays 16-byte aligned
+hipError_t launch_copy_rows(const int64_t* off, const int32_t* vtx, int64_t n, int64_t n_entries,
+                            int64_t* out_off, int32_t* out_vtx, hipStream_t st);
 // start[c] / vstart[c] (c = 0 .. n_comp) of the test paths
 hipError_t launch_comp_tp_starts(int n_comp, const int32_t* gbase, const int64_t* first,
                                  const int64_t* off, int64_t* start, int64_t* vstart,

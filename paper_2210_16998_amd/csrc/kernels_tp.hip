@@ -884,6 +884,27 @@ hipError_t launch_emit_rows(const int32_t* src, int64_t n, int64_t n_entries, co
   return hipGetLastError();
 }
 
+// A set as it is, 16 bytes a lane and step.
+__global__ __launch_bounds__(kBlock) void k_copy_rows(const int64_t* off, const int32_t* vtx,
+                                                      int64_t n, int64_t* out_off,
+                                                      int32_t* out_vtx) {
+  const int64_t at = (int64_t)blockIdx.x * kBlock + threadIdx.x, step = (int64_t)gridDim.x * kBlock;
+  const int64_t nv = off[n];
+  for (int64_t i = at; i <= n; i += step) out_off[i] = off[i];
+  const int4* from = reinterpret_cast<const int4*>(vtx);
+  int4* to = reinterpret_cast<int4*>(out_vtx);
+  for (int64_t i = at; i < nv / 4; i += step) to[i] = from[i];
+  if (at < nv % 4) out_vtx[nv / 4 * 4 + at] = vtx[nv / 4 * 4 + at];
+}
+
+hipError_t launch_copy_rows(const int64_t* off, const int32_t* vtx, int64_t n, int64_t n_entries,
+                            int64_t* out_off, int32_t* out_vtx, hipStream_t st) {
+  const int64_t work = std::max(n + 1, n_entries / 4 + 1);
+  const int64_t grid = std::min<int64_t>(8192, (work + kBlock - 1) / kBlock);
+  k_copy_rows<<<(unsigned)grid, kBlock, 0, st>>>(off, vtx, n, out_off, out_vtx);
+  return hipGetLastError();
+}
+
 // Starts of the components' test paths: start[c] = first[gbase[c]] (first:
 // see k_tp_arc_starts), vstart[c] = the offset there (c = 0 .. n_comp).
 __global__ void k_comp_tp_starts(int n_comp, const int32_t* gbase, const int64_t* first,

@@ -14,6 +14,11 @@ from tests.test_gpu_narrow import _fans
 pytestmark = pytest.mark.gpu
 
 
+def _looped(g, v):
+    """g with an arc from v to itself: its test paths are not its prime paths."""
+    return cfggen.from_edges(g.n, sorted(g.edges() + [(v, v)]), name=g.name + "_looped")
+
+
 def _guards(n, flip=False):
     """n vertices in a row, each of which may leave to the exit; flip: with the
     inner ones numbered from the end."""
@@ -53,12 +58,16 @@ def _rails(length, fan, flip):
 def test_early_exits(n, flip):
     say("case", n, flip)
     check_tp(_guards(n, flip), local=True)
+    for v in {1, n // 2, n - 2}:
+        check_tp(_looped(_guards(n, flip), v), local=True)
 
 
 @pytest.mark.parametrize("a,b", [(8, 8), (13, 5), (5, 13), (15, 16), (31, 32), (33, 60)])
 def test_switches_into_one_exit(a, b):
     say("case", a, b)
     check_tp(_switches(a, b), local=True)
+    check_tp(_looped(_switches(a, b), a), local=True)
+    check_tp(_looped(_switches(a, b), a + b // 2), local=True)
 
 
 # levels of more than 2048 nodes, swept one or two to a launch: 16 successors and
@@ -71,6 +80,8 @@ def test_wide_levels_by_successors(widths, back):
     g, _ = _fans(widths, back)
     say("case", g.name, back)
     check_tp(g, local=True)
+    if not back:
+        check_tp(_looped(g, g.n // 2), local=True)
 
 
 # fan 31: 63 predecessors, one thread's; 34: a wave's.  The thread's walks pass
@@ -85,7 +96,7 @@ def test_ties_after_long_ways(length, fan, flip):
 def test_batch_of_deep_graphs():
     """Enough of them for a wave each, and with larger ones among them."""
     for sizes in ([30 + k for k in range(70)], [30 + k for k in range(8)] + [300, 1030]):
-        gs = [_guards(n, bool(n & 1)) for n in sizes] + [_rails(30, 31, True)]
+        gs = [_looped(_guards(n, bool(n & 1)), n // 2) for n in sizes] + [_rails(30, 31, True)]
         r, _ = tpg.batch_test_paths([tpg.load_cfg(g) for g in gs], ws=ws())
         for k, g in enumerate(gs):
             say("case", g.name)
@@ -97,7 +108,7 @@ def test_batch_of_deep_graphs():
 def test_deep_graph_costs_no_pass_per_level():
     """1000 early exits: with the test paths a call takes about what the prime
     paths alone take (6.3 times that when every level looked at all arcs)."""
-    h = tpg.load_cfg(_guards(1000))
+    h = tpg.load_cfg(_looped(_guards(1000), 500))
     flags = tpg.TPG_NO_TIMING | tpg.TPG_OUT_DEVICE
 
     def ms(f):
@@ -125,3 +136,4 @@ def test_narrow_levels_by_words(widths, exits):
     g = cfggen.from_edges(end + 1, edges, name=f"{g.name}_{exits}")
     say("case", g.name, g.n)
     check_tp(g, local=True)
+    check_tp(_looped(g, 3), local=True)
