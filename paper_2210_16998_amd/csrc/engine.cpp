@@ -1268,15 +1268,22 @@ tpg_status greedy_select(tpg_workspace* ws, const HostUnion& U, hipStream_t st, 
 tpg_status acyclic_test_paths(tpg_workspace* ws, int nc, hipStream_t st, PPResult& P, TPResult& T,
                               OutSet& o) {
   const int64_t np = P.n_pp;
-  const int64_t most = P.ahead ? np * PathTotals::bins(ws->xg) : P.n_vtx;
+  auto entries = [&]() -> tpg_status {
+    TPG_TRY(io_read(ws, st, ws->h_scalars + 6, ws->scalars.as<int64_t>() + 6, sizeof(int64_t)));
+    o.n_ppv = P.n_vtx = ws->h_scalars[6];
+    return TPG_OK;
+  };
+  int64_t most = P.ahead ? np * PathTotals::bins(ws->xg) : P.n_vtx;
+  const bool ahead = P.ahead && room_ahead(ws, o.tp_vtx, most);
+  if (P.ahead && !ahead) {
+    TPG_TRY(entries());
+    most = P.n_vtx;
+  }
   TPG_TRY(ws_reserve(ws, o.tp_off, sizeof(int64_t) * (np + 1)));
   TPG_TRY(ws_reserve(ws, o.tp_vtx, sizeof(int32_t) * (most + 1)));
   TPG_HIP(launch_copy_rows(o.pp_off.as<int64_t>(), o.pp_vtx.as<int32_t>(), np, most,
                            o.tp_off.as<int64_t>(), o.tp_vtx.as<int32_t>(), st));
-  if (P.ahead) {
-    TPG_TRY(io_read(ws, st, ws->h_scalars + 6, ws->scalars.as<int64_t>() + 6, sizeof(int64_t)));
-    o.n_ppv = P.n_vtx = ws->h_scalars[6];
-  }
+  if (ahead) TPG_TRY(entries());
   if (nc > 1) {
     int64_t* cs = o.comp_starts.as<int64_t>();
     TPG_HIP(hipMemcpyAsync(cs + 2 * (nc + 1), cs, sizeof(int64_t) * 2 * (nc + 1),

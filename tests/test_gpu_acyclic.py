@@ -75,3 +75,24 @@ def test_batches(mixed):
                 assert np.array_equal(off, ref.offsets) and np.array_equal(vtx, ref.vertices), (k, cap)
         assert st["n_tp"] == sum(len(t) for _, t in want)
     w.close()
+
+
+def test_caps_between_the_room_ahead_and_none():
+    """4000 paths of 11 entries, 176 KB a set, and 688 KB with room ahead."""
+    g = _fans((10, 10, 10, 4))[0]
+    h, pp = tpg.load_cfg(g), oracle.prime_paths_local(g, 0, g.n)[0]
+    w = tpg.Workspace()
+    tpg.test_paths(h, ws=w)
+    full = w.bytes
+    w.close()
+    fits = 0
+    for cap in range(full // 2, full + 65536, max(4096, full // 60)):
+        w = tpg.Workspace()
+        try:
+            a, b, _ = tpg.test_paths(h, ws=w, pool_cap=cap)
+            assert same(a, pp) and same(b, pp) and w.bytes <= cap
+            fits += 1
+        except tpg.TpgError as e:
+            assert e.name == "TPG_ERR_CAPACITY" and fits == 0
+        w.close()
+    assert fits > 20
