@@ -1042,8 +1042,13 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
   // and 17.6 ms, 12 switches of 16 of 16 0.74 and 0.68, fans of 16 0.55 and 0.53),
   // below it two are as fast or faster (fans of 8 0.41 and 0.42, of 4 0.48 and
   // 0.50, a 212-vertex CFG 1.74 and 1.78), above it one is (fans of 32 0.70 and
-  // 0.63, 4 switches of 30 of 30 0.83 and 0.74)
-  const int kRun = U.max_deg <= 16 ? 2 : 1;
+  // 0.63, 4 switches of 30 of 30 0.83 and 0.74), except where the levels do not
+  // grow, which is past the switches (2.6 million nodes over 3147 chains, most of
+  // them a row of 3000 early exits: 73.8 and 78.6)
+  auto two_levels = [&](int top) {
+    return U.max_deg <= 16 ||
+           (R.count[top + 1] <= R.count[top] && R.count[top + 2] <= R.count[top + 1]);
+  };
   TPG_TRY(run_seq(ws, ws->rank_up, std::move(key), st, [&]() -> hipError_t {
     hipError_t e = launch_path_lengths(a, R.count[1], N, st);
     for (int L = R.Lmax; L >= 1 && e == hipSuccess;) {
@@ -1053,7 +1058,7 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
         L -= s.n;
         continue;
       }
-      const int n = std::min(kRun, L);  // levels L - n + 1 .. L
+      const int n = L > 1 && two_levels(L - 1) ? 2 : 1;  // levels L - n + 1 .. L
       const int top = L - n + 1;
       e = n > 1 ? launch_up_run(a, R.off[top], R.count[top], sc, st)
                 : launch_up(a, R.off[top], R.count[top], sc, st);
@@ -1106,7 +1111,7 @@ tpg_status rank_and_materialize(tpg_workspace* ws, const HostUnion& U, hipStream
         L += s.n;
         continue;
       }
-      const int n = std::max(1, std::min(kRun, R.Lmax - L));  // parents of levels L .. L + n - 1
+      const int n = R.Lmax - L > 1 && two_levels(L) ? 2 : 1;  // parents of levels L .. L + n - 1
       e = n > 1 ? launch_down_run(a, tt, L, R.off[L], R.count[L], sc, leaf, len, st)
                 : launch_down(a, tt, L, R.off[L], R.count[L], sc, leaf, len, st);
       L += n;
