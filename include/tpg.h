@@ -135,7 +135,10 @@ typedef struct tpg_paths {
  * first vertices [first, end) whose prime paths the chunk holds (the
  * canonical order is by first vertex, so the chunks concatenate to the
  * canonical set); for test paths the index range of the chunk's paths in the
- * canonical set.  A nonzero return stops the call with TPG_ERR_CALLBACK. */
+ * canonical set.  A nonzero return stops the call with TPG_ERR_CALLBACK.
+ * The callback may make other calls on the same workspace while prime paths
+ * are streamed to host memory; device chunks, and the test paths still to
+ * come, lie in the workspace and would be overwritten. */
 typedef int32_t (*tpg_chunk_fn)(void* ctx, const tpg_paths* chunk, int64_t first, int64_t end);
 
 typedef struct tpg_stats {
@@ -151,8 +154,10 @@ typedef struct tpg_stats {
   int64_t n_overflows;    /* device-sized levels that overflowed and were grown */
   int64_t device_bytes;   /* workspace device memory in use                  */
   double ms_extend;       /* frontier extension + filter (all levels)        */
-  double ms_rank;         /* canonical-order ranking + PP materialization    */
-  double ms_tp;           /* BFS tables + splice + sort + dedup              */
+  double ms_rank;         /* canonical-order ranking + PP materialization
+                             (the shortest paths to and from the graph's ends
+                             are found beside the extension)                 */
+  double ms_tp;           /* test paths: order, duplicates, rows             */
   double ms_total;        /* device time of the whole call                   */
   double ms_extend_kernel;/* summed duration of the extension kernel launches */
   int64_t n_extend_launches;
@@ -175,7 +180,10 @@ typedef struct tpg_opts {
   uint32_t flags;           /* TPG_OUT_DEVICE | TPG_FORCE_TWO_PASS | ...     */
   void* stream;             /* hipStream_t to run on; NULL: the workspace's  */
   tpg_workspace* ws;        /* NULL: a temporary workspace for this call     */
-  uint64_t pool_cap_bytes;  /* 0: no cap                                    */
+  uint64_t pool_cap_bytes;  /* 0: no cap; else the most device memory that the
+                               workspace may hold.  A call that would pass it
+                               is run again with exact sizes before it fails
+                               with TPG_ERR_CAPACITY                        */
   tpg_stats* stats;         /* optional                                     */
   int64_t* level_counts;    /* optional: level_counts[L] = simple paths with L
                                entries (closed cycles included), for

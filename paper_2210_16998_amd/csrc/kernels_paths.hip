@@ -22,11 +22,10 @@
 //    chains' lengths (k_path_lengths).  A CFG's statements sit mostly on such
 //    lines: the 400-vertex stress CFG has 189 chains, and its tree 1.85e8
 //    nodes on 36 levels instead of 4.66e8 on 213; a ~200-vertex CFG about a
-//    quarter of the nodes and half the levels.  Whole calls on it went from
-//    41.0 to 30.8 ms, on a 212-vertex CFG from 3.27 to 1.88 ms, on a
-//    1000-vertex one (174 chains) from 24.9 to 6.7 ms, and a batch of 4096
-//    from 24.1 to 11.1 ms.  "Vertex" below means a vertex of the graph of
-//    chains.
+//    quarter of the nodes and half the levels.  A whole call
+//    on it takes 17.8 ms, one on a 212-vertex CFG 1.74, on a 1000-vertex one
+//    (174 chains) 2.1, and a batch of 4096 5.6 (each kernel below has its own
+//    share of that).  "Vertex" below means a vertex of the graph of chains.
 //  * All paths of one level form a frontier of (parent index, vertex) nodes;
 //    the children of one parent are contiguous and in ascending successor
 //    order, and each node records where its children start and how many
@@ -38,18 +37,18 @@
 //    parent's (siblings read the same stored set).  Sets are stored
 //    word-major: word q of slot j sits at q * stride + j, so the threads of
 //    a wave, which own consecutive slots, read and write consecutive words.
-//  * One workgroup handles a tile of 256 * ITEMS parents: choice masks over
-//    successor slots, a block scan of child counts, then ONE device-scope
-//    atomic claim of the tile's slice of the next level, then a
-//    load-balanced expansion where consecutive threads write consecutive
-//    children, so record and mask stores are coalesced.  No workgroup ever
+//  * One workgroup handles a tile of its threads * ITEMS parents: choice masks
+//    over successor slots, a block scan of child counts, then ONE device-scope
+//    atomic claim of the tile's slice of the next level, then the children's
+//    records and sets on neighbouring slots.  No workgroup ever
 //    waits for another one; the order of tile slices inside a level is the
 //    order in which the claims landed, which ranking does not depend on.
 //  * Levels follow each other on the device: per-level counts and offsets
 //    live in device memory; a launch extends the level that the one before
-//    it has left (narrow levels many at a time, see LevelCursor), derives
-//    its offset from the level before, or raises the overflow flag when that level's children did not fit; the
-//    host then grows the buffers to the exact size and replays the level.
+//    it has left (narrow levels many at a time, see LevelCursor) and derives
+//    its offset from the level before, or raises the overflow flag when that
+//    level's nodes did not fit; the host then grows the buffers to the exact
+//    size and replays the level.
 //  * The plain two-pass form (count, scan, host-visible size, fill) keeps
 //    children in parent order and serves as the exact reference form.
 
@@ -301,10 +300,10 @@ struct LevelCursor {
   }
 };
 
-// A tile is 256 * ir consecutive parents (ir <= ITEMS, chosen per level so
+// A tile is NT * ir consecutive parents (ir <= ITEMS, chosen per level so
 // that large levels need few claims and small ones still spread over the
 // grid); tile t goes to workgroup t mod grid.  Thread tid owns parents
-// i * 256 + tid (i < ir): their records and visited sets are loaded together
+// i * NT + tid (i < ir): their records and visited sets are loaded together
 // (coalesced), the visited sets stay in registers, and the thread writes its
 // own parents' children.  Children are laid out item-major and, inside an
 // item, in thread order, so a wave's stores land on neighbouring slots.  A

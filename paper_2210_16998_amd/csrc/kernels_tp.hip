@@ -1,4 +1,5 @@
-// Test-path kernels: BFS tables, splice, canonical sort and deduplication.
+// Test-path kernels: shortest paths from the entry and to the exit, the test
+// paths' order and duplicates read off the path tree, and their rows.
 //
 // A test path extends a prime path to the initial and final nodes (paper
 // Sec. 7.3, the Ammann-Offutt construction; Problem 1 asks for test paths
@@ -518,12 +519,12 @@ hipError_t launch_chain_bfs(const DGraph& g, const DGraph& x, const DChains& ch,
 // So the test paths' nodes are marked (k_tp_mark, with a prime path for each),
 // counted bottom-up, and given their places top-down.  k_down_run finds, for
 // every node with prime paths below it, the node of the path with its
-// BFS-tree part dropped, from its parent's.  Before, every test path was
-// spliced packed, sorted by merge rounds that compared them and unpacked
-// again: the test-path stage of the 400-vertex stress CFG took 21 ms of a
-// 30.8 ms call, with this order 11 ms of 19.9, and 9.3 of 17.8 since (its rows
-// alone are 21.8 GB, 7.2 ms); a batch of 4096 CFGs went from 11.1 to 7.6 ms, a
-// 1000-vertex CFG from 6.7 to 4.3.
+// BFS-tree part dropped, from its parent's.  The test-path stage of the
+// 400-vertex stress CFG takes 9.3 ms of a 17.8 ms call (its rows alone are
+// 21.8 GB, 7.2 ms); splicing every test path, sorting them by merge rounds that
+// compared them and unpacking them took 21 of 30.8.  The same change took a
+// batch of 4096 CFGs from 11.1 to 7.6 ms and a 1000-vertex CFG from 6.7 to 4.3
+// (5.6 and 2.1 with what has changed elsewhere since).
 
 // The child of node c labelled chain y (-1: none).
 __device__ __forceinline__ int64_t child_of(const TreeBufs& t, int64_t c, int y) {
